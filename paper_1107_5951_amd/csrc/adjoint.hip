@@ -23,6 +23,7 @@
 #include <algorithm>
 
 #include "harmonics.hpp"
+#include "octet.hpp"
 #include "resolve.hpp"
 
 namespace grav {
@@ -554,87 +555,6 @@ k_t_p2m(DevGeom g, const double *A, int RBT, const double *me, double *drho)
         }
 }
 
-// M2L^T runs on the forward's stream-K M2L kernel (transposed operators,
-// columns = source boxes of each level's column block, see
-// build_m2l_transposed).  Its B operand: the adjoint LE of each level's
-// gather region regathered in the kernel's layout (class-split boxes,
-// chunk-major planes (q, kr) of four coefficients 16 q + kr + 4 u), zero
-// where the region has no target box and for the padding coefficients.
-// The target box at a position comes from the level's target map (source
-// block plus a halo of 3, which holds the region).  One thread per (region
-// box, model, plane).
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_le_gather(DevGeom gt, DevGeom g, const int32_t *tmap, int64_t n_tmap, int64_t n_tbox, const double *le,
-            int64_t n_leg, const int32_t *kmap, int NP, T *out)
-{
-    // the forward regather's coefficient map (value u of plane pl is
-    // coefficient kmap[4 pl + u], -1: zero), through LDS
-    __shared__ int32_t km[256];
-    for (int e = threadIdx.x; e < 4 * NP; e += blockDim.x)
-        km[e] = kmap[e];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_leg * g.B * NP)
-        return;
-    const int plane = (int)(i % NP);
-    const int64_t col = i / NP;  // region box * B + model
-    const int bm = (int)(col % g.B);
-    const int64_t box = col / g.B;
-    int l = 2;
-    while (l < g.L && box >= gt.lev[l + 1].me_off)
-        ++l;
-    const DevLev &lt = gt.lev[l];
-    const DevLev &lv = g.lev[l];
-    const int64_t r = box - lt.me_off;
-    const int x = lt.s0[0] + (int)(r % lt.ns[0]), y = lt.s0[1] + (int)((r / lt.ns[0]) % lt.ns[1]),
-              z = lt.s0[2] + (int)(r / ((int64_t)lt.ns[0] * lt.ns[1]));
-    int first[3], cnt[3];
-    const int64_t pos = class_split(lt, (x & 1) | ((y & 1) << 1) | ((z & 1) << 2), first, cnt) +
-                        ((int64_t)((z - first[2]) >> 1) * cnt[1] + ((y - first[1]) >> 1)) * cnt[0] +
-                        ((x - first[0]) >> 1);
-    int64_t tb = -1;
-    const int mx = x - lv.s0[0] + 3, my = y - lv.s0[1] + 3, mz = z - lv.s0[2] + 3;
-    if (mx >= 0 && my >= 0 && mz >= 0 && mx < lv.ns[0] + 6 && my < lv.ns[1] + 6 && mz < lv.ns[2] + 6) {
-        const int64_t mi = lv.tmap_off + ((int64_t)mz * (lv.ns[1] + 6) + my) * (lv.ns[0] + 6) + mx;
-        if (mi < n_tmap) {
-            const int64_t v = tmap[mi];
-            if (v >= 0 && v < lv.n_tgt && lv.tgt_off + v < n_tbox)
-                tb = v;
-        }
-    }
-    const int64_t nB = (int64_t)lt.ns[0] * lt.ns[1] * lt.ns[2] * g.B;
-    T *dst = out + lt.me_off * g.B * (4 * NP) + ((int64_t)plane * nB + pos * g.B + bm) * 4;
-    const double *src = le + (tb >= 0 ? ((lv.tgt_off + tb) * g.B + bm) * g.PS : 0);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int c = km[4 * plane + u];
-        dst[u] = (T)(tb >= 0 && c >= 0 ? src[c] : 0.0);
-    }
-}
-
-// ME of the transposed M2L's columns from its segment slots: the sum, over
-// the segments of the column's unit in their order, of the slot entry, in
-// FP64 (as the forward's k_m2l_sum); the column's ME is overwritten.  A
-// unit without segments (no target box at any offset) gives zero.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_m2lt_sum(const T *part, const int32_t *colmap, const int64_t *colbox, const int32_t *tseg_start,
-           const int32_t *tsegs, int64_t ncols, int PS, int ncw, double *me)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ncols * PS)
-        return;
-    const int64_t c = i / PS;
-    const int k = (int)(i - c * PS);
-    const int32_t m = colmap[c];
-    const int t = m >> 6, cl = m & 63;
-    double acc = 0.0;
-    for (int j = tseg_start[t]; j < tseg_start[t + 1]; ++j)
-        acc += (double)part[((int64_t)tsegs[j] * ncw + cl) * PS + k];
-    me[colbox[c] * PS + k] = acc;
-}
-
 // The near-field transpose, per cell: drho[cell] = (with `prior`, the terms
 // already in drho, else 0) plus, over the targets j (with `pend`, the user
 // points only: the lattice kernel takes the cell centres) of the 27 leaves
@@ -874,67 +794,58 @@ __global__ void __launch_bounds__(256) k_t_zero(double *x, int64_t n)
 
 }  // namespace
 
-// M2L^T: regather the adjoint LE, run the forward kernel on the transposed
-// problem, add each column's segment slots into its ME.
+// The transposed M2L's input in its element type: the adjoint LE over each
+// level's gather region, zero where the region has no target box (found
+// through the level's target map, the source block plus a halo of 3, which
+// holds the region).  One thread per four coefficients.
 template <typename T>
-static grav_status m2l_transposed_t(Plan *p, const DevGeom &g, hipStream_t s, const T *Kt)
+__global__ void __launch_bounds__(256)
+k_le_rows(DevGeom g, OctGeom og, const int32_t *tmap, const double *le, int64_t n4, T *out)
 {
-    DevGeom gt = g;  // the kernel's view: columns = source boxes, B = gathered adjoint LE
-    for (int l = 2; l <= p->L; ++l) {
-        const LevelInfo &lv = p->lev[l];
-        DevLev &d = gt.lev[l];
-        for (int a = 0; a < 3; ++a) {
-            d.s0[a] = lv.gs0[a];
-            d.ns[a] = lv.gns[a];
-        }
-        d.me_off = lv.g_off;
-        d.tbox_off = lv.me_off;
-        for (int c = 0; c < 9; ++c)
-            d.class_start[c] = lv.col_class_start[c];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n4)
+        return;
+    const int P4 = g.PS / 4;
+    const int k4 = (int)(i % P4);
+    const int64_t col = i / P4;  // row * B + model
+    const int64_t row = col / g.B;
+    const int bm = (int)(col - row * g.B);
+    int l = 2;
+    while (l < g.L && row >= og.lev[l + 1].row0)
+        ++l;
+    const OctLev &lt = og.lev[l];
+    const DevLev &lv = g.lev[l];
+    const int64_t j = row - lt.row0;
+    const int64_t tb = tmap_lookup(lv, tmap, 3, lt.s0[0] + (int)(j % lt.ns[0]), lt.s0[1] + (int)((j / lt.ns[0]) % lt.ns[1]),
+                                   lt.s0[2] + (int)(j / ((int64_t)lt.ns[0] * lt.ns[1])));
+    double2 a = double2{0.0, 0.0}, b = a;
+    if (tb >= 0 && tb < lv.n_tgt) {
+        const double2 *src = reinterpret_cast<const double2 *>(le + ((lv.tgt_off + tb) * g.B + bm) * g.PS) + 2 * k4;
+        a = src[0];
+        b = src[1];
     }
-    T *leg = reinterpret_cast<T *>(p->d_leg);
-    const int64_t n = p->n_leg * p->B * p->m2l_npl;
-    if (n > 0 && p->d_kmap != nullptr) {
-        hipLaunchKernelGGL((k_le_gather<T>), dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, gt, g,
-                           (const int32_t *)p->d_tmap, p->n_tmap, p->n_tbox, (const double *)p->d_le, p->n_leg,
-                           (const int32_t *)p->d_kmap, p->m2l_npl, leg);
-        GRAV_HIP(hipGetLastError());
+    if constexpr (sizeof(T) == 4) {
+        reinterpret_cast<float4 *>(out)[i] = make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
+    } else {
+        reinterpret_cast<double2 *>(out)[2 * i] = a;
+        reinterpret_cast<double2 *>(out)[2 * i + 1] = b;
     }
-    M2LRun<T> r;
-    r.tiles = (const GemmTile *)p->d_m2lt_tiles;
-    r.keys = (const uint32_t *)p->d_skey;
-    r.order = (const int32_t *)p->d_sorder;
-    r.class_off = (const int32_t *)p->d_tclass_off;
-    r.K = Kt;
-    r.b_in = leg;
-    r.segs = (const int32_t *)p->d_m2lt_segs;
-    r.wgseg = (const int32_t *)p->d_m2lt_wgseg;
-    r.items = (const int32_t *)p->d_m2lt_items;
-    r.part = reinterpret_cast<T *>(p->d_partt);
-    r.wgs = p->m2lt_wgs;
-    r.nset = p->m2lt_nset;
-    r.nc = p->m2lt_nc;
-    if (sizeof(T) == 4 && p->m2l_orbit) {
-        r.K = reinterpret_cast<const T *>(p->d_kt32o);
-        r.orbtab = (const int32_t *)p->d_orbtab_t;
-        r.ccoef = (const int32_t *)p->d_ccoef;
-    }
-    GRAV_CHECK(launch_m2l<T>(p, gt, s, r));
-    const int64_t ns = p->m2lt_ncols * p->PS;
-    if (ns > 0) {
-        hipLaunchKernelGGL((k_m2lt_sum<T>), dim3((unsigned)ceil_div(ns, 256)), dim3(256), 0, s,
-                           (const T *)p->d_partt, (const int32_t *)p->d_m2lt_colmap, (const int64_t *)p->d_m2lt_colbox,
-                           (const int32_t *)p->d_m2lt_tseg_start, (const int32_t *)p->d_m2lt_tsegs, p->m2lt_ncols,
-                           p->PS, p->m2lt_ncw, p->d_me);
-        GRAV_HIP(hipGetLastError());
-    }
-    return GRAV_OK;
 }
 
+// M2L^T on the forward's kernel with the transposed operators: columns are
+// the octets of source boxes.
+template <typename T>
 static grav_status enqueue_m2l_transposed(Plan *p, const DevGeom &g, hipStream_t s)
 {
-    return p->d.precision == GRAV_FP64 ? m2l_transposed_t<double>(p, g, s, p->d_kt64)
-                                       : m2l_transposed_t<float>(p, g, s, p->d_kt32);
+    const OctGeom og = octet_geom(p, true);
+    T *rows = reinterpret_cast<T *>(p->d_rows);
+    const int64_t n4 = p->n_grow * p->B * (p->PS / 4);
+    if (n4 > 0) {
+        hipLaunchKernelGGL((k_le_rows<T>), dim3((unsigned)ceil_div(n4, 256)), dim3(256), 0, s, g, og,
+                           (const int32_t *)p->d_tmap, (const double *)p->d_le, n4, rows);
+        GRAV_HIP(hipGetLastError());
+    }
+    return launch_m2l<T>(p, p->m2lt, s, og, rows, p->d_me);
 }
 
 // Workgroups of the grouped P2M^T (each takes G groups of 64 columns so that
@@ -1442,7 +1353,10 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
                 GRAV_CHECK(launch_t_l2l(p, g, l, s));
         stage_end(p, s);
         stage_begin(p, "m2lT", s);
-        GRAV_CHECK(enqueue_m2l_transposed(p, g, s));
+        if (p->d.precision == GRAV_FP64)
+            GRAV_CHECK(enqueue_m2l_transposed<double>(p, g, s));
+        else
+            GRAV_CHECK(enqueue_m2l_transposed<float>(p, g, s));
         stage_end(p, s);
         stage_begin(p, "m2mT", s);
         for (int l = 3; l <= L; ++l)

@@ -7,11 +7,13 @@
 // size of the buffer it addresses, and that no two columns of one stage
 // write the same expansion.  No compute kernel is launched.
 #include <algorithm>
+#include <functional>
 #include <cstdio>
 #include <string>
 #include <tuple>
 #include <vector>
 
+#include "octet.hpp"
 #include "resolve.hpp"
 
 namespace grav {
@@ -41,49 +43,81 @@ struct Checker {
     }
 };
 
-// Tiles of a stage whose offsets are split S ways: tile.pad in [0, S) names
-// the offset range [pad * 189 / S, (pad + 1) * 189 / S) and, for S > 1, the
-// slab of the partial-sum workspace it writes ([S][ysize] expansions).
-template <class Res>
-void check_stage(Checker &ck, const char *name, const Res &res, const TileRange &r, int S,
-                 int64_t n_ids, int64_t xsize, int64_t ysize, std::vector<char> &written)
+// One M2L direction: the groups cover every column of every level, the
+// segments every orbit of a unit with a source once, in one slot each, every
+// input row lies in [0, nin), and every output row is written by exactly one octet.
+void check_octets(Checker &ck, const char *name, const Plan *p, const OctPlan &o, const OctGeom &g,
+                  int64_t nin, int64_t nout, bool all_out,
+                  const std::function<bool(int, int32_t)> &present)
 {
-    written.assign((size_t)(S > 1 ? S : 1) * ysize, 0);
-    for (int64_t b = 0; b < r.n && ck.ok; ++b) {
-        const GemmTile &tile = res.tiles[b];
-        if (tile.ncol < 1 || tile.ncol > kTileCols)
-            ck.fail(name, "tile width out of range", tile.ncol, kTileCols);
-        if (tile.pad < 0 || tile.pad >= S)
-            ck.fail(name, "split index out of range", tile.pad, S);
-        if (!ck.ok)
-            break;
-        const int t0 = tile.pad * res.nterms(tile) / S, t1 = (tile.pad + 1) * res.nterms(tile) / S;
-        for (int cl = 0; cl < kTileCols && ck.ok; ++cl) {
-            const GemmCol col = res.column(tile, cl);
-            if (!col.valid)
-                continue;
-            for (int it = t0; it < t1; ++it) {
-                const GemmTerm tm = res.term(tile, it);
-                if (tm.kid < 0 || tm.kid >= n_ids)
-                    ck.fail(name, "matrix id out of range", tm.kid, n_ids);
-                const int64_t s = res.src(tile, col, tm);
-                if (s < -1 || s >= xsize)
-                    ck.fail(name, "source expansion out of range", s, xsize);
-            }
-            const int64_t o = res.out(tile, col);
-            if (o < 0 || o >= ysize) {
-                ck.fail(name, "destination expansion out of range", o, ysize);
-            } else {
-                const int64_t w = (S > 1 ? tile.pad : 0) * ysize + o;
-                if (written[w])
-                    ck.fail(name, "two columns write one expansion", o, ysize);
-                written[w] = 1;
-            }
-        }
+    const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
+    const auto key = fetch(o.d_key, (size_t)o.noct);
+    const auto child = fetch(o.d_child, (size_t)o.noct * 8);
+    const auto groups = fetch(o.d_groups, (size_t)o.ngroup);
+    const auto segs = fetch(o.d_segs, (size_t)o.nseg * 4);
+    const auto wgseg = fetch(o.d_wgseg, (size_t)o.wgs + (o.wgs > 0 ? 1 : 0));
+    const auto uslot = fetch(o.d_uslot, (size_t)o.nunit + 1);
+    // segment of each slot
+    std::vector<int32_t> slot_seg((size_t)o.nseg, -1);
+    for (int64_t sg = 0; sg < o.nseg && ck.ok; ++sg) {
+        const int32_t sl = segs[4 * sg + 2];
+        if (sl < 0 || sl >= o.nseg || slot_seg[sl] >= 0)
+            ck.fail(name, "slot out of range or repeated", sg, sl);
+        else
+            slot_seg[sl] = (int32_t)sg;
     }
-    for (size_t i = 0; i < written.size() && ck.ok; ++i)
+    std::vector<char> written((size_t)nout, 0);
+    for (int64_t i = 0; i < o.noct * 8 && ck.ok; ++i)
+        if (child[i] >= 0 && (child[i] >= nout || written[child[i]]++))
+            ck.fail(name, "output row out of range or repeated", i, child[i]);
+    for (int64_t i = 0; i < nout && ck.ok && all_out; ++i)
         if (!written[i])
-            ck.fail(name, "expansion never written", (long long)i, ysize);
+            ck.fail(name, "expansion never written", i, nout);
+    int64_t covered = 0;
+    for (int64_t i = 0; i < o.ngroup && ck.ok; ++i) {
+        const OctGroup &gr = groups[i];
+        covered += gr.ncol;
+        if (gr.level < 2 || gr.level > p->L || gr.ncol < 1 || gr.ncol > 16 * o.nc || gr.col0 < 0 ||
+            gr.oct0 + (gr.col0 + gr.ncol - 1) / p->B >= o.noct)
+            ck.fail(name, "group out of range", i, gr.level);
+    }
+    if (ck.ok && covered != o.noct * p->B)
+        ck.fail(name, "groups do not cover the columns", covered, o.noct * p->B);
+    if (ck.ok && o.nunit != (int64_t)o.ngroup * in.RS)
+        ck.fail(name, "units do not match the groups", o.nunit, o.ngroup);
+    if (ck.ok && o.wgs > 0 && (wgseg[0] != 0 || wgseg[o.wgs] != o.nseg))
+        ck.fail(name, "segment ranges do not cover the segments", wgseg[0], o.nseg);
+    if (ck.ok && (uslot[0] != 0 || uslot[o.nunit] != o.nseg))
+        ck.fail(name, "unit slots do not cover the segments", uslot[o.nunit], o.nseg);
+    for (int64_t u = 0; u < o.nunit && ck.ok; ++u) {
+        const OctGroup &gr = groups[u / in.RS];
+        uint32_t done = 0;
+        for (int32_t j = uslot[u]; j < uslot[u + 1] && ck.ok; ++j) {
+            const int32_t sg = slot_seg[j];
+            const uint32_t mask = (uint32_t)segs[4 * sg + 1];
+            if (segs[4 * sg] != u || mask == 0 || (mask & done) || mask >> kOrbits)
+                ck.fail(name, "unit's segments inconsistent", u, sg);
+            done |= mask;
+        }
+        for (int ob = 1; ob <= kOrbits && ck.ok; ++ob)
+            for (int64_t c = 0; c < gr.ncol && ck.ok; c += p->B - (gr.col0 + c) % p->B) {
+                const uint32_t k = key[gr.oct0 + (gr.col0 + c) / p->B];
+                const OctLev &lv = g.lev[gr.level];
+                for (int r = 0; r < 8 && ck.ok; ++r) {
+                    const int32_t j = octet_place(lv, orbit_coord((int)compact3(k), orbit_axis(ob, 0), r & 1),
+                                                  orbit_coord((int)compact3(k >> 1), orbit_axis(ob, 1), r & 2),
+                                                  orbit_coord((int)compact3(k >> 2), orbit_axis(ob, 2), r & 4));
+                    if (j < 0)
+                        continue;
+                    if (lv.row0 + j >= nin)
+                        ck.fail(name, "input row out of range", lv.row0 + j, nin);
+                    if (present && !present(gr.level, j))
+                        continue;
+                    if (!((done >> (ob - 1)) & 1u))
+                        ck.fail(name, "an orbit with a source is in no segment", u, ob);
+                }
+            }
+    }
 }
 
 }  // namespace
@@ -132,11 +166,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
     const auto leaf_pend = fetch(p->d_leaf_pend, (size_t)p->n_leaf);
     const int64_t ncell = (int64_t)p->d.nx * p->d.ny * p->d.nz;
     const auto cell_slot = p->lat_near ? fetch(p->d_cell_slot, (size_t)ncell) : std::vector<int32_t>();
-    std::vector<int32_t> coff, roff;
-    if (L >= 2) {
-        coff = fetch(p->d_class_off, 8 * kClassOffsets * 4);
-        roff = fetch(p->d_rclass_off, 8 * kClassOffsets * 4);
-    }
     (void)hipSetDevice(cur);
 
     // target tables
@@ -202,26 +231,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
                 ck.fail("tmap", "entry out of range", v, p->lev[l].n_tgt);
         }
     }
-    // reverse interaction lists of the adjoint's M2L: offsets of the list and
-    // operator ids inside the 316 stored transposes
-    for (size_t e = 0; e < roff.size() && ck.ok; e += 4) {
-        const int mx = std::max(std::abs(roff[e]), std::max(std::abs(roff[e + 1]), std::abs(roff[e + 2])));
-        if (mx < 2 || mx > 3 || roff[e + 3] < 0 || roff[e + 3] >= kNumOffsets)
-            ck.fail("m2lT", "reverse list entry out of range", (long long)e, roff[e + 3]);
-    }
-    // the transposed M2L's offset table: (-d) of a reverse list entry, and
-    // an operator index inside the stored transposes (56 canonical ones
-    // with reflection bits in mixed plans, 316 in FP64)
-    if (p->d_tclass_off) {
-        const auto tco = fetch(p->d_tclass_off, (size_t)8 * kClassOffsets * 4);
-        const bool f64 = p->d.precision == GRAV_FP64;
-        for (size_t e = 0; e < tco.size() && ck.ok; e += 4) {
-            const int id = tco[e + 3] % kReflShift, refl = tco[e + 3] / kReflShift;
-            if (tco[e] != -roff[e] || tco[e + 1] != -roff[e + 1] || tco[e + 2] != -roff[e + 2] || tco[e + 3] < 0 ||
-                id >= (f64 ? kNumOffsets : kCanonOffsets) || refl > (f64 ? 0 : 7))
-                ck.fail("m2lT", "transposed offset entry out of range", (long long)e, tco[e + 3]);
-        }
-    }
     for (int l = 2; l < L && ck.ok; ++l) {
         const DevLev &lv = g.lev[l];
         for (int64_t i = 0; i < p->lev[l].n_tgt && ck.ok; ++i) {
@@ -243,110 +252,41 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
     }
 
     if (L >= 2 && ck.ok) {
-        // the forward M2L's stream-K schedule: segments cover every work item
-        // once, in order, one unit per segment; each unit lists its segments
-        // in order; every LE column maps to one valid (unit, column)
-        auto schedule = [&](const char *name, const int32_t *d_items, int64_t n_items, const int32_t *d_segs,
-                            int64_t nseg, const int32_t *d_wgseg, int32_t wgs, const int32_t *d_tstart,
-                            const int32_t *d_tsegs, int64_t nunit) {
-            const auto items = fetch(d_items, (size_t)std::max<int64_t>(1, n_items));
-            const auto segs = fetch(d_segs, (size_t)std::max<int64_t>(1, nseg) * 4);
-            const auto wgseg = fetch(d_wgseg, (size_t)wgs + 1);
-            const auto tstart = fetch(d_tstart, (size_t)nunit + 1);
-            const auto tsegs = fetch(d_tsegs, (size_t)std::max<int64_t>(1, nseg));
-            if (wgseg[0] != 0 || wgseg[wgs] != nseg)
-                ck.fail(name, "segment ranges do not cover the segments", wgseg[0], nseg);
-            int64_t next = 0;
-            for (int64_t sg = 0; sg < nseg && ck.ok; ++sg) {
-                const int32_t t = segs[4 * sg], ib = segs[4 * sg + 1], ie = segs[4 * sg + 2];
-                if (t < 0 || t >= nunit || ib != next || ie <= ib || ie > n_items)
-                    ck.fail(name, "segment out of order or range", sg, t);
-                for (int32_t it = ib; it < ie && ck.ok; ++it)
-                    if (items[it] < 0 || items[it] >= kClassOffsets)
-                        ck.fail(name, "work item offset out of range", it, items[it]);
-                next = ie;
-            }
-            if (ck.ok && next != n_items)
-                ck.fail(name, "segments do not cover the work items", next, n_items);
-            if (ck.ok && (tstart[0] != 0 || tstart[nunit] != nseg))
-                ck.fail(name, "unit segment lists do not cover the segments", tstart[nunit], nseg);
-            for (int64_t t = 0; t < nunit && ck.ok; ++t)
-                for (int32_t j = tstart[t]; j < tstart[t + 1] && ck.ok; ++j)
-                    if (tsegs[j] < 0 || tsegs[j] >= nseg || segs[4 * tsegs[j]] != t ||
-                        (j > tstart[t] && tsegs[j] <= tsegs[j - 1]))
-                        ck.fail(name, "unit segment list inconsistent", t, j);
-        };
-        const TileRange &r = p->tiles[TK_M2L][0];
-        const int64_t upt = 64 / p->m2l_ncw;
-        if (p->m2l_wgs > 0) {
-            const int64_t nunit = p->m2l_nunit;
-            schedule("m2l", p->d_m2l_items, p->m2l_items, p->d_m2l_segs, p->m2l_nseg, p->d_m2l_wgseg, p->m2l_wgs,
-                     p->d_m2l_tseg_start, p->d_m2l_tsegs, nunit);
-            const auto colmap = fetch(p->d_m2l_colmap, (size_t)(p->n_tbox * p->B));
-            for (int64_t c = 0; c < p->n_tbox * p->B && ck.ok; ++c) {
-                const int32_t m = colmap[c];
-                const int64_t u = m >> 6;
-                if (m < 0 || u >= nunit || (m & 63) >= p->m2l_ncw ||
-                    (u % upt) * p->m2l_ncw + (m & 63) >= tiles[r.off + u / upt].ncol)
-                    ck.fail("m2l", "LE column without a unit column", c, m);
+        // the L2L's tiles: columns inside their class, every box once
+        const TileRange &r = p->tiles[TK_L2L][0];
+        std::vector<char> seen_le((size_t)p->n_tbox * p->B, 0);
+        for (int64_t t = 0; t < r.n && ck.ok; ++t) {
+            const GemmTile &tl = tiles[r.off + t];
+            const LevelInfo &lv = p->lev[tl.level];
+            if (tl.ncol < 1 || tl.ncol > kTileCols || tl.col0 < 0 ||
+                tl.col0 + tl.ncol > (lv.class_start[tl.cls + 1] - lv.class_start[tl.cls]) * p->B)
+                ck.fail("l2l", "tile outside its class", t, tl.ncol);
+            for (int64_t c = tl.col0; c < tl.col0 + tl.ncol && ck.ok; ++c) {
+                const int64_t box = torder[p->tbox_off[tl.level] + lv.class_start[tl.cls] + c / p->B];
+                if (seen_le[(lv.tgt_off + box) * p->B + c % p->B]++)
+                    ck.fail("l2l", "two columns write one expansion", box, tl.level);
             }
         }
-        // the transposed M2L (adjoint): the same schedule checks; its tiles
-        // address the column blocks, its columns map to units and to ME
-        // columns, each ME column at most once; the gather regions lie in
+        for (size_t i = 0; i < seen_le.size() && ck.ok; ++i)
+            if (!seen_le[i])
+                ck.fail("l2l", "expansion in no tile", (long long)i, (long long)seen_le.size());
+        // both M2L directions
+        const OctGeom fg = octet_geom(p, false), tg = octet_geom(p, true);
+        check_octets(ck, "m2l", p, p->m2l, fg, p->n_me, p->n_tbox, true, nullptr);
+        // the gather regions hold every target box within reach and lie in
         // the target maps (source block + halo 3)
-        if (ck.ok) {
-            const int64_t uptt = 64 / p->m2lt_ncw, nunit = p->m2lt_nunit, ntile = nunit / uptt;
-            if (p->m2lt_wgs > 0)
-                schedule("m2lT", p->d_m2lt_items, p->m2lt_items, p->d_m2lt_segs, p->m2lt_nseg, p->d_m2lt_wgseg,
-                         p->m2lt_wgs, p->d_m2lt_tseg_start, p->d_m2lt_tsegs, nunit);
-            const auto ttiles = fetch(p->d_m2lt_tiles, (size_t)std::max<int64_t>(1, ntile));
-            const auto sorder = fetch(p->d_sorder, (size_t)std::max<int64_t>(1, p->n_me));
-            for (int64_t t = 0; t < ntile && ck.ok; ++t) {
-                const GemmTile &tl = ttiles[t];
-                if (tl.level < 2 || tl.level > L || tl.cls < 0 || tl.cls > 7 || tl.ncol < 1 || tl.ncol > kTileCols)
-                    ck.fail("m2lT", "tile out of range", t, tl.level);
-                else {
-                    const LevelInfo &lv = p->lev[tl.level];
-                    const int64_t nb = lv.col_class_start[tl.cls + 1] - lv.col_class_start[tl.cls];
-                    if (tl.col0 < 0 || tl.col0 + tl.ncol > nb * p->B)
-                        ck.fail("m2lT", "tile columns outside its class", t, tl.col0);
-                }
-            }
-            for (int l = 2; l <= L && ck.ok; ++l) {
-                const LevelInfo &lv = p->lev[l];
-                if (lv.col_class_start[8] > lv.n_src)
-                    ck.fail("m2lT", "column block larger than the source block", l, lv.col_class_start[8]);
-                for (int64_t i = 0; i < lv.col_class_start[8] && ck.ok; ++i)
-                    if (sorder[lv.me_off + i] < 0 || sorder[lv.me_off + i] >= lv.n_src)
-                        ck.fail("m2lT", "column box outside the source block", l, sorder[lv.me_off + i]);
-                for (int a = 0; a < 3 && ck.ok; ++a)
-                    if (lv.gns[a] > 0 && (lv.gs0[a] < lv.s0[a] - 3 || lv.gs0[a] + lv.gns[a] > lv.s0[a] + lv.ns[a] + 3))
-                        ck.fail("m2lT", "gather region outside the target map", l, a);
-            }
-            const auto colmap = fetch(p->d_m2lt_colmap, (size_t)std::max<int64_t>(1, p->m2lt_ncols));
-            const auto colbox = fetch(p->d_m2lt_colbox, (size_t)std::max<int64_t>(1, p->m2lt_ncols));
-            std::vector<char> seen((size_t)std::max<int64_t>(1, p->n_me * p->B), 0);
-            for (int64_t c = 0; c < p->m2lt_ncols && ck.ok; ++c) {
-                const int32_t m = colmap[c];
-                const int64_t u = m >> 6;
-                if (m < 0 || u >= nunit || (m & 63) >= p->m2lt_ncw ||
-                    (u % uptt) * p->m2lt_ncw + (m & 63) >= ttiles[u / uptt].ncol)
-                    ck.fail("m2lT", "column without a unit column", c, m);
-                else if (colbox[c] < 0 || colbox[c] >= p->n_me * p->B || seen[colbox[c]]++)
-                    ck.fail("m2lT", "ME column out of range or repeated", c, colbox[c]);
-            }
-        }
+        for (int l = 2; l <= L && ck.ok; ++l)
+            for (int a = 0; a < 3 && ck.ok; ++a)
+                if (tg.lev[l].ns[a] > 0 && (tg.lev[l].s0[a] < p->lev[l].s0[a] - 3 ||
+                                            tg.lev[l].s0[a] + tg.lev[l].ns[a] > p->lev[l].s0[a] + p->lev[l].ns[a] + 3))
+                    ck.fail("m2lT", "gather region outside the target map", l, a);
+        check_octets(ck, "m2lT", p, p->m2lt, tg, p->n_grow, p->n_me, false, [&](int l, int32_t j) {
+            const OctLev &t = tg.lev[l];
+            return tmap_lookup(g.lev[l], tmap.data(), 3, t.s0[0] + j % t.ns[0], t.s0[1] + j / t.ns[0] % t.ns[1],
+                               t.s0[2] + j / (t.ns[0] * t.ns[1])) >= 0;
+        });
     }
     if (L >= 2 && ck.ok) {
-        const int64_t xme = p->n_me * p->B, xle = p->n_tbox * p->B;
-        std::vector<char> w;
-        {
-            const TileRange &r = p->tiles[TK_M2L][0];
-            ResM2L res{&g, tiles.data() + r.off, tkey.data(), torder.data(), coff.data()};
-            check_stage(ck, "m2l", res, r, p->split[TK_M2L],
-                        p->d.precision == GRAV_FP64 ? kNumOffsets : kCanonOffsets, xme, xle, w);
-        }
         // M2M / M2M^T: every parent of a level >= 3 box lies in the block above
         for (int l = 3; l <= L && ck.ok; ++l) {
             const DevLev &lv = g.lev[l];

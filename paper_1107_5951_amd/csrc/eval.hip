@@ -6,6 +6,7 @@
 #include <cmath>
 
 #include "harmonics.hpp"
+#include "octet.hpp"
 #include "resolve.hpp"
 
 #ifndef GRAV_M2M_LDS_MIN_WG
@@ -550,129 +551,29 @@ k_l2l_mfma(DevGeom g, const GemmTile *tiles, int stride, const uint32_t *tkey, c
         dst[16 * rb + kr + 4 * r] = old[r] + acc[r];
 }
 
-// The multipole expansions regathered for the M2L's B operand, in the
-// M2L's element type.  Per level, boxes are ordered by parity class (x
-// fastest within a class, see class_split) and the coefficients chunk-major
-// in the M2L's interleaved contraction order:
-//   out[level][q][kr][pos * B + model][u],  coefficient kmap[4 (4 q + kr) + u]
-// (-1: zero), NP = 4 q + kr planes: in natural order coefficient 4 (4 q + u)
-// + kr; for the reflection-orbit M2L position 4 u + kr of sign class q.
-// The source boxes that one wave's 16 columns read at one interaction offset
-// are boxes of a single class with consecutive x, so each B fragment load
-// of the M2L covers a few contiguous runs instead of 64 scattered lines.
-// Boxes farther than 3 boxes from every target box of their level (for
-// surface stations, the deep part of the mesh) are skipped: the M2L reads
-// only sources within its interaction offsets.  One thread per (box, model,
-// chunk q, sub-row kr).
-template <typename T>
-__global__ void __launch_bounds__(256) k_me_gather(DevGeom g, const double *me, int64_t n_me, const int32_t *kmap,
-                                                   int NP, T *out)
+// Expansions in FP32 for the mixed M2L, natural order.  Boxes farther than 3
+// boxes from every target box of their level are skipped (for
+// surface stations, the deep part of the mesh): no M2L reads them.  One thread per four coefficients.
+__global__ void __launch_bounds__(256)
+k_me_f32(DevGeom g, const double *src, int64_t n4, float *dst)
 {
-    // the coefficient map (at most PS <= 256 entries) through LDS: its
-    // loads would otherwise sit in a dependent chain before the gathers
-    __shared__ int32_t km[256];
-    for (int e = threadIdx.x; e < 4 * NP; e += blockDim.x)
-        km[e] = kmap[e];
-    __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_me * g.B * NP)
+    if (i >= n4)
         return;
-    const int plane = (int)(i % NP);
-    const int64_t col = i / NP;  // box * B + model
-    const int bm = (int)(col % g.B);
-    const int64_t box = col / g.B;
+    const int64_t box = i / ((int64_t)(g.PS / 4) * g.B);
     int l = 2;
     while (l < g.L && box >= g.lev[l + 1].me_off)
         ++l;
     const DevLev &lv = g.lev[l];
     const int64_t j = box - lv.me_off;
-    const int ax = lv.s0[0] + (int)(j % lv.ns[0]), ay = lv.s0[1] + (int)((j / lv.ns[0]) % lv.ns[1]),
-              az = lv.s0[2] + (int)(j / ((int64_t)lv.ns[0] * lv.ns[1]));
-    if (ax < lv.need_lo[0] || ax > lv.need_hi[0] || ay < lv.need_lo[1] || ay > lv.need_hi[1] ||
-        az < lv.need_lo[2] || az > lv.need_hi[2])
-        return;  // no target box within reach: the M2L never reads this expansion
-    int first[3], cnt[3];
-    const int64_t pos = class_split(lv, (ax & 1) | ((ay & 1) << 1) | ((az & 1) << 2), first, cnt) +
-                        ((int64_t)((az - first[2]) >> 1) * cnt[1] + ((ay - first[1]) >> 1)) * cnt[0] +
-                        ((ax - first[0]) >> 1);
-    const int64_t nB = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2] * g.B;
-    const double *src = me + col * g.PS;
-    T *dst = out + lv.me_off * g.B * (4 * NP) + ((int64_t)plane * nB + pos * g.B + bm) * 4;
-    T v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = km[4 * plane + u];
-        v[u] = k >= 0 ? (T)src[k] : (T)0;
-    }
-    if constexpr (sizeof(T) == 4) {
-        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            dst[u] = v[u];
-    }
-}
-template __global__ void k_me_gather<double>(DevGeom, const double *, int64_t, const int32_t *, int, double *);
-template __global__ void k_me_gather<float>(DevGeom, const double *, int64_t, const int32_t *, int, float *);
-
-// out[i] = sum over s < S of part[s * n + i], in order s = 0, 1, ..., in FP64
-template <typename T>
-__global__ void __launch_bounds__(256) k_sum_parts(const T *part, int S, int64_t n, double *out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
+    const int x = lv.s0[0] + (int)(j % lv.ns[0]), y = lv.s0[1] + (int)((j / lv.ns[0]) % lv.ns[1]),
+              z = lv.s0[2] + (int)(j / ((int64_t)lv.ns[0] * lv.ns[1]));
+    if (x < lv.need_lo[0] || x > lv.need_hi[0] || y < lv.need_lo[1] || y > lv.need_hi[1] || z < lv.need_lo[2] ||
+        z > lv.need_hi[2])
         return;
-    double acc = (double)part[i];
-    for (int s = 1; s < S; ++s)
-        acc += (double)part[(int64_t)s * n + i];
-    out[i] = acc;
+    const double2 a = reinterpret_cast<const double2 *>(src)[2 * i], b = reinterpret_cast<const double2 *>(src)[2 * i + 1];
+    reinterpret_cast<float4 *>(dst)[i] = make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
 }
-template __global__ void k_sum_parts<double>(const double *, int, int64_t, double *);
-template __global__ void k_sum_parts<float>(const float *, int, int64_t, double *);
-
-// LE from the forward M2L's segment slots: element (column, k) of the LE is
-// the sum, over the segments of the column's unit in their order, of the
-// slot entry (column in unit, k), in FP64.  A unit without segments (no
-// source box at any offset) gives zero.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_m2l_sum(const T *part, const int32_t *colmap, const int32_t *tseg_start, const int32_t *tsegs, int64_t n, int PS,
-          int ncw, double *le)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    const int64_t col = i / PS;
-    const int k = (int)(i - col * PS);
-    const int32_t m = colmap[col];
-    const int t = m >> 6, cl = m & 63;
-    const int j0 = tseg_start[t], j1 = tseg_start[t + 1];
-    double acc = 0.0;
-    // SB slots at a time: their indices, then their values, are loaded
-    // together (no chain of dependent loads); the sum stays in slot order.
-    // A unit typically spans one or two workers' shares (the 256^3 plan:
-    // about 400 items per worker, 189 per unit), so one round usually does.
-    constexpr int SB = 4;
-    for (int jb = j0; jb < j1; jb += SB) {
-        int32_t sl[SB];
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            sl[u] = jb + u < j1 ? tsegs[jb + u] : -1;
-        T v[SB];
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            v[u] = sl[u] >= 0 ? part[((int64_t)sl[u] * ncw + cl) * PS + k] : (T)0;
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            if (jb + u < j1)
-                acc += (double)v[u];
-    }
-    le[i] = acc;
-}
-template __global__ void k_m2l_sum<double>(const double *, const int32_t *, const int32_t *, const int32_t *,
-                                           int64_t, int, int, double *);
-template __global__ void k_m2l_sum<float>(const float *, const int32_t *, const int32_t *, const int32_t *,
-                                          int64_t, int, int, double *);
 
 // --------------------------------------------------------------------------
 // Near field (P2P): direct sum over the quadrature points of the cells of the
@@ -1427,31 +1328,6 @@ void stage_end(Plan *p, hipStream_t s)
     ++p->n_stage_used;
 }
 
-template <typename T>
-static M2LRun<T> forward_m2l(const Plan *p, const T *K)
-{
-    M2LRun<T> r;
-    r.tiles = (const GemmTile *)(p->d_tiles + p->tiles[TK_M2L][0].off);
-    r.keys = (const uint32_t *)p->d_tkey;
-    r.order = (const int32_t *)p->d_torder;
-    r.class_off = (const int32_t *)p->d_class_off;
-    r.K = K;
-    r.b_in = reinterpret_cast<const T *>(p->d_meg);
-    r.segs = (const int32_t *)p->d_m2l_segs;
-    r.wgseg = (const int32_t *)p->d_m2l_wgseg;
-    r.items = (const int32_t *)p->d_m2l_items;
-    r.part = reinterpret_cast<T *>(p->d_part);
-    r.wgs = p->m2l_wgs;
-    r.nset = p->m2l_nset;
-    r.nc = p->m2l_nc;
-    if (sizeof(T) == 4 && p->m2l_orbit) {
-        r.K = reinterpret_cast<const T *>(p->d_k32o);
-        r.orbtab = (const int32_t *)p->d_orbtab;
-        r.ccoef = (const int32_t *)p->d_ccoef;
-    }
-    return r;
-}
-
 static grav_status launch_m2m(Plan *p, const DevGeom &g, int l, hipStream_t s)
 {
     const int RB = p->PS / 16;
@@ -1533,11 +1409,11 @@ static grav_status launch_p2m(Plan *p, const DevGeom &g, const double *rho, hipS
 
 static grav_status launch_l2l(Plan *p, const DevGeom &g, int l, hipStream_t s)
 {
-    const TileRange &all = p->tiles[TK_M2L][0];
-    const TileRange &r = p->tiles[TK_M2L][l];
+    const TileRange &all = p->tiles[TK_L2L][0];
+    const TileRange &r = p->tiles[TK_L2L][l];
     if (r.n == 0)
         return GRAV_OK;
-    const int S = p->split[TK_M2L];
+    const int S = p->split[TK_L2L];
     const GemmTile *t0 = (const GemmTile *)(p->d_tiles + all.off) + r.off * S;
     dim3 grid((unsigned)r.n, (unsigned)(p->PS / 16)), blk(256);
     // one workgroup per tile with all row blocks once the level has enough
@@ -1655,46 +1531,21 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
         for (int l = L - 1; l >= 2; --l)
             GRAV_CHECK(launch_m2m(p, g, l, s));
         stage_end(p, s);
-        stage_begin(p, "me_gather", s);
-        {
-            const int64_t n = p->n_me * p->B * p->m2l_npl;
-            const dim3 gg((unsigned)((n + 255) / 256));
-            const int32_t *kmap = (const int32_t *)p->d_kmap;
-            if (n == 0 || kmap == nullptr) {
-            } else if (p->d.precision == GRAV_FP64)
-                hipLaunchKernelGGL((k_me_gather<double>), gg, dim3(256), 0, s, g, (const double *)p->d_me, p->n_me,
-                                   kmap, p->m2l_npl, p->d_meg);
-            else
-                hipLaunchKernelGGL((k_me_gather<float>), gg, dim3(256), 0, s, g, (const double *)p->d_me, p->n_me,
-                                   kmap, p->m2l_npl, reinterpret_cast<float *>(p->d_meg));
-            GRAV_HIP(hipGetLastError());
-        }
-        stage_end(p, s);
         stage_begin(p, "m2l", s);
-        if (p->tiles[TK_M2L][0].n > 0) {
-            // the segment slots are sized for FP64; the regathered expansions
-            // are FP32 in mixed plans (see k_me_gather)
-            if (p->d.precision == GRAV_FP64)
-                GRAV_CHECK(launch_m2l<double>(p, g, s, forward_m2l<double>(p, p->d_k64)));
-            else
-                GRAV_CHECK(launch_m2l<float>(p, g, s, forward_m2l<float>(p, p->d_k32)));
+        {
+            const OctGeom og = octet_geom(p, false);
+            if (p->d.precision == GRAV_FP64) {
+                GRAV_CHECK(launch_m2l<double>(p, p->m2l, s, og, p->d_me, p->d_le));
+            } else {
+                float *rows = reinterpret_cast<float *>(p->d_rows);
+                const int64_t n4 = p->n_me * p->B * (p->PS / 4);
+                hipLaunchKernelGGL(k_me_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
+                                   (const double *)p->d_me, n4, rows);
+                GRAV_HIP(hipGetLastError());
+                GRAV_CHECK(launch_m2l<float>(p, p->m2l, s, og, rows, p->d_le));
+            }
         }
         stage_end(p, s);
-        {
-            stage_begin(p, "m2l_sum", s);
-            const int64_t n = p->n_tbox * p->B * p->PS;
-            const dim3 gs((unsigned)((n + 255) / 256));
-            if (p->d.precision == GRAV_FP64)
-                hipLaunchKernelGGL(k_m2l_sum<double>, gs, dim3(256), 0, s, (const double *)p->d_part,
-                                   (const int32_t *)p->d_m2l_colmap, (const int32_t *)p->d_m2l_tseg_start,
-                                   (const int32_t *)p->d_m2l_tsegs, n, p->PS, p->m2l_ncw, p->d_le);
-            else
-                hipLaunchKernelGGL(k_m2l_sum<float>, gs, dim3(256), 0, s, (const float *)p->d_part,
-                                   (const int32_t *)p->d_m2l_colmap, (const int32_t *)p->d_m2l_tseg_start,
-                                   (const int32_t *)p->d_m2l_tsegs, n, p->PS, p->m2l_ncw, p->d_le);
-            GRAV_HIP(hipGetLastError());
-            stage_end(p, s);
-        }
         stage_begin(p, "l2l", s);
         for (int l = 3; l <= L; ++l)
             GRAV_CHECK(launch_l2l(p, g, l, s));

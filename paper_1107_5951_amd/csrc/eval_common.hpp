@@ -28,59 +28,14 @@ struct DevGeom {
     double G, h;
 };
 
-// Boxes of one parity class (bit a of cls = parity of coordinate a) of a
-// level's source block, in x-fastest order; classes follow each other in
-// order 0..7.  Returns the class's first box position and, per axis, its
-// first absolute coordinate and box count.
-__host__ __device__ inline int64_t class_split(const DevLev &lv, int cls, int first[3], int cnt[3])
-{
-    int64_t start = 0;
-    for (int c = 0; c <= cls; ++c) {
-        int64_t n = 1;
-        for (int a = 0; a < 3; ++a) {
-            const int f = lv.s0[a] + ((((c >> a) & 1) - lv.s0[a]) & 1);
-            const int k = (lv.ns[a] - (f - lv.s0[a]) + 1) / 2;
-            const int kk = k > 0 ? k : 0;
-            if (c == cls) {
-                first[a] = f;
-                cnt[a] = kk;
-            }
-            n *= kk;
-        }
-        if (c < cls)
-            start += n;
-    }
-    return start;
-}
-
 DevGeom make_geom(const Plan *p);
+struct OctGeom;
+// The M2L of one direction on `in` ([row][model][PS], the element type of
+// the plan's M2L), setting the expansions of the octets' boxes in `out`.
 template <typename T>
-__global__ void k_sum_parts(const T *part, int S, int64_t n, double *out);
-// One M2L problem on the stream-K kernel: the forward M2L (columns are
-// target boxes, B the regathered multipole expansions) or the adjoint's
-// transposed M2L (columns are source boxes, B the regathered adjoint local
-// expansions, operators K_d^T).
-template <typename T>
-struct M2LRun {
-    const GemmTile *tiles;
-    const uint32_t *keys;      // Morton key of each column box (per level, from lev.tbox_off)
-    const int32_t *order;      // class-grouped column order -> box (per level, from lev.tbox_off)
-    const int32_t *class_off;  // [8][189][4] (dx, dy, dz, operator) per column class
-    const T *K;                // operators in the panel layout
-    const T *b_in;             // regathered B operand
-    const int32_t *segs, *wgseg, *items;
-    T *part;                   // segment slots
-    int32_t wgs;               // workgroups (0: nothing to do)
-    int nset;                  // operand register sets of the FP32 kernel
-    int nc;                    // 16-column blocks per wave (FP32: 2 or 4; FP64: 1)
-    // the reflection-orbit M2L (forward, mixed plans): items are canonical
-    // offsets, K the class-blocked canonical operators, orbtab the class
-    // offset of each reflection, ccoef the coefficient of each class row
-    const int32_t *orbtab = nullptr, *ccoef = nullptr;
-};
-template <typename T>
-grav_status launch_m2l(const Plan *p, const DevGeom &g, hipStream_t s, const M2LRun<T> &r);
-grav_status m2l_resident_workers(const Plan *p, int nset, int nc, bool orbit, int *workers);
+grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in, double *out);
+OctInfo octet_info(int P, bool f64);
+grav_status m2l_resident_workgroups(const Plan *p, int nc, int *workers);
 grav_status begin_call(Plan *p, hipStream_t s);
 grav_status end_call(Plan *p, hipStream_t s);
 

@@ -12,15 +12,15 @@
 #include <cstring>
 #include <new>
 
+#include "octet.hpp"
 #include "resolve.hpp"
 #include "internal.hpp"
 #include "operators.hpp"
 
-// Upper bound on the one-wave workgroups of the forward M2L's stream-K
-// schedule; the plan takes as many as the device holds at once
-// (m2l_resident_workers), up to this.
-#ifndef GRAV_M2L_WAVES
-#define GRAV_M2L_WAVES 8192
+// Wide M2L units (see build_octet_schedule) from this many work items per
+// resident workgroup on.
+#ifndef GRAV_M2L_WIDE_ROUNDS
+#define GRAV_M2L_WIDE_ROUNDS 2
 #endif
 
 namespace grav {
@@ -309,17 +309,19 @@ void free_plan(Plan *p)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p->device);
     void *bufs[] = {p->d_points, p->d_perm, p->d_tpos, p->d_tleaf, p->d_leaf_start, p->d_tkey,
-                    p->d_tparent, p->d_torder, p->d_tiles, p->d_class_off, p->d_rclass_off,
-                    p->d_tmap, p->d_tchild, p->d_geom, p->d_pm, p->d_pm_sw, p->d_m2m,
-                    p->d_l2l, p->d_k64, p->d_k32, p->d_me,
-                    p->d_le, p->d_near, p->d_part, p->d_tn64, p->d_tn32, p->d_m2m_sw, p->d_l2l_sw, p->d_rho_blk, p->d_tl2p, p->d_dpart, p->d_meg, p->d_lat_tab, p->d_m2l_items, p->d_m2l_segs,
-                    p->d_m2l_wgseg, p->d_m2l_tseg_start, p->d_m2l_tsegs, p->d_m2l_colmap,
-                    p->d_cell_slot, p->d_leaf_pend, p->d_m2lt_tiles, p->d_m2lt_items, p->d_m2lt_segs,
-                    p->d_m2lt_wgseg, p->d_m2lt_tseg_start, p->d_m2lt_tsegs, p->d_m2lt_colmap, p->d_m2lt_colbox,
-                    p->d_skey, p->d_sorder, p->d_tclass_off, p->d_kt64, p->d_kt32, p->d_leg, p->d_partt, p->d_kt32o, p->d_orbtab_t,
+                    p->d_tparent, p->d_torder, p->d_tiles, p->d_class_off, p->d_tmap, p->d_tchild, p->d_geom,
+                    p->d_pm, p->d_pm_sw, p->d_m2m, p->d_l2l, p->d_me, p->d_le, p->d_near, p->d_part, p->d_rows,
+                    p->d_tn64, p->d_tn32, p->d_m2m_sw, p->d_l2l_sw, p->d_rho_blk, p->d_tl2p, p->d_dpart,
+                    p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
                     p->d_m2mt_sw, p->d_l2lt_sw, p->d_l2l_msw, p->d_pmt_sw, p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
-                    p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
-                    p->d_k32o, p->d_orbtab, p->d_ccoef, p->d_kmap};
+                    p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves};
+    for (OctPlan *o : {&p->m2l, &p->m2lt}) {
+        void *ob[] = {o->d_key, o->d_child, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
+                      o->d_ops};
+        for (void *b : ob)
+            if (b)
+                (void)hipFree(b);
+    }
     for (void *b : bufs)
         if (b)
             (void)hipFree(b);
@@ -385,24 +387,8 @@ grav_status validate(const grav_plan_desc *d)
     return GRAV_OK;
 }
 
-// Index of the operator of offset |d| (components 0..3, largest >= 2) among
-// the 56 stored for the mixed-precision forward M2L, z slowest, x fastest.
-// Sign class of real coefficient c under the z, y and x reflections (bits
-// 2, 1, 0; the bits of the reflection index of an offset): degree n block of
-// 2n+1 values, the real part of order 0, then real and imaginary parts of
-// orders 1..n; z -> -z gives (-1)^(n+m), y -> -y -1 on imaginary parts, x ->
-// -x (-1)^m on real and -(-1)^m on imaginary parts.
-static int sign_class(int c)
-{
-    int n = 0;
-    while ((n + 1) * (n + 1) <= c)
-        ++n;
-    const int i = c - n * n;
-    const int m = (i + 1) / 2;
-    const int im = (i > 0 && (i & 1) == 0) ? 1 : 0;
-    return (((n + m) & 1) << 2) | (im << 1) | ((m + im) & 1);
-}
-
+// Index of offset |d| (components 0..3, largest >= 2) among the 56 canonical
+// ones, z slowest, x fastest.
 int canon_index(int ax, int ay, int az)
 {
     int k = 0;
@@ -418,53 +404,25 @@ int canon_index(int ax, int ay, int az)
     return -1;
 }
 
-// The 316 M2L offsets (2 <= |d|_inf <= 3), and per child-parity class the
-// 189 valid ones, entries (dx, dy, dz, operator).  Forward: a target box of
-// class c sees sources at T + d for d_a in [-2 - c_a, 3 - c_a]; the operator
-// field is, with `canonical`, the index of |d| among the 56 stored operators
-// plus kReflShift times the reflection bits (bit a set where d_a < 0), else
-// the offset id.  Transposed: a source box S of class c
-// feeds targets T = S - d whose class admits d; the operator field is the
-// offset id (0..315, the transposed operators are stored per offset).
-void offsets_tables(std::vector<int> &all, std::vector<int32_t> &fwd, std::vector<int32_t> &rev, bool canonical)
+// Per child-parity class the 189 M2L offsets (2 <= |d|_inf <= 3), entries
+// (dx, dy, dz, canonical index of |d|): a target box of class c sees sources
+// at T + d for d_a in [-2 - c_a, 3 - c_a].
+std::vector<int32_t> offsets_table()
 {
-    all.clear();
-    for (int dz = -3; dz <= 3; ++dz)
-        for (int dy = -3; dy <= 3; ++dy)
-            for (int dx = -3; dx <= 3; ++dx)
-                if (std::max(std::abs(dx), std::max(std::abs(dy), std::abs(dz))) >= 2) {
-                    all.push_back(dx);
-                    all.push_back(dy);
-                    all.push_back(dz);
-                }
-    fwd.assign(8 * kClassOffsets * 4, 0);
-    rev.assign(8 * kClassOffsets * 4, 0);
+    std::vector<int32_t> fwd(8 * kClassOffsets * 4, 0);
     for (int c = 0; c < 8; ++c) {
-        int nf = 0, nr = 0;
-        for (int id = 0; id < (int)all.size() / 3; ++id) {
-            const int *d = &all[3 * id];
-            bool okf = true, okr = true;
-            for (int a = 0; a < 3; ++a) {
-                const int pc = (c >> a) & 1;           // target class bit (forward)
-                if (d[a] < -2 - pc || d[a] > 3 - pc)
-                    okf = false;
-                const int pt = ((c >> a) - d[a]) & 1;  // class bit of T = S - d
-                if (d[a] < -2 - pt || d[a] > 3 - pt)
-                    okr = false;
-            }
-            if (okf) {
-                int32_t *e = &fwd[(c * kClassOffsets + nf++) * 4];
-                const int refl = (d[0] < 0 ? 1 : 0) | (d[1] < 0 ? 2 : 0) | (d[2] < 0 ? 4 : 0);
-                e[0] = d[0], e[1] = d[1], e[2] = d[2];
-                e[3] = canonical ? canon_index(std::abs(d[0]), std::abs(d[1]), std::abs(d[2])) + kReflShift * refl
-                                 : id;
-            }
-            if (okr) {
-                int32_t *e = &rev[(c * kClassOffsets + nr++) * 4];
-                e[0] = d[0], e[1] = d[1], e[2] = d[2], e[3] = id;
-            }
-        }
+        int nf = 0;
+        for (int dz = -2 - (c >> 2 & 1); dz <= 3 - (c >> 2 & 1); ++dz)
+            for (int dy = -2 - (c >> 1 & 1); dy <= 3 - (c >> 1 & 1); ++dy)
+                for (int dx = -2 - (c & 1); dx <= 3 - (c & 1); ++dx) {
+                    const int ci = canon_index(std::abs(dx), std::abs(dy), std::abs(dz));
+                    if (ci < 0)
+                        continue;
+                    int32_t *e = &fwd[(c * kClassOffsets + nf++) * 4];
+                    e[0] = dx, e[1] = dy, e[2] = dz, e[3] = ci;
+                }
     }
+    return fwd;
 }
 
 // Position of value e (of E per lane) of a lane in a set of MFMA operand
@@ -474,29 +432,6 @@ void offsets_tables(std::vector<int> &all, std::vector<int32_t> &fwd, std::vecto
 static inline size_t frag_pos(int lane, int e, int G)
 {
     return ((size_t)(e / G) * 64 + lane) * G + e % G;
-}
-
-// M2L operand layout (all row blocks per lane): k step ks (0 .. PS/4 - 1)
-// and instruction sub-row kr = lane / 16 contract coefficient 4 ks + kr (the
-// M2L's B operand is regathered in the same order; this puts the padding
-// coefficients in whole trailing k steps).  The fragments of four
-// consecutive k steps (ks = 4 q + u) and all row blocks form one set of
-// E = 4 RB values per lane, value e = u * RB + rb:
-// set q, value (lane, e)  =  m[16 rb + lane % 16][4 (4 q + u) + lane / 16],
-// except that with tail4 the last row block (at most four rows of
-// coefficients) takes row 16 rb + lane % 4, the A operand of the 4x4x1
-// instructions that replace its 16x16x4 ones.
-void swizzle_panel(const double *m, int PS, int G, double *dst, bool tail4)
-{
-    const int RB = PS / 16;
-    for (int q = 0; q < RB; ++q)
-        for (int lane = 0; lane < 64; ++lane)
-            for (int u = 0; u < 4; ++u)
-                for (int rb = 0; rb < RB; ++rb) {
-                    const int row = 16 * rb + (tail4 && rb == RB - 1 ? (lane & 3) : (lane & 15));
-                    const int col = 4 * (4 * q + u) + (lane >> 4);
-                    dst[(size_t)q * 64 * 4 * RB + frag_pos(lane, u * RB + rb, G)] = m[(size_t)row * PS + col];
-                }
 }
 
 // Row-blocked layout (M2M, L2L), contraction order kr * PS/4 + ks (their B
@@ -523,6 +458,80 @@ grav_status upload(Plan *p, T **dst, const std::vector<T> &src)
     if (!src.empty())
         GRAV_HIP(hipMemcpyAsync(*dst, src.data(), sizeof(T) * src.size(), hipMemcpyHostToDevice, p->bs));
     GRAV_HIP(hipStreamSynchronize(p->bs));
+    return GRAV_OK;
+}
+
+// The octet M2L's operators as MFMA A fragments, [orbit - 1][parity][part of
+// the row blocks][k step][EA values per lane, see frag_at].  The
+// image r of orbit o lies at offset e(r) from the (+,+,+) child; the forward
+// takes K_e, the transposed M2L (a source box fed by the target box at e) the
+// transpose of K_{-e}, both from the canonical operators by reflection.
+template <class T>
+grav_status upload_octet_operators(Plan *p, const std::vector<std::vector<double>> &kc, bool transposed, OctPlan &o)
+{
+    const int P2 = p->P2, PS = p->PS, RB = PS / 16;
+    const OctInfo in = octet_info(p->P, sizeof(T) == 8);
+    const size_t blk = (size_t)in.EA * 64, per = blk * in.KS;
+    std::vector<T> ops(per * kOrbits * 8 * in.RS, (T)0);
+    std::vector<int> cls(P2);
+    for (int k = 0; k < P2; ++k)
+        cls[k] = sign_class(k);
+    // sign tables: (-1)^popcount(a & b)
+    double sg[8][8];
+    for (int a = 0; a < 8; ++a)
+        for (int b = 0; b < 8; ++b)
+            sg[a][b] = odd_parity(a & b) ? -1.0 : 1.0;
+    std::vector<double> f((size_t)8 * P2 * P2);  // [chi][i][k]
+    for (int ob = 1; ob <= kOrbits; ++ob) {
+        const double *src[8];
+        int refl[8];
+        for (int r = 0; r < 8; ++r) {
+            int e[3];
+            refl[r] = 0;
+            for (int a = 0; a < 3; ++a) {
+                const int x = orbit_axis(ob, a);
+                e[a] = (r >> a & 1) ? -x : x - 1;
+                if ((transposed ? -e[a] : e[a]) < 0)
+                    refl[r] |= 1 << a;
+            }
+            const int ci = canon_index(std::abs(e[0]), std::abs(e[1]), std::abs(e[2]));
+            src[r] = ci >= 0 ? kc[ci].data() : nullptr;
+        }
+        for (int i = 0; i < P2; ++i)
+            for (int k = 0; k < P2; ++k) {
+                const size_t at = transposed ? (size_t)k * PS + i : (size_t)i * PS + k;
+                const int si = cls[i], sk = cls[k];
+                double v[8];
+                for (int r = 0; r < 8; ++r)
+                    v[r] = src[r] ? 0.125 * sg[r][sk] * sg[refl[r]][si ^ sk] * src[r][at] : 0.0;
+                for (int bit = 1; bit < 8; bit <<= 1)
+                    for (int r = 0; r < 8; ++r)
+                        if ((r & bit) == 0) {
+                            const double x = v[r], y = v[r | bit];
+                            v[r] = x + y;
+                            v[r | bit] = x - y;
+                        }
+                for (int x = 0; x < 8; ++x)
+                    f[((size_t)x * P2 + i) * P2 + k] = v[x];
+            }
+        for (int x = 0; x < 8; ++x)
+            for (int part = 0; part < in.RS; ++part) {
+                T *dst = ops.data() + (((size_t)(ob - 1) * 8 + x) * in.RS + part) * per;
+                for (int ks = 0; ks < in.KS; ++ks) {
+                    for (int rb = 0; rb < in.RBW; ++rb)
+                        for (int lane = 0; lane < 64; ++lane) {
+                            const int rbg = part * in.RBW + rb;
+                            const int row = 16 * rbg + (in.tail4 && rbg == RB - 1 ? (lane & 3) : (lane & 15));
+                            const int col = 4 * ks + (lane >> 4);
+                            if (row < P2 && col < P2)
+                                dst[ks * blk + frag_at<T>(in.EA, lane, rb)] = (T)f[((size_t)x * P2 + row) * P2 + col];
+                        }
+                }
+            }
+    }
+    T *d = nullptr;
+    GRAV_CHECK(upload(p, &d, ops));
+    o.d_ops = d;
     return GRAV_OK;
 }
 
@@ -630,262 +639,203 @@ grav_status build_operators(Plan *p)
         GRAV_CHECK(upload(p, &p->d_l2l_msw, lmsw));
     }
 
-    // M2L for all 316 offsets, swizzled for the MFMA A operand, and their transposes
-    const bool canonical = p->d.precision != GRAV_FP64;
-    std::vector<int> all;
-    std::vector<int32_t> fwd, rev;
-    offsets_tables(all, fwd, rev, canonical);
-    const size_t perp = (size_t)RB * 64 * 4 * RB;  // forward M2L: PS/4 k steps, grouped by four
-    // FP32 plans whose last row block holds at most four coefficient rows
-    // run it as 4x4 instructions: its A fragment repeats those rows
-    const bool tail4 = p->d.precision != GRAV_FP64 && p->P2 % 16 != 0 && p->P2 % 16 <= 4;
-    std::vector<double> k(perp * (canonical ? kCanonOffsets : kNumOffsets)), kt(k.size()), mt((size_t)PS * PS);
-    // Reflection-orbit M2L (mixed plans whose sign classes hold at most 16
-    // coefficients each): the coefficients of each class in natural order,
-    // and the 56 canonical operators with rows and columns grouped by class
-    // (class rb's rows, class q's columns: 16 x 16 blocks, one per (q, rb)),
-    // as A fragments [ci][q][rb][lane][u] = K[row rb, lane%16][col q, 4 u +
-    // lane/16]
-    std::vector<int32_t> ccoef(8 * 16, -1);
-    {
-        int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        // (the kernel addresses a level's regathered expansions with 32-bit
-        // byte offsets)
-        bool fits = canonical && p->L >= 2 && p->P >= GRAV_M2L_ORB_MIN_P &&
-                    (int64_t)p->n_me * p->B * 128 * 4 < (int64_t(1) << 32);
-        for (int c = 0; c < p->P2; ++c) {
-            const int s = sign_class(c);
-            if (cnt[s] >= 16)
-                fits = false;
-            else
-                ccoef[s * 16 + cnt[s]] = c;
-            ++cnt[s];
-        }
-        p->m2l_orbit = fits;  // tentative: build_tiles keeps it where it pays
-        p->m2l_npl = PS / 4;
+    GRAV_CHECK(upload(p, &p->d_class_off, offsets_table()));
+    if (p->M == 0)
+        return GRAV_OK;
+    // M2L over sibling octets: F_{chi,o} of both directions (octet.hpp)
+    std::vector<std::vector<double>> kc(kCanonOffsets, std::vector<double>((size_t)PS * PS));
+    for (int z = 0; z <= 3; ++z)
+        for (int y = 0; y <= 3; ++y)
+            for (int x = 0; x <= 3; ++x) {
+                const int ci = canon_index(x, y, z);
+                if (ci < 0)
+                    continue;
+                // source = target + d  =>  target centre - source centre = -d
+                const double dd[3] = {-(double)x, -(double)y, -(double)z};
+                m2l_matrix(P, dd, PS, kc[ci].data());
+            }
+    for (int t = 0; t < 2; ++t) {
+        OctPlan &o = t ? p->m2lt : p->m2l;
+        GRAV_CHECK(p->d.precision == GRAV_FP64 ? upload_octet_operators<double>(p, kc, t != 0, o)
+                                               : upload_octet_operators<float>(p, kc, t != 0, o));
     }
-    std::vector<double> ko(p->m2l_orbit ? (size_t)kCanonOffsets * 8 * 8 * 256 : 0, 0.0), kot(ko.size(), 0.0);
-    for (int id = 0; id < kNumOffsets; ++id) {
-        // source = target + d  =>  target centre - source centre = -d
-        const double dd[3] = {-(double)all[3 * id], -(double)all[3 * id + 1], -(double)all[3 * id + 2]};
-        m2l_matrix(P, dd, PS, m.data());
-        // the forward operators: all 316, or the 56 with non-negative
-        // components; the adjoint's transposes in the same layout (the
-        // reflections act on K_d^T as on K_d: K_d^T = S K_|d|^T S)
-        const int ci = canonical ? canon_index(all[3 * id], all[3 * id + 1], all[3 * id + 2]) : id;
-        if (ci >= 0) {
-            swizzle_panel(m.data(), PS, p->d.precision == GRAV_FP64 ? 2 : 4, k.data() + perp * ci, tail4);
-            for (int i = 0; i < PS; ++i)
-                for (int j = 0; j < PS; ++j)
-                    mt[(size_t)j * PS + i] = m[(size_t)i * PS + j];
-            swizzle_panel(mt.data(), PS, p->d.precision == GRAV_FP64 ? 2 : 4, kt.data() + perp * ci, tail4);
-            if (p->m2l_orbit)
-                for (int q = 0; q < 8; ++q)
-                    for (int rb = 0; rb < 8; ++rb)
-                        for (int lane = 0; lane < 64; ++lane)
-                            for (int u = 0; u < 4; ++u) {
-                                const int row = ccoef[rb * 16 + (lane & 15)], col = ccoef[q * 16 + 4 * u + (lane >> 4)];
-                                ko[((((size_t)ci * 8 + q) * 8 + rb) * 64 + lane) * 4 + u] =
-                                    row >= 0 && col >= 0 ? m[(size_t)row * PS + col] : 0.0;
-                                kot[((((size_t)ci * 8 + q) * 8 + rb) * 64 + lane) * 4 + u] =
-                                    row >= 0 && col >= 0 ? m[(size_t)col * PS + row] : 0.0;
-                            }
-        }
-    }
-    if (p->m2l_orbit) {
-        std::vector<float> ko32(ko.begin(), ko.end());
-        GRAV_CHECK(upload(p, &p->d_k32o, ko32));
-        std::vector<float> kot32(kot.begin(), kot.end());
-        GRAV_CHECK(upload(p, &p->d_kt32o, kot32));
-        GRAV_CHECK(upload(p, &p->d_ccoef, ccoef));
-    }
-    if (p->d.precision == GRAV_FP64) {
-        GRAV_CHECK(upload(p, &p->d_k64, k));
-        GRAV_CHECK(upload(p, &p->d_kt64, kt));
-    } else {
-        // the FP32 copies are exactly what both directions multiply by
-        std::vector<float> k32(k.begin(), k.end());
-        GRAV_CHECK(upload(p, &p->d_k32, k32));
-        std::vector<float> kt32(kt.begin(), kt.end());
-        GRAV_CHECK(upload(p, &p->d_kt32, kt32));
-    }
-    GRAV_CHECK(upload(p, &p->d_class_off, fwd));
-    // the transposed M2L's offset table, keyed by the class of the source
-    // box S: entry (-d, operator of K_d^T) for each d of the reverse list
-    // (T = S - d), the operator field packed as in the forward table
-    std::vector<int32_t> tco(rev.size());
-    for (size_t e = 0; e < rev.size(); e += 4) {
-        const int d[3] = {rev[e], rev[e + 1], rev[e + 2]};
-        const int refl = (d[0] < 0 ? 1 : 0) | (d[1] < 0 ? 2 : 0) | (d[2] < 0 ? 4 : 0);
-        tco[e] = -d[0];
-        tco[e + 1] = -d[1];
-        tco[e + 2] = -d[2];
-        tco[e + 3] = canonical ? canon_index(std::abs(d[0]), std::abs(d[1]), std::abs(d[2])) + kReflShift * refl
-                               : rev[e + 3];
-    }
-    GRAV_CHECK(upload(p, &p->d_tclass_off, tco));
-    GRAV_CHECK(upload(p, &p->d_rclass_off, rev));
     return GRAV_OK;
 }
 
-// Stream-K partition of an M2L's work items (see build_tiles): item i
-// belongs to unit item_unit[i], units in order.  A fixed number of one-wave
-// workgroups, all resident at once, take equal contiguous shares of the
-// items; a share is cut into segments {unit, first item, end item, 0} at
-// unit boundaries (wgseg: CSR over workgroups), and per unit its segment
-// slots are listed in workgroup order (tseg_start/tsegs: CSR over units).
-struct StreamK {
-    std::vector<int32_t> seg, wgseg, tseg_start, tsegs;
-    int64_t P = 0, nseg = 0;
-    int nset = 2;
+// Octets of one M2L direction, level by level in Morton order: the key of the
+// parent and the output row of each child (-1: not written).
+struct Octets {
+    std::vector<uint32_t> key;
+    std::vector<int32_t> child;
+    int64_t first[kMaxLevels + 2] = {0};  // octets of level l: [first[l], first[l + 1])
+    void add(uint32_t k, int32_t row)
+    {
+        if (key.empty() || (int64_t)key.size() == open || key.back() != k >> 3) {
+            key.push_back(k >> 3);
+            child.insert(child.end(), 8, -1);
+        }
+        child[8 * (key.size() - 1) + (k & 7)] = row;
+    }
+    void level(int l)
+    {
+        first[l] = open = (int64_t)key.size();
+        first[l + 1] = open;
+    }
+    void done(int l) { first[l + 1] = (int64_t)key.size(); }
+
+private:
+    int64_t open = 0;
 };
 
-// The regather's coefficient map (k_me_gather): value u of plane pl of a
-// box's regathered expansion is coefficient kmap[4 pl + u] (-1: zero).  The
-// orbit M2L reads chunk q = sign class q, sub-row kr, value u = position
-// 4 u + kr of the class; the per-offset M2L reads coefficient 16 q + 4 u + kr.
-static grav_status upload_gather_map(Plan *p)
+// Groups, work items and schedule of one direction.  A unit is a group of
+// 16 nc columns and one of RS parts of the parities; its items are the
+// orbits at which some column has an input row (`has`: whether a box of a
+// level has one).  A fixed number of workgroups, all resident at once: units
+// that fill whole rounds of them run unsplit, one per workgroup and round, so
+// that the workgroups of an XCD walk the operators together; the items of the
+// remaining units are cut into equal contiguous shares, split into segments at
+// unit boundaries.  Workgroups w, w + 8, ... share an XCD and take
+// neighbouring units.
+template <class Has>
+static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, Has &&has)
 {
-    std::vector<int32_t> kmap;
-    if (p->m2l_orbit) {
-        p->m2l_npl = 32;
-        int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        std::vector<int32_t> ccoef(8 * 16, -1);
-        for (int c = 0; c < p->P2; ++c) {
-            const int s = sign_class(c);
-            if (cnt[s] < 16)
-                ccoef[s * 16 + cnt[s]] = c;
-            ++cnt[s];
-        }
-        kmap.resize(32 * 4);
-        for (int q = 0; q < 8; ++q)
-            for (int kr = 0; kr < 4; ++kr)
-                for (int u = 0; u < 4; ++u)
-                    kmap[(q * 4 + kr) * 4 + u] = ccoef[q * 16 + 4 * u + kr];
-    } else {
-        p->m2l_npl = p->PS / 4;
-        kmap.resize((size_t)p->PS);
-        for (int pl = 0; pl < p->PS / 4; ++pl)
-            for (int u = 0; u < 4; ++u) {
-                const int c = 16 * (pl / 4) + 4 * u + pl % 4;
-                kmap[pl * 4 + u] = c < p->P2 ? c : -1;
-            }
-    }
-    return upload(p, &p->d_kmap, kmap);
-}
-
-// 16-column blocks per wave of the per-offset M2L kernel (FP32: four on
-// plans with many columns; FP64: two on plans with many columns)
-static int m2l_blocks_per_wave(const Plan *p)
-{
-    const int64_t ncol = p->n_tbox * p->B;
-    return p->d.precision == GRAV_FP64 ? (ncol >= GRAV_M2L_WIDE_COLUMNS64 ? GRAV_M2L_NC64_WIDE : GRAV_M2L_NC64)
-                                       : (ncol >= GRAV_M2L_WIDE_COLUMNS ? GRAV_M2L_NC32_WIDE : GRAV_M2L_NC32);
-}
-
-static grav_status stream_k(const Plan *p, const std::vector<int32_t> &item_unit, int64_t nunit, int nc, StreamK &o,
-                            bool orbit = false)
-{
-    const int64_t T = (int64_t)item_unit.size();
-    // at least kMinItems items per workgroup: small plans get fewer
-    // workgroups rather than one partial slot per item
-    constexpr int64_t kMinItems = 8;
-    constexpr int64_t kItemsOneSet = 32;  // items per resident wave above which one set pays
-    // FP32: one operand register set (more resident waves) when every wave
-    // gets a long run of items, two sets on small plans
+    const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
+    const int64_t B = p->B;
+    o.noct = (int64_t)oc.key.size();
+    // four (or two) column blocks per wave once there are units for every CU
+    // twice over; else single blocks, for more units than CUs on small plans
     int resident = 0;
-    o.nset = 2;
-    if (p->d.precision != GRAV_FP64) {
-        GRAV_CHECK(m2l_resident_workers(p, 1, nc, orbit, &resident));
-        if (T >= kItemsOneSet * resident)
-            o.nset = 1;
-    }
-    GRAV_CHECK(m2l_resident_workers(p, o.nset, nc, orbit, &resident));
-    const int64_t P = T == 0 ? 0
-                             : std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(GRAV_M2L_WAVES, resident),
-                                                                      T / kMinItems));
-    o.seg.clear();
-    o.wgseg.assign(P + 1, 0);
-    std::vector<int32_t> tseg_n(nunit + 1, 0);
-    for (int64_t w = 0; w < P; ++w) {
-        o.wgseg[w] = (int32_t)(o.seg.size() / 4);
-        const int64_t ie = (w + 1) * T / P;
-        for (int64_t i = w * T / P; i < ie;) {
-            int64_t j = i;
-            while (j < ie && item_unit[j] == item_unit[i])
-                ++j;
-            o.seg.insert(o.seg.end(), {item_unit[i], (int32_t)i, (int32_t)j, 0});
-            ++tseg_n[item_unit[i] + 1];
-            i = j;
+    GRAV_CHECK(m2l_resident_workgroups(p, in.NCW, &resident));
+    o.nc = o.noct * B * in.RS >= (int64_t)GRAV_M2L_WIDE_ROUNDS * resident * 16 * in.NCW / kOrbits ? in.NCW : 1;
+    GRAV_CHECK(m2l_resident_workgroups(p, o.nc, &resident));
+    const int ncol = 16 * o.nc;
+    std::vector<OctGroup> groups;
+    std::vector<uint32_t> umask;          // orbits of a unit
+    std::vector<int64_t> ustart(1, 0);    // its first work item
+    for (int l = 2; l <= p->L; ++l) {
+        const int64_t cols = (oc.first[l + 1] - oc.first[l]) * B;
+        for (int64_t c0 = 0; c0 < cols; c0 += ncol) {
+            OctGroup g{};
+            g.level = l;
+            g.ncol = (int32_t)std::min<int64_t>(ncol, cols - c0);
+            g.col0 = c0;
+            g.oct0 = oc.first[l];
+            groups.push_back(g);
+            uint32_t mask = 0;
+            for (int ob = 1; ob <= kOrbits; ++ob) {
+                bool hit = false;
+                for (int64_t j = c0 / B; j <= (c0 + g.ncol - 1) / B && !hit; ++j) {
+                    const uint32_t k = oc.key[oc.first[l] + j];
+                    const int c[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
+                    for (int r = 0; r < 8 && !hit; ++r)
+                        hit = has(l, orbit_coord(c[0], orbit_axis(ob, 0), r & 1),
+                                  orbit_coord(c[1], orbit_axis(ob, 1), r & 2),
+                                  orbit_coord(c[2], orbit_axis(ob, 2), r & 4));
+                }
+                if (hit)
+                    mask |= 1u << (ob - 1);
+            }
+            for (int xh = 0; xh < in.RS; ++xh) {
+                umask.push_back(mask);
+                ustart.push_back(ustart.back() + __builtin_popcount(mask));
+            }
         }
     }
-    o.nseg = (int64_t)o.seg.size() / 4;
-    o.wgseg[P] = (int32_t)o.nseg;
-    o.tseg_start.assign(nunit + 1, 0);
-    o.tsegs.assign(o.nseg, 0);
-    std::vector<int32_t> fill(nunit, 0);
-    for (int64_t u = 0; u < nunit; ++u)
-        o.tseg_start[u + 1] = o.tseg_start[u] + tseg_n[u + 1];
-    for (int64_t sgi = 0; sgi < o.nseg; ++sgi) {
-        const int32_t u = o.seg[4 * sgi];
-        o.tsegs[o.tseg_start[u] + fill[u]++] = (int32_t)sgi;
+    const int64_t nunit = (int64_t)ustart.size() - 1, T = ustart.back();
+    const int64_t W = T == 0 ? 0 : std::min<int64_t>(resident, T);
+    const int64_t rounds = W > 0 ? nunit / W : 0;
+    std::vector<int32_t> seg, wgseg(W + 1, 0);
+    std::vector<std::vector<int32_t>> useg(nunit);
+    const int64_t u0 = rounds * W, rest = T - ustart[u0];
+    // position of workgroup w in its round: XCD w % 8 takes a contiguous range
+    std::vector<int64_t> pos(W);
+    {
+        int64_t n = 0;
+        for (int64_t x = 0; x < 8; ++x)
+            for (int64_t w = x; w < W; w += 8)
+                pos[w] = n++;
     }
-    o.P = P;
+    for (int64_t w = 0; w < W; ++w) {
+        wgseg[w] = (int32_t)(seg.size() / 4);
+        auto add = [&](int64_t u, int64_t i, int64_t j) {
+            if (i >= j)
+                return;
+            uint32_t left = umask[u], mask = 0;  // the i-th to (j - 1)-th orbits of the unit
+            for (int64_t n = ustart[u]; n < j; ++n, left &= left - 1)
+                mask |= n >= i ? left & -left : 0u;
+            useg[u].push_back((int32_t)(seg.size() / 4));
+            seg.insert(seg.end(), {(int32_t)u, (int32_t)mask, 0, 0});
+        };
+        for (int64_t r = 0; r < rounds; ++r) {
+            const int64_t u = r * W + pos[w];
+            add(u, ustart[u], ustart[u + 1]);
+        }
+        const int64_t ib = ustart[u0] + pos[w] * rest / W, ie = ustart[u0] + (pos[w] + 1) * rest / W;
+        int64_t u = std::upper_bound(ustart.begin() + u0, ustart.end(), ib) - ustart.begin() - 1;
+        for (int64_t i = ib; i < ie; ++u) {
+            const int64_t j = std::min(ie, ustart[u + 1]);
+            add(u, i, j);
+            i = std::max(i, j);
+        }
+    }
+    o.wgs = (int32_t)W;
+    o.nseg = (int64_t)seg.size() / 4;
+    o.ngroup = (int32_t)groups.size();
+    o.nunit = (int32_t)nunit;
+    if (W > 0)
+        wgseg[W] = (int32_t)o.nseg;
+    // slots: the segments of each unit in orbit order, unit by unit
+    std::vector<int32_t> uslot(nunit + 1, 0);
+    for (int64_t u = 0; u < nunit; ++u) {
+        std::sort(useg[u].begin(), useg[u].end(), [&](int32_t a, int32_t b) { return (uint32_t)seg[4 * a + 1] < (uint32_t)seg[4 * b + 1]; });
+        uslot[u + 1] = uslot[u] + (int32_t)useg[u].size();
+        for (size_t j = 0; j < useg[u].size(); ++j)
+            seg[4 * useg[u][j] + 2] = uslot[u] + (int32_t)j;
+    }
+    GRAV_CHECK(upload(p, &o.d_key, oc.key));
+    GRAV_CHECK(upload(p, &o.d_child, oc.child));
+    GRAV_CHECK(upload(p, &o.d_groups, groups));
+    GRAV_CHECK(upload(p, &o.d_segs, seg));
+    GRAV_CHECK(upload(p, &o.d_wgseg, wgseg));
+    GRAV_CHECK(upload(p, &o.d_uslot, uslot));
     return GRAV_OK;
 }
 
-// The adjoint's transposed M2L on the forward kernel: ME_l[S] = sum over the
-// reverse list of S's class of K_d^T LE_l[S - d] (the forward adds K_d
-// ME[T + d] into LE[T] for exactly these pairs).  Per level, the columns
-// are the source boxes of the column block, class-grouped as the forward
-// groups its target boxes, 64 (box, model) columns per tile, units of
-// 16 NC columns; the B operand is the adjoint LE regathered over the gather
-// region; a work item is a (unit, offset) pair at which some column meets
-// a target box.  Everything else (stream-K, slots, sums) is the forward's.
-static grav_status build_m2l_transposed(Plan *p, const std::vector<std::vector<uint32_t>> &key,
-                                        const std::vector<int32_t> &rev)
+// Octets and schedules of both M2L directions, from the target boxes' keys.
+// Forward: the octets of the target boxes, fed by the source blocks.
+// Transposed: the octets of the column block's source boxes (those within
+// reach of a target box; all of level 2, so that every level-2 ME is written
+// -- below, M2M^T sets the boxes outside the column block), fed by the target
+// boxes.
+static grav_status build_m2l(Plan *p)
 {
     const int L = p->L;
-    const int64_t B = p->B;
-    // the forward's kernel choice (the transposed M2L has the forward's box
-    // pairs): the orbit kernel's column blocks, or the per-offset one's
-    const int nc = p->m2l_orbit ? GRAV_M2L_ORB_NC : m2l_blocks_per_wave(p);
-    // orbit kernel: per source class, canonical offset |d| and reflection
-    // (sign bits of d, which give the operator S K_|d|^T S), the entry of the
-    // reverse list or -1
-    std::vector<int> rcanon(8 * kClassOffsets);
-    std::vector<int32_t> orbtab(8 * kCanonOffsets * 8, -1);
-    for (int c = 0; c < 8; ++c)
-        for (int o = 0; o < kClassOffsets; ++o) {
-            const int32_t *e = &rev[((size_t)c * kClassOffsets + o) * 4];
-            const int ci = canon_index(std::abs(e[0]), std::abs(e[1]), std::abs(e[2]));
-            const int r = (e[0] < 0 ? 1 : 0) | (e[1] < 0 ? 2 : 0) | (e[2] < 0 ? 4 : 0);
-            rcanon[c * kClassOffsets + o] = ci;
-            orbtab[((size_t)c * kCanonOffsets + ci) * 8 + r] = o;
-        }
-    std::vector<char> ohit(kCanonOffsets);
-    const int ncw = 16 * nc, upt = 4 / nc;
-    std::vector<uint32_t> skey((size_t)std::max<int64_t>(p->n_me, 1), 0);
-    std::vector<int32_t> sorder((size_t)std::max<int64_t>(p->n_me, 1), 0);
-    std::vector<GemmTile> tiles;
-    std::vector<int32_t> item_unit, item_off, colmap;
-    std::vector<int64_t> colbox;
-    std::vector<char> hit(kClassOffsets);
-    int64_t goff = 0;
+    std::vector<std::vector<uint32_t>> key(L + 1);
+    for (int l = 2; l <= L; ++l) {
+        const int64_t n = p->lev[l].n_tgt;
+        key[l].resize(n);
+        if (n > 0)
+            GRAV_HIP(hipMemcpyAsync(key[l].data(), p->d_tkey + p->tbox_off[l], 4 * n, hipMemcpyDeviceToHost, p->bs));
+    }
+    GRAV_HIP(hipStreamSynchronize(p->bs));
+    Octets fo, to;
+    std::vector<std::vector<char>> tb(L + 1);  // target boxes in a level's gather region
+    p->n_grow = 0;
     for (int l = 2; l <= L; ++l) {
         LevelInfo &lv = p->lev[l];
-        // target boxes of the level within reach of the source block
-        int lo[3], hi[3];
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = lv.s0[a] - 3;
-            hi[a] = lv.s0[a] + lv.ns[a] + 2;
-        }
+        fo.level(l);
+        int lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
         int blo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, bhi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
-        for (const uint32_t k : key[l]) {
+        for (size_t i = 0; i < key[l].size(); ++i) {
+            const uint32_t k = key[l][i];
+            fo.add(k, (int32_t)(lv.tgt_off + (int64_t)i));
             const int c[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
             bool in = true;
-            for (int a = 0; a < 3; ++a)
-                in = in && c[a] >= lo[a] && c[a] <= hi[a];
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = std::min(lo[a], c[a]);
+                hi[a] = std::max(hi[a], c[a]);
+                in = in && c[a] >= lv.s0[a] - 3 && c[a] < lv.s0[a] + lv.ns[a] + 3;
+            }
             if (!in)
                 continue;
             for (int a = 0; a < 3; ++a) {
@@ -893,140 +843,58 @@ static grav_status build_m2l_transposed(Plan *p, const std::vector<std::vector<u
                 bhi[a] = std::max(bhi[a], c[a]);
             }
         }
+        fo.done(l);
+        // boxes whose expansions the M2L can read, and the transposed M2L's
+        // column block
         const bool any = blo[0] <= bhi[0];
-        int64_t gn = 1;
         for (int a = 0; a < 3; ++a) {
-            lv.gs0[a] = any ? blo[a] : 0;
-            lv.gns[a] = any ? bhi[a] - blo[a] + 1 : 0;
-            gn *= lv.gns[a];
-        }
-        lv.g_off = goff;
-        goff += gn;
-        std::vector<char> tb((size_t)gn, 0);
-        for (const uint32_t k : key[l]) {
-            const int c[3] = {(int)compact3(k) - lv.gs0[0], (int)compact3(k >> 1) - lv.gs0[1],
-                              (int)compact3(k >> 2) - lv.gs0[2]};
-            if (c[0] >= 0 && c[1] >= 0 && c[2] >= 0 && c[0] < lv.gns[0] && c[1] < lv.gns[1] && c[2] < lv.gns[2])
-                tb[((size_t)c[2] * lv.gns[1] + c[1]) * lv.gns[0] + c[0]] = 1;
-        }
-        // column block: the source boxes within 3 of the gather region (the
-        // whole source block at level 2, so that every level-2 expansion is
-        // written; below, M2M^T sets the boxes outside the column block)
-        for (int a = 0; a < 3; ++a) {
+            lv.need_lo[a] = key[l].empty() ? 0 : lo[a] - 3;
+            lv.need_hi[a] = key[l].empty() ? -1 : hi[a] + 3;
             int c0 = lv.s0[a], c1 = lv.s0[a] + lv.ns[a] - 1;
             if (l > 2) {
-                c0 = std::max(c0, any ? lv.gs0[a] - 3 : c1 + 1);
-                c1 = std::min(c1, any ? lv.gs0[a] + lv.gns[a] + 2 : c0 - 1);
+                c0 = std::max(c0, any ? blo[a] - 3 : c1 + 1);
+                c1 = std::min(c1, any ? bhi[a] + 3 : c0 - 1);
             }
             lv.cs0[a] = c0;
             lv.cns[a] = std::max(0, c1 - c0 + 1);
+            lv.gs0[a] = any ? blo[a] : 0;
+            lv.gns[a] = any ? bhi[a] - blo[a] + 1 : 0;
         }
-        for (int64_t j = 0; j < lv.n_src; ++j) {
-            const int x = lv.s0[0] + (int)(j % lv.ns[0]), y = lv.s0[1] + (int)((j / lv.ns[0]) % lv.ns[1]),
-                      z = lv.s0[2] + (int)(j / ((int64_t)lv.ns[0] * lv.ns[1]));
-            skey[(size_t)(lv.me_off + j)] = morton3((uint32_t)x, (uint32_t)y, (uint32_t)z);
+        lv.g_off = p->n_grow;
+        const int64_t gn = (int64_t)lv.gns[0] * lv.gns[1] * lv.gns[2];
+        p->n_grow += gn;
+        tb[l].assign((size_t)gn, 0);
+        const OctLev gl{{lv.gs0[0], lv.gs0[1], lv.gs0[2]}, {lv.gns[0], lv.gns[1], lv.gns[2]}, 0};
+        for (const uint32_t k : key[l]) {
+            const int32_t j = octet_place(gl, (int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2));
+            if (j >= 0)
+                tb[l][j] = 1;
         }
-        DevLev cb{};
-        for (int a = 0; a < 3; ++a) {
-            cb.s0[a] = lv.cs0[a];
-            cb.ns[a] = lv.cns[a];
-        }
-        int64_t pos = 0;
-        for (int cls = 0; cls < 8; ++cls) {
-            int first[3], cnt[3];
-            lv.col_class_start[cls] = pos;
-            class_split(cb, cls, first, cnt);
-            for (int iz = 0; iz < cnt[2]; ++iz)
-                for (int iy = 0; iy < cnt[1]; ++iy)
-                    for (int ix = 0; ix < cnt[0]; ++ix) {
-                        const int x = first[0] + 2 * ix, y = first[1] + 2 * iy, z = first[2] + 2 * iz;
-                        sorder[(size_t)(lv.me_off + pos++)] =
-                            (int32_t)(((int64_t)(z - lv.s0[2]) * lv.ns[1] + (y - lv.s0[1])) * lv.ns[0] + (x - lv.s0[0]));
-                    }
-        }
-        lv.col_class_start[8] = pos;
-        for (int cls = 0; cls < 8; ++cls) {
-            const int64_t ncols = (lv.col_class_start[cls + 1] - lv.col_class_start[cls]) * B;
-            for (int64_t c0 = 0; c0 < ncols; c0 += kTileCols) {
-                GemmTile t{};
-                t.level = l;
-                t.cls = cls;
-                t.col0 = c0;
-                t.ncol = (int32_t)std::min<int64_t>(kTileCols, ncols - c0);
-                const int64_t u0 = (int64_t)tiles.size() * upt;
-                tiles.push_back(t);
-                for (int hq = 0; hq < upt; ++hq) {
-                    std::fill(hit.begin(), hit.end(), 0);
-                    for (int cl = hq * ncw; cl < std::min(t.ncol, (hq + 1) * ncw); ++cl) {
-                        const int64_t col = t.col0 + cl;
-                        const int32_t j = sorder[(size_t)(lv.me_off + lv.col_class_start[cls] + col / B)];
-                        colmap.push_back((int32_t)((u0 + hq) * 64 + cl - hq * ncw));
-                        colbox.push_back((lv.me_off + j) * B + col % B);
-                        const int c[3] = {lv.s0[0] + (int)(j % lv.ns[0]), lv.s0[1] + (int)((j / lv.ns[0]) % lv.ns[1]),
-                                          lv.s0[2] + (int)(j / ((int64_t)lv.ns[0] * lv.ns[1]))};
-                        for (int o = 0; o < kClassOffsets && any; ++o) {
-                            const int32_t *e = &rev[((size_t)cls * kClassOffsets + o) * 4];
-                            int g[3];
-                            bool in = true;
-                            for (int a = 0; a < 3; ++a) {
-                                g[a] = c[a] - e[a] - lv.gs0[a];  // T = S - d
-                                in = in && g[a] >= 0 && g[a] < lv.gns[a];
-                            }
-                            if (in && tb[((size_t)g[2] * lv.gns[1] + g[1]) * lv.gns[0] + g[0]])
-                                hit[o] = 1;
-                        }
-                    }
-                    if (p->m2l_orbit) {
-                        std::fill(ohit.begin(), ohit.end(), 0);
-                        for (int o = 0; o < kClassOffsets; ++o)
-                            ohit[rcanon[cls * kClassOffsets + o]] |= hit[o];
-                        for (int ci = 0; ci < kCanonOffsets; ++ci)
-                            if (ohit[ci]) {
-                                item_unit.push_back((int32_t)(u0 + hq));
-                                item_off.push_back(ci);
-                            }
-                    } else {
-                        for (int o = 0; o < kClassOffsets; ++o)
-                            if (hit[o]) {
-                                item_unit.push_back((int32_t)(u0 + hq));
-                                item_off.push_back(o);
-                            }
-                    }
-                }
-            }
-        }
+        to.level(l);
+        std::vector<std::pair<uint32_t, int32_t>> box;
+        for (int z = lv.cs0[2]; z < lv.cs0[2] + lv.cns[2]; ++z)
+            for (int y = lv.cs0[1]; y < lv.cs0[1] + lv.cns[1]; ++y)
+                for (int x = lv.cs0[0]; x < lv.cs0[0] + lv.cns[0]; ++x)
+                    box.emplace_back(morton3(x, y, z),
+                                     (int32_t)(lv.me_off + ((int64_t)(z - lv.s0[2]) * lv.ns[1] + (y - lv.s0[1])) * lv.ns[0] +
+                                               (x - lv.s0[0])));
+        std::sort(box.begin(), box.end());
+        for (const auto &e : box)
+            to.add(e.first, e.second);
+        to.done(l);
     }
-    const int64_t nunit = (int64_t)tiles.size() * upt;
-    StreamK sk;
-    GRAV_CHECK(stream_k(p, item_unit, nunit, nc, sk, p->m2l_orbit));
-    if (p->m2l_orbit)
-        GRAV_CHECK(upload(p, &p->d_orbtab_t, orbtab));
-    if (item_off.empty())
-        item_off.push_back(0);
-    GRAV_CHECK(upload(p, &p->d_m2lt_tiles, tiles.empty() ? std::vector<GemmTile>(1) : tiles));
-    GRAV_CHECK(upload(p, &p->d_m2lt_items, item_off));
-    GRAV_CHECK(upload(p, &p->d_m2lt_segs, sk.seg.empty() ? std::vector<int32_t>(4, 0) : sk.seg));
-    GRAV_CHECK(upload(p, &p->d_m2lt_wgseg, sk.wgseg));
-    GRAV_CHECK(upload(p, &p->d_m2lt_tseg_start, sk.tseg_start));
-    GRAV_CHECK(upload(p, &p->d_m2lt_tsegs, sk.tsegs.empty() ? std::vector<int32_t>(1, 0) : sk.tsegs));
-    GRAV_CHECK(upload(p, &p->d_m2lt_colmap, colmap.empty() ? std::vector<int32_t>(1, 0) : colmap));
-    GRAV_CHECK(upload(p, &p->d_m2lt_colbox, colbox.empty() ? std::vector<int64_t>(1, 0) : colbox));
-    GRAV_CHECK(upload(p, &p->d_skey, skey));
-    GRAV_CHECK(upload(p, &p->d_sorder, sorder));
-    p->m2lt_wgs = (int32_t)sk.P;
-    p->m2lt_nset = sk.nset;
-    p->m2lt_nc = nc;
-    p->m2lt_ncw = ncw;
-    p->m2lt_nseg = sk.nseg;
-    p->m2lt_ncols = (int64_t)colmap.size();
-    p->m2lt_nunit = nunit;
-    p->m2lt_items = (int64_t)item_unit.size();
-    p->n_leg = goff;
-    return GRAV_OK;
+    const OctGeom fg = octet_geom(p, false), tg = octet_geom(p, true);
+    GRAV_CHECK(build_octet_schedule(p, fo, p->m2l, [&](int l, int x, int y, int z) {
+        return octet_place(fg.lev[l], x, y, z) >= 0;
+    }));
+    return build_octet_schedule(p, to, p->m2lt, [&](int l, int x, int y, int z) {
+        const int32_t j = octet_place(tg.lev[l], x, y, z);
+        return j >= 0 && tb[l][j] != 0;
+    });
 }
 
-// Tile lists of the M2L stage: 64 columns (4 waves x 16) per tile, per
-// level and child-parity class; the columns are target boxes (x models).
+// Tile lists of the L2L: 64 columns (4 waves x 16) per tile, per level and
+// child-parity class; the columns are target boxes (x models).
 grav_status build_tiles(Plan *p)
 {
     std::vector<GemmTile> all;
@@ -1058,207 +926,14 @@ grav_status build_tiles(Plan *p)
     if (L >= 2) {
         for (int l = 2; l <= L; ++l) {
             for (int c = 0; c < 8; ++c)
-                add(TK_M2L, l, c, (p->lev[l].class_start[c + 1] - p->lev[l].class_start[c]) * B);
+                add(TK_L2L, l, c, (p->lev[l].class_start[c + 1] - p->lev[l].class_start[c]) * B);
         }
     }
-    // Tiles are not split over workgroups (S = 1): the forward M2L runs on
-    // the stream-K schedule below.
-    std::vector<GemmTile> split;
-    for (int k = 0; k < TK_COUNT; ++k) {
-        TileRange &r = p->tiles[k][0];
-        const int S = 1;
-        p->split[k] = S;
-        const int64_t off = (int64_t)split.size();
-        for (int64_t i = 0; i < r.n; ++i)
-            for (int q = 0; q < S; ++q) {
-                GemmTile t = all[r.off + i];
-                t.pad = q;
-                split.push_back(t);
-            }
-        r.off = off;
-        r.n *= S;
-    }
-    // Stream-K schedule of the forward M2L.  A unit is the 16 NC columns of
-    // one wave of a tile; work items are the (unit, offset) pairs in which
-    // some column of the unit has a source box (the others cost nothing), so
-    // every item costs the same.  A fixed number of one-wave workgroups, all
-    // resident at once, take equal contiguous shares of the item list; a
-    // share is cut into segments at unit boundaries, and each segment writes
-    // the partial LE of its unit's columns to a slot of its own.  k_m2l_sum
-    // then adds, per unit, its segments' slots in order (deterministic).  The
-    // work is balanced to one item per wave and there are at most
-    // (units + workgroups) partial slots.
-    p->m2l_wgs = 0;
-    p->m2l_nseg = 0;
-    {
-        const TileRange &r = p->tiles[TK_M2L][0];  // S = 1: one entry per tile
-        if (r.n > 0) {
-            std::vector<int> alloffs;
-            std::vector<int32_t> fwd, rev;
-            offsets_tables(alloffs, fwd, rev, false);  // only the offsets themselves are used here
-            std::vector<std::vector<uint32_t>> key(L + 1);
-            std::vector<std::vector<int32_t>> ord(L + 1);
-            for (int l = 2; l <= L; ++l) {
-                const int64_t n = p->lev[l].n_tgt;
-                key[l].resize(n);
-                ord[l].resize(n);
-                if (n > 0) {
-                    GRAV_HIP(hipMemcpyAsync(key[l].data(), p->d_tkey + p->tbox_off[l], 4 * n, hipMemcpyDeviceToHost,
-                                            p->bs));
-                    GRAV_HIP(hipMemcpyAsync(ord[l].data(), p->d_torder + p->tbox_off[l], 4 * n,
-                                            hipMemcpyDeviceToHost, p->bs));
-                }
-            }
-            GRAV_HIP(hipStreamSynchronize(p->bs));
-            // per level, the box range whose expansions the M2L can read: the
-            // target boxes' bounding box widened by the largest offset (3)
-            for (int l = 2; l <= L; ++l) {
-                LevelInfo &lv = p->lev[l];
-                int lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
-                for (const uint32_t k : key[l]) {
-                    const int c[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
-                    for (int a = 0; a < 3; ++a) {
-                        lo[a] = std::min(lo[a], c[a]);
-                        hi[a] = std::max(hi[a], c[a]);
-                    }
-                }
-                for (int a = 0; a < 3; ++a) {
-                    lv.need_lo[a] = key[l].empty() ? 0 : lo[a] - 3;
-                    lv.need_hi[a] = key[l].empty() ? -1 : hi[a] + 3;
-                }
-            }
-            // The orbit M2L costs one operator per (column, orbit with a
-            // source), the per-offset one an operator per (column, offset with
-            // a source): keep the orbit kernel only where orbits hold enough
-            // offsets with sources on average (target boxes near the edge of
-            // the source block, such as surface stations, see few).
-            if (p->m2l_orbit) {
-                int64_t n_off = 0, n_orb = 0;
-                for (int l = 2; l <= L; ++l) {
-                    const LevelInfo &lv = p->lev[l];
-                    for (int c = 0; c < 8; ++c)
-                        for (int64_t j = lv.class_start[c]; j < lv.class_start[c + 1]; ++j) {
-                            const uint32_t k = key[l][ord[l][j]];
-                            const int x[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
-                            uint64_t orbs = 0;
-                            for (int o = 0; o < kClassOffsets; ++o) {
-                                const int32_t *e = &fwd[((size_t)c * kClassOffsets + o) * 4];
-                                bool in = true;
-                                for (int a = 0; a < 3; ++a) {
-                                    const int s = x[a] + e[a] - lv.s0[a];
-                                    in = in && s >= 0 && s < lv.ns[a];
-                                }
-                                if (in) {
-                                    ++n_off;
-                                    orbs |= 1ull << canon_index(std::abs(e[0]), std::abs(e[1]), std::abs(e[2]));
-                                }
-                            }
-                            n_orb += __builtin_popcountll(orbs);
-                        }
-                }
-                // the transposed M2L's gather regions (at most 3 boxes past the
-                // source block on each side) also take 32-bit byte offsets
-                double leg_bytes = 0.0;
-                for (int l = 2; l <= L; ++l)
-                    leg_bytes += 512.0 * (double)B * (p->lev[l].ns[0] + 6) * (p->lev[l].ns[1] + 6) *
-                                 (p->lev[l].ns[2] + 6);
-                if ((double)n_off < GRAV_M2L_ORB_MIN_RATIO * (double)n_orb || leg_bytes >= 4294967296.0) {
-                    p->m2l_orbit = false;
-                    (void)hipFree(p->d_k32o);
-                    (void)hipFree(p->d_kt32o);
-                    p->d_k32o = nullptr;
-                    p->d_kt32o = nullptr;
-                    p->bytes_resident -= 2 * sizeof(float) * (size_t)kCanonOffsets * 8 * 8 * 256;
-                }
-            }
-            GRAV_CHECK(upload_gather_map(p));
-            // a unit is the columns of one wave: 16 NC columns of a tile
-            // (FP32: four blocks on plans with many columns)
-            const int nc = p->m2l_orbit ? GRAV_M2L_ORB_NC : m2l_blocks_per_wave(p);
-            const int ncw = 16 * nc, upt = 4 / nc;
-            const int64_t nunit = r.n * upt;
-            std::vector<int32_t> item_tile, item_off;  // item_tile holds the unit
-            std::vector<int32_t> colmap((size_t)p->n_tbox * B, -1);
-            std::vector<char> hit(kClassOffsets);
-            // reflection-orbit M2L: per class, the canonical offset of each
-            // of its offsets, and per (class, canonical offset, reflection)
-            // the class offset index or -1
-            std::vector<int> ocanon(8 * kClassOffsets);
-            std::vector<int32_t> orbtab(8 * kCanonOffsets * 8, -1);
-            for (int c = 0; c < 8; ++c)
-                for (int o = 0; o < kClassOffsets; ++o) {
-                    const int32_t *e = &fwd[((size_t)c * kClassOffsets + o) * 4];
-                    const int ci = canon_index(std::abs(e[0]), std::abs(e[1]), std::abs(e[2]));
-                    const int s = (e[0] < 0 ? 1 : 0) | (e[1] < 0 ? 2 : 0) | (e[2] < 0 ? 4 : 0);
-                    ocanon[c * kClassOffsets + o] = ci;
-                    orbtab[((size_t)c * kCanonOffsets + ci) * 8 + s] = o;
-                }
-            std::vector<char> ohit(kCanonOffsets);
-            for (int64_t u = 0; u < r.n; ++u) {
-                const GemmTile &t = split[r.off + u];
-                const LevelInfo &lv = p->lev[t.level];
-                for (int hq = 0; hq < upt; ++hq) {
-                    std::fill(hit.begin(), hit.end(), 0);
-                    for (int cl = hq * ncw; cl < std::min(t.ncol, (hq + 1) * ncw); ++cl) {
-                        const int64_t col = t.col0 + cl;
-                        const int32_t box = ord[t.level][lv.class_start[t.cls] + col / B];
-                        colmap[(size_t)((lv.tgt_off + box) * B + col % B)] =
-                            (int32_t)((u * upt + hq) * 64 + cl - hq * ncw);
-                        const uint32_t k = key[t.level][box];
-                        const int c[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
-                        for (int o = 0; o < kClassOffsets; ++o) {
-                            const int32_t *e = &fwd[((size_t)t.cls * kClassOffsets + o) * 4];
-                            bool in = true;
-                            for (int a = 0; a < 3; ++a) {
-                                const int s = c[a] + e[a] - lv.s0[a];
-                                in = in && s >= 0 && s < lv.ns[a];
-                            }
-                            hit[o] |= in;
-                        }
-                    }
-                    if (p->m2l_orbit) {
-                        std::fill(ohit.begin(), ohit.end(), 0);
-                        for (int o = 0; o < kClassOffsets; ++o)
-                            ohit[ocanon[t.cls * kClassOffsets + o]] |= hit[o];
-                        for (int ci = 0; ci < kCanonOffsets; ++ci)
-                            if (ohit[ci]) {
-                                item_tile.push_back((int32_t)(u * upt + hq));
-                                item_off.push_back(ci);
-                            }
-                    } else {
-                        for (int o = 0; o < kClassOffsets; ++o)
-                            if (hit[o]) {
-                                item_tile.push_back((int32_t)(u * upt + hq));
-                                item_off.push_back(o);
-                            }
-                    }
-                }
-            }
-            StreamK sk;
-            GRAV_CHECK(stream_k(p, item_tile, nunit, nc, sk, p->m2l_orbit));
-            if (item_off.empty())
-                item_off.push_back(0);
-            GRAV_CHECK(upload(p, &p->d_m2l_items, item_off));
-            if (p->m2l_orbit)
-                GRAV_CHECK(upload(p, &p->d_orbtab, orbtab));
-            GRAV_CHECK(upload(p, &p->d_m2l_segs, sk.seg.empty() ? std::vector<int32_t>(4, 0) : sk.seg));
-            GRAV_CHECK(upload(p, &p->d_m2l_wgseg, sk.wgseg));
-            GRAV_CHECK(upload(p, &p->d_m2l_tseg_start, sk.tseg_start));
-            GRAV_CHECK(upload(p, &p->d_m2l_tsegs, sk.tsegs.empty() ? std::vector<int32_t>(1, 0) : sk.tsegs));
-            GRAV_CHECK(upload(p, &p->d_m2l_colmap, colmap));
-            p->m2l_nset = sk.nset;
-            p->m2l_wgs = (int32_t)sk.P;
-            p->m2l_nseg = sk.nseg;
-            p->m2l_items = (int64_t)item_tile.size();
-            p->m2l_ncw = ncw;
-            p->m2l_nc = nc;
-            p->m2l_nunit = nunit;
-            GRAV_CHECK(build_m2l_transposed(p, key, rev));
-        }
-    }
-    if (!split.empty())
-        GRAV_CHECK(upload(p, &p->d_tiles, split));
-    return GRAV_OK;
+    for (int k = 0; k < TK_COUNT; ++k)
+        p->split[k] = 1;
+    if (!all.empty())
+        GRAV_CHECK(upload(p, &p->d_tiles, all));
+    return L >= 2 ? build_m2l(p) : GRAV_OK;
 }
 
 __global__ void k_fill_tmap(const uint32_t *bkeys, int64_t n, int s0x, int s0y, int s0z, int mx,
@@ -2158,9 +1833,12 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
             break;
         if ((st = dalloc(p, &p->d_le, (size_t)p->n_tbox * p->B * p->PS, false)) != GRAV_OK)
             break;
-        if (p->L >= 2 &&
-            (st = dalloc(p, &p->d_meg, (size_t)p->n_me * p->B * std::max(p->PS, 4 * p->m2l_npl), false)) != GRAV_OK)
-            break;
+        if (p->L >= 2 && p->M > 0) {
+            const bool f64 = p->d.precision == GRAV_FP64;
+            const size_t n = (size_t)(f64 ? p->n_grow : std::max(p->n_me, p->n_grow)) * p->B * p->PS;
+            if ((st = dalloc(p, &p->d_rows, f64 ? n : (n + 1) / 2, false)) != GRAV_OK)
+                break;
+        }
         if ((st = dalloc(p, &p->d_near, (size_t)p->M * p->B * 4, false)) != GRAV_OK)
             break;
         {
@@ -2177,32 +1855,12 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
                 break;
         }
         {
-            // segment slots of the forward and the transposed M2L, and the
-            // adjoint LE regathered for the latter
-            const size_t part = (size_t)p->m2l_nseg * p->m2l_ncw * p->PS;
-            if ((st = dalloc(p, &p->d_part, part, false)) != GRAV_OK)
-                break;
-            // the orbit M2L writes the coefficients only: the padding of its
-            // slots stays zero from here on
-            if (p->m2l_orbit && part > 0 &&
-                (hipMemsetAsync(p->d_part, 0, part * sizeof(float), s) != hipSuccess ||
-                 hipStreamSynchronize(s) != hipSuccess)) {
-                st = GRAV_EDEVICE;
-                break;
-            }
-            const size_t partt = (size_t)p->m2lt_nseg * p->m2lt_ncw * p->PS;
-            if ((st = dalloc(p, &p->d_partt, partt, false)) != GRAV_OK)
-                break;
-            // as in the forward: the orbit kernel leaves the slots' padding
-            // entries alone, so they are cleared once here
-            if (p->m2l_orbit && partt > 0 &&
-                (hipMemsetAsync(p->d_partt, 0, partt * sizeof(float), s) != hipSuccess ||
-                 hipStreamSynchronize(s) != hipSuccess)) {
-                st = GRAV_EDEVICE;
-                break;
-            }
-            if ((st = dalloc(p, &p->d_leg, (size_t)p->n_leg * p->B * std::max(p->PS, 4 * p->m2l_npl), false)) !=
-                GRAV_OK)
+            // segment slots of the M2L, [parity][column][PS] each, in its
+            // element type; both directions use them in turn
+            const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
+            const size_t slot = (size_t)std::max(p->m2l.nseg * p->m2l.nc, p->m2lt.nseg * p->m2lt.nc) * 16 *
+                                (8 / in.RS) * p->PS;
+            if ((st = dalloc(p, &p->d_part, p->d.precision == GRAV_FP64 ? slot : (slot + 1) / 2, false)) != GRAV_OK)
                 break;
         }
         {

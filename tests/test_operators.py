@@ -243,3 +243,41 @@ def test_m2l_orbit_walsh_hadamard_identity():
                 H[t] += (-1) ** bin(t & r).count("1") * M[r]
         got = np.array([sum(Kc[i, k] * H[cls[i] ^ cls[k], k] for k in range(p * p)) for i in range(p * p)])
         np.testing.assert_allclose(got, ref, rtol=1e-11, atol=1e-13 * np.abs(ref).max())
+
+
+def test_m2l_octet_parity_identity():
+    """The M2L of a sibling octet through the eight parities: per parity chi
+    and positive-octant box o of the 6^3 block, F = 1/8 sum_r (-1)^(chi.r)
+    S_r-signed K applied to the Walsh-Hadamard sums of the images of o gives
+    G_chi, and the children's expansions are their signed sums."""
+    p = 4
+    s = _reflection_signs(p)
+    rng = np.random.default_rng(12)
+    # box positions: half-widths from the parent's centre, +-1, +-2, +-3
+    M = {}
+    for x in (-3, -2, -1, 1, 2, 3):
+        for y in (-3, -2, -1, 1, 2, 3):
+            for z in (-3, -2, -1, 1, 2, 3):
+                M[(x, y, z)] = rng.standard_normal(p * p)
+    coord = lambda v: tuple(c if c > 0 else c + 1 for c in v)  # child coordinate, the (+,+,+) child at 1
+    image = lambda o, r: tuple(-c if r >> a & 1 else c for a, c in enumerate(o))
+    chi = lambda a, b: -1.0 if bin(a & b).count("1") & 1 else 1.0
+
+    def op(t, src):
+        d = tuple(b - a for a, b in zip(coord(t), coord(src)))
+        return G.grav_operator(p, 2, 0, d) if max(abs(c) for c in d) >= 2 else np.zeros((p * p, p * p))
+
+    ref = {t: sum(op(t, src) @ m for src, m in M.items()) for t in [image((1, 1, 1), r) for r in range(8)]}
+    g = np.zeros((8, p * p))
+    for o in [(x, y, z) for x in (1, 2, 3) for y in (1, 2, 3) for z in (1, 2, 3)]:
+        Ks = [op((1, 1, 1), image(o, r)) for r in range(8)]
+        if o == (1, 1, 1):
+            assert all(not K.any() for K in Ks)  # the octet itself: 26 orbits remain
+            continue
+        for x in range(8):
+            F = sum(chi(x, r) * Ks[r] * s[r][None, :] for r in range(8)) / 8
+            H = sum(chi(x, r) * s[r] * M[image(o, r)] for r in range(8))
+            g[x] += F @ H
+    for r in range(8):
+        got = s[r] * sum(chi(x, r) * g[x] for x in range(8))
+        np.testing.assert_allclose(got, ref[image((1, 1, 1), r)], rtol=1e-11, atol=1e-12)
