@@ -1026,7 +1026,8 @@ k_t_wblocks(DevGeom g, const double *resid, int64_t npts, int KQ, int64_t nplB, 
     }
 }
 
-// near^T: a workgroup owns CW blocks of 16 (source leaf, model) columns and
+// near^T for leaves of 1 to 3 cells a side (4^3-cell leaves: near.hip): a
+// workgroup owns CW blocks of 16 (source leaf, model) columns and
 // four 16-cell row blocks (blockIdx.y); its four waves split the 27 KQ
 // chunks (neighbour d, chunk q of the target leaf's C b^3 weights) and add
 // their partial tiles through LDS in wave order (deterministic), as
@@ -1393,7 +1394,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
     // other plans) pair by pair
     if (p->lat_near) {
         stage_begin(p, "nearT", s);
-        GRAV_CHECK(launch_t_near_lat(p, g, resid, L >= 2 ? 1 : 0, drho, s));
+        GRAV_CHECK(p->near_par ? launch_t_near_par(p, g, resid, L >= 2 ? 1 : 0, drho, s)
+                               : launch_t_near_lat(p, g, resid, L >= 2 ? 1 : 0, drho, s));
         stage_end(p, s);
     }
     const bool pts = p->lat_near ? p->d.n_points > 0 : (p->p2p_pairs > 0 || L < 2);

@@ -957,7 +957,8 @@ k_rho_blocks(DevGeom g, const double *rho, int Qn, int64_t nplB, T *blk)
 #endif
 
 // --------------------------------------------------------------------------
-// The voxel-centre targets, fused: near field + far field + combine.
+// The voxel-centre targets, fused: near field + far field + combine, for
+// leaves of 1 to 3 cells a side (4^3-cell leaves: near.hip).
 // Targets and Gauss points both sit on the lattice, so the near field of a
 // leaf's b^3 cell centres is
 //   near[leaf] = sum over the 27 neighbour offsets d of  A_d rho[leaf + d],
@@ -975,10 +976,7 @@ k_rho_blocks(DevGeom g, const double *rho, int Qn, int64_t nplB, T *blk)
 // workgroup share one tile and split the contraction (wave w a quarter of
 // the near chunks and every fourth far-field chunk); the four partial tiles
 // meet in LDS and are added in wave order (fixed, so the result is
-// deterministic).  Measured: 256^3 cells at leaf 4^3, 24,576 tiles: 1.82 ms
-// with NW = 1 against 1.96 with NW = 4 (the 64 KB reduction buffer held the
-// CU to two workgroups); 64^3 cells, 384 tiles: 0.094 ms against 0.053 (too
-// few waves to fill the chip).  Operand fragments are group-major sets per (d, q, rb), the
+// deterministic).  Operand fragments are group-major sets per (d, q, rb), the
 // densities chunk-major (both read with contiguous-kilobyte vector loads).
 // --------------------------------------------------------------------------
 template <int RW, int CW, typename T, int NW>
@@ -1476,8 +1474,7 @@ static grav_status launch_near_lat(Plan *p, const DevGeom &g, const double *rho,
         return GRAV_EUNSUPPORTED;
     const int64_t ntile = ncg * nrg;
     // a tile per wave once there are tiles for every wave slot of the chip,
-    // else four waves per tile (small plans: 64^3 cells at leaf 4^3 with two
-    // Gauss points have 384 tiles)
+    // else four waves per tile
     const bool per_wave = ntile >= GRAV_NEAR_WAVE_TILES;
     dim3 grid((unsigned)(per_wave ? (ntile + 3) / 4 : ntile)), blk(256);
     const int64_t npts = p->d.n_points;
@@ -1553,7 +1550,7 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
     }
     if (p->lat_near) {
         stage_begin(p, "near_lat", s);
-        GRAV_CHECK(launch_near_lat(p, g, rho, out, s));
+        GRAV_CHECK(p->near_par ? launch_near_par(p, g, rho, out, s) : launch_near_lat(p, g, rho, out, s));
         stage_end(p, s);
     }
     if (!p->lat_near || p->d.n_points > 0) {

@@ -34,6 +34,8 @@ struct OctGeom;
 // the plan's M2L), setting the expansions of the octets' boxes in `out`.
 template <typename T>
 grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in, double *out);
+grav_status launch_near_par(const Plan *p, const DevGeom &g, const double *rho, double *out, hipStream_t s);
+grav_status launch_t_near_par(const Plan *p, const DevGeom &g, const double *resid, int add, double *drho, hipStream_t s);
 OctInfo octet_info(int P, bool f64);
 grav_status m2l_resident_workgroups(const Plan *p, int nc, int *workers);
 grav_status begin_call(Plan *p, hipStream_t s);

@@ -18,6 +18,7 @@ constexpr int kCanonOffsets = 56;  // M2L offsets d, 2 <= max |d_a| <= 3, with n
 constexpr int kClassOffsets = 189; // offsets valid for one child-parity class
 constexpr int kTileCols = 64;      // columns (box, model) per L2L tile
 constexpr int kMaxLeafCells = 8;     // leaf edge cap: a leaf's densities fit one 512-entry LDS stage
+constexpr int kNearChunk = 3;        // k steps per chunk of the near field by parity (54 in all)
 constexpr int kMaxLatticeLeaf = 4;   // largest leaf edge with lattice near-field matrices
 
 struct LevelInfo {
@@ -140,6 +141,14 @@ struct Plan {
     // near field of voxel-centre targets by lattice matrices (b <= 4)
     bool lat_near = false;
     int lat_RB = 0, lat_Q = 0;                     // row blocks (C b^3 / 16); chunks of four k steps
+    // near field by reflection parity (4^3-cell leaves, near.hip): operators
+    // of both directions in the near field's element type, the far field at
+    // the base centres and its coefficients by class
+    bool near_par = false;
+    void *d_near_op = nullptr, *d_near_opt = nullptr;
+    double *d_near_far = nullptr;
+    int32_t *d_near_coef = nullptr;
+    int near_KC = 0;                               // k steps of a class
     double *d_tl2p = nullptr;                      // [PS/16][RB][64][4] far field (L2P) at the cell centres, FP64
     int64_t *d_lat_tab = nullptr;                  // [27 Q][2] per near chunk: density and operator offsets
     double *d_m2m_sw = nullptr;                    // [8][PS/4][RB][64] M2M as MFMA A fragments (FP64)

@@ -314,7 +314,8 @@ void free_plan(Plan *p)
                     p->d_tn64, p->d_tn32, p->d_m2m_sw, p->d_l2l_sw, p->d_rho_blk, p->d_tl2p, p->d_dpart,
                     p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
                     p->d_m2mt_sw, p->d_l2lt_sw, p->d_l2l_msw, p->d_pmt_sw, p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
-                    p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves};
+                    p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
+                    p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_coef};
     for (OctPlan *o : {&p->m2l, &p->m2lt}) {
         void *ob[] = {o->d_key, o->d_child, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
                       o->d_ops};
@@ -1081,6 +1082,110 @@ grav_status build_adjoint_maps(Plan *p)
     return GRAV_OK;
 }
 
+// Cell of a 4^3 leaf's 12^3 neighbourhood along one axis: base cell v of the
+// positive side or its image, relative to the leaf's corner -> (neighbour
+// offset, cell in that leaf).
+static void near_axis(int v, bool neg, int &d, int &cell)
+{
+    const int x = neg ? 1 - v : 2 + v;
+    d = x < 0 ? -1 : x < 4 ? 0 : 1;
+    cell = x - 4 * d;
+}
+
+// Operators of the near field by parity, F_chi and F^T_chi of near.hip, from
+// the dense pair terms of near_lattice.  A set holds the CK RBN values of a
+// chunk per lane (frag_at), value u RBN + rb = row 16 rb + lane % 16, base
+// cell 4 (CK chunk + u) + lane / 16; [parity][chunk], transposed
+// [component][parity][chunk].
+template <class T>
+static grav_status build_near_parity(Plan *p, const std::vector<double> &dense)
+{
+    constexpr int b3 = 64, CK = kNearChunk, NJ = 54 / CK;
+    const int C = p->C, RBN = (8 * C + 15) / 16, E = CK * RBN;
+    // transposed: rows t in two groups of four (FP32 4x4x1 instructions, row
+    // lane % 4), or in the first half of a block of 16
+    constexpr int RT = sizeof(T) == 4 ? 2 : 1, ET = CK * RT;
+    std::vector<T> op((size_t)8 * NJ * E * 64, (T)0), opt((size_t)C * 8 * NJ * ET * 64, (T)0);
+    for (int s = 0; s < 216; ++s) {
+        const int sb[3] = {s % 6, s / 6 % 6, s / 36};
+        // per reflection: neighbour index and cell of the base cell's image
+        int nb[8], nbt[8], cell[8];
+        for (int r = 0; r < 8; ++r) {
+            int d[3], c[3];
+            for (int a = 0; a < 3; ++a)
+                near_axis(sb[a], r >> a & 1, d[a], c[a]);
+            nb[r] = (d[0] + 1) + 3 * (d[1] + 1) + 9 * (d[2] + 1);
+            nbt[r] = (1 - d[0]) + 3 * (1 - d[1]) + 9 * (1 - d[2]);
+            cell[r] = c[0] + 4 * c[1] + 16 * c[2];
+        }
+        const int ks = s / 4, lane4 = 16 * (s % 4), j = ks / CK, u = ks % CK;
+        for (int c = 0; c < C; ++c) {
+            const int comp = c + 4 - C;  // of (phi, gx, gy, gz)
+            const int cls = comp == 0 ? 0 : 1 << (comp - 1);
+            for (int t = 0; t < 8; ++t) {
+                const int tc = (2 + (t & 1)) + 4 * (2 + (t >> 1 & 1)) + 16 * (2 + (t >> 2));
+                for (int x = 0; x < 8; ++x) {
+                    double f = 0.0, ft = 0.0;
+                    for (int r = 0; r < 8; ++r) {
+                        const double v = dense[((size_t)nb[r] * 4 * b3 + 4 * tc + comp) * b3 + cell[r]];
+                        const double w = dense[((size_t)nbt[r] * 4 * b3 + 4 * cell[r] + comp) * b3 + tc];
+                        f += odd_parity(x & r) ? -v : v;
+                        ft += odd_parity((x ^ cls) & r) ? -w : w;
+                    }
+                    const int R = 8 * c + t;
+                    op[((size_t)x * NJ + j) * E * 64 + frag_at<T>(E, lane4 + R % 16, u * RBN + R / 16)] = (T)(f / 8);
+                    T *set = &opt[(((size_t)c * 8 + x) * NJ + j) * ET * 64];
+                    if (RT == 1)
+                        set[frag_at<T>(ET, lane4 + t, u)] = (T)(ft / 8);
+                    else
+                        for (int i = 0; i < 16; i += 4)
+                            set[frag_at<T>(ET, lane4 + i + t % 4, u * RT + t / 4)] = (T)(ft / 8);
+                }
+            }
+        }
+    }
+    T *d = nullptr;
+    GRAV_CHECK(upload(p, &d, op));
+    p->d_near_op = d;
+    GRAV_CHECK(upload(p, &d, opt));
+    p->d_near_opt = d;
+    return GRAV_OK;
+}
+
+// The far field at the base centres by coefficient class: [parity][k step][row
+// block][lane], coefficient 4 q + lane / 16 of the class (coef; past its end
+// coefficient 0 with a zero operator).
+static grav_status build_near_far(Plan *p, const std::vector<double> &full)
+{
+    const int C = p->C, RBN = (8 * C + 15) / 16, PS = p->PS;
+    const bool f64 = p->d.precision == GRAV_FP64;
+    std::vector<int> cls[8];
+    for (int k = 0; k < p->P2; ++k)
+        cls[sign_class(k)].push_back(k);
+    int KC = 0;
+    for (const auto &c : cls)
+        KC = std::max(KC, (int)ceil_div((int64_t)c.size(), 4));
+    p->near_KC = KC;
+    std::vector<int32_t> coef((size_t)8 * KC * 4, 0);
+    std::vector<double> lm((size_t)8 * KC * RBN * 64, 0.0);
+    for (int x = 0; x < 8; ++x)
+        for (size_t n = 0; n < cls[x].size(); ++n) {
+            const int k = cls[x][n], q = (int)n / 4, kr = (int)n % 4;
+            coef[((size_t)x * KC + q) * 4 + kr] = k;
+            for (int a = 0; a < 16 * RBN; ++a) {
+                // next to FP32 sums, row i holds row 4 (i % 4) + i / 4
+                const int i = a % 16, R = 16 * (a / 16) + (f64 ? i : 4 * (i % 4) + i / 4);
+                if (R >= 8 * C)
+                    continue;
+                const int t = R % 8, comp = R / 8 + 4 - C;
+                const int tc = (2 + (t & 1)) + 4 * (2 + (t >> 1 & 1)) + 16 * (2 + (t >> 2));
+                lm[((size_t)(x * KC + q) * RBN + a / 16) * 64 + 16 * kr + i] = full[(size_t)(4 * tc + comp) * PS + k];
+            }
+        }
+    GRAV_CHECK(upload(p, &p->d_near_coef, coef));
+    return upload(p, &p->d_near_far, lm);
+}
+
 // Near field of voxel-centre targets as 27 dense lattice matrices (leaf
 // edges b <= 4), the slot of every voxel centre in sorted order, and the end
 // of the user points of every leaf (the direct near-field kernel visits only
@@ -1119,101 +1224,106 @@ grav_status build_near_lattice(Plan *p, hipStream_t s)
     const bool f64 = p->d.precision == GRAV_FP64;
     std::vector<double> dense((size_t)27 * 4 * b3 * b3);
     near_lattice(b, p->q, f64 ? 1e-20 : 1e-10, dense.data());
-    // Row r of block rb is target 16 (rb % RBc) + r of output component
-    // rb / RBc; the lattice matrices hold (phi, gx, gy, gz), of which
-    // components 1 and 3 take the trailing one or three.  The FP32
-    // instruction returns rows 4 (lane / 16) + k of a block and the FP64 one
-    // rows lane / 16 + 4 k, so a lane's accumulator holds four targets of one
-    // component.  The far field (FP64) is added element by element to the
-    // near field's accumulator, so next to an FP32 near field its rows take
-    // the FP32 order (swap: row 4 i + j holds target 4 j + i).  Layout
-    // [nb][q][rb][lane][u], ks = 4 q + u.
+    const int TQ = (int)ceil_div(b3, 4), RBt = (int)ceil_div(b3, 16);
+    p->lat_TQ = TQ;
+    p->near_par = b == 4;
+    if (p->near_par)
+        GRAV_CHECK(f64 ? build_near_parity<double>(p, dense) : build_near_parity<float>(p, dense));
     auto row_target = [C, RBc](int row, int rb, bool swap, int &t, int &comp) {
         t = 16 * (rb % RBc) + (swap ? 4 * (row % 4) + row / 4 : row);
         comp = rb / RBc + 4 - C;
     };
-    std::vector<double> sw((size_t)27 * Qn * RBn * 64 * 4, 0.0);
-    for (int nb = 0; nb < 27; ++nb)
-        for (int q = 0; q < Qn; ++q)
-            for (int rb = 0; rb < RBn; ++rb)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int u = 0; u < 4; ++u) {
-                        int t, comp;
-                        row_target(lane & 15, rb, false, t, comp);
-                        const int cell = (lane >> 4) * 4 * Qn + 4 * q + u;
-                        double v = 0.0;
-                        if (t < b3 && cell < b3)
-                            v = dense[((size_t)nb * 4 * b3 + 4 * t + comp) * b3 + cell];
-                        sw[(((size_t)nb * Qn + q) * RBn + rb) * 256 + frag_pos(lane, u, f64 ? 2 : 4)] = v;
-                    }
-    {
-        // leaf blocks of the densities, padded by one leaf per side; the
-        // padding and the rows past b^3 stay zero
-        const LevelInfo &lv = p->lev[p->L];
-        const size_t n = (size_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B * KP;
-        GRAV_CHECK(dalloc(p, &p->d_rho_blk, n, false));
-        GRAV_HIP(hipMemsetAsync(p->d_rho_blk, 0, sizeof(double) * n, p->bs));
-        GRAV_HIP(hipStreamSynchronize(p->bs));
-        // per near chunk i = (neighbour nb, four k steps q): element offsets
-        // of its density fragment (from a column's block at nb = (0, 0, 0))
-        // and of its operator fragments; the kernel reads them with scalar
-        // loads instead of recomputing them
-        const int64_t px = lv.ns[0] + 2, py = lv.ns[1] + 2, nplB = px * py * (lv.ns[2] + 2) * p->B;
-        std::vector<int64_t> tab((size_t)27 * Qn * 2);
+    if (!p->near_par) {
+        // Row r of block rb is target 16 (rb % RBc) + r of output component
+        // rb / RBc; the lattice matrices hold (phi, gx, gy, gz), of which
+        // components 1 and 3 take the trailing one or three.  The FP32
+        // instruction returns rows 4 (lane / 16) + k of a block and the FP64 one
+        // rows lane / 16 + 4 k, so a lane's accumulator holds four targets of one
+        // component.  The far field (FP64) is added element by element to the
+        // near field's accumulator, so next to an FP32 near field its rows take
+        // the FP32 order (swap: row 4 i + j holds target 4 j + i).  Layout
+        // [nb][q][rb][lane][u], ks = 4 q + u.
+        std::vector<double> sw((size_t)27 * Qn * RBn * 64 * 4, 0.0);
         for (int nb = 0; nb < 27; ++nb)
-            for (int q = 0; q < Qn; ++q) {
-                const int64_t nboff = ((int64_t)(nb / 9) * py + (nb / 3) % 3) * px + nb % 3;
-                tab[((size_t)nb * Qn + q) * 2 + 0] = ((int64_t)q * 4 * nplB + nboff * p->B) * 4;
-                tab[((size_t)nb * Qn + q) * 2 + 1] = ((int64_t)nb * Qn + q) * RBn * 256;
-            }
-        GRAV_CHECK(upload(p, &p->d_lat_tab, tab));
-    }
-    if (f64) {
-        GRAV_CHECK(upload(p, &p->d_tn64, sw));
-    } else {
-        std::vector<float> sw32(sw.begin(), sw.end());
-        GRAV_CHECK(upload(p, &p->d_tn32, sw32));
-    }
-    // the adjoint's transposes: rows = the cells of the source leaf (RBt
-    // blocks of 16), contraction over (target t, component) of the target
-    // leaf (near^T: the C output components; L2P^T: chunk q and k step u
-    // taking t = (lane/16) TQ + q, component u); [nb][q][rb][lane][u]
-    // group-major sets
-    const int TQ = (int)ceil_div(b3, 4), RBt = (int)ceil_div(b3, 16);
-    p->lat_TQ = TQ;
-    {
-        // the weights of the cell centres in leaf blocks (padded by one leaf
-        // per side, 4 TQ x 4 values per leaf and model, in the near field's
-        // element type); the padding and the slots past b^3 stay zero
-        const LevelInfo &lv = p->lev[p->L];
-        const size_t n = (size_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B * 16 * TQ;
-        const size_t nd = f64 ? n : (n + 1) / 2;  // in doubles
-        GRAV_CHECK(dalloc(p, &p->d_w_blk, nd, false));
-        GRAV_HIP(hipMemsetAsync(p->d_w_blk, 0, sizeof(double) * nd, p->bs));
-        GRAV_HIP(hipStreamSynchronize(p->bs));
-    }
-    {
-        // contraction over the C b^3 (centre, output component) pairs of the
-        // target leaf: value e = C t + c in chunk q, sub-row kr, k step u
-        // with e = 4 KQ kr + 4 q + u (the weight blocks' order)
-        const int KQ = (int)ceil_div((int64_t)C * b3, 16);
-        std::vector<double> swt((size_t)27 * KQ * RBt * 256, 0.0);
-        for (int nb = 0; nb < 27; ++nb)
-            for (int q = 0; q < KQ; ++q)
-                for (int rb = 0; rb < RBt; ++rb)
+            for (int q = 0; q < Qn; ++q)
+                for (int rb = 0; rb < RBn; ++rb)
                     for (int lane = 0; lane < 64; ++lane)
                         for (int u = 0; u < 4; ++u) {
-                            const int e = 4 * KQ * (lane >> 4) + 4 * q + u, cell = 16 * rb + (lane & 15);
-                            const int t = e / C, comp = e % C + 4 - C;
-                            const double v =
-                                t < b3 && cell < b3 ? dense[((size_t)nb * 4 * b3 + 4 * t + comp) * b3 + cell] : 0.0;
-                            swt[(((size_t)nb * KQ + q) * RBt + rb) * 256 + frag_pos(lane, u, f64 ? 2 : 4)] = v;
+                            int t, comp;
+                            row_target(lane & 15, rb, false, t, comp);
+                            const int cell = (lane >> 4) * 4 * Qn + 4 * q + u;
+                            double v = 0.0;
+                            if (t < b3 && cell < b3)
+                                v = dense[((size_t)nb * 4 * b3 + 4 * t + comp) * b3 + cell];
+                            sw[(((size_t)nb * Qn + q) * RBn + rb) * 256 + frag_pos(lane, u, f64 ? 2 : 4)] = v;
                         }
+        {
+            // leaf blocks of the densities, padded by one leaf per side; the
+            // padding and the rows past b^3 stay zero
+            const LevelInfo &lv = p->lev[p->L];
+            const size_t n = (size_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B * KP;
+            GRAV_CHECK(dalloc(p, &p->d_rho_blk, n, false));
+            GRAV_HIP(hipMemsetAsync(p->d_rho_blk, 0, sizeof(double) * n, p->bs));
+            GRAV_HIP(hipStreamSynchronize(p->bs));
+            // per near chunk i = (neighbour nb, four k steps q): element offsets
+            // of its density fragment (from a column's block at nb = (0, 0, 0))
+            // and of its operator fragments; the kernel reads them with scalar
+            // loads instead of recomputing them
+            const int64_t px = lv.ns[0] + 2, py = lv.ns[1] + 2, nplB = px * py * (lv.ns[2] + 2) * p->B;
+            std::vector<int64_t> tab((size_t)27 * Qn * 2);
+            for (int nb = 0; nb < 27; ++nb)
+                for (int q = 0; q < Qn; ++q) {
+                    const int64_t nboff = ((int64_t)(nb / 9) * py + (nb / 3) % 3) * px + nb % 3;
+                    tab[((size_t)nb * Qn + q) * 2 + 0] = ((int64_t)q * 4 * nplB + nboff * p->B) * 4;
+                    tab[((size_t)nb * Qn + q) * 2 + 1] = ((int64_t)nb * Qn + q) * RBn * 256;
+                }
+            GRAV_CHECK(upload(p, &p->d_lat_tab, tab));
+        }
         if (f64) {
-            GRAV_CHECK(upload(p, &p->d_tnt64, swt));
+            GRAV_CHECK(upload(p, &p->d_tn64, sw));
         } else {
-            std::vector<float> swt32(swt.begin(), swt.end());
-            GRAV_CHECK(upload(p, &p->d_tnt32, swt32));
+            std::vector<float> sw32(sw.begin(), sw.end());
+            GRAV_CHECK(upload(p, &p->d_tn32, sw32));
+        }
+        // the adjoint's transposes: rows = the cells of the source leaf (RBt
+        // blocks of 16), contraction over (target t, component) of the target
+        // leaf (near^T: the C output components; L2P^T: chunk q and k step u
+        // taking t = (lane/16) TQ + q, component u); [nb][q][rb][lane][u]
+        // group-major sets
+        {
+            // the weights of the cell centres in leaf blocks (padded by one leaf
+            // per side, 4 TQ x 4 values per leaf and model, in the near field's
+            // element type); the padding and the slots past b^3 stay zero
+            const LevelInfo &lv = p->lev[p->L];
+            const size_t n = (size_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B * 16 * TQ;
+            const size_t nd = f64 ? n : (n + 1) / 2;  // in doubles
+            GRAV_CHECK(dalloc(p, &p->d_w_blk, nd, false));
+            GRAV_HIP(hipMemsetAsync(p->d_w_blk, 0, sizeof(double) * nd, p->bs));
+            GRAV_HIP(hipStreamSynchronize(p->bs));
+        }
+        {
+            // contraction over the C b^3 (centre, output component) pairs of the
+            // target leaf: value e = C t + c in chunk q, sub-row kr, k step u
+            // with e = 4 KQ kr + 4 q + u (the weight blocks' order)
+            const int KQ = (int)ceil_div((int64_t)C * b3, 16);
+            std::vector<double> swt((size_t)27 * KQ * RBt * 256, 0.0);
+            for (int nb = 0; nb < 27; ++nb)
+                for (int q = 0; q < KQ; ++q)
+                    for (int rb = 0; rb < RBt; ++rb)
+                        for (int lane = 0; lane < 64; ++lane)
+                            for (int u = 0; u < 4; ++u) {
+                                const int e = 4 * KQ * (lane >> 4) + 4 * q + u, cell = 16 * rb + (lane & 15);
+                                const int t = e / C, comp = e % C + 4 - C;
+                                const double v =
+                                    t < b3 && cell < b3 ? dense[((size_t)nb * 4 * b3 + 4 * t + comp) * b3 + cell] : 0.0;
+                                swt[(((size_t)nb * KQ + q) * RBt + rb) * 256 + frag_pos(lane, u, f64 ? 2 : 4)] = v;
+                            }
+            if (f64) {
+                GRAV_CHECK(upload(p, &p->d_tnt64, swt));
+            } else {
+                std::vector<float> swt32(swt.begin(), swt.end());
+                GRAV_CHECK(upload(p, &p->d_tnt32, swt32));
+            }
         }
     }
     if (p->L >= 2) {
@@ -1237,18 +1347,22 @@ grav_status build_near_lattice(Plan *p, hipStream_t s)
                     full[(size_t)(4 * t + 1 + a) * PS + c] = -o[1 + a] * inv_w * inv_w;
             }
         }
-        std::vector<double> lsw((size_t)QL * RBn * 64 * 4, 0.0);
-        for (int q = 0; q < QL; ++q)
-            for (int rb = 0; rb < RBn; ++rb)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int u = 0; u < 4; ++u) {
-                        int t, comp;
-                        row_target(lane & 15, rb, !f64, t, comp);
-                        const int c = (lane >> 4) * (PS / 4) + 4 * q + u;
-                        lsw[((size_t)q * RBn + rb) * 256 + frag_pos(lane, u, 2)] =
-                            t < b3 ? full[(size_t)(4 * t + comp) * PS + c] : 0.0;
-                    }
-        GRAV_CHECK(upload(p, &p->d_tl2p, lsw));
+        if (p->near_par)
+            GRAV_CHECK(build_near_far(p, full));
+        else {
+            std::vector<double> lsw((size_t)QL * RBn * 64 * 4, 0.0);
+            for (int q = 0; q < QL; ++q)
+                for (int rb = 0; rb < RBn; ++rb)
+                    for (int lane = 0; lane < 64; ++lane)
+                        for (int u = 0; u < 4; ++u) {
+                            int t, comp;
+                            row_target(lane & 15, rb, !f64, t, comp);
+                            const int c = (lane >> 4) * (PS / 4) + 4 * q + u;
+                            lsw[((size_t)q * RBn + rb) * 256 + frag_pos(lane, u, 2)] =
+                                t < b3 ? full[(size_t)(4 * t + comp) * PS + c] : 0.0;
+                        }
+            GRAV_CHECK(upload(p, &p->d_tl2p, lsw));
+        }
         // its transpose for the adjoint: rows = coefficients (QL blocks),
         // contraction over (t, component) as the transposed near field
         std::vector<double> lst((size_t)TQ * QL * 256, 0.0);
