@@ -212,8 +212,9 @@ def roofline(plan, stages, p, prec, profile):
         "near_lat": (27 * 2.0 * (plan.spec.components * b ** 3) * b ** 3 * n_leaf_src * B,
                      "k_near_lat<%d,2,%s> (lattice near field, %s MFMA 16x16x4)"
                      % ((2, "double", "FP64") if f64 else (4, "float", "FP32")), "mfma", mm, "TFLOP/s"),
-        "m2m": (8 * 2.0 * p ** 4 * parents * B, "k_m2m_lds<%d> / k_m2m_split<%d> (M2M, FP64 MFMA 16x16x4)"
-                % (ps // 16, ps // 16), "mfma", "fp64_mfma", "TFLOP/s"),
+        # by parity: each coefficient row once per parent, not per child
+        "m2m": (2.0 * p ** 4 * parents * B, "k_octet_up<%d> / k_octet_up_short<%d> (M2M, FP64 MFMA 16x16x4)" % (p, p),
+                "mfma", "fp64_mfma", "TFLOP/s"),
         # the leaf's cells times the lattice P2M matrix (p^2 x b^3, FP64)
         "p2m": (2.0 * p * p * b ** 3 * n_leaf_src * B, "k_p2m_mfma<%d> (P2M, FP64 MFMA 16x16x4)" % (ps // 16),
                 "mfma", "fp64_mfma", "TFLOP/s"),

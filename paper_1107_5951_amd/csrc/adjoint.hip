@@ -220,279 +220,6 @@ k_t_l2p(DevGeom g, const double *tpos, const int64_t *leaf_start, const int64_t 
     }
 }
 
-// The column blocks of the transposed M2L: the boxes of level l whose ME it
-// writes (inclusive range); M2M^T adds to these and sets the others.
-struct ColBlock {
-    int lo[3], hi[3];
-};
-
-// The transposed translations M2M^T (downward over the source blocks) and
-// L2L^T (upward over the target boxes) as FP64 MFMA GEMMs in the layout of
-// the forward's k_m2m_lds: a workgroup owns 64 (box, model) columns, 16 per
-// wave, and all row blocks; the operator chunks (four k steps, all row
-// blocks) pass through LDS double-buffered, one barrier per chunk.
-//
-// L2L^T: LE_l[box] = sum over the box's children c of L2L_c^T LE_l+1[c];
-// the children of a target box are a contiguous range of level l+1 whose
-// keys give their octants.  K = 8 x p^2 (absent children read zero).
-template <int RB>
-__global__ void __launch_bounds__(256)
-k_t_l2l(DevGeom g, int l, const uint32_t *tkey, const int32_t *tchild, const double *A, double *le)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    constexpr int CH = 4 * RB * 64;
-    constexpr int NCH = 8 * RB;
-    __shared__ double sa[2][CH];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4;
-    const DevLev &lv = g.lev[l];
-    const DevLev &lc = g.lev[l + 1];
-    const int64_t col = (int64_t)blockIdx.x * 64 + wave * 16 + (lane & 15);
-    const bool cvalid = col < lv.n_tgt * g.B;
-    const int64_t box = cvalid ? col / g.B : 0;
-    const int bm = cvalid ? (int)(col % g.B) : 0;
-    int32_t ca = 0, ce = 0;
-    if (cvalid) {
-        ca = max(tchild[lv.tchild_off + box], 0);
-        ce = min(tchild[lv.tchild_off + box + 1], (int32_t)lc.n_tgt);
-    }
-    auto child = [&](int c) -> const double2 * {
-        for (int32_t ch = ca; ch < ce; ++ch)
-            if ((int)(tkey[lc.tbox_off + ch] & 7u) == c)
-                return (const double2 *)(le + ((lc.tgt_off + ch) * g.B + bm) * PS + kr * K4);
-        return nullptr;
-    };
-    vec4 acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    double ra[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        ra[i] = A[i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        sa[0][i * 256 + tid] = ra[i];
-    const double2 *bp = child(0);
-    double2 b01 = bp ? bp[0] : double2{0.0, 0.0};
-    double2 b23 = bp ? bp[1] : double2{0.0, 0.0};
-    __syncthreads();
-    for (int j = 0; j < NCH; ++j) {
-        const int buf = j & 1;
-        const bool more = j + 1 < NCH;
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                ra[i] = A[(int64_t)(j + 1) * CH + i * 256 + tid];
-        }
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-        if (more) {
-            const int qn = (j + 1) % RB;
-            if (qn == 0)
-                bp = child((j + 1) / RB);
-            b01 = bp ? bp[2 * qn] : double2{0.0, 0.0};
-            b23 = bp ? bp[2 * qn + 1] : double2{0.0, 0.0};
-        }
-        // the children's expansions as the A operand and the matrix as B:
-        // the product is the transposed tile (rows = columns, columns =
-        // coefficients)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[u], sa[buf][(u * RB + r) * 64 + lane], acc[r], 0, 0,
-                                                             0);
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        __syncthreads();
-    }
-    // output fragment: rows kr + 4 i = columns of the wave, column lane % 16
-    // = coefficient 16 r + lane % 16: 16 lanes write 128 contiguous bytes
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t oc = (int64_t)blockIdx.x * 64 + wave * 16 + kr + 4 * i;
-        if (oc >= lv.n_tgt * g.B)
-            continue;
-        double *dst = le + (lv.tgt_off * g.B + oc) * PS + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            dst[16 * r] = acc[r][i];
-    }
-}
-
-// L2L^T on levels with few boxes: a workgroup owns 16 columns and one
-// 16-row block; its eight waves take one child octant each (a chain of PS/4
-// instructions instead of 8 PS/4) and add their fragments through LDS in
-// octant order.
-template <int RB>
-__global__ void __launch_bounds__(512)
-k_t_l2l_split(DevGeom g, int l, const uint32_t *tkey, const int32_t *tchild, const double *A, double *le)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    __shared__ double red[8][256];
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    const int lane = threadIdx.x & 63, kr = lane >> 4;
-    const int c = threadIdx.x >> 6;  // the wave's child octant
-    const DevLev &lv = g.lev[l];
-    const DevLev &lc = g.lev[l + 1];
-    const int64_t cg = blockIdx.x / RB;
-    const int rb = (int)(blockIdx.x % RB);
-    const int64_t col = cg * 16 + (lane & 15);
-    const bool cvalid = col < lv.n_tgt * g.B;
-    const int64_t box = cvalid ? col / g.B : 0;
-    const int bm = cvalid ? (int)(col % g.B) : 0;
-    int64_t ci = -1;
-    if (cvalid) {
-        const int32_t ca = max(tchild[lv.tchild_off + box], 0);
-        const int32_t ce = min(tchild[lv.tchild_off + box + 1], (int32_t)lc.n_tgt);
-        for (int32_t ch = ca; ch < ce; ++ch)
-            if ((int)(tkey[lc.tbox_off + ch] & 7u) == c)
-                ci = ch;
-    }
-    vec4 acc = vec4{0, 0, 0, 0};
-    if (__ballot(ci >= 0) != 0ull) {
-        const double2 *bp = (const double2 *)(le + (ci >= 0 ? ((lc.tgt_off + ci) * g.B + bm) * PS : 0) + kr * K4);
-        const double *ap = A + (int64_t)c * PS * PS + rb * 64 + lane;  // k step ks at ap[ks * RB * 64]
-        constexpr int U = RB < 8 ? RB : 8;
-        for (int q0 = 0; q0 < RB; q0 += U) {
-            double av[U][4];
-            double2 bb[U][2];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int q = min(q0 + u, RB - 1);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    av[u][k] = ap[(int64_t)(4 * q + k) * RB * 64];
-                bb[u][0] = ci >= 0 ? bp[2 * q] : double2{0.0, 0.0};
-                bb[u][1] = ci >= 0 ? bp[2 * q + 1] : double2{0.0, 0.0};
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool in = q0 + u < RB;
-                const double bv[4] = {in ? bb[u][0].x : 0.0, in ? bb[u][0].y : 0.0, in ? bb[u][1].x : 0.0,
-                                      in ? bb[u][1].y : 0.0};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][k], bv[k], acc, 0, 0, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        red[c][lane * 4 + r] = acc[r];
-    __syncthreads();
-    if (c == 0 && cvalid) {
-        double *dst = le + ((lv.tgt_off + box) * g.B + bm) * PS;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double v = red[0][lane * 4 + r];
-#pragma unroll
-            for (int w = 1; w < 8; ++w)
-                v += red[w][lane * 4 + r];
-            dst[16 * rb + kr + 4 * r] = v;
-        }
-    }
-}
-
-// M2M^T: ME_l[child] (+)= M2M_c^T ME_l-1[parent] for the children of octant c
-// = blockIdx.y; the columns are the parent boxes of level l-1 (x models),
-// K = p^2.  Inside the transposed M2L's column block the child's ME already
-// holds the M2L^T terms and the product is added; elsewhere it is set.
-template <int RB>
-__global__ void __launch_bounds__(256)
-k_t_m2m(DevGeom g, int l, ColBlock cb, const double *A, double *me)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    constexpr int CH = 4 * RB * 64;
-    __shared__ double sa[2][CH];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4;
-    const int oct = blockIdx.y;
-    const DevLev &lv = g.lev[l];
-    const DevLev &lp = g.lev[l - 1];
-    const int64_t nbox = (int64_t)lp.ns[0] * lp.ns[1] * lp.ns[2];
-    const int64_t col = (int64_t)blockIdx.x * 64 + wave * 16 + (lane & 15);
-    const bool cvalid = col < nbox * g.B;
-    const int64_t box = cvalid ? col / g.B : 0;
-    const int bm = cvalid ? (int)(col % g.B) : 0;
-    const int x = 2 * (lp.s0[0] + (int)(box % lp.ns[0])) + (oct & 1);
-    const int y = 2 * (lp.s0[1] + (int)((box / lp.ns[0]) % lp.ns[1])) + ((oct >> 1) & 1);
-    const int z = 2 * (lp.s0[2] + (int)(box / ((int64_t)lp.ns[0] * lp.ns[1]))) + ((oct >> 2) & 1);
-    const int64_t ci = cvalid ? dense_index(lv, x, y, z) : -1;
-    const double2 *bp = (const double2 *)(me + ((lp.me_off + box) * g.B + bm) * PS + kr * K4);
-    const double *Ao = A + (int64_t)oct * PS * PS;
-    vec4 acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    double ra[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        ra[i] = Ao[i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        sa[0][i * 256 + tid] = ra[i];
-    double2 b01 = cvalid ? bp[0] : double2{0.0, 0.0};
-    double2 b23 = cvalid ? bp[1] : double2{0.0, 0.0};
-    __syncthreads();
-    for (int j = 0; j < RB; ++j) {
-        const int buf = j & 1;
-        const bool more = j + 1 < RB;
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                ra[i] = Ao[(int64_t)(j + 1) * CH + i * 256 + tid];
-        }
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-        if (more) {
-            b01 = cvalid ? bp[2 * (j + 1)] : double2{0.0, 0.0};
-            b23 = cvalid ? bp[2 * (j + 1) + 1] : double2{0.0, 0.0};
-        }
-        // the parents' expansions as the A operand and the matrix as B: the
-        // product is the transposed tile (rows = columns, columns =
-        // coefficients)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[u], sa[buf][(u * RB + r) * 64 + lane], acc[r], 0, 0,
-                                                             0);
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        __syncthreads();
-    }
-    // output fragment: rows kr + 4 i = columns of the wave (child and add
-    // flag from the lanes that own them), column lane % 16 = coefficient
-    // 16 r + lane % 16: 16 lanes write 128 contiguous bytes
-    const bool add = x >= cb.lo[0] && x <= cb.hi[0] && y >= cb.lo[1] && y <= cb.hi[1] && z >= cb.lo[2] &&
-                     z <= cb.hi[2];
-    const int ci32 = (int)ci, add32 = add ? 1 : 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int oc = kr + 4 * i;
-        const int oci = __shfl(ci32, oc);
-        const int oadd = __shfl(add32, oc);
-        if (oci < 0)
-            continue;
-        const int obm = (int)(((int64_t)blockIdx.x * 64 + wave * 16 + oc) % g.B);
-        double *dst = me + ((lv.me_off + oci) * g.B + obm) * PS + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            double *o = dst + 16 * r;
-            *o = oadd ? *o + acc[r][i] : acc[r][i];
-        }
-    }
-}
-
 // P2M^T: drho[cell] = sum_k Pm[v][k] ME_L[leaf][k] for the cells v of every
 // leaf of the source block (each mesh cell once), as FP64 MFMA: one wave
 // owns 16 (leaf, model) columns and four 16-cell row blocks (blockIdx.y
@@ -845,15 +572,15 @@ static grav_status enqueue_m2l_transposed(Plan *p, const DevGeom &g, hipStream_t
                            (const int32_t *)p->d_tmap, (const double *)p->d_le, n4, rows);
         GRAV_HIP(hipGetLastError());
     }
-    return launch_m2l<T>(p, p->m2lt, s, og, rows, p->d_me);
+    return launch_m2l<T>(p, p->m2lt, s, og, rows);
 }
 
 // Workgroups of the grouped P2M^T (each takes G groups of 64 columns so that
 // about this many cover the plan: eight per CU).
 constexpr int64_t kGroupedWorkgroups = 2048;
 
-// P2M^T for leaves of at most 64 cells (four row blocks): the layout of
-// k_m2m_lds, a workgroup owning groups of 64 leaf-fastest columns, G groups
+// P2M^T for leaves of at most 64 cells (four row blocks): a workgroup
+// owning groups of 64 leaf-fastest columns, G groups
 // one after the other, with the chunks of the operator (four k steps, all
 // row blocks) double-buffered in LDS.  The chunk sequence runs on across
 // its groups (step s = chunk s % RB of group s / RB), so the loads of a
@@ -1178,58 +905,6 @@ k_t_l2p_lat(DevGeom g, const double *A, int TQ, const int32_t *tmap, const doubl
 
 #define GRAV_T_RB_CASES(X) X(1) X(2) X(3) X(4) X(6) X(7) X(8) X(9) X(11) X(13) X(15) X(16)
 
-// levels with fewer 64-column workgroups than this take the split kernel
-constexpr int64_t kTileWgsMin = 256;
-
-static grav_status launch_t_l2l(Plan *p, const DevGeom &g, int l, hipStream_t s)
-{
-    const int64_t ncol = p->lev[l].n_tgt * p->B;
-    const int RB = p->PS / 16;
-    const bool tiled = ceil_div(ncol, 64) >= kTileWgsMin;
-    const dim3 grid((unsigned)ceil_div(ncol, 64)), grid_split((unsigned)(ceil_div(ncol, 16) * RB));
-#define CASE(R)                                                                                            \
-    case R:                                                                                                \
-        if (tiled)                                                                                         \
-            hipLaunchKernelGGL((k_t_l2l<R>), grid, dim3(256), 0, s, g, l, (const uint32_t *)p->d_tkey,     \
-                               (const int32_t *)p->d_tchild, (const double *)p->d_l2lt_sw, p->d_le);       \
-        else                                                                                               \
-            hipLaunchKernelGGL((k_t_l2l_split<R>), grid_split, dim3(512), 0, s, g, l,                      \
-                               (const uint32_t *)p->d_tkey, (const int32_t *)p->d_tchild,                  \
-                               (const double *)p->d_l2lt_sw, p->d_le);                                     \
-        break;
-    switch (RB) {
-        GRAV_T_RB_CASES(CASE)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
-static grav_status launch_t_m2m(Plan *p, const DevGeom &g, int l, hipStream_t s)
-{
-    const LevelInfo &lv = p->lev[l];
-    ColBlock cb;
-    for (int a = 0; a < 3; ++a) {
-        cb.lo[a] = lv.cs0[a];
-        cb.hi[a] = lv.cs0[a] + lv.cns[a] - 1;
-    }
-    const dim3 grid((unsigned)ceil_div(p->lev[l - 1].n_src * p->B, 64), 8);
-#define CASE(R)                                                                                             \
-    case R:                                                                                                 \
-        hipLaunchKernelGGL((k_t_m2m<R>), grid, dim3(256), 0, s, g, l, cb, (const double *)p->d_m2mt_sw, p->d_me); \
-        break;
-    switch (p->PS / 16) {
-        GRAV_T_RB_CASES(CASE)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
 static grav_status launch_t_p2m(Plan *p, const DevGeom &g, double *drho, hipStream_t s)
 {
     const int b3 = p->b * p->b * p->b, RBT = (b3 + 15) / 16;
@@ -1349,9 +1024,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
             GRAV_CHECK(launch_t_l2p_lat(p, g, resid, pts ? 1 : 0, s));
         stage_end(p, s);
         stage_begin(p, "l2lT", s);
-        for (int l = L - 1; l >= 2; --l)
-            if (p->lev[l].n_tgt > 0)
-                GRAV_CHECK(launch_t_l2l(p, g, l, s));
+        for (int l = L; l >= 3; --l)
+            GRAV_CHECK(launch_octet_up(p, p->m2l, l, s, p->d_l2lt, p->d_le, nullptr));
         stage_end(p, s);
         stage_begin(p, "m2lT", s);
         if (p->d.precision == GRAV_FP64)
@@ -1360,8 +1034,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
             GRAV_CHECK(enqueue_m2l_transposed<float>(p, g, s));
         stage_end(p, s);
         stage_begin(p, "m2mT", s);
-        for (int l = 3; l <= L; ++l)
-            GRAV_CHECK(launch_t_m2m(p, g, l, s));
+        for (int l = 2; l <= L; ++l)
+            GRAV_CHECK(launch_octet_down(p, p->m2lt, l, s, p->d_m2mt, p->d_me));
         stage_end(p, s);
         if (p->n_spts == 0) {
             stage_begin(p, "p2mT", s);

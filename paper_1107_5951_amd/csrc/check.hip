@@ -47,8 +47,7 @@ struct Checker {
 // segments every orbit of a unit with a source once, in one slot each, every
 // input row lies in [0, nin), and every output row is written by exactly one octet.
 void check_octets(Checker &ck, const char *name, const Plan *p, const OctPlan &o, const OctGeom &g,
-                  int64_t nin, int64_t nout, bool all_out,
-                  const std::function<bool(int, int32_t)> &present)
+                  int64_t nin, int64_t nout, const std::function<bool(int, int32_t)> &present)
 {
     const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
     const auto key = fetch(o.d_key, (size_t)o.noct);
@@ -70,9 +69,26 @@ void check_octets(Checker &ck, const char *name, const Plan *p, const OctPlan &o
     for (int64_t i = 0; i < o.noct * 8 && ck.ok; ++i)
         if (child[i] >= 0 && (child[i] >= nout || written[child[i]]++))
             ck.fail(name, "output row out of range or repeated", i, child[i]);
-    for (int64_t i = 0; i < nout && ck.ok && all_out; ++i)
+    for (int64_t i = 0; i < nout && ck.ok; ++i)
         if (!written[i])
             ck.fail(name, "expansion never written", i, nout);
+    // the parent of an octet is the box of its key in the level above, whose own
+    // row is a child of exactly one octet there
+    const auto parent = fetch(o.d_parent, (size_t)o.noct);
+    std::vector<int64_t> octet_of((size_t)nout, -1);
+    for (int64_t i = 0; i < o.noct * 8 && ck.ok; ++i)
+        if (child[i] >= 0)
+            octet_of[child[i]] = i;
+    for (int l = 2; l <= p->L && ck.ok; ++l)
+        for (int64_t i = o.first[l]; i < o.first[l + 1] && ck.ok; ++i) {
+            if (l == 2 ? parent[i] != -1 : parent[i] < 0 || parent[i] >= nout)
+                ck.fail(name, "parent row out of range", i, parent[i]);
+            else if (l > 2) {
+                const int64_t at = octet_of[parent[i]];
+                if (at < 8 * o.first[l - 1] || at >= 8 * o.first[l] || ((key[at / 8] << 3) | (uint32_t)(at % 8)) != key[i])
+                    ck.fail(name, "parent row is another box's", i, parent[i]);
+            }
+        }
     int64_t covered = 0;
     for (int64_t i = 0; i < o.ngroup && ck.ok; ++i) {
         const OctGroup &gr = groups[i];
@@ -146,20 +162,12 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
     GRAV_HIP(hipDeviceSynchronize());
     const DevGeom g = make_geom(p);
     const int L = p->L;
-    int64_t ntile = 0;
-    for (int k = 0; k < TK_COUNT; ++k)
-        for (int l = 0; l <= kMaxLevels; ++l)
-            ntile = std::max<int64_t>(ntile, p->tiles[k][l].off + p->tiles[k][l].n);
     int64_t ntb = 0;
     const int lo = L >= 2 ? 2 : L;
     for (int l = lo; l <= L; ++l)
         ntb = std::max<int64_t>(ntb, p->tbox_off[l] + p->lev[l].n_tgt);
-    const auto tiles = fetch(p->d_tiles, (size_t)ntile);
     const auto tkey = fetch(p->d_tkey, (size_t)ntb);
-    const auto torder = fetch(p->d_torder, (size_t)ntb);
-    const auto tparent = fetch(p->d_tparent, (size_t)ntb);
     const auto tmap = fetch(p->d_tmap, (size_t)p->n_tmap);
-    const auto tchild = fetch(p->d_tchild, (size_t)p->n_tchild);
     const auto leaf_start = fetch(p->d_leaf_start, (size_t)p->n_leaf + 1);
     const auto tleaf = fetch(p->d_tleaf, (size_t)p->M);
     const auto perm = fetch(p->d_perm, (size_t)p->M);
@@ -210,18 +218,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
             const uint32_t k = tkey[lv.tbox_off + i];
             if (i > 0 && k <= tkey[lv.tbox_off + i - 1])
                 ck.fail("tree", "box keys not strictly increasing", l, i);
-            if (l > lo) {
-                const int32_t par = tparent[lv.tbox_off + i];
-                if (par < 0 || par >= p->lev[l - 1].n_tgt)
-                    ck.fail("tree", "parent out of range", par, p->lev[l - 1].n_tgt);
-                else if (tkey[g.lev[l - 1].tbox_off + par] != (k >> 3))
-                    ck.fail("tree", "parent key mismatch", l, i);
-            }
-            if (l >= 2) {
-                const int32_t o = torder[lv.tbox_off + i];
-                if (o < 0 || o >= p->lev[l].n_tgt)
-                    ck.fail("tree", "class order out of range", o, p->lev[l].n_tgt);
-            }
         }
         // target map entries
         const int64_t msz = (int64_t)(lv.ns[0] + 6) * (lv.ns[1] + 6) * (lv.ns[2] + 6);
@@ -229,14 +225,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
             const int32_t v = tmap[lv.tmap_off + i];
             if (v < -1 || v >= p->lev[l].n_tgt)
                 ck.fail("tmap", "entry out of range", v, p->lev[l].n_tgt);
-        }
-    }
-    for (int l = 2; l < L && ck.ok; ++l) {
-        const DevLev &lv = g.lev[l];
-        for (int64_t i = 0; i < p->lev[l].n_tgt && ck.ok; ++i) {
-            const int32_t a = tchild[lv.tchild_off + i], b = tchild[lv.tchild_off + i + 1];
-            if (!(0 <= a && a < b && b <= p->lev[l + 1].n_tgt && b - a <= 8))
-                ck.fail("tchild", "bad child range", a, b);
         }
     }
     // near field / leaf kernels: neighbour leaves within the source block or skipped
@@ -252,27 +240,9 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
     }
 
     if (L >= 2 && ck.ok) {
-        // the L2L's tiles: columns inside their class, every box once
-        const TileRange &r = p->tiles[TK_L2L][0];
-        std::vector<char> seen_le((size_t)p->n_tbox * p->B, 0);
-        for (int64_t t = 0; t < r.n && ck.ok; ++t) {
-            const GemmTile &tl = tiles[r.off + t];
-            const LevelInfo &lv = p->lev[tl.level];
-            if (tl.ncol < 1 || tl.ncol > kTileCols || tl.col0 < 0 ||
-                tl.col0 + tl.ncol > (lv.class_start[tl.cls + 1] - lv.class_start[tl.cls]) * p->B)
-                ck.fail("l2l", "tile outside its class", t, tl.ncol);
-            for (int64_t c = tl.col0; c < tl.col0 + tl.ncol && ck.ok; ++c) {
-                const int64_t box = torder[p->tbox_off[tl.level] + lv.class_start[tl.cls] + c / p->B];
-                if (seen_le[(lv.tgt_off + box) * p->B + c % p->B]++)
-                    ck.fail("l2l", "two columns write one expansion", box, tl.level);
-            }
-        }
-        for (size_t i = 0; i < seen_le.size() && ck.ok; ++i)
-            if (!seen_le[i])
-                ck.fail("l2l", "expansion in no tile", (long long)i, (long long)seen_le.size());
-        // both M2L directions
+        // the octets of the target and of the source boxes
         const OctGeom fg = octet_geom(p, false), tg = octet_geom(p, true);
-        check_octets(ck, "m2l", p, p->m2l, fg, p->n_me, p->n_tbox, true, nullptr);
+        check_octets(ck, "m2l", p, p->m2l, fg, p->n_me, p->n_tbox, nullptr);
         // the gather regions hold every target box within reach and lie in
         // the target maps (source block + halo 3)
         for (int l = 2; l <= L && ck.ok; ++l)
@@ -280,7 +250,7 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
                 if (tg.lev[l].ns[a] > 0 && (tg.lev[l].s0[a] < p->lev[l].s0[a] - 3 ||
                                             tg.lev[l].s0[a] + tg.lev[l].ns[a] > p->lev[l].s0[a] + p->lev[l].ns[a] + 3))
                     ck.fail("m2lT", "gather region outside the target map", l, a);
-        check_octets(ck, "m2lT", p, p->m2lt, tg, p->n_grow, p->n_me, false, [&](int l, int32_t j) {
+        check_octets(ck, "m2lT", p, p->m2lt, tg, p->n_grow, p->n_me, [&](int l, int32_t j) {
             const OctLev &t = tg.lev[l];
             return tmap_lookup(g.lev[l], tmap.data(), 3, t.s0[0] + j % t.ns[0], t.s0[1] + j / t.ns[0] % t.ns[1],
                                t.s0[2] + j / (t.ns[0] * t.ns[1])) >= 0;

@@ -9,10 +9,6 @@
 #include "octet.hpp"
 #include "resolve.hpp"
 
-#ifndef GRAV_M2M_LDS_MIN_WG
-#define GRAV_M2M_LDS_MIN_WG 256  // 64-column M2M tiles from this many workgroups on
-#endif
-
 namespace grav {
 
 // --------------------------------------------------------------------------
@@ -202,370 +198,17 @@ __global__ void __launch_bounds__(256) k_p2m_lds(DevGeom g, const double *rho, c
         }
 }
 
-// --------------------------------------------------------------------------
-// M2M on MFMA (FP64): ME[parent] = sum over the 8 children c of T_c ME[child],
-// a GEMM with M = p^2 rows, K = 8 p^2 and columns = (parent box, model).
-// The operator is stored as 8 RB chunks of four k steps each (all row
-// blocks of a k step together, 64 lanes per fragment); within a child the
-// contraction order is kr * PS/4 + ks, so a lane's four k steps of a chunk
-// are four consecutive coefficients of its child's expansion.  A child
-// outside the source block contributes zero.
-//
-// Large levels: k_m2m_lds.  A workgroup owns 64 columns (16 per wave) and
-// all row blocks; the chunks of the operator pass through LDS (double
-// buffered, one barrier per chunk), so each is read from L2 once per 64
-// columns instead of once per wave, and each wave streams its columns'
-// child expansions once.
-// --------------------------------------------------------------------------
-template <int RB>
-__global__ void __launch_bounds__(256) k_m2m_lds(DevGeom g, int l, const double *A, double *me)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    constexpr int CH = 4 * RB * 64;  // doubles per chunk: 4 k steps x RB blocks x 64 lanes
-    constexpr int NCH = 8 * RB;      // chunks: 8 children x RB chunks of 4 k steps
-    __shared__ double sa[2][CH];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const DevLev &lp = g.lev[l];
-    const DevLev &lc = g.lev[l + 1];
-    const int64_t nbox = (int64_t)lp.ns[0] * lp.ns[1] * lp.ns[2];
-    const int64_t col = (int64_t)blockIdx.x * 64 + wave * 16 + (lane & 15);
-    const bool cvalid = col < nbox * g.B;
-    const int64_t box = cvalid ? col / g.B : 0;
-    const int bm = cvalid ? (int)(col % g.B) : 0;
-    const int px = lp.s0[0] + (int)(box % lp.ns[0]);
-    const int py = lp.s0[1] + (int)((box / lp.ns[0]) % lp.ns[1]);
-    const int pz = lp.s0[2] + (int)(box / ((int64_t)lp.ns[0] * lp.ns[1]));
-    const int kr = lane >> 4;
-    // the column's expansion of child c (nullptr: no such child)
-    auto child = [&](int c) -> const double2 * {
-        const int64_t ci = cvalid ? dense_index(lc, 2 * px + (c & 1), 2 * py + ((c >> 1) & 1),
-                                                2 * pz + ((c >> 2) & 1))
-                                  : -1;
-        return ci >= 0 ? (const double2 *)(me + ((lc.me_off + ci) * g.B + bm) * PS + kr * K4) : nullptr;
-    };
-    vec4 acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    double ra[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        ra[i] = A[i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        sa[0][i * 256 + tid] = ra[i];
-    const double2 *bp = child(0);
-    double2 b01 = bp ? bp[0] : double2{0.0, 0.0};
-    double2 b23 = bp ? bp[1] : double2{0.0, 0.0};
-    __syncthreads();
-    for (int j = 0; j < NCH; ++j) {
-        const int buf = j & 1;
-        const bool more = j + 1 < NCH;
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                ra[i] = A[(int64_t)(j + 1) * CH + i * 256 + tid];
-        }
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-        if (more) {
-            const int qn = (j + 1) % RB;
-            if (qn == 0)
-                bp = child((j + 1) / RB);
-            b01 = bp ? bp[2 * qn] : double2{0.0, 0.0};
-            b23 = bp ? bp[2 * qn + 1] : double2{0.0, 0.0};
-        }
-        // the expansions as the A operand and the operator as B: the product
-        // is the transposed tile (rows = columns, columns = coefficients)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[u], sa[buf][(u * RB + r) * 64 + lane], acc[r], 0, 0,
-                                                             0);
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        __syncthreads();
-    }
-    // output fragment: rows kr + 4 i = columns of the wave, column lane % 16
-    // = coefficient 16 r + lane % 16: 16 lanes write 128 contiguous bytes
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t oc = (int64_t)blockIdx.x * 64 + wave * 16 + kr + 4 * i;
-        if (oc >= nbox * g.B)
-            continue;
-        double *dst = me + (lp.me_off * g.B + oc) * PS + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            dst[16 * r] = acc[r][i];
-    }
-}
-
-// Small levels (too few columns to fill the chip with 64-column tiles):
-// k_m2m_split.  A workgroup owns 16 columns and one 16-row block; its eight
-// waves take one child each, so every wave runs PS/4 MFMAs behind a single
-// round of loads, and the eight partial fragments are added through LDS in
-// child order.
-template <int RB>
-__global__ void __launch_bounds__(512) k_m2m_split(DevGeom g, int l, const double *A, double *me)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    __shared__ double red[8][256];
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    const int lane = threadIdx.x & 63;
-    const int c = threadIdx.x >> 6;  // the wave's child
-    const DevLev &lp = g.lev[l];
-    const DevLev &lc = g.lev[l + 1];
-    const int64_t cg = blockIdx.x / RB;
-    const int rb = (int)(blockIdx.x % RB);
-    const int64_t nbox = (int64_t)lp.ns[0] * lp.ns[1] * lp.ns[2];
-    const int64_t col = cg * 16 + (lane & 15);
-    const bool cvalid = col < nbox * g.B;
-    const int64_t box = cvalid ? col / g.B : 0;
-    const int bm = cvalid ? (int)(col % g.B) : 0;
-    const int px = lp.s0[0] + (int)(box % lp.ns[0]);
-    const int py = lp.s0[1] + (int)((box / lp.ns[0]) % lp.ns[1]);
-    const int pz = lp.s0[2] + (int)(box / ((int64_t)lp.ns[0] * lp.ns[1]));
-    const int kr = lane >> 4;
-    const int64_t ci =
-        cvalid ? dense_index(lc, 2 * px + (c & 1), 2 * py + ((c >> 1) & 1), 2 * pz + ((c >> 2) & 1)) : -1;
-    vec4 acc = vec4{0, 0, 0, 0};
-    if (__ballot(ci >= 0) != 0ull) {
-        const double2 *bp = (const double2 *)(me + (ci >= 0 ? ((lc.me_off + ci) * g.B + bm) * PS : 0) + kr * K4);
-        const double *ap = A + (int64_t)c * PS * PS + rb * 64 + lane;  // k step ks at ap[ks * RB * 64]
-        constexpr int U = RB < 8 ? RB : 8;  // chunks of four k steps loaded together
-        for (int q0 = 0; q0 < RB; q0 += U) {
-            double av[U][4];
-            double2 bb[U][2];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int q = min(q0 + u, RB - 1);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    av[u][k] = ap[(int64_t)(4 * q + k) * RB * 64];
-                bb[u][0] = ci >= 0 ? bp[2 * q] : double2{0.0, 0.0};
-                bb[u][1] = ci >= 0 ? bp[2 * q + 1] : double2{0.0, 0.0};
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool in = q0 + u < RB;
-                const double bv[4] = {in ? bb[u][0].x : 0.0, in ? bb[u][0].y : 0.0, in ? bb[u][1].x : 0.0,
-                                      in ? bb[u][1].y : 0.0};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][k], bv[k], acc, 0, 0, 0);
-            }
-        }
-    }
-    // the eight waves' fragments share one lane layout: add them in child order
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        red[c][lane * 4 + r] = acc[r];
-    __syncthreads();
-    if (c == 0 && cvalid) {
-        double *dst = me + ((lp.me_off + box) * g.B + bm) * PS;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            double v = red[0][lane * 4 + r];
-#pragma unroll
-            for (int w = 1; w < 8; ++w)
-                v += red[w][lane * 4 + r];
-            dst[16 * rb + kr + 4 * r] = v;
-        }
-    }
-}
-
-// --------------------------------------------------------------------------
-// L2L on MFMA (FP64): LE[child] += T_c LE[parent] for the target boxes of
-// level l, grouped by child octant c (the M2L tiles of the level: same
-// columns, one matrix per tile).  Four waves of 16 columns per workgroup.
-// --------------------------------------------------------------------------
-// L2L, LDS-tiled (FP64 MFMA): a workgroup takes one M2L tile of a level (64
-// target-box columns of one child octant, so one matrix) with all row
-// blocks; the matrix passes through LDS in double-buffered chunks of four k
-// steps, each wave streams its 16 columns' parent expansions once and adds
-// the products into the children's LE.
-// --------------------------------------------------------------------------
-template <int RB>
-__global__ void __launch_bounds__(256)
-k_l2l_lds(DevGeom g, const GemmTile *tiles, int stride, const int32_t *torder, const int32_t *tparent, const double *A,
-          double *le)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int K4 = PS / 4;
-    constexpr int CH = 4 * RB * 64;
-    __shared__ double sa[2][CH];
-    const GemmTile tile = tiles[(int64_t)blockIdx.x * stride];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4;
-    const DevLev &lv = g.lev[tile.level];
-    const DevLev &lp = g.lev[tile.level - 1];
-    const int cl = wave * 16 + (lane & 15);
-    const bool cvalid = cl < tile.ncol;
-    const int64_t col = tile.col0 + cl;
-    const int bm = (int)(col % g.B);
-    int64_t box = 0, par = 0;
-    if (cvalid) {
-        box = torder[lv.tbox_off + lv.class_start[tile.cls] + col / g.B];
-        par = tparent[lv.tbox_off + box];
-    }
-    const double2 *bp = (const double2 *)(le + ((lp.tgt_off + par) * g.B + bm) * PS + kr * K4);
-    const double *Ao = A + (int64_t)tile.cls * PS * PS;
-    vec4 acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    double ra[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        ra[i] = Ao[i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        sa[0][i * 256 + tid] = ra[i];
-    double2 b01 = cvalid ? bp[0] : double2{0.0, 0.0};
-    double2 b23 = cvalid ? bp[1] : double2{0.0, 0.0};
-    __syncthreads();
-    for (int j = 0; j < RB; ++j) {
-        const int buf = j & 1;
-        const bool more = j + 1 < RB;
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                ra[i] = Ao[(int64_t)(j + 1) * CH + i * 256 + tid];
-        }
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-        if (more) {
-            b01 = cvalid ? bp[2 * (j + 1)] : double2{0.0, 0.0};
-            b23 = cvalid ? bp[2 * (j + 1) + 1] : double2{0.0, 0.0};
-        }
-        // the parents' expansions as the A operand and the matrix as B: the
-        // product is the transposed tile (rows = columns, columns =
-        // coefficients)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[u], sa[buf][(u * RB + r) * 64 + lane], acc[r], 0, 0,
-                                                             0);
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        __syncthreads();
-    }
-    // output fragment: rows kr + 4 i = columns of the wave (their boxes from
-    // the lanes that own them), column lane % 16 = coefficient 16 r +
-    // lane % 16: 16 lanes add into 128 contiguous bytes
-    const int box32 = (int)box;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int oc = kr + 4 * i;
-        const int obox = __shfl(box32, oc);
-        if (wave * 16 + oc >= tile.ncol)
-            continue;
-        const int obm = (int)((tile.col0 + wave * 16 + oc) % g.B);
-        double *dst = le + ((lv.tgt_off + obox) * g.B + obm) * PS + (lane & 15);
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            dst[16 * r] += acc[r][i];
-    }
-}
-
-// --------------------------------------------------------------------------
-// L2L on MFMA (FP64): LE[child] += T_c LE[parent] for the target boxes of
-// level l, grouped by child octant c (the M2L tiles of the level: same
-// columns, one matrix per tile).  A workgroup takes one tile (four waves of
-// 16 columns) and one 16-row block (blockIdx.y), so a level has RB times
-// as many workgroups as tiles.
-// --------------------------------------------------------------------------
-template <int RB>
-__global__ void __launch_bounds__(256)
-k_l2l_mfma(DevGeom g, const GemmTile *tiles, int stride, const uint32_t *tkey, const int32_t *torder,
-           const int32_t *tparent, const double *A, double *le)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    const GemmTile tile = tiles[(int64_t)blockIdx.x * stride];
-    const int rb = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const DevLev &lv = g.lev[tile.level];
-    const DevLev &lp = g.lev[tile.level - 1];
-    const int cl = wave * 16 + (lane & 15);
-    const bool cvalid = cl < tile.ncol;
-    const int64_t col = tile.col0 + cl;
-    const int bm = (int)(col % g.B);
-    int64_t box = 0, par = 0;
-    if (cvalid) {
-        box = torder[lv.tbox_off + lv.class_start[tile.cls] + col / g.B];
-        par = tparent[lv.tbox_off + box];
-    }
-    vec4 acc = vec4{0, 0, 0, 0};
-    const int kr = lane >> 4;
-    // B: column (lane % 16) of the parent LE, contraction order kr * PS/4 + ks
-    const double2 *bp = (const double2 *)(le + (cvalid ? ((lp.tgt_off + par) * g.B + bm) * PS : 0) + kr * (PS / 4));
-    const double *ap = A + ((int64_t)tile.cls * RB * RB + rb) * 256;  // [c][q][rb] sets of 4 per lane
-    // the child's LE (from the M2L) is read with the operands, not after the
-    // products: no other workgroup writes these entries during the launch
-    double *dst = le + ((lv.tgt_off + box) * g.B + bm) * PS;
-    double old[4] = {0.0, 0.0, 0.0, 0.0};
-    if (cvalid) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            old[r] = dst[16 * rb + kr + 4 * r];
-    }
-    constexpr int U = RB < 8 ? RB : 8;  // chunks of four k steps loaded together
-    for (int q0 = 0; q0 < RB; q0 += U) {
-        double av[U][4];
-        double2 bb[U][2];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = min(q0 + u, RB - 1);
-            load_frags<double, 4>(ap + (int64_t)q * RB * 256, lane, av[u]);
-            bb[u][0] = bp[2 * q];
-            bb[u][1] = bp[2 * q + 1];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = cvalid && q0 + u < RB;
-            const double bv[4] = {in ? bb[u][0].x : 0.0, in ? bb[u][0].y : 0.0, in ? bb[u][1].x : 0.0,
-                                  in ? bb[u][1].y : 0.0};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][k], bv[k], acc, 0, 0, 0);
-        }
-    }
-    if (!cvalid)
-        return;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        dst[16 * rb + kr + 4 * r] = old[r] + acc[r];
-}
-
-// Expansions in FP32 for the mixed M2L, natural order.  Boxes farther than 3
-// boxes from every target box of their level are skipped (for
-// surface stations, the deep part of the mesh): no M2L reads them.  One thread per four coefficients.
-__global__ void __launch_bounds__(256)
-k_me_f32(DevGeom g, const double *src, int64_t n4, float *dst)
+// The leaves' expansions in FP32 for the mixed M2L (the levels above are
+// written by the M2M).  Leaves farther than 3 boxes from every target box (for
+// surface stations, the deep part of the mesh) are skipped: no M2L reads them.
+// One thread per four coefficients; src and dst at the level's first row.
+__global__ void __launch_bounds__(256) k_leaf_f32(DevGeom g, const double *src, int64_t n4, float *dst)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n4)
         return;
-    const int64_t box = i / ((int64_t)(g.PS / 4) * g.B);
-    int l = 2;
-    while (l < g.L && box >= g.lev[l + 1].me_off)
-        ++l;
-    const DevLev &lv = g.lev[l];
-    const int64_t j = box - lv.me_off;
+    const int64_t j = i / ((int64_t)(g.PS / 4) * g.B);
+    const DevLev &lv = g.lev[g.L];
     const int x = lv.s0[0] + (int)(j % lv.ns[0]), y = lv.s0[1] + (int)((j / lv.ns[0]) % lv.ns[1]),
               z = lv.s0[2] + (int)(j / ((int64_t)lv.ns[0] * lv.ns[1]));
     if (x < lv.need_lo[0] || x > lv.need_hi[0] || y < lv.need_lo[1] || y > lv.need_hi[1] || z < lv.need_lo[2] ||
@@ -1273,10 +916,7 @@ DevGeom make_geom(const Plan *p)
         d.me_off = s.me_off;
         d.tgt_off = s.tgt_off;
         d.tbox_off = p->tbox_off[l];
-        for (int c = 0; c < 9; ++c)
-            d.class_start[c] = s.class_start[c];
         d.tmap_off = s.tmap_off;
-        d.tchild_off = s.tchild_off;
         d.n_tgt = s.n_tgt;
         for (int a = 0; a < 3; ++a) {
             d.need_lo[a] = s.need_lo[a];
@@ -1326,43 +966,6 @@ void stage_end(Plan *p, hipStream_t s)
     ++p->n_stage_used;
 }
 
-static grav_status launch_m2m(Plan *p, const DevGeom &g, int l, hipStream_t s)
-{
-    const int RB = p->PS / 16;
-    const int64_t ncol = p->lev[l].n_src * p->B;
-    // 64-column tiles once they give every CU a workgroup or more
-    const bool lds = (ncol + 63) / 64 >= GRAV_M2M_LDS_MIN_WG;
-    const dim3 grid_lds((unsigned)((ncol + 63) / 64)), grid_split((unsigned)((ncol + 15) / 16 * RB));
-#define M2M_CASE(R)                                                                                          \
-    case R:                                                                                                  \
-        if (lds)                                                                                             \
-            hipLaunchKernelGGL((k_m2m_lds<R>), grid_lds, dim3(256), 0, s, g, l, (const double *)p->d_m2m_sw, \
-                               p->d_me);                                                                     \
-        else                                                                                                 \
-            hipLaunchKernelGGL((k_m2m_split<R>), grid_split, dim3(512), 0, s, g, l,                          \
-                               (const double *)p->d_m2m_sw, p->d_me);                                        \
-        break;
-    switch (RB) {
-        M2M_CASE(1)
-        M2M_CASE(2)
-        M2M_CASE(3)
-        M2M_CASE(4)
-        M2M_CASE(6)
-        M2M_CASE(7)
-        M2M_CASE(8)
-        M2M_CASE(9)
-        M2M_CASE(11)
-        M2M_CASE(13)
-        M2M_CASE(15)
-        M2M_CASE(16)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef M2M_CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
 static grav_status launch_p2m(Plan *p, const DevGeom &g, const double *rho, hipStream_t s)
 {
     const int RB = p->PS / 16;
@@ -1401,50 +1004,6 @@ static grav_status launch_p2m(Plan *p, const DevGeom &g, const double *rho, hipS
         return GRAV_EUNSUPPORTED;
     }
 #undef P2M_CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
-static grav_status launch_l2l(Plan *p, const DevGeom &g, int l, hipStream_t s)
-{
-    const TileRange &all = p->tiles[TK_L2L][0];
-    const TileRange &r = p->tiles[TK_L2L][l];
-    if (r.n == 0)
-        return GRAV_OK;
-    const int S = p->split[TK_L2L];
-    const GemmTile *t0 = (const GemmTile *)(p->d_tiles + all.off) + r.off * S;
-    dim3 grid((unsigned)r.n, (unsigned)(p->PS / 16)), blk(256);
-    // one workgroup per tile with all row blocks once the level has enough
-    // tiles to fill the chip; otherwise one workgroup per (tile, row block)
-    const bool tiled = r.n >= GRAV_M2M_LDS_MIN_WG;
-#define L2L_CASE(R)                                                                             \
-    case R:                                                                                     \
-        if (tiled)                                                                              \
-            hipLaunchKernelGGL((k_l2l_lds<R>), dim3((unsigned)r.n), blk, 0, s, g, t0, S,        \
-                               (const int32_t *)p->d_torder, (const int32_t *)p->d_tparent,     \
-                               (const double *)p->d_l2l_msw, p->d_le);                          \
-        else                                                                                    \
-            hipLaunchKernelGGL((k_l2l_mfma<R>), grid, blk, 0, s, g, t0, S, (const uint32_t *)p->d_tkey, \
-                               (const int32_t *)p->d_torder, (const int32_t *)p->d_tparent,     \
-                               (const double *)p->d_l2l_sw, p->d_le);                           \
-        break;
-    switch (p->PS / 16) {
-        L2L_CASE(1)
-        L2L_CASE(2)
-        L2L_CASE(3)
-        L2L_CASE(4)
-        L2L_CASE(6)
-        L2L_CASE(7)
-        L2L_CASE(8)
-        L2L_CASE(9)
-        L2L_CASE(11)
-        L2L_CASE(13)
-        L2L_CASE(15)
-        L2L_CASE(16)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef L2L_CASE
     GRAV_HIP(hipGetLastError());
     return GRAV_OK;
 }
@@ -1524,28 +1083,29 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
             GRAV_CHECK(launch_p2m(p, g, rho, s));
         }
         stage_end(p, s);
+        // expansions in FP32 for the M2L of mixed plans
+        float *rows = p->d.precision == GRAV_FP64 ? nullptr : reinterpret_cast<float *>(p->d_rows);
         stage_begin(p, "m2m", s);
-        for (int l = L - 1; l >= 2; --l)
-            GRAV_CHECK(launch_m2m(p, g, l, s));
+        for (int l = L; l >= 3; --l)
+            GRAV_CHECK(launch_octet_up(p, p->m2lt, l, s, p->d_m2m, p->d_me, rows));
         stage_end(p, s);
         stage_begin(p, "m2l", s);
         {
             const OctGeom og = octet_geom(p, false);
-            if (p->d.precision == GRAV_FP64) {
-                GRAV_CHECK(launch_m2l<double>(p, p->m2l, s, og, p->d_me, p->d_le));
+            if (!rows) {
+                GRAV_CHECK(launch_m2l<double>(p, p->m2l, s, og, p->d_me));
             } else {
-                float *rows = reinterpret_cast<float *>(p->d_rows);
-                const int64_t n4 = p->n_me * p->B * (p->PS / 4);
-                hipLaunchKernelGGL(k_me_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
-                                   (const double *)p->d_me, n4, rows);
+                const int64_t at = p->lev[L].me_off * p->B * p->PS, n4 = p->lev[L].n_src * p->B * (p->PS / 4);
+                hipLaunchKernelGGL(k_leaf_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
+                                   (const double *)(p->d_me + at), n4, rows + at);
                 GRAV_HIP(hipGetLastError());
-                GRAV_CHECK(launch_m2l<float>(p, p->m2l, s, og, rows, p->d_le));
+                GRAV_CHECK(launch_m2l<float>(p, p->m2l, s, og, rows));
             }
         }
         stage_end(p, s);
         stage_begin(p, "l2l", s);
-        for (int l = 3; l <= L; ++l)
-            GRAV_CHECK(launch_l2l(p, g, l, s));
+        for (int l = 2; l <= L; ++l)
+            GRAV_CHECK(launch_octet_down(p, p->m2l, l, s, p->d_l2l, p->d_le));
         stage_end(p, s);
     }
     if (p->lat_near) {

@@ -11,9 +11,7 @@ struct DevLev {
     int64_t me_off;
     int64_t tgt_off;
     int64_t tbox_off;
-    int64_t class_start[9];
     int64_t tmap_off;
-    int64_t tchild_off;
     int64_t n_tgt;       // target boxes of the level
     int need_lo[3];      // box range (inclusive) whose expansions the M2L reads
     int need_hi[3];
@@ -31,9 +29,12 @@ struct DevGeom {
 DevGeom make_geom(const Plan *p);
 struct OctGeom;
 // The M2L of one direction on `in` ([row][model][PS], the element type of
-// the plan's M2L), setting the expansions of the octets' boxes in `out`.
+// the plan's M2L) into the segment slots.
 template <typename T>
-grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in, double *out);
+grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in);
+grav_status launch_octet_up(const Plan *p, const OctPlan &o, int l, hipStream_t s, const double *A, double *x,
+                            float *out32);
+grav_status launch_octet_down(const Plan *p, const OctPlan &o, int l, hipStream_t s, const double *A, double *x);
 grav_status launch_near_par(const Plan *p, const DevGeom &g, const double *rho, double *out, hipStream_t s);
 grav_status launch_t_near_par(const Plan *p, const DevGeom &g, const double *resid, int add, double *drho, hipStream_t s);
 OctInfo octet_info(int P, bool f64);

@@ -16,7 +16,6 @@ constexpr int kMaxLevels = 10;
 
 constexpr int kCanonOffsets = 56;  // M2L offsets d, 2 <= max |d_a| <= 3, with non-negative components
 constexpr int kClassOffsets = 189; // offsets valid for one child-parity class
-constexpr int kTileCols = 64;      // columns (box, model) per L2L tile
 constexpr int kMaxLeafCells = 8;     // leaf edge cap: a leaf's densities fit one 512-entry LDS stage
 constexpr int kNearChunk = 3;        // k steps per chunk of the near field by parity (54 in all)
 constexpr int kMaxLatticeLeaf = 4;   // largest leaf edge with lattice near-field matrices
@@ -30,25 +29,13 @@ struct LevelInfo {
     int64_t me_off = 0;               // offset (in expansions) of this level in the ME array
     int64_t n_tgt = 0;                // boxes holding evaluation points
     int64_t tgt_off = 0;              // offset of this level in the per-target-box arrays
-    int64_t class_start[9] = {0};     // class-grouped order boundaries
     int64_t tmap_off = 0;             // offset of this level's target map (source block + halo 3)
-    int64_t tchild_off = 0;           // offset of this level's first-child table
     int need_lo[3] = {0, 0, 0};       // box range whose expansions the M2L reads (the
     int need_hi[3] = {-1, -1, -1};    // target boxes' range widened by 3, inclusive)
-    // adjoint: the source boxes whose ME the transposed M2L sets (the source
-    // block within reach of a target box; the whole block at level 2)
-    int cs0[3] = {0, 0, 0}, cns[3] = {0, 0, 0};
-    // its input: the block of boxes that holds the target boxes within reach
+    // transposed M2L's input: the block of boxes that holds the target boxes
+    // within reach of the source block
     int gs0[3] = {0, 0, 0}, gns[3] = {0, 0, 0};
     int64_t g_off = 0;                // first row of the level in that input
-};
-
-// Tiled stages: the L2L.
-enum TileKind { TK_L2L = 0, TK_COUNT };
-
-struct TileRange {
-    int64_t off = 0;
-    int32_t n = 0;
 };
 
 // One direction of the M2L over sibling octets (octet.hpp): columns are
@@ -60,7 +47,7 @@ struct OctGroup {      // 16 nc columns of one level
 };
 struct OctTables {
     const uint32_t *key;       // [noct] Morton key of the parent
-    const int32_t *child;      // [noct][8] output row of each child octant, -1: none
+    const int32_t *child;      // [noct][8] row of each child octant, -1: none
     const OctGroup *groups;
     const int32_t *segs;       // [nseg][4] unit, its orbits (bit o - 1), slot, 0
     const int32_t *wgseg;      // [wgs + 1] segments of a workgroup
@@ -70,6 +57,9 @@ struct OctPlan {
     int32_t wgs = 0, nc = 1, ngroup = 0, nunit = 0;
     int64_t noct = 0, nseg = 0;
     uint32_t *d_key = nullptr;
+    int64_t first[kMaxLevels + 2] = {0};  // octets of level l: [first[l], first[l + 1])
+    int32_t gfirst[kMaxLevels + 1] = {0}; // first group of level l
+    int32_t *d_parent = nullptr;          // [noct] row of the parent, -1 at level 2
     int32_t *d_child = nullptr, *d_segs = nullptr, *d_wgseg = nullptr;
     int32_t *d_uslot = nullptr;
     OctGroup *d_groups = nullptr;
@@ -107,7 +97,7 @@ struct Plan {
     LevelInfo lev[kMaxLevels + 1];
     int64_t n_me = 0, n_le = 0;    // expansions (per model) in the ME / LE arrays
     int64_t n_tbox = 0;            // target boxes over all levels >= 2
-    int64_t n_tmap = 0, n_tchild = 0;
+    int64_t n_tmap = 0;
 
     // device buffers
     double *d_points = nullptr;    // [n_points][3] user points (unsorted)
@@ -124,15 +114,14 @@ struct Plan {
     int32_t *d_tleaf = nullptr;    // [M] sorted target -> leaf (index in level-L list)
     int64_t *d_leaf_start = nullptr; // [n_leaf + 1]
     uint32_t *d_tkey = nullptr;    // [n_tbox_all] Morton key of every target box, per level
-    int32_t *d_tparent = nullptr;  // [n_tbox_all] index (within its level) of the parent box
-    int32_t *d_torder = nullptr;   // [n_tbox_all] class-grouped order -> box index (per level)
-    int64_t tbox_off[kMaxLevels + 1] = {0}; // start of each level in the three arrays above
-    struct GemmTile *d_tiles = nullptr;            // all M2L tiles
-    // per stage: slot 0 = all levels, in launch order (each tile repeated
-    // split[k] times); slot l >= 2 = level l's tiles in the unrepeated numbering
-    TileRange tiles[TK_COUNT][kMaxLevels + 1];
-    int split[TK_COUNT] = {1};
-    OctPlan m2l, m2lt;                  // forward M2L; transposed M2L (columns: octets of source boxes)
+    int64_t tbox_off[kMaxLevels + 1] = {0}; // start of each level in the array above
+    OctPlan m2l, m2lt;                  // octets of the target boxes (M2L, L2L, L2L^T) and of the
+                                        // source boxes (M2L^T, M2M, M2M^T)
+    // the translations between levels by parity (levels.hip), operators of the
+    // (+,+,+) child as MFMA A fragments, and the coefficients of each class
+    double *d_m2m = nullptr, *d_l2lt = nullptr;    // up: [8][k steps][row blocks of a class][64]
+    double *d_l2l = nullptr, *d_m2mt = nullptr;    // down: [8][k steps of a class][PS/16][64]
+    int32_t *d_class_coef = nullptr;               // [8][16 x row blocks of a class], -1 past its end
     double *d_part = nullptr;           // segment slots, shared by both directions
     // the M2L's input where it is not the ME itself: FP32 copies of the ME
     // (mixed plans), the gathered adjoint LE
@@ -151,11 +140,6 @@ struct Plan {
     int near_KC = 0;                               // k steps of a class
     double *d_tl2p = nullptr;                      // [PS/16][RB][64][4] far field (L2P) at the cell centres, FP64
     int64_t *d_lat_tab = nullptr;                  // [27 Q][2] per near chunk: density and operator offsets
-    double *d_m2m_sw = nullptr;                    // [8][PS/4][RB][64] M2M as MFMA A fragments (FP64)
-    double *d_l2l_sw = nullptr;                    // [8][KS][RB][64] L2L likewise
-    double *d_l2l_msw = nullptr;                   // [8][PS/4][RB][64] L2L, as d_m2m_sw (forward, LDS-tiled)
-    double *d_m2mt_sw = nullptr;                   // [8][PS/4][RB][64] M2M^T, as d_m2m_sw (adjoint)
-    double *d_l2lt_sw = nullptr;                   // [8][PS/4][RB][64] L2L^T, as d_m2m_sw (adjoint)
     double *d_pmt_sw = nullptr;                    // [PS/4][ceil(b^3/16)][64] P2M^T fragments (adjoint)
     double *d_tn64 = nullptr;                      // [27][KS][RB][64] swizzled, FP64 plans
     float *d_tn32 = nullptr;                       // same, mixed plans
@@ -176,13 +160,10 @@ struct Plan {
     int64_t n_user_leaves = 0;                     // the point near field
     int32_t *d_class_off = nullptr;  // [8][189][4] (dx, dy, dz, offset id)
     int32_t *d_tmap = nullptr;       // per level: target-box index over source block + halo 3
-    int32_t *d_tchild = nullptr;     // per level: first child (in level l+1) of each box, + sentinel
     struct DevGeom *d_geom = nullptr;
 
     double *d_pm = nullptr;        // [b^3][PS] lattice P2M
     double *d_pm_sw = nullptr;     // [b^3/4][RB][64] the same as MFMA A fragments (FP64)
-    double *d_m2m = nullptr;       // [8][PS][PS] M2M per child octant, row-major [out][in] (adjoint)
-    double *d_l2l = nullptr;       // [8][PS][PS] L2L per child octant, row-major [out][in] (adjoint)
     double *d_me = nullptr;        // [n_me][B][PS]
     double *d_le = nullptr;        // [n_tbox][B][PS]
     double *d_near = nullptr;      // [M][B][4] near field (phi, gx, gy, gz), sorted order

@@ -289,92 +289,21 @@ k_m2l_octet(OctGeom g, OctTables t, const T *K, const T *in, T *part)
     }
 }
 
-// Expansions of the octets' boxes from the segment slots: per (column,
-// coefficient) the eight G_chi, each the sum over its unit's segments in
-// order (FP64), the inverse transform, and one store per box.  A column
-// without sources gives zero.
-template <typename T, int RS>
-__global__ void __launch_bounds__(256)
-k_octet_sum(OctTables t, const T *part, int B, int PS, int ncol, int ngroup, double *out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = (int)(i % PS);
-    const int64_t gc = i / PS;
-    const int cl = (int)(gc % ncol);
-    const int64_t gi = gc / ncol;
-    if (gi >= ngroup)
-        return;
-    const OctGroup grp = t.groups[gi];
-    if (cl >= grp.ncol)
-        return;
-    constexpr int NX = 8 / RS;
-    const int64_t xs = (int64_t)ncol * PS;  // between parities of a slot
-    double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int xh = 0; xh < RS; ++xh) {
-        const int j0 = t.uslot[gi * RS + xh], j1 = t.uslot[gi * RS + xh + 1];
-        const T *src = part + ((int64_t)j0 * NX * ncol + cl) * PS + k;
-        int j = j0;
-        // four slots at a time, loaded together (small plans have a slot per
-        // item, up to 26 a unit); the sum stays in slot order
-        for (; j + 4 <= j1; j += 4, src += 4 * NX * xs) {
-            T p[4][NX];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-                    p[u][x] = src[(u * NX + x) * xs];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-                    v[NX * xh + x] += (double)p[u][x];
-        }
-        for (; j < j1; ++j, src += NX * xs) {
-#pragma unroll
-            for (int x = 0; x < NX; ++x)
-                v[NX * xh + x] += (double)src[x * xs];
-        }
-    }
-#pragma unroll
-    for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if ((r & bit) == 0) {
-                const double x = v[r], y = v[r | bit];
-                v[r] = x + y;
-                v[r | bit] = x - y;
-            }
-    const int64_t col = grp.col0 + cl;
-    const int bm = (int)(col % B);
-    const int32_t *child = t.child + (grp.oct0 + col / B) * 8;
-    const int s = sign_class(k);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int32_t row = child[7 ^ r];  // reflection bit a set: the lower child
-        if (row >= 0)
-            out[((int64_t)row * B + bm) * PS + k] = odd_parity(s & r) ? -v[r] : v[r];
-    }
-}
-
 #define GRAV_ORDERS(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
 template <typename T>
-grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in, double *out)
+grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const OctGeom &g, const T *in)
 {
-    if (o.noct == 0)
+    if (o.wgs == 0)
         return GRAV_OK;
     const T *K = reinterpret_cast<const T *>(o.d_ops);
     T *part = reinterpret_cast<T *>(p->d_part);
     const OctTables t = o.tables();
-    int RS = 1;
     const dim3 grid((unsigned)o.wgs), blk(512);
 #define M2L_CASE(P)                                                                                              \
     case P:                                                                                                      \
-        RS = OctShape<P, T>::RS;                                                                                 \
-        if (o.wgs == 0) {                                                                                        \
-        } else if (o.nc == 1)                                                                                    \
+        if (o.nc == 1)                                                                                           \
             hipLaunchKernelGGL((k_m2l_octet<P, T, 1>), grid, blk, 0, s, g, t, K, in, part);                 \
         else if (o.nc == OctShape<P, T>::NCW)                                                                    \
             hipLaunchKernelGGL((k_m2l_octet<P, T, OctShape<P, T>::NCW>), grid, blk, 0, s, g, t, K, in, part); \
@@ -388,23 +317,11 @@ grav_status launch_m2l(const Plan *p, const OctPlan &o, hipStream_t s, const Oct
     }
 #undef M2L_CASE
     GRAV_HIP(hipGetLastError());
-    const int ncol = 16 * o.nc;
-    const int64_t n = (int64_t)o.ngroup * ncol * p->PS;
-    const dim3 sgrid((unsigned)((n + 255) / 256));
-    if (RS == 1)
-        hipLaunchKernelGGL((k_octet_sum<T, 1>), sgrid, dim3(256), 0, s, t, (const T *)part, p->B, p->PS, ncol, o.ngroup,
-                           out);
-    else
-        hipLaunchKernelGGL((k_octet_sum<T, 2>), sgrid, dim3(256), 0, s, t, (const T *)part, p->B, p->PS, ncol, o.ngroup,
-                           out);
-    GRAV_HIP(hipGetLastError());
     return GRAV_OK;
 }
 
-template grav_status launch_m2l<double>(const Plan *, const OctPlan &, hipStream_t, const OctGeom &, const double *,
-                                        double *);
-template grav_status launch_m2l<float>(const Plan *, const OctPlan &, hipStream_t, const OctGeom &, const float *,
-                                       double *);
+template grav_status launch_m2l<double>(const Plan *, const OctPlan &, hipStream_t, const OctGeom &, const double *);
+template grav_status launch_m2l<float>(const Plan *, const OctPlan &, hipStream_t, const OctGeom &, const float *);
 
 OctGeom octet_geom(const Plan *p, bool transposed)
 {

@@ -115,55 +115,14 @@ __global__ void k_leaf_build(const uint32_t *keys, const uint32_t *flags, const 
 
 // Parent level from the sorted child box keys.
 __global__ void k_parent_build(const uint32_t *ckeys, const uint32_t *flags, const uint32_t *scan,
-                               int64_t n, int32_t *cparent, uint32_t *pkeys)
+                               int64_t n, uint32_t *pkeys)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
     const uint32_t id = scan[i] + flags[i] - 1u;
-    cparent[i] = (int32_t)id;
     if (flags[i])
         pkeys[id] = ckeys[i] >> 3;
-}
-
-// Sort keys of the target boxes of a level for the class-grouped order
-// (the column order of the M2L and L2L tiles).  First pass: x-fastest
-// lexicographic order of the boxes.  Second, stable pass: parity class
-// (Morton bits 0..2), then the box's boundary signature in y and z (the
-// range of interaction-list offsets, |d| <= 3, that stay inside the source
-// block on those axes).  A wave's 16 columns are then boxes of one class
-// along x rows that mostly see the same source offsets, so (i) the waves
-// skip the same missing offsets and waste little MFMA work, and (ii) the
-// source boxes a wave reads at one offset are consecutive in x, which the
-// regathered expansions store contiguously.
-__global__ void k_lex_keys(const uint32_t *bkeys, int64_t n, int bits, uint32_t *ck, uint32_t *cv)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint32_t k = bkeys[i];
-    ck[i] = (compact3(k >> 2) << (2 * bits)) | (compact3(k >> 1) << bits) | compact3(k);
-    cv[i] = (uint32_t)i;
-}
-
-__global__ void k_class_keys(const uint32_t *bkeys, const uint32_t *order, int64_t n, int3 s0, int3 ns,
-                             uint32_t *ck, uint32_t *counts)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint32_t k = bkeys[order[i]];
-    const uint32_t cls = k & 7u;  // Morton bits 0,1,2 = x, y, z parity
-    const int c[2] = {(int)compact3(k >> 1), (int)compact3(k >> 2)};
-    const int lo[2] = {s0.y, s0.z}, len[2] = {ns.y, ns.z};
-    uint32_t sig = 0;
-    for (int a = 0; a < 2; ++a) {
-        const int dlo = min(4, max(-3, lo[a] - c[a]));               // lowest valid offset
-        const int dhi = max(-4, min(3, lo[a] + len[a] - 1 - c[a]));  // highest valid offset
-        sig = sig * 64u + (uint32_t)((dlo + 3) * 8 + (dhi + 4));
-    }
-    ck[i] = (cls << 12) | sig;
-    atomicAdd(&counts[cls], 1u);
 }
 
 struct CountArgs {
@@ -309,15 +268,15 @@ void free_plan(Plan *p)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p->device);
     void *bufs[] = {p->d_points, p->d_perm, p->d_tpos, p->d_tleaf, p->d_leaf_start, p->d_tkey,
-                    p->d_tparent, p->d_torder, p->d_tiles, p->d_class_off, p->d_tmap, p->d_tchild, p->d_geom,
-                    p->d_pm, p->d_pm_sw, p->d_m2m, p->d_l2l, p->d_me, p->d_le, p->d_near, p->d_part, p->d_rows,
-                    p->d_tn64, p->d_tn32, p->d_m2m_sw, p->d_l2l_sw, p->d_rho_blk, p->d_tl2p, p->d_dpart,
+                    p->d_class_off, p->d_tmap, p->d_geom, p->d_pm, p->d_pm_sw, p->d_m2m, p->d_l2l, p->d_m2mt,
+                    p->d_l2lt, p->d_class_coef, p->d_me, p->d_le, p->d_near, p->d_part, p->d_rows,
+                    p->d_tn64, p->d_tn32, p->d_rho_blk, p->d_tl2p, p->d_dpart,
                     p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
-                    p->d_m2mt_sw, p->d_l2lt_sw, p->d_l2l_msw, p->d_pmt_sw, p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
+                    p->d_pmt_sw, p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
                     p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
                     p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_coef};
     for (OctPlan *o : {&p->m2l, &p->m2lt}) {
-        void *ob[] = {o->d_key, o->d_child, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
+        void *ob[] = {o->d_key, o->d_child, o->d_parent, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
                       o->d_ops};
         for (void *b : ob)
             if (b)
@@ -435,23 +394,6 @@ static inline size_t frag_pos(int lane, int e, int G)
     return ((size_t)(e / G) * 64 + lane) * G + e % G;
 }
 
-// Row-blocked layout (M2M, L2L), contraction order kr * PS/4 + ks (their B
-// operand is read straight from the expansions), one set of four values per
-// (q, rb):
-// set (q, rb), value (lane, u)  =  m[16 rb + lane % 16][(lane / 16) * PS/4 + 4 q + u].
-void swizzle_rows(const double *m, int PS, int G, double *dst)
-{
-    const int RB = PS / 16, KP = PS / 4;
-    for (int q = 0; q < RB; ++q)
-        for (int rb = 0; rb < RB; ++rb)
-            for (int lane = 0; lane < 64; ++lane)
-                for (int u = 0; u < 4; ++u) {
-                    const int row = 16 * rb + (lane & 15);
-                    const int col = (lane >> 4) * KP + 4 * q + u;
-                    dst[((size_t)q * RB + rb) * 256 + frag_pos(lane, u, G)] = m[(size_t)row * PS + col];
-                }
-}
-
 template <class T>
 grav_status upload(Plan *p, T **dst, const std::vector<T> &src)
 {
@@ -536,6 +478,52 @@ grav_status upload_octet_operators(Plan *p, const std::vector<std::vector<double
     return GRAV_OK;
 }
 
+// Operators of the translations between levels (levels.hip).  m and l: M2M and
+// L2L of the (+,+,+) child.  Up: [class][k step][row block of the class][lane],
+// row = coefficient 16 rb + lane % 16 of the class, column 4 ks + lane / 16.
+// Down: [class][k step of the class][row block][lane], row 16 rb + lane % 16,
+// column = coefficient 4 q + lane / 16 of the class.
+static grav_status upload_level_operators(Plan *p, const std::vector<double> &m, const std::vector<double> &l)
+{
+    const int P2 = p->P2, PS = p->PS, RB = PS / 16;
+    const int KS = octet_info(p->P, true).KS;
+    std::vector<int> cls[8];
+    size_t most = 0;
+    for (int k = 0; k < P2; ++k) {
+        cls[sign_class(k)].push_back(k);
+        most = std::max(most, cls[sign_class(k)].size());
+    }
+    const int RBC = (int)ceil_div((int64_t)most, 16), KC = (int)ceil_div((int64_t)most, 4);
+    std::vector<int32_t> coef((size_t)8 * 16 * RBC, -1);
+    for (int x = 0; x < 8; ++x)
+        std::copy(cls[x].begin(), cls[x].end(), coef.begin() + (size_t)x * 16 * RBC);
+    GRAV_CHECK(upload(p, &p->d_class_coef, coef));
+    for (int t = 0; t < 2; ++t) {
+        // up: M2M, and L2L transposed; down: L2L, and M2M transposed
+        std::vector<double> up((size_t)8 * KS * RBC * 64, 0.0), dn((size_t)8 * KC * RB * 64, 0.0);
+        auto at_up = [&](int i, int k) { return t ? l[(size_t)k * PS + i] : m[(size_t)i * PS + k]; };
+        auto at_dn = [&](int i, int k) { return t ? m[(size_t)k * PS + i] : l[(size_t)i * PS + k]; };
+        for (int x = 0; x < 8; ++x)
+            for (int lane = 0; lane < 64; ++lane) {
+                for (int ks = 0; ks < KS; ++ks)
+                    for (int rb = 0; rb < RBC; ++rb) {
+                        const int n = 16 * rb + lane % 16, k = 4 * ks + lane / 16;
+                        if (n < (int)cls[x].size() && k < P2)
+                            up[(((size_t)x * KS + ks) * RBC + rb) * 64 + lane] = at_up(cls[x][n], k);
+                    }
+                for (int q = 0; q < KC; ++q)
+                    for (int rb = 0; rb < RB; ++rb) {
+                        const int n = 4 * q + lane / 16, i = 16 * rb + lane % 16;
+                        if (n < (int)cls[x].size() && i < P2)
+                            dn[(((size_t)x * KC + q) * RB + rb) * 64 + lane] = at_dn(i, cls[x][n]);
+                    }
+            }
+        GRAV_CHECK(upload(p, t ? &p->d_l2lt : &p->d_m2m, up));
+        GRAV_CHECK(upload(p, t ? &p->d_m2mt : &p->d_l2l, dn));
+    }
+    return GRAV_OK;
+}
+
 grav_status build_operators(Plan *p)
 {
     const int P = p->P, PS = p->PS, RB = PS / 16;
@@ -578,68 +566,15 @@ grav_status build_operators(Plan *p)
     if (p->L < 2)
         return GRAV_OK;
 
-    // M2M / L2L row-major, [octant][out][in], for the adjoint: its thread
-    // for input coefficient j reads column j, so a wave's loads at one row
-    // are consecutive
-    std::vector<double> m((size_t)PS * PS), m2m(8 * (size_t)PS * PS), l2l(8 * (size_t)PS * PS);
-    for (int c = 0; c < 8; ++c) {
-        const double delta[3] = {((c & 1) - 0.5) * 0.5, (((c >> 1) & 1) - 0.5) * 0.5,
-                                 (((c >> 2) & 1) - 0.5) * 0.5};
-        m2m_matrix(P, delta, PS, m.data());
-        std::copy(m.begin(), m.end(), m2m.begin() + (size_t)c * PS * PS);
-        l2l_matrix(P, delta, PS, m.data());
-        std::copy(m.begin(), m.end(), l2l.begin() + (size_t)c * PS * PS);
-    }
-    GRAV_CHECK(upload(p, &p->d_m2m, m2m));
-    GRAV_CHECK(upload(p, &p->d_l2l, l2l));
     {
-        // the same matrices as MFMA A operands (rows = output coefficient),
-        // contraction order kr * PS/4 + ks.  L2L: one set of four k steps per
-        // (q, row block) (a workgroup takes one row block).  M2M: one fragment
-        // per (k step, row block), [octant][ks][rb][lane] = m[16 rb + lane%16][
-        // (lane/16) PS/4 + ks] (a wave takes all row blocks).
-        const size_t per8 = (size_t)PS * PS;
-        const int K4 = PS / 4;
-        std::vector<double> msw(8 * per8), lsw(8 * per8);
-        for (int c = 0; c < 8; ++c) {
-            const double delta[3] = {((c & 1) - 0.5) * 0.5, (((c >> 1) & 1) - 0.5) * 0.5,
-                                     (((c >> 2) & 1) - 0.5) * 0.5};
-            m2m_matrix(P, delta, PS, m.data());
-            for (int ks = 0; ks < K4; ++ks)
-                for (int rb = 0; rb < RB; ++rb)
-                    for (int lane = 0; lane < 64; ++lane)
-                        msw[per8 * c + ((size_t)ks * RB + rb) * 64 + lane] =
-                            m[(size_t)(16 * rb + lane % 16) * PS + (lane / 16) * K4 + ks];
-            l2l_matrix(P, delta, PS, m.data());
-            swizzle_rows(m.data(), PS, 2, lsw.data() + per8 * c);
-        }
-        GRAV_CHECK(upload(p, &p->d_m2m_sw, msw));
-        GRAV_CHECK(upload(p, &p->d_l2l_sw, lsw));
-        // the adjoint's M2M^T and L2L^T in the M2M fragment layout: row =
-        // output coefficient of the transpose (a column of the matrix),
-        // contraction index (lane/16) PS/4 + ks (a row of the matrix)
-        std::vector<double> mtsw(8 * per8), ltsw(8 * per8);
-        for (int c = 0; c < 8; ++c)
-            for (int ks = 0; ks < K4; ++ks)
-                for (int rb = 0; rb < RB; ++rb)
-                    for (int lane = 0; lane < 64; ++lane) {
-                        const size_t src = per8 * c + (size_t)((lane / 16) * K4 + ks) * PS + 16 * rb + lane % 16;
-                        mtsw[per8 * c + ((size_t)ks * RB + rb) * 64 + lane] = m2m[src];
-                        ltsw[per8 * c + ((size_t)ks * RB + rb) * 64 + lane] = l2l[src];
-                    }
-        GRAV_CHECK(upload(p, &p->d_m2mt_sw, mtsw));
-        GRAV_CHECK(upload(p, &p->d_l2lt_sw, ltsw));
-        // L2L in the same layout for the forward's LDS-tiled kernel
-        std::vector<double> lmsw(8 * per8);
-        for (int c = 0; c < 8; ++c)
-            for (int ks = 0; ks < K4; ++ks)
-                for (int rb = 0; rb < RB; ++rb)
-                    for (int lane = 0; lane < 64; ++lane)
-                        lmsw[per8 * c + ((size_t)ks * RB + rb) * 64 + lane] =
-                            l2l[per8 * c + (size_t)(16 * rb + lane % 16) * PS + (lane / 16) * K4 + ks];
-        GRAV_CHECK(upload(p, &p->d_l2l_msw, lmsw));
+        // translations between levels by parity (levels.hip), from the
+        // operators of the (+,+,+) child
+        const double delta[3] = {0.25, 0.25, 0.25};
+        std::vector<double> m((size_t)PS * PS), l((size_t)PS * PS);
+        m2m_matrix(P, delta, PS, m.data());
+        l2l_matrix(P, delta, PS, l.data());
+        GRAV_CHECK(upload_level_operators(p, m, l));
     }
-
     GRAV_CHECK(upload(p, &p->d_class_off, offsets_table()));
     if (p->M == 0)
         return GRAV_OK;
@@ -663,15 +598,16 @@ grav_status build_operators(Plan *p)
     return GRAV_OK;
 }
 
-// Octets of one M2L direction, level by level in Morton order: the key of the
-// parent and the output row of each child (-1: not written).
+// Octets of the target or source boxes, level by level: the key of the parent,
+// its row in the level above (-1 at level 2) and the rows of its children.
 struct Octets {
     std::vector<uint32_t> key;
-    std::vector<int32_t> child;
+    std::vector<int32_t> child, parent;
     int64_t first[kMaxLevels + 2] = {0};  // octets of level l: [first[l], first[l + 1])
+    int64_t reach[kMaxLevels + 1] = {0};  // those before reach[l] are within reach of M2L input
     void add(uint32_t k, int32_t row)
     {
-        if (key.empty() || (int64_t)key.size() == open || key.back() != k >> 3) {
+        if ((int64_t)key.size() == open || key.back() != k >> 3) {
             key.push_back(k >> 3);
             child.insert(child.end(), 8, -1);
         }
@@ -682,6 +618,7 @@ struct Octets {
         first[l] = open = (int64_t)key.size();
         first[l + 1] = open;
     }
+    void reached(int l) { reach[l] = (int64_t)key.size(); }
     void done(int l) { first[l + 1] = (int64_t)key.size(); }
 
 private:
@@ -703,18 +640,24 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
     const int64_t B = p->B;
     o.noct = (int64_t)oc.key.size();
+    std::copy(std::begin(oc.first), std::end(oc.first), std::begin(o.first));
     // four (or two) column blocks per wave once there are units for every CU
     // twice over; else single blocks, for more units than CUs on small plans
     int resident = 0;
     GRAV_CHECK(m2l_resident_workgroups(p, in.NCW, &resident));
-    o.nc = o.noct * B * in.RS >= (int64_t)GRAV_M2L_WIDE_ROUNDS * resident * 16 * in.NCW / kOrbits ? in.NCW : 1;
+    int64_t near = 0;
+    for (int l = 2; l <= p->L; ++l)
+        near += oc.reach[l] - oc.first[l];
+    o.nc = near * B * in.RS >= (int64_t)GRAV_M2L_WIDE_ROUNDS * resident * 16 * in.NCW / kOrbits ? in.NCW : 1;
     GRAV_CHECK(m2l_resident_workgroups(p, o.nc, &resident));
     const int ncol = 16 * o.nc;
     std::vector<OctGroup> groups;
     std::vector<uint32_t> umask;          // orbits of a unit
-    std::vector<int64_t> ustart(1, 0);    // its first work item
+    std::vector<int32_t> live;            // units with orbits
+    std::vector<int64_t> ustart(1, 0);    // first work item of each of those
     for (int l = 2; l <= p->L; ++l) {
         const int64_t cols = (oc.first[l + 1] - oc.first[l]) * B;
+        o.gfirst[l] = (int32_t)groups.size();
         for (int64_t c0 = 0; c0 < cols; c0 += ncol) {
             OctGroup g{};
             g.level = l;
@@ -725,7 +668,7 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
             uint32_t mask = 0;
             for (int ob = 1; ob <= kOrbits; ++ob) {
                 bool hit = false;
-                for (int64_t j = c0 / B; j <= (c0 + g.ncol - 1) / B && !hit; ++j) {
+                for (int64_t j = c0 / B; j <= std::min((c0 + g.ncol - 1) / B, oc.reach[l] - oc.first[l] - 1) && !hit; ++j) {
                     const uint32_t k = oc.key[oc.first[l] + j];
                     const int c[3] = {(int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2)};
                     for (int r = 0; r < 8 && !hit; ++r)
@@ -737,14 +680,17 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
                     mask |= 1u << (ob - 1);
             }
             for (int xh = 0; xh < in.RS; ++xh) {
+                if (mask) {
+                    live.push_back((int32_t)umask.size());
+                    ustart.push_back(ustart.back() + __builtin_popcount(mask));
+                }
                 umask.push_back(mask);
-                ustart.push_back(ustart.back() + __builtin_popcount(mask));
             }
         }
     }
-    const int64_t nunit = (int64_t)ustart.size() - 1, T = ustart.back();
+    const int64_t nunit = (int64_t)umask.size(), nlive = (int64_t)live.size(), T = ustart.back();
     const int64_t W = T == 0 ? 0 : std::min<int64_t>(resident, T);
-    const int64_t rounds = W > 0 ? nunit / W : 0;
+    const int64_t rounds = W > 0 ? nlive / W : 0;
     std::vector<int32_t> seg, wgseg(W + 1, 0);
     std::vector<std::vector<int32_t>> useg(nunit);
     const int64_t u0 = rounds * W, rest = T - ustart[u0];
@@ -758,14 +704,15 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     }
     for (int64_t w = 0; w < W; ++w) {
         wgseg[w] = (int32_t)(seg.size() / 4);
-        auto add = [&](int64_t u, int64_t i, int64_t j) {
+        auto add = [&](int64_t v, int64_t i, int64_t j) {
             if (i >= j)
                 return;
+            const int32_t u = live[v];
             uint32_t left = umask[u], mask = 0;  // the i-th to (j - 1)-th orbits of the unit
-            for (int64_t n = ustart[u]; n < j; ++n, left &= left - 1)
+            for (int64_t n = ustart[v]; n < j; ++n, left &= left - 1)
                 mask |= n >= i ? left & -left : 0u;
             useg[u].push_back((int32_t)(seg.size() / 4));
-            seg.insert(seg.end(), {(int32_t)u, (int32_t)mask, 0, 0});
+            seg.insert(seg.end(), {u, (int32_t)mask, 0, 0});
         };
         for (int64_t r = 0; r < rounds; ++r) {
             const int64_t u = r * W + pos[w];
@@ -795,6 +742,7 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     }
     GRAV_CHECK(upload(p, &o.d_key, oc.key));
     GRAV_CHECK(upload(p, &o.d_child, oc.child));
+    GRAV_CHECK(upload(p, &o.d_parent, oc.parent));
     GRAV_CHECK(upload(p, &o.d_groups, groups));
     GRAV_CHECK(upload(p, &o.d_segs, seg));
     GRAV_CHECK(upload(p, &o.d_wgseg, wgseg));
@@ -802,12 +750,11 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     return GRAV_OK;
 }
 
-// Octets and schedules of both M2L directions, from the target boxes' keys.
+// Octets and M2L schedules of both directions, from the target boxes' keys.
 // Forward: the octets of the target boxes, fed by the source blocks.
-// Transposed: the octets of the column block's source boxes (those within
-// reach of a target box; all of level 2, so that every level-2 ME is written
-// -- below, M2M^T sets the boxes outside the column block), fed by the target
-// boxes.
+// Transposed: the octets of all source boxes (the M2M and its transpose run
+// over them too), fed by the target boxes; the octets within reach of a target
+// box come first in their level, so that the M2L's groups hold few others.
 static grav_status build_m2l(Plan *p)
 {
     const int L = p->L;
@@ -844,20 +791,19 @@ static grav_status build_m2l(Plan *p)
                 bhi[a] = std::max(bhi[a], c[a]);
             }
         }
+        fo.reached(l);
         fo.done(l);
-        // boxes whose expansions the M2L can read, and the transposed M2L's
-        // column block
+        for (int64_t j = 0; j < fo.first[l + 1] - fo.first[l]; ++j)
+            fo.parent.push_back(l > 2 ? (int32_t)(p->lev[l - 1].tgt_off + j) : -1);
+        // boxes whose expansions the M2L can read, and the source boxes within
+        // reach of a target box
         const bool any = blo[0] <= bhi[0];
+        int c0[3], c1[3];
         for (int a = 0; a < 3; ++a) {
             lv.need_lo[a] = key[l].empty() ? 0 : lo[a] - 3;
             lv.need_hi[a] = key[l].empty() ? -1 : hi[a] + 3;
-            int c0 = lv.s0[a], c1 = lv.s0[a] + lv.ns[a] - 1;
-            if (l > 2) {
-                c0 = std::max(c0, any ? blo[a] - 3 : c1 + 1);
-                c1 = std::min(c1, any ? bhi[a] + 3 : c0 - 1);
-            }
-            lv.cs0[a] = c0;
-            lv.cns[a] = std::max(0, c1 - c0 + 1);
+            c0[a] = any ? std::max(lv.s0[a], blo[a] - 3) : 1;
+            c1[a] = any ? std::min(lv.s0[a] + lv.ns[a] - 1, bhi[a] + 3) : 0;
             lv.gs0[a] = any ? blo[a] : 0;
             lv.gns[a] = any ? bhi[a] - blo[a] + 1 : 0;
         }
@@ -872,17 +818,49 @@ static grav_status build_m2l(Plan *p)
                 tb[l][j] = 1;
         }
         to.level(l);
-        std::vector<std::pair<uint32_t, int32_t>> box;
-        for (int z = lv.cs0[2]; z < lv.cs0[2] + lv.cns[2]; ++z)
-            for (int y = lv.cs0[1]; y < lv.cs0[1] + lv.cns[1]; ++y)
-                for (int x = lv.cs0[0]; x < lv.cs0[0] + lv.cns[0]; ++x)
-                    box.emplace_back(morton3(x, y, z),
-                                     (int32_t)(lv.me_off + ((int64_t)(z - lv.s0[2]) * lv.ns[1] + (y - lv.s0[1])) * lv.ns[0] +
-                                               (x - lv.s0[0])));
-        std::sort(box.begin(), box.end());
-        for (const auto &e : box)
-            to.add(e.first, e.second);
+        std::vector<uint64_t> oct;
+        int p0[3], p1[3];
+        for (int a = 0; a < 3; ++a) {
+            p0[a] = lv.s0[a] >> 1;
+            p1[a] = (lv.s0[a] + lv.ns[a] - 1) >> 1;
+        }
+        for (int z = p0[2]; z <= p1[2]; ++z)
+            for (int y = p0[1]; y <= p1[1]; ++y)
+                for (int x = p0[0]; x <= p1[0]; ++x) {
+                    const int c[3] = {x, y, z};
+                    uint64_t far = 0;
+                    for (int a = 0; a < 3; ++a)
+                        if (c[a] < c0[a] >> 1 || c[a] > c1[a] >> 1)
+                            far = 1;
+                    oct.push_back(far << 32 | morton3(x, y, z));
+                }
+        std::sort(oct.begin(), oct.end());
+        const OctLev sl{{lv.s0[0], lv.s0[1], lv.s0[2]}, {lv.ns[0], lv.ns[1], lv.ns[2]}, 0};
+        const size_t near = std::lower_bound(oct.begin(), oct.end(), (uint64_t)1 << 32) - oct.begin();
+        for (size_t i = 0; i <= oct.size(); ++i) {
+            if (i == near)
+                to.reached(l);
+            if (i == oct.size())
+                break;
+            const uint32_t k = (uint32_t)oct[i];
+            const int c[3] = {2 * (int)compact3(k), 2 * (int)compact3(k >> 1), 2 * (int)compact3(k >> 2)};
+            for (uint32_t r = 0; r < 8; ++r) {
+                const int32_t j = octet_place(sl, c[0] + (int)(r & 1), c[1] + (int)(r >> 1 & 1), c[2] + (int)(r >> 2));
+                if (j >= 0)
+                    to.add(k << 3 | r, (int32_t)lv.me_off + j);
+            }
+        }
         to.done(l);
+        for (int64_t j = to.first[l]; j < to.first[l + 1]; ++j) {
+            const uint32_t k = to.key[j];
+            int32_t row = -1;
+            if (l > 2) {
+                const LevelInfo &lp = p->lev[l - 1];
+                const OctLev pl{{lp.s0[0], lp.s0[1], lp.s0[2]}, {lp.ns[0], lp.ns[1], lp.ns[2]}, 0};
+                row = (int32_t)lp.me_off + octet_place(pl, (int)compact3(k), (int)compact3(k >> 1), (int)compact3(k >> 2));
+            }
+            to.parent.push_back(row);
+        }
     }
     const OctGeom fg = octet_geom(p, false), tg = octet_geom(p, true);
     GRAV_CHECK(build_octet_schedule(p, fo, p->m2l, [&](int l, int x, int y, int z) {
@@ -892,49 +870,6 @@ static grav_status build_m2l(Plan *p)
         const int32_t j = octet_place(tg.lev[l], x, y, z);
         return j >= 0 && tb[l][j] != 0;
     });
-}
-
-// Tile lists of the L2L: 64 columns (4 waves x 16) per tile, per level and
-// child-parity class; the columns are target boxes (x models).
-grav_status build_tiles(Plan *p)
-{
-    std::vector<GemmTile> all;
-    const int L = p->L;
-    const int64_t B = p->B;
-    auto add_tile = [&](int kind, int level, int cls, int64_t c0, int64_t ncol) {
-        TileRange &r = p->tiles[kind][0];
-        if (r.n == 0)
-            r.off = (int64_t)all.size();
-        TileRange &rl = p->tiles[kind][level];
-        if (rl.n == 0)
-            rl.off = r.n;  // level range, in this kind's own numbering
-        GemmTile t{};
-        t.level = level;
-        t.cls = cls;
-        t.col0 = c0;
-        t.ncol = (int32_t)ncol;
-        all.push_back(t);
-        ++r.n;
-        ++rl.n;
-    };
-    auto add = [&](int kind, int level, int cls, int64_t ncols) {
-        for (int64_t c0 = 0; c0 < ncols; c0 += kTileCols)
-            add_tile(kind, level, cls, c0, std::min<int64_t>(kTileCols, ncols - c0));
-    };
-    for (int k = 0; k < TK_COUNT; ++k)
-        for (int l = 0; l <= kMaxLevels; ++l)
-            p->tiles[k][l] = TileRange{};
-    if (L >= 2) {
-        for (int l = 2; l <= L; ++l) {
-            for (int c = 0; c < 8; ++c)
-                add(TK_L2L, l, c, (p->lev[l].class_start[c + 1] - p->lev[l].class_start[c]) * B);
-        }
-    }
-    for (int k = 0; k < TK_COUNT; ++k)
-        p->split[k] = 1;
-    if (!all.empty())
-        GRAV_CHECK(upload(p, &p->d_tiles, all));
-    return L >= 2 ? build_m2l(p) : GRAV_OK;
 }
 
 __global__ void k_fill_tmap(const uint32_t *bkeys, int64_t n, int s0x, int s0y, int s0z, int mx,
@@ -948,19 +883,6 @@ __global__ void k_fill_tmap(const uint32_t *bkeys, int64_t n, int s0x, int s0y, 
               z = (int)compact3(k >> 2) - s0z + 3;
     if (x >= 0 && y >= 0 && z >= 0 && x < mx && y < my && z < mz)
         tmap[((int64_t)z * my + y) * mx + x] = (int32_t)i;
-}
-
-__global__ void k_fill_tchild(const int32_t *cparent, int64_t nc, int64_t np, int32_t *tchild)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > nc)
-        return;
-    if (i == nc) {
-        tchild[np] = (int32_t)nc;
-        return;
-    }
-    if (i == 0 || cparent[i] != cparent[i - 1])
-        tchild[cparent[i]] = (int32_t)i;
 }
 
 // Lookup tables of the adjoint: target-box maps over each level's source
@@ -1027,21 +949,6 @@ grav_status build_adjoint_maps(Plan *p)
                            lv.s0[2], lv.ns[0] + 6, lv.ns[1] + 6, lv.ns[2] + 6,
                            p->d_tmap + lv.tmap_off);
         GRAV_HIP(hipGetLastError());
-    }
-    p->n_tchild = 0;
-    for (int l = 2; l < L; ++l) {
-        p->lev[l].tchild_off = p->n_tchild;
-        p->n_tchild += p->lev[l].n_tgt + 1;
-    }
-    if (p->n_tchild > 0) {
-        GRAV_CHECK(dalloc(p, &p->d_tchild, (size_t)p->n_tchild, true));
-        for (int l = 2; l < L; ++l) {
-            const int64_t nc = p->lev[l + 1].n_tgt;
-            hipLaunchKernelGGL(k_fill_tchild, dim3((unsigned)ceil_div(nc + 1, 256)), dim3(256), 0, p->bs,
-                               (const int32_t *)(p->d_tparent + p->tbox_off[l + 1]), nc,
-                               p->lev[l].n_tgt, p->d_tchild + p->lev[l].tchild_off);
-            GRAV_HIP(hipGetLastError());
-        }
     }
     {
         // the leaf level's source leaves near user points, and the target
@@ -1558,7 +1465,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
     const int T = 256;
     // temporaries (freed at the end)
     uint32_t *keys = nullptr, *vals = nullptr, *ktmp = nullptr, *vtmp = nullptr;
-    uint32_t *flags = nullptr, *scan = nullptr, *scr = nullptr, *ccount = nullptr;
+    uint32_t *flags = nullptr, *scan = nullptr, *scr = nullptr;
     const int64_t nmax = std::max<int64_t>(M, 1);
     const size_t scr_words = std::max(radix_scratch_words(nmax), scan_tmp_words(nmax));
     grav_status st = GRAV_OK;
@@ -1567,7 +1474,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
         return e;
     };
     auto cleanup = [&]() {
-        uint32_t *bufs[] = {keys, vals, ktmp, vtmp, flags, scan, scr, ccount};
+        uint32_t *bufs[] = {keys, vals, ktmp, vtmp, flags, scan, scr};
         for (auto *b : bufs)
             if (b)
                 (void)hipFree(b);
@@ -1575,7 +1482,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
     if (hipMalloc(&keys, 4 * nmax) != hipSuccess || hipMalloc(&vals, 4 * nmax) != hipSuccess ||
         hipMalloc(&ktmp, 4 * nmax) != hipSuccess || hipMalloc(&vtmp, 4 * nmax) != hipSuccess ||
         hipMalloc(&flags, 4 * nmax) != hipSuccess || hipMalloc(&scan, 4 * nmax) != hipSuccess ||
-        hipMalloc(&scr, 4 * scr_words) != hipSuccess || hipMalloc(&ccount, 4 * 8) != hipSuccess) {
+        hipMalloc(&scr, 4 * scr_words) != hipSuccess) {
         cleanup();
         return GRAV_ENOMEM;
     }
@@ -1645,11 +1552,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
         for (int l = lo; l <= L; ++l)
             total += p->n_leaf;
         uint32_t *bk = nullptr;
-        int32_t *bp = nullptr;
-        if (hipMalloc(&bk, 4 * std::max<int64_t>(total, 1)) != hipSuccess ||
-            hipMalloc(&bp, 4 * std::max<int64_t>(total, 1)) != hipSuccess) {
-            if (bk)
-                (void)hipFree(bk);
+        if (hipMalloc(&bk, 4 * std::max<int64_t>(total, 1)) != hipSuccess) {
             fail(GRAV_ENOMEM);
             break;
         }
@@ -1664,7 +1567,6 @@ grav_status build_tree(Plan *p, hipStream_t s)
         }
         if (dalloc(p, &p->d_leaf_start, p->n_leaf + 1, true)) {
             (void)hipFree(bk);
-            (void)hipFree(bp);
             fail(GRAV_ENOMEM);
             break;
         }
@@ -1684,8 +1586,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
             }
             hipLaunchKernelGGL(k_parent_build, dim3(g), dim3(T), 0, s,
                                (const uint32_t *)(bk + off_bound[l + 1]), (const uint32_t *)flags,
-                               (const uint32_t *)scan, nc, bp + off_bound[l + 1],
-                               bk + off_bound[l]);
+                               (const uint32_t *)scan, nc, bk + off_bound[l]);
             if (hipMemcpyAsync(&last[0], scan + (nc - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
                 hipMemcpyAsync(&last[1], flags + (nc - 1), 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
                 hipStreamSynchronize(s) != hipSuccess) {
@@ -1696,7 +1597,6 @@ grav_status build_tree(Plan *p, hipStream_t s)
         }
         if (!ok) {
             (void)hipFree(bk);
-            (void)hipFree(bp);
             fail(GRAV_EDEVICE);
             break;
         }
@@ -1710,10 +1610,8 @@ grav_status build_tree(Plan *p, hipStream_t s)
             o += cnt[l];
         }
         const int64_t nall = std::max<int64_t>(o, 1);
-        if (dalloc(p, &p->d_tkey, nall, true) || dalloc(p, &p->d_tparent, nall, true) ||
-            dalloc(p, &p->d_torder, nall, true)) {
+        if (dalloc(p, &p->d_tkey, nall, true)) {
             (void)hipFree(bk);
-            (void)hipFree(bp);
             fail(GRAV_ENOMEM);
             break;
         }
@@ -1721,19 +1619,10 @@ grav_status build_tree(Plan *p, hipStream_t s)
             if (hipMemcpyAsync(p->d_tkey + p->tbox_off[l], bk + off_bound[l], 4 * cnt[l],
                                hipMemcpyDeviceToDevice, s) != hipSuccess)
                 ok = false;
-            if (l > lo) {
-                if (hipMemcpyAsync(p->d_tparent + p->tbox_off[l], bp + off_bound[l], 4 * cnt[l],
-                                   hipMemcpyDeviceToDevice, s) != hipSuccess)
-                    ok = false;
-            } else {
-                if (hipMemsetAsync(p->d_tparent + p->tbox_off[l], 0xff, 4 * cnt[l], s) != hipSuccess)
-                    ok = false;
-            }
         }
         if (hipStreamSynchronize(s) != hipSuccess)
             ok = false;
         (void)hipFree(bk);
-        (void)hipFree(bp);
         if (!ok) {
             fail(GRAV_EDEVICE);
             break;
@@ -1745,50 +1634,6 @@ grav_status build_tree(Plan *p, hipStream_t s)
                 p->n_tbox += cnt[l];
             }
 
-        // class grouping per level (levels >= 2): lexicographic, then stable on (class, signature)
-        for (int l = 2; l <= L && ok; ++l) {
-            const int64_t n = cnt[l];
-            const unsigned g = (unsigned)ceil_div(n, T);
-            if (hipMemsetAsync(ccount, 0, 32, s) != hipSuccess) {
-                ok = false;
-                break;
-            }
-            const LevelInfo &lv = p->lev[l];
-            const uint32_t *bk_l = (const uint32_t *)(p->d_tkey + p->tbox_off[l]);
-            hipLaunchKernelGGL(k_lex_keys, dim3(g), dim3(T), 0, s, bk_l, n, l, keys, vals);
-            if (radix_sort_pairs(keys, vals, ktmp, vtmp, n, 3 * l, scr, s) != GRAV_OK) {
-                ok = false;
-                break;
-            }
-            hipLaunchKernelGGL(k_class_keys, dim3(g), dim3(T), 0, s, bk_l, (const uint32_t *)vals, n,
-                               make_int3(lv.s0[0], lv.s0[1], lv.s0[2]), make_int3(lv.ns[0], lv.ns[1], lv.ns[2]),
-                               keys, ccount);
-            if (radix_sort_pairs(keys, vals, ktmp, vtmp, n, 15, scr, s) != GRAV_OK) {
-                ok = false;
-                break;
-            }
-            if (hipMemcpyAsync(p->d_torder + p->tbox_off[l], vals, 4 * n, hipMemcpyDeviceToDevice,
-                               s) != hipSuccess) {
-                ok = false;
-                break;
-            }
-            uint32_t cc[8];
-            if (hipMemcpyAsync(cc, ccount, 32, hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess) {
-                ok = false;
-                break;
-            }
-            int64_t acc = 0;
-            for (int c = 0; c < 8; ++c) {
-                p->lev[l].class_start[c] = acc;
-                acc += cc[c];
-            }
-            p->lev[l].class_start[8] = acc;
-        }
-        if (!ok) {
-            fail(GRAV_EDEVICE);
-            break;
-        }
     } while (0);
     cleanup();
     return st;
@@ -1936,7 +1781,7 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
             break;
         if ((st = build_operators(p)) != GRAV_OK)
             break;
-        if (p->M > 0 && (st = build_tiles(p)) != GRAV_OK)
+        if (p->M > 0 && p->L >= 2 && (st = build_m2l(p)) != GRAV_OK)
             break;
         if (p->M > 0 && (st = build_adjoint_maps(p)) != GRAV_OK)
             break;
@@ -1972,8 +1817,8 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
             // segment slots of the M2L, [parity][column][PS] each, in its
             // element type; both directions use them in turn
             const OctInfo in = octet_info(p->P, p->d.precision == GRAV_FP64);
-            const size_t slot = (size_t)std::max(p->m2l.nseg * p->m2l.nc, p->m2lt.nseg * p->m2lt.nc) * 16 *
-                                (8 / in.RS) * p->PS;
+            auto cols = [](const OctPlan &o) { return 16 * o.nc * std::max<int64_t>(o.nseg, 1); };
+            const size_t slot = (size_t)std::max(cols(p->m2l), cols(p->m2lt)) * (8 / in.RS) * p->PS;
             if ((st = dalloc(p, &p->d_part, p->d.precision == GRAV_FP64 ? slot : (slot + 1) / 2, false)) != GRAV_OK)
                 break;
         }

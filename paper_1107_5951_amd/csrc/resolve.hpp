@@ -5,15 +5,6 @@
 
 namespace grav {
 
-// A tile of columns: one level, one class (or none), columns [col0, col0 + ncol).
-struct GemmTile {
-    int32_t level;
-    int32_t cls;
-    int64_t col0;
-    int32_t ncol;
-    int32_t pad;
-};
-
 __host__ __device__ inline int64_t dense_index(const DevLev &lv, int x, int y, int z)
 {
     const int sx = x - lv.s0[0], sy = y - lv.s0[1], sz = z - lv.s0[2];
