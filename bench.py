@@ -198,8 +198,8 @@ def roofline(plan, stages, p, prec, profile):
     L = plan.levels
     leaves = [-(-v // b) for v in n]
     n_leaf_src = leaves[0] * leaves[1] * leaves[2]
-    parents = 0
-    for lvl in range(2, L):
+    parents = 0  # of M2M: the leaves' own parents are set by the P2M
+    for lvl in range(2, L - 1):
         c = 1
         for a in range(3):
             c *= -(-leaves[a] // (1 << (L - lvl)))
@@ -215,8 +215,9 @@ def roofline(plan, stages, p, prec, profile):
         # by parity: each coefficient row once per parent, not per child
         "m2m": (2.0 * p ** 4 * parents * B, "k_octet_up<%d> / k_octet_up_short<%d> (M2M, FP64 MFMA 16x16x4)" % (p, p),
                 "mfma", "fp64_mfma", "TFLOP/s"),
-        # the leaf's cells times the lattice P2M matrix (p^2 x b^3, FP64)
-        "p2m": (2.0 * p * p * b ** 3 * n_leaf_src * B, "k_p2m_mfma<%d> (P2M, FP64 MFMA 16x16x4)" % (ps // 16),
+        # the leaf's cells times the lattice P2M matrix (p^2 x b^3, FP64), and an
+        # octet's parity sums times its parent's
+        "p2m": (2.0 * p * p * b ** 3 * (n_leaf_src + n_leaf_src / 8) * B, "k_p2m_octet<%d> (P2M, FP64 MFMA 16x16x4)" % p,
                 "mfma", "fp64_mfma", "TFLOP/s"),
     }
     if "near_lat" not in stages:

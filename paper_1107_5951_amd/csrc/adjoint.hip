@@ -220,68 +220,6 @@ k_t_l2p(DevGeom g, const double *tpos, const int64_t *leaf_start, const int64_t 
     }
 }
 
-// P2M^T: drho[cell] = sum_k Pm[v][k] ME_L[leaf][k] for the cells v of every
-// leaf of the source block (each mesh cell once), as FP64 MFMA: one wave
-// owns 16 (leaf, model) columns and four 16-cell row blocks (blockIdx.y
-// selects the blocks), K = the coefficients in the order 16 (ks/4) +
-// 4 (lane/16) + ks%4: a lane's four k steps of chunk q are the coefficients
-// 16 q + 4 (lane/16) + 0..3, one 32-byte read, and the four sub-rows of a
-// column read one contiguous 128 bytes.
-template <int RB>
-__global__ void __launch_bounds__(64)
-k_t_p2m(DevGeom g, const double *A, int RBT, const double *me, double *drho)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    const int lane = threadIdx.x, kr = lane >> 4;
-    const DevLev &lv = g.lev[g.L];
-    const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    // columns leaf-fastest: a row of the output fragment is 16 neighbouring
-    // leaves of one model, so the stores of x-runs of cells coalesce
-    const int64_t col = (int64_t)blockIdx.x * 16 + (lane & 15);
-    const bool cvalid = col < nleaf * g.B;
-    const int64_t leaf = cvalid ? col % nleaf : 0;
-    const int bm = cvalid ? (int)(col / nleaf) : 0;
-    const int rb0 = 4 * blockIdx.y;
-    const double2 *bp = (const double2 *)(me + ((lv.me_off + leaf) * g.B + bm) * PS + 4 * kr);
-    vec4 acc[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    for (int q = 0; q < RB; ++q) {
-        const double2 b01 = cvalid ? bp[8 * q] : double2{0.0, 0.0};
-        const double2 b23 = cvalid ? bp[8 * q + 1] : double2{0.0, 0.0};
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double *ap = A + ((int64_t)(4 * q + u) * RBT + rb0) * 64 + lane;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (rb0 + r < RBT)
-                    acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[r * 64], bv[u], acc[r], 0, 0, 0);
-        }
-    }
-    if (!cvalid)
-        return;
-    const int b = g.b, b3 = b * b * b;
-    const int lx = lv.s0[0] + (int)(leaf % lv.ns[0]), ly = lv.s0[1] + (int)((leaf / lv.ns[0]) % lv.ns[1]),
-              lz = lv.s0[2] + (int)(leaf / ((int64_t)lv.ns[0] * lv.ns[1]));
-    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int v = 16 * (rb0 + r) + kr + 4 * i;
-            if (rb0 + r >= RBT || v >= b3)
-                continue;
-            const int ix = (lx - g.shift[0]) * b + v % b, iy = (ly - g.shift[1]) * b + (v / b) % b,
-                      iz = (lz - g.shift[2]) * b + v / (b * b);
-            if (ix < 0 || iy < 0 || iz < 0 || ix >= g.n[0] || iy >= g.n[1] || iz >= g.n[2])
-                continue;
-            drho[(int64_t)bm * ncell + ((int64_t)iz * g.n[1] + iy) * g.n[0] + ix] = acc[r][i];
-        }
-}
-
 // The near-field transpose, per cell: drho[cell] = (with `prior`, the terms
 // already in drho, else 0) plus, over the targets j (with `pend`, the user
 // points only: the lattice kernel takes the cell centres) of the 27 leaves
@@ -575,128 +513,6 @@ static grav_status enqueue_m2l_transposed(Plan *p, const DevGeom &g, hipStream_t
     return launch_m2l<T>(p, p->m2lt, s, og, rows);
 }
 
-// Workgroups of the grouped P2M^T (each takes G groups of 64 columns so that
-// about this many cover the plan: eight per CU).
-constexpr int64_t kGroupedWorkgroups = 2048;
-
-// P2M^T for leaves of at most 64 cells (four row blocks): a workgroup
-// owning groups of 64 leaf-fastest columns, G groups
-// one after the other, with the chunks of the operator (four k steps, all
-// row blocks) double-buffered in LDS.  The chunk sequence runs on across
-// its groups (step s = chunk s % RB of group s / RB), so the loads of a
-// group's first chunk are in flight during the previous group's last one:
-// a short workgroup per group left the matrix units idle most of the time.
-template <int RB>
-__global__ void __launch_bounds__(256)
-k_t_p2m_lds(DevGeom g, const double *A, int RBT, const double *me, double *drho, int G)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    __shared__ double sa[2][4 * 4 * 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4;
-    const int CH = 4 * RBT * 64;  // doubles per chunk
-    const DevLev &lv = g.lev[g.L];
-    const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t ncol = nleaf * g.B;
-    const int64_t ngrp = (ncol + 63) / 64;
-    const int64_t g0 = (int64_t)blockIdx.x * G;
-    const int ng = (int)min((int64_t)G, ngrp - g0);  // >= 1: the grid covers ngrp
-    const int b = g.b, b3 = b * b * b;
-    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    // this lane's column in group gi; chunk j reads coefficients 16 j +
-    // 4 kr + 0..3 (the order of the fragments)
-    struct Col {
-        bool valid;
-        int64_t leaf;
-        int bm;
-        const double2 *bp;
-    };
-    auto column = [&](int gi) {
-        Col c;
-        const int64_t col = (g0 + gi) * 64 + wave * 16 + (lane & 15);
-        c.valid = col < ncol;
-        c.leaf = c.valid ? col % nleaf : 0;
-        c.bm = c.valid ? (int)(col / nleaf) : 0;
-        c.bp = (const double2 *)(me + ((lv.me_off + c.leaf) * g.B + c.bm) * PS + 4 * kr);
-        return c;
-    };
-    Col cur = column(0), nxt = cur;
-    vec4 acc[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    double ra[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (i < RBT)
-            ra[i] = A[i * 256 + tid];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (i < RBT)
-            sa[0][i * 256 + tid] = ra[i];
-    double2 b01 = cur.valid ? cur.bp[0] : double2{0.0, 0.0};
-    double2 b23 = cur.valid ? cur.bp[1] : double2{0.0, 0.0};
-    __syncthreads();
-    const int S = ng * RB;
-    for (int s = 0; s < S; ++s) {
-        const int buf = s & 1, j = s % RB;
-        const bool more = s + 1 < S;
-        const int jn = j + 1 < RB ? j + 1 : 0;  // chunk of step s + 1
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (i < RBT)
-                    ra[i] = A[(int64_t)jn * CH + i * 256 + tid];
-        }
-        const double bv[4] = {b01.x, b01.y, b23.x, b23.y};
-        if (more) {
-            if (jn == 0)
-                nxt = column(s / RB + 1);
-            b01 = nxt.valid ? nxt.bp[8 * jn] : double2{0.0, 0.0};
-            b23 = nxt.valid ? nxt.bp[8 * jn + 1] : double2{0.0, 0.0};
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (r < RBT)
-                    acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[buf][(u * RBT + r) * 64 + lane], bv[u], acc[r], 0,
-                                                                 0, 0);
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (i < RBT)
-                    sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        if (j == RB - 1) {
-            // the group is done: its cells, then the next group's sums
-            if (cur.valid) {
-                const int lx = lv.s0[0] + (int)(cur.leaf % lv.ns[0]),
-                          ly = lv.s0[1] + (int)((cur.leaf / lv.ns[0]) % lv.ns[1]),
-                          lz = lv.s0[2] + (int)(cur.leaf / ((int64_t)lv.ns[0] * lv.ns[1]));
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int v = 16 * r + kr + 4 * i;
-                        if (r >= RBT || v >= b3)
-                            continue;
-                        const int ix = (lx - g.shift[0]) * b + v % b, iy = (ly - g.shift[1]) * b + (v / b) % b,
-                                  iz = (lz - g.shift[2]) * b + v / (b * b);
-                        if (ix < 0 || iy < 0 || iz < 0 || ix >= g.n[0] || iy >= g.n[1] || iz >= g.n[2])
-                            continue;
-                        drho[(int64_t)cur.bm * ncell + ((int64_t)iz * g.n[1] + iy) * g.n[0] + ix] = acc[r][i];
-                    }
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                acc[r] = vec4{0, 0, 0, 0};
-            cur = nxt;
-        }
-        __syncthreads();
-    }
-}
-
 // The lattice transposes for voxel-centre targets (see k_near_lat): with w_T
 // the combine^T weights of target leaf T's b^3 cell centres (4 per centre),
 //   drho[S] (+)= sum over the 27 neighbours d of A_d^T w_{S - d}   (near^T)
@@ -905,33 +721,6 @@ k_t_l2p_lat(DevGeom g, const double *A, int TQ, const int32_t *tmap, const doubl
 
 #define GRAV_T_RB_CASES(X) X(1) X(2) X(3) X(4) X(6) X(7) X(8) X(9) X(11) X(13) X(15) X(16)
 
-static grav_status launch_t_p2m(Plan *p, const DevGeom &g, double *drho, hipStream_t s)
-{
-    const int b3 = p->b * p->b * p->b, RBT = (b3 + 15) / 16;
-    const int64_t ncol = p->lev[p->L].n_src * p->B;
-    // LDS kernel: groups of 64 columns, about kGroupedWorkgroups workgroups
-    const int64_t ngrp = ceil_div(ncol, 64);
-    const int G = (int)std::max<int64_t>(1, ceil_div(ngrp, kGroupedWorkgroups));
-    const dim3 grid((unsigned)ceil_div(ncol, 16), (unsigned)ceil_div(RBT, 4)), grid_lds((unsigned)ceil_div(ngrp, G));
-#define CASE(R)                                                                                             \
-    case R:                                                                                                 \
-        if (RBT <= 4)                                                                                       \
-            hipLaunchKernelGGL((k_t_p2m_lds<R>), grid_lds, dim3(256), 0, s, g, (const double *)p->d_pmt_sw, RBT, \
-                               (const double *)p->d_me, drho, G);                                           \
-        else                                                                                                \
-            hipLaunchKernelGGL((k_t_p2m<R>), grid, dim3(64), 0, s, g, (const double *)p->d_pmt_sw, RBT,     \
-                               (const double *)p->d_me, drho);                                              \
-        break;
-    switch (p->PS / 16) {
-        GRAV_T_RB_CASES(CASE)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
 static grav_status launch_t_l2p_lat(Plan *p, const DevGeom &g, const double *resid, int add, hipStream_t s)
 {
     const dim3 grid((unsigned)ceil_div(p->lev[p->L].n_src * p->B, 16));
@@ -1034,7 +823,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
             GRAV_CHECK(enqueue_m2l_transposed<float>(p, g, s));
         stage_end(p, s);
         stage_begin(p, "m2mT", s);
-        for (int l = 2; l <= L; ++l)
+        // (to lattice sources, the P2M^T goes on from the level above)
+        for (int l = 2; l <= (p->n_spts > 0 ? L : L - 1); ++l)
             GRAV_CHECK(launch_octet_down(p, p->m2lt, l, s, p->d_m2mt, p->d_me));
         stage_end(p, s);
         if (p->n_spts == 0) {

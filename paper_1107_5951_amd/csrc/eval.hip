@@ -11,195 +11,8 @@
 
 namespace grav {
 
-// --------------------------------------------------------------------------
-// P2M on the lattice: the scaled ME of a leaf is a fixed linear map of its
-// b^3 cell densities (all leaves share the point layout), ME = Pm^T rho_leaf,
-// a GEMM with rows = coefficients, contraction = the leaf's cells and
-// columns = (model, leaf), leaves fastest.  FP64 MFMA: a wave owns 16
-// columns and all row blocks; k step kv and sub-row kr take cell 4 kv + kr.
-// With b = 4 the 64 lanes of one k step read one contiguous run of 64 cell
-// densities (16 consecutive leaves along x, four cells each), and every
-// density is read once.
-// --------------------------------------------------------------------------
-template <int RB>
-__global__ void __launch_bounds__(64) k_p2m_mfma(DevGeom g, const double *rho, const double *A, int KV, double *me)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int KB = 8;  // density loads issued together
-    const DevLev &lv = g.lev[g.L];
-    const int lane = threadIdx.x;
-    const int b = g.b, b2 = b * b, b3 = b2 * b;
-    const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const int64_t col = (int64_t)blockIdx.x * 16 + (lane & 15);
-    const bool cvalid = col < nleaf * g.B;
-    const int bm = cvalid ? (int)(col / nleaf) : 0;
-    const int64_t leaf = cvalid ? col - (int64_t)bm * nleaf : 0;
-    const int lx = (int)(leaf % lv.ns[0]), ly = (int)((leaf / lv.ns[0]) % lv.ns[1]),
-              lz = (int)(leaf / ((int64_t)lv.ns[0] * lv.ns[1]));
-    const int cx = (lv.s0[0] + lx - g.shift[0]) * b, cy = (lv.s0[1] + ly - g.shift[1]) * b,
-              cz = (lv.s0[2] + lz - g.shift[2]) * b;
-    const double *rb0 = rho + (int64_t)bm * ncell;
-    const int kr = lane >> 4;
-    vec4 acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        acc[r] = vec4{0, 0, 0, 0};
-    for (int k0 = 0; k0 < KV; k0 += KB) {
-        double rv[KB];
-#pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            const int v = 4 * (k0 + u) + kr;
-            rv[u] = 0.0;
-            if (cvalid && k0 + u < KV && v < b3) {
-                const int ix = cx + v % b, iy = cy + (v / b) % b, iz = cz + v / b2;
-                if (ix >= 0 && iy >= 0 && iz >= 0 && ix < g.n[0] && iy < g.n[1] && iz < g.n[2])
-                    rv[u] = rb0[((int64_t)iz * g.n[1] + iy) * g.n[0] + ix];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            if (k0 + u >= KV)
-                break;
-            const double *ap = A + (int64_t)(k0 + u) * RB * 64 + lane;
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[r * 64], rv[u], acc[r], 0, 0, 0);
-        }
-    }
-    if (!cvalid)
-        return;
-    // output fragment: column lane % 16, rows lane / 16 + 4 r of each block
-    double *dst = me + ((lv.me_off + leaf) * g.B + bm) * PS;
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            dst[16 * r + kr + 4 * i] = acc[r][i];
-}
-
-// The same GEMM with the operator staged through LDS: a workgroup of four
-// waves owns 64 NCG columns (each wave NCG blocks of 16) and all row
-// blocks; the operator passes through LDS in double-buffered chunks of four
-// k steps (one barrier per chunk), so each chunk is read from L2 once per
-// 64 NCG columns instead of once per 16.
-template <int RB, int NCG>
-__global__ void __launch_bounds__(256) k_p2m_lds(DevGeom g, const double *rho, const double *A, int KV, double *me)
-{
-    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = 16 * RB;
-    constexpr int CH = 4 * RB * 64;  // doubles per chunk
-    __shared__ double sa[2][CH];
-    const DevLev &lv = g.lev[g.L];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4;
-    const int b = g.b, b2 = b * b, b3 = b2 * b;
-    const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    bool cvalid[NCG];
-    int bm[NCG], cx[NCG], cy[NCG], cz[NCG];
-    int64_t leaf[NCG];
-#pragma unroll
-    for (int c = 0; c < NCG; ++c) {
-        const int64_t col = ((int64_t)blockIdx.x * 4 + wave) * 16 * NCG + c * 16 + (lane & 15);
-        cvalid[c] = col < nleaf * g.B;
-        bm[c] = cvalid[c] ? (int)(col / nleaf) : 0;
-        leaf[c] = cvalid[c] ? col - (int64_t)bm[c] * nleaf : 0;
-        const int lx = (int)(leaf[c] % lv.ns[0]), ly = (int)((leaf[c] / lv.ns[0]) % lv.ns[1]),
-                  lz = (int)(leaf[c] / ((int64_t)lv.ns[0] * lv.ns[1]));
-        cx[c] = (lv.s0[0] + lx - g.shift[0]) * b;
-        cy[c] = (lv.s0[1] + ly - g.shift[1]) * b;
-        cz[c] = (lv.s0[2] + lz - g.shift[2]) * b;
-    }
-    auto density = [&](int c, int ks) -> double {
-        const int v = 4 * ks + kr;
-        if (!cvalid[c] || ks >= KV || v >= b3)
-            return 0.0;
-        const int ix = cx[c] + v % b, iy = cy[c] + (v / b) % b, iz = cz[c] + v / b2;
-        if (ix < 0 || iy < 0 || iz < 0 || ix >= g.n[0] || iy >= g.n[1] || iz >= g.n[2])
-            return 0.0;
-        return rho[(int64_t)bm[c] * ncell + ((int64_t)iz * g.n[1] + iy) * g.n[0] + ix];
-    };
-    // chunk j holds k steps 4 j .. 4 j + 3 (those past KV read zero)
-    auto load_chunk = [&](int j, double (&ra)[RB]) {
-#pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            const int e = i * 256 + tid;
-            const int ks = 4 * j + e / (RB * 64);
-            ra[i] = ks < KV ? A[(int64_t)4 * j * RB * 64 + e] : 0.0;
-        }
-    };
-    const int NCH = (KV + 3) / 4;
-    vec4 acc[NCG][RB];
-#pragma unroll
-    for (int c = 0; c < NCG; ++c)
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-            acc[c][r] = vec4{0, 0, 0, 0};
-    double ra[RB];
-    load_chunk(0, ra);
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-        sa[0][i * 256 + tid] = ra[i];
-    double bv[NCG][4];
-#pragma unroll
-    for (int c = 0; c < NCG; ++c)
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            bv[c][u] = density(c, u);
-    __syncthreads();
-    for (int j = 0; j < NCH; ++j) {
-        const int buf = j & 1;
-        const bool more = j + 1 < NCH;
-        if (more)
-            load_chunk(j + 1, ra);
-        double cur[NCG][4];
-#pragma unroll
-        for (int c = 0; c < NCG; ++c)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                cur[c][u] = bv[c][u];
-                if (more)
-                    bv[c][u] = density(c, 4 * (j + 1) + u);
-            }
-        // the densities as the A operand and the operator as B: the product
-        // is the transposed tile (rows = columns, columns = coefficients),
-        // so that the stores below write whole rows of 16 coefficients
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const double a = sa[buf][(u * RB + r) * 64 + lane];
-#pragma unroll
-                for (int c = 0; c < NCG; ++c)
-                    acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[c][u], a, acc[c][r], 0, 0, 0);
-            }
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-                sa[buf ^ 1][i * 256 + tid] = ra[i];
-        }
-        __syncthreads();
-    }
-    // output fragment: rows kr + 4 i = columns of the block, column lane % 16
-    // = coefficient 16 r + lane % 16: 16 lanes write 128 contiguous bytes
-#pragma unroll
-    for (int c = 0; c < NCG; ++c)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t col = ((int64_t)blockIdx.x * 4 + wave) * 16 * NCG + c * 16 + kr + 4 * i;
-            if (col >= nleaf * g.B)
-                continue;
-            const int cbm = (int)(col / nleaf);
-            double *dst = me + ((lv.me_off + col - (int64_t)cbm * nleaf) * g.B + cbm) * PS + (lane & 15);
-#pragma unroll
-            for (int r = 0; r < RB; ++r)
-                dst[16 * r] = acc[c][r][i];
-        }
-}
-
-// The leaves' expansions in FP32 for the mixed M2L (the levels above are
-// written by the M2M).  Leaves farther than 3 boxes from every target box (for
+// Explicit sources: the leaves' expansions in FP32 for the mixed M2L (the
+// levels above are written by the M2M).  Leaves farther than 3 boxes from every target box (for
 // surface stations, the deep part of the mesh) are skipped: no M2L reads them.
 // One thread per four coefficients; src and dst at the level's first row.
 __global__ void __launch_bounds__(256) k_leaf_f32(DevGeom g, const double *src, int64_t n4, float *dst)
@@ -966,48 +779,6 @@ void stage_end(Plan *p, hipStream_t s)
     ++p->n_stage_used;
 }
 
-static grav_status launch_p2m(Plan *p, const DevGeom &g, const double *rho, hipStream_t s)
-{
-    const int RB = p->PS / 16;
-    const int b3 = p->b * p->b * p->b;
-    const int KV = (b3 + 3) / 4;
-    const dim3 grid((unsigned)((p->lev[p->L].n_src * p->B + 15) / 16)), blk(64);
-    // the LDS-staged GEMM once it gives every CU a few workgroups
-    const int64_t ncol = p->lev[p->L].n_src * p->B;
-    const bool lds = (ncol + 127) / 128 >= 1024;
-    const dim3 grid2((unsigned)((ncol + 127) / 128)), grid1((unsigned)((ncol + 63) / 64));
-#define P2M_CASE(R)                                                                             \
-    case R:                                                                                     \
-        if (lds && R <= 8)                                                                      \
-            hipLaunchKernelGGL((k_p2m_lds<R, 2>), grid2, dim3(256), 0, s, g, rho, (const double *)p->d_pm_sw, KV, \
-                               p->d_me);                                                        \
-        else if (lds)                                                                           \
-            hipLaunchKernelGGL((k_p2m_lds<R, 1>), grid1, dim3(256), 0, s, g, rho, (const double *)p->d_pm_sw, KV, \
-                               p->d_me);                                                        \
-        else                                                                                    \
-            hipLaunchKernelGGL((k_p2m_mfma<R>), grid, blk, 0, s, g, rho, (const double *)p->d_pm_sw, KV, p->d_me); \
-        break;
-    switch (RB) {
-        P2M_CASE(1)
-        P2M_CASE(2)
-        P2M_CASE(3)
-        P2M_CASE(4)
-        P2M_CASE(6)
-        P2M_CASE(7)
-        P2M_CASE(8)
-        P2M_CASE(9)
-        P2M_CASE(11)
-        P2M_CASE(13)
-        P2M_CASE(15)
-        P2M_CASE(16)
-    default:
-        return GRAV_EUNSUPPORTED;
-    }
-#undef P2M_CASE
-    GRAV_HIP(hipGetLastError());
-    return GRAV_OK;
-}
-
 static grav_status launch_near_lat(Plan *p, const DevGeom &g, const double *rho, double *out, hipStream_t s)
 {
     const LevelInfo &lv = p->lev[p->L];
@@ -1086,7 +857,8 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
         // expansions in FP32 for the M2L of mixed plans
         float *rows = p->d.precision == GRAV_FP64 ? nullptr : reinterpret_cast<float *>(p->d_rows);
         stage_begin(p, "m2m", s);
-        for (int l = L; l >= 3; --l)
+        // (from lattice sources, the leaves' parents are set by the P2M)
+        for (int l = p->n_spts > 0 ? L : L - 1; l >= 3; --l)
             GRAV_CHECK(launch_octet_up(p, p->m2lt, l, s, p->d_m2m, p->d_me, rows));
         stage_end(p, s);
         stage_begin(p, "m2l", s);
@@ -1095,10 +867,12 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
             if (!rows) {
                 GRAV_CHECK(launch_m2l<double>(p, p->m2l, s, og, p->d_me));
             } else {
-                const int64_t at = p->lev[L].me_off * p->B * p->PS, n4 = p->lev[L].n_src * p->B * (p->PS / 4);
-                hipLaunchKernelGGL(k_leaf_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
-                                   (const double *)(p->d_me + at), n4, rows + at);
-                GRAV_HIP(hipGetLastError());
+                if (p->n_spts > 0) {
+                    const int64_t at = p->lev[L].me_off * p->B * p->PS, n4 = p->lev[L].n_src * p->B * (p->PS / 4);
+                    hipLaunchKernelGGL(k_leaf_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
+                                       (const double *)(p->d_me + at), n4, rows + at);
+                    GRAV_HIP(hipGetLastError());
+                }
                 GRAV_CHECK(launch_m2l<float>(p, p->m2l, s, og, rows));
             }
         }

@@ -58,6 +58,7 @@ struct OctPlan {
     int64_t noct = 0, nseg = 0;
     uint32_t *d_key = nullptr;
     int64_t first[kMaxLevels + 2] = {0};  // octets of level l: [first[l], first[l + 1])
+    int64_t reach[kMaxLevels + 1] = {0};  // those from reach[l] on have no M2L input
     int32_t gfirst[kMaxLevels + 1] = {0}; // first group of level l
     int32_t *d_parent = nullptr;          // [noct] row of the parent, -1 at level 2
     int32_t *d_child = nullptr, *d_segs = nullptr, *d_wgseg = nullptr;
@@ -140,7 +141,6 @@ struct Plan {
     int near_KC = 0;                               // k steps of a class
     double *d_tl2p = nullptr;                      // [PS/16][RB][64][4] far field (L2P) at the cell centres, FP64
     int64_t *d_lat_tab = nullptr;                  // [27 Q][2] per near chunk: density and operator offsets
-    double *d_pmt_sw = nullptr;                    // [PS/4][ceil(b^3/16)][64] P2M^T fragments (adjoint)
     double *d_tn64 = nullptr;                      // [27][KS][RB][64] swizzled, FP64 plans
     float *d_tn32 = nullptr;                       // same, mixed plans
     int lat_TQ = 0;                                // adjoint: chunks of the (target, component) contraction
@@ -162,8 +162,9 @@ struct Plan {
     int32_t *d_tmap = nullptr;       // per level: target-box index over source block + halo 3
     struct DevGeom *d_geom = nullptr;
 
-    double *d_pm = nullptr;        // [b^3][PS] lattice P2M
-    double *d_pm_sw = nullptr;     // [b^3/4][RB][64] the same as MFMA A fragments (FP64)
+    // lattice P2M by octets (p2m.hip) as MFMA A fragments: leaf, parent by
+    // class, and their transposes (rows: cells, to whole sets of row blocks)
+    double *d_pm = nullptr, *d_pm_up = nullptr, *d_pmt = nullptr, *d_pmt_down = nullptr;
     double *d_me = nullptr;        // [n_me][B][PS]
     double *d_le = nullptr;        // [n_tbox][B][PS]
     double *d_near = nullptr;      // [M][B][4] near field (phi, gx, gy, gz), sorted order

@@ -35,14 +35,6 @@ namespace grav {
 
 namespace {
 
-// Parities' rows: class sizes are at most h (h + 1) / 2, h = ceil(P / 2).
-template <int P>
-struct ClassShape {
-    static constexpr int h = (P + 1) / 2, MAXC = h * (h + 1) / 2;
-    static constexpr int RBC = (MAXC + 15) / 16;  // row blocks of a class
-    static constexpr int KC = (MAXC + 3) / 4;     // k steps of a class
-};
-
 struct LevelArgs {
     const int32_t *child, *parent;  // of the level's first octet
     int64_t ncols;                  // octets x models
@@ -170,8 +162,7 @@ k_octet_up(LevelArgs lv, const double *A, const int32_t *coef, const double *x, 
             const int k = coef[chi * 16 * C::RBC + 16 * rb + kr + 4 * r];
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                if (k >= 0)
-                    sm[(c * 16 + (lane & 15)) * OP + k] = acc[c][rb][r];
+                sm[(c * 16 + (lane & 15)) * OP + (k >= 0 ? k : PS)] = acc[c][rb][r];  // (PS: a spare place)
         }
     if constexpr (PS > P * P)
         for (int i = tid; i < NCOL * (PS - P * P); i += 512)
@@ -203,9 +194,12 @@ k_octet_up_short(LevelArgs lv, const double *A, const int32_t *coef, const doubl
     constexpr int US = 65;  // doubles per k step and class: the staging stores of 32 lanes, one step each, spread
     constexpr int kTile = 8 * (KS < CS ? KS : CS) * US, kOut = 16 * OP;
     __shared__ double sm[kTile > kOut ? kTile : kOut];
+    __shared__ int32_t srow[16];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t col0 = (int64_t)blockIdx.x * 16;
+    if (tid < 16)
+        srow[tid] = lv.parent[min(col0 + tid, lv.ncols - 1) / lv.B];
     const int scol = tid >> 5, su = tid & 31;  // staging column and k step of the chunk
     const int64_t col = min(col0 + scol, lv.ncols - 1);
     const int32_t *ch = lv.child + col / lv.B * 8;
@@ -269,8 +263,7 @@ k_octet_up_short(LevelArgs lv, const double *A, const int32_t *coef, const doubl
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int k = coef[chi * 16 * C::RBC + 16 * rb + kr + 4 * r];
-            if (k >= 0)
-                sm[(lane & 15) * OP + k] = acc[rb][r];
+            sm[(lane & 15) * OP + (k >= 0 ? k : PS)] = acc[rb][r];  // (PS: a spare place)
         }
     if constexpr (PS > P * P)
         for (int i = tid; i < 16 * (PS - P * P); i += 512)
@@ -280,22 +273,13 @@ k_octet_up_short(LevelArgs lv, const double *A, const int32_t *coef, const doubl
         const int c = i / PS, k = i % PS;
         if (col0 + c >= lv.ncols)
             continue;
-        const int64_t o = ((int64_t)lv.parent[(col0 + c) / lv.B] * lv.B + (col0 + c) % lv.B) * PS + k;
+        const int64_t o = ((int64_t)srow[c] * lv.B + (col0 + c) % lv.B) * PS + k;
         const double v = sm[c * OP + k];
         out[o] = v;
         if (out32)
             out32[o] = (float)v;
     }
 }
-
-// The M2L slots of a level's columns (T: the M2L's element type): group g0 +
-// column / ncol holds column % ncol; RS units per group, 8 / RS parities each.
-template <typename T>
-struct SlotArgs {
-    const T *part;
-    const int32_t *uslot;
-    int g0, ncol;
-};
 
 // Down.  A workgroup takes 16 NC columns, wave chi the products of class chi;
 // row block by row block the eight parities meet in LDS, the slots are added,
@@ -336,9 +320,18 @@ k_octet_down(LevelArgs lv, SlotArgs<T> sl, const double *A, const int32_t *coef,
     const T *pc = sl.part + cs % sl.ncol * PS + orow;
     // the parents' rows
     if (x != nullptr) {
-        for (int i = tid; i < NCOL * PS; i += 512) {
+        constexpr int NI = (NCOL * PS + 511) / 512;
+        double y[NI];
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int i = min(tid + 512 * n, NCOL * PS - 1);
             const int64_t c = min(col0 + i / PS, lv.ncols - 1);
-            g1[i / PS * XP + i % PS] = x[((int64_t)lv.parent[c / lv.B] * lv.B + c % lv.B) * PS + i % PS];
+            y[n] = x[((int64_t)lv.parent[c / lv.B] * lv.B + c % lv.B) * PS + i % PS];
+        }
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int i = min(tid + 512 * n, NCOL * PS - 1);
+            g1[i / PS * XP + i % PS] = y[n];
         }
         __syncthreads();
     }

@@ -32,9 +32,7 @@ constexpr int kOrbits = 26;  // boxes (x, y, z) in {1, 2, 3}^3 without (1, 1, 1)
 // imaginary parts, x -> -x (-1)^m on real and -(-1)^m on imaginary parts.
 __host__ __device__ inline int sign_class(int c)
 {
-    int n = 0;
-    while ((n + 1) * (n + 1) <= c)
-        ++n;
+    const int n = (int)sqrtf((float)c + 0.5f);  // exact: c < 2^16
     const int i = c - n * n;
     const int m = (i + 1) / 2;
     const int im = (i > 0 && (i & 1) == 0) ? 1 : 0;
@@ -140,6 +138,23 @@ struct OctShape {
     // FP32 with at most four coefficient rows in the last row block: that
     // block runs as 4x4x1 instructions, a quarter of the cycles
     static constexpr bool TAIL4 = sizeof(T) == 4 && P2 % 16 >= 1 && P2 % 16 <= 4;
+};
+
+// Parities' rows: class sizes are at most h (h + 1) / 2, h = ceil(P / 2).
+template <int P>
+struct ClassShape {
+    static constexpr int h = (P + 1) / 2, MAXC = h * (h + 1) / 2;
+    static constexpr int RBC = (MAXC + 15) / 16;  // row blocks of a class
+    static constexpr int KC = (MAXC + 3) / 4;     // k steps of a class
+};
+
+// The M2L slots of a level's columns (T: the M2L's element type): group g0 +
+// column / ncol holds column % ncol; RS units per group, 8 / RS parities each.
+template <typename T>
+struct SlotArgs {
+    const T *part;
+    const int32_t *uslot;
+    int g0, ncol;
 };
 
 }  // namespace grav

@@ -268,11 +268,11 @@ void free_plan(Plan *p)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p->device);
     void *bufs[] = {p->d_points, p->d_perm, p->d_tpos, p->d_tleaf, p->d_leaf_start, p->d_tkey,
-                    p->d_class_off, p->d_tmap, p->d_geom, p->d_pm, p->d_pm_sw, p->d_m2m, p->d_l2l, p->d_m2mt,
+                    p->d_class_off, p->d_tmap, p->d_geom, p->d_pm, p->d_pm_up, p->d_pmt, p->d_pmt_down, p->d_m2m, p->d_l2l, p->d_m2mt,
                     p->d_l2lt, p->d_class_coef, p->d_me, p->d_le, p->d_near, p->d_part, p->d_rows,
                     p->d_tn64, p->d_tn32, p->d_rho_blk, p->d_tl2p, p->d_dpart,
                     p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
-                    p->d_pmt_sw, p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
+                    p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
                     p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
                     p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_coef};
     for (OctPlan *o : {&p->m2l, &p->m2lt}) {
@@ -524,45 +524,69 @@ static grav_status upload_level_operators(Plan *p, const std::vector<double> &m,
     return GRAV_OK;
 }
 
+// Operators of the lattice P2M and its transpose by octets (p2m.hip).  m: the
+// M2M of the (+,+,+) child.  Forward, in chunks of 16 cells, zero past the last:
+// k step ks and sub-row kr take cell 4 ks + kr; leaf rows, in one part or two, 16 rb + 4 (lane % 4) + lane % 16 / 4 (a lane of the product then
+// holds four consecutive coefficients), parent rows coefficient 16 rb + lane %
+// 16 of the class.  Transpose: rows = cells 16 rb + lane % 16, to whole sets of
+// row blocks; contraction over the leaf's coefficients in the order 16 (ks / 4)
+// + 4 (lane / 16) + ks % 4 (four consecutive ones per lane and chunk of four k
+// steps), over the parent's class in order.
+static grav_status upload_lattice_p2m(Plan *p, const std::vector<double> &m)
+{
+    const int P = p->P, P2 = p->P2, PS = p->PS, RB = PS / 16;
+    const int b3 = p->b * p->b * p->b, KV = (int)ceil_div(b3, 16) * 4;
+    const int NP = RB > 8 ? 2 : 1, RBL = (int)ceil_div(RB, NP);
+    const int R0 = (int)ceil_div(b3, 16), RBT = R0 <= 2 ? 2 : (int)ceil_div(R0, 4) * 4;
+    std::vector<double> pm((size_t)b3 * PS), up((size_t)b3 * PS, 0.0);
+    p2m_lattice(P, p->b, p->q, 1.0, PS, pm.data());
+    for (int v = 0; v < b3; ++v)
+        for (int i = 0; i < P2; ++i)
+            for (int k = 0; k < P2; ++k)
+                up[(size_t)v * PS + i] += m[(size_t)i * PS + k] * pm[(size_t)v * PS + k];
+    std::vector<int> cls[8];
+    size_t most = 0;
+    for (int k = 0; k < P2; ++k) {
+        cls[sign_class(k)].push_back(k);
+        most = std::max(most, cls[sign_class(k)].size());
+    }
+    const int RBC = (int)ceil_div((int64_t)most, 16), KC = (int)ceil_div((int64_t)most, 4);
+    std::vector<double> a((size_t)KV * NP * RBL * 64, 0.0), au((size_t)8 * KV * RBC * 64, 0.0);
+    std::vector<double> t((size_t)PS / 4 * RBT * 64, 0.0), td((size_t)8 * KC * RBT * 64, 0.0);
+    for (int lane = 0; lane < 64; ++lane) {
+        for (int ks = 0; ks < KV; ++ks) {
+            const int v = 4 * ks + lane / 16;
+            if (v >= b3)
+                continue;
+            for (int rb = 0; rb < RB; ++rb)
+                a[((((size_t)ks / 4 * NP + rb / RBL) * 4 + ks % 4) * RBL + rb % RBL) * 64 + lane] = pm[(size_t)v * PS + 16 * rb + 4 * (lane % 4) + lane % 16 / 4];
+            for (int x = 0; x < 8; ++x)
+                for (int rb = 0; rb < RBC; ++rb)
+                    if (16 * rb + lane % 16 < (int)cls[x].size())
+                        au[(((size_t)x * KV + ks) * RBC + rb) * 64 + lane] = up[(size_t)v * PS + cls[x][16 * rb + lane % 16]];
+        }
+        for (int rb = 0; rb < RBT; ++rb) {
+            const int v = 16 * rb + lane % 16;
+            if (v >= b3)
+                continue;
+            for (int ks = 0; ks < PS / 4; ++ks)
+                t[((size_t)ks * RBT + rb) * 64 + lane] = pm[(size_t)v * PS + 16 * (ks / 4) + 4 * (lane / 16) + ks % 4];
+            for (int x = 0; x < 8; ++x)
+                for (int q = 0; q < KC; ++q)
+                    if (4 * q + lane / 16 < (int)cls[x].size())
+                        td[(((size_t)x * KC + q) * RBT + rb) * 64 + lane] = up[(size_t)v * PS + cls[x][4 * q + lane / 16]];
+        }
+    }
+    GRAV_CHECK(upload(p, &p->d_pm, a));
+    GRAV_CHECK(upload(p, &p->d_pm_up, au));
+    GRAV_CHECK(upload(p, &p->d_pmt, t));
+    GRAV_CHECK(upload(p, &p->d_pmt_down, td));
+    return GRAV_OK;
+}
+
 grav_status build_operators(Plan *p)
 {
-    const int P = p->P, PS = p->PS, RB = PS / 16;
-    const int b3 = p->b * p->b * p->b;
-    std::vector<double> pm((size_t)b3 * PS);
-    p2m_lattice(P, p->b, p->q, 1.0, PS, pm.data());
-    GRAV_CHECK(upload(p, &p->d_pm, pm));
-    {
-        // the same map as FP64 MFMA A fragments: rows = coefficients, the
-        // contraction runs over the leaf's cells, k step kv and sub-row kr
-        // taking cell 4 kv + kr; [kv][rb][lane] = pm[4 kv + lane/16][16 rb + lane%16]
-        const int KV = (b3 + 3) / 4;
-        std::vector<double> psw((size_t)KV * RB * 64, 0.0);
-        for (int kv = 0; kv < KV; ++kv)
-            for (int rb = 0; rb < RB; ++rb)
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int v = 4 * kv + lane / 16;
-                    if (v < b3)
-                        psw[((size_t)kv * RB + rb) * 64 + lane] = pm[(size_t)v * PS + 16 * rb + lane % 16];
-                }
-        GRAV_CHECK(upload(p, &p->d_pm_sw, psw));
-        // the adjoint's P2M^T: rows = the leaf's cells (RBT blocks of 16),
-        // contraction over the coefficients in the order 16 (ks/4) +
-        // 4 (lane/16) + ks%4, so that a chunk of four k steps takes 16
-        // consecutive coefficients of a column, four per sub-row (one
-        // 128-byte line per column and chunk in FP64);
-        // [ks][rbt][lane] = pm[16 rbt + lane%16][16 (ks/4) + 4 (lane/16) + ks%4]
-        const int RBT = (b3 + 15) / 16, K4 = PS / 4;
-        std::vector<double> pmt((size_t)K4 * RBT * 64, 0.0);
-        for (int ks = 0; ks < K4; ++ks)
-            for (int rb = 0; rb < RBT; ++rb)
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int v = 16 * rb + lane % 16;
-                    if (v < b3)
-                        pmt[((size_t)ks * RBT + rb) * 64 + lane] =
-                            pm[(size_t)v * PS + 16 * (ks / 4) + 4 * (lane / 16) + ks % 4];
-                }
-        GRAV_CHECK(upload(p, &p->d_pmt_sw, pmt));
-    }
+    const int P = p->P, PS = p->PS;
     if (p->L < 2)
         return GRAV_OK;
 
@@ -574,6 +598,8 @@ grav_status build_operators(Plan *p)
         m2m_matrix(P, delta, PS, m.data());
         l2l_matrix(P, delta, PS, l.data());
         GRAV_CHECK(upload_level_operators(p, m, l));
+        if (p->n_spts == 0)
+            GRAV_CHECK(upload_lattice_p2m(p, m));
     }
     GRAV_CHECK(upload(p, &p->d_class_off, offsets_table()));
     if (p->M == 0)
@@ -641,6 +667,7 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     const int64_t B = p->B;
     o.noct = (int64_t)oc.key.size();
     std::copy(std::begin(oc.first), std::end(oc.first), std::begin(o.first));
+    std::copy(std::begin(oc.reach), std::end(oc.reach), std::begin(o.reach));
     // four (or two) column blocks per wave once there are units for every CU
     // twice over; else single blocks, for more units than CUs on small plans
     int resident = 0;
