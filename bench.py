@@ -206,7 +206,6 @@ def roofline(plan, stages, p, prec, profile):
         parents += c
     f64 = prec == GRAV_FP64
     mm = "fp64_mfma" if f64 else "fp32_mfma"
-    ps = -(-p * p // 16) * 16
     cand = {
         "m2l": (2.0 * p ** 4 * M2L_OPS_PER_PAIR * m2l_pairs * B, m2l_label(p, prec), "mfma", mm, "TFLOP/s"),
         "near_lat": (27 * 2.0 * (plan.spec.components * b ** 3) * b ** 3 * n_leaf_src * B,

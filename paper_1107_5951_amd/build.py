@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libgrav.so")
 SOURCES = ["operators.cpp", "sort.hip", "plan.hip", "eval.hip", "adjoint.hip", "check.hip", "direct.hip", "m2l.hip",
-           "levels.hip", "p2m.hip", "near.hip", "analytic.hip"]
+           "levels.hip", "p2m.hip", "points.hip", "near.hip", "analytic.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

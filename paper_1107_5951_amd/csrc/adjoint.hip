@@ -86,140 +86,6 @@ k_t_weights(DevGeom g, const double *resid, const uint32_t *perm, int64_t limit,
 // group), so that every operator entry or pair geometry it loads serves MT
 // models; groups are ceil(B / MT).
 
-// L2P^T: the adjoint LE of a leaf is the derivative, with respect to its
-// coefficients, of the sum over the leaf's targets (with `pend`, its user
-// points only) of a phi - (b1 gx + b2 gy + b3 gz), with (a, b) the target's
-// weights scaled as the combine scales the far field (a = w0 / w, b = w_1..3
-// / w^2).  That derivative is linear in the weights: with the sums
-//   S_c[h] = sum over targets of (a, b1, b2, b3)_c R_h(target)
-// of the regular harmonics, coefficient (n, m) collects a R_n^m (x2 for
-// m > 0) and the gradient terms of degree n-1 and orders m-1, m, m+1, as
-// the evaluation pairs them (d/dz R_n^m = R_{n-1}^m, d/dx and d/dy from
-// R_{n-1}^{m-1} and R_{n-1}^{m+1}).  One workgroup per (target leaf, group
-// of MG models: 1 for single-model plans, else kL2PTModels); targets in
-// chunks of kL2PTChunk: their harmonics
-// and weights go to LDS, and every thread adds, in target order, the
-// products of the (c, model, h) sums it owns (deterministic).
-constexpr int kL2PTChunk = 24, kL2PTModels = 4;
-
-template <int MG>
-__device__ __forceinline__ double l2pt_gather(const double *S, int P2, int mg, int n, int m, int part)
-{
-    auto h = [&](int c, int nn, int mm, int pp) -> double {
-        if (nn < 0 || mm > nn || (mm == 0 && pp == 1))
-            return 0.0;
-        return S[(c * MG + mg) * P2 + harm_index(nn, mm, pp)];
-    };
-    const int q = n - 1;  // degree of the gradient terms
-    double v;
-    if (part == 0) {
-        v = (m == 0 ? 1.0 : 2.0) * h(0, n, m, 0);
-        if (q >= 0) {
-            if (m == 0) {
-                v += -h(3, q, 0, 0) + h(1, q, 1, 0) + h(2, q, 1, 1);
-            } else {
-                v += -2.0 * h(3, q, m, 0);
-                if (m == 1)
-                    v -= h(1, q, 0, 0);
-                else
-                    v += h(2, q, m - 1, 1) - h(1, q, m - 1, 0);
-                v += h(1, q, m + 1, 0) + h(2, q, m + 1, 1);
-            }
-        }
-    } else {
-        v = -2.0 * h(0, n, m, 1);
-        if (q >= 0) {
-            v += 2.0 * h(3, q, m, 1);
-            if (m == 1)
-                v += h(2, q, 0, 0);
-            else
-                v += h(1, q, m - 1, 1) + h(2, q, m - 1, 0);
-            v += h(2, q, m + 1, 0) - h(1, q, m + 1, 1);
-        }
-    }
-    return v;
-}
-
-template <int MG>
-__global__ void __launch_bounds__(256)
-k_t_l2p(DevGeom g, const double *tpos, const int64_t *leaf_start, const int64_t *pend, const uint32_t *tkey,
-        int64_t n_leaf, const int32_t *leaves, const double *w, double *le)
-{
-    extern __shared__ double sh[];
-    constexpr int TC = kL2PTChunk;
-    const int P2 = g.P2;
-    double *H = sh;             // [TC][P2] harmonics of the chunk's targets
-    double *W = sh + TC * P2;   // [TC][MG][4] their scaled weights
-    const int64_t leaf = leaves[blockIdx.x];  // the target leaves holding user points
-    const int bm0 = blockIdx.y * MG;
-    const int tid = threadIdx.x;
-    const DevLev &lv = g.lev[g.L];
-    const uint32_t key = tkey[lv.tbox_off + leaf];
-    const int lc[3] = {(int)compact3(key), (int)compact3(key >> 1), (int)compact3(key >> 2)};
-    double centre[3];
-    for (int a = 0; a < 3; ++a)
-        centre[a] = ((double)(lc[a] - g.shift[a]) + 0.5) * g.b;
-    const double inv_w = 1.0 / (double)g.b, inv_w2 = inv_w * inv_w;
-    const int64_t ts = max(leaf_start[leaf], (int64_t)0);
-    const int64_t te = min(pend ? pend[leaf] : leaf_start[leaf + 1], g.M);
-    const int NO = 4 * MG * P2;  // sums (c, model, h), output o = (c MG + mg) P2 + h
-    constexpr int NJ = 4 * MG * 256 / 256;  // sums per thread (p^2 <= 256)
-    double acc[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-        acc[j] = 0.0;
-    for (int64_t j0 = ts; j0 < te; j0 += TC) {
-        const int nt = (int)min((int64_t)TC, te - j0);
-        if (tid < nt) {
-            const int64_t j = j0 + tid;
-            regular_harmonics(g.P, (tpos[3 * j + 0] - centre[0]) * inv_w, (tpos[3 * j + 1] - centre[1]) * inv_w,
-                              (tpos[3 * j + 2] - centre[2]) * inv_w, H + tid * P2, 1);
-        }
-        for (int i = tid; i < nt * MG * 4; i += 256) {
-            const int t = i / (MG * 4), mg = (i / 4) % MG, c = i % 4;
-            const int bm = bm0 + mg;
-            W[i] = bm < g.B ? w[((j0 + t) * g.B + bm) * 4 + c] * (c == 0 ? inv_w : inv_w2) : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int o = tid + 256 * j;
-            if (o < NO) {
-                const int h = o % P2, cm = o / P2;  // cm = c MG + mg
-                const int c = cm / MG, mg = cm % MG;
-                double v = acc[j];
-                for (int t = 0; t < nt; ++t)
-                    v += H[t * P2 + h] * W[(t * MG + mg) * 4 + c];
-                acc[j] = v;
-            }
-        }
-        __syncthreads();
-    }
-    double *S = sh;  // [4][MG][P2]
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int o = tid + 256 * j;
-        if (o < NO)
-            S[o] = acc[j];
-    }
-    __syncthreads();
-    for (int i = tid; i < MG * g.PS; i += 256) {
-        const int mg = i / g.PS, k = i % g.PS;
-        const int bm = bm0 + mg;
-        if (bm >= g.B)
-            continue;
-        double v = 0.0;  // padding coefficients stay zero
-        if (k < P2) {
-            int n = 0;
-            while ((n + 1) * (n + 1) <= k)
-                ++n;
-            const int r = k - n * n;
-            v = l2pt_gather<MG>(S, P2, mg, n, (r + 1) / 2, (r > 0 && (r & 1) == 0) ? 1 : 0);
-        }
-        le[((lv.tgt_off + leaf) * g.B + bm) * g.PS + k] = v;
-    }
-}
-
 // The near-field transpose, per cell: drho[cell] = (with `prior`, the terms
 // already in drho, else 0) plus, over the targets j (with `pend`, the user
 // points only: the lattice kernel takes the cell centres) of the 27 leaves
@@ -670,7 +536,7 @@ k_t_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, int RBt, int KQ,
 // L2P^T at the cell centres (FP64): one wave owns 16 (leaf, model) columns
 // and all RB coefficient blocks; the column's target leaf is found in the
 // leaf level's target map.  With `add`, the LE of a leaf that also holds
-// user points (written by k_t_l2p) is added to, every other one set.
+// user points (written by k_t_l2p_points) is added to, every other one set.
 template <int RB>
 __global__ void __launch_bounds__(64)
 k_t_l2p_lat(DevGeom g, const double *A, int TQ, const int32_t *tmap, const double *resid, int64_t npts,
@@ -789,26 +655,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
         // user points by the transposed recurrence; cell centres of lattice
         // plans by the transposed lattice L2P
         const bool pts = !p->lat_near || p->d.n_points > 0;
-        if (p->n_leaf > 0 && pts) {
-            const int MG = p->B == 1 ? 1 : kL2PTModels;
-            const size_t lds = sizeof(double) * std::max(kL2PTChunk * (p->P2 + 4 * MG), 4 * MG * p->P2);
-            // one workgroup per target leaf holding user points (the LE of
-            // the other leaves, cell centres only, is set by the lattice
-            // L2P^T below)
-            const dim3 lgrid((unsigned)p->n_user_leaves, (unsigned)ceil_div(p->B, MG));
-            const int64_t *pend = p->lat_near ? (const int64_t *)p->d_leaf_pend : nullptr;
-            const int32_t *ul = (const int32_t *)p->d_user_leaves;
-            if (p->n_user_leaves == 0) {
-            } else if (MG == 1)
-                hipLaunchKernelGGL((k_t_l2p<1>), lgrid, dim3(256), lds, s, g, (const double *)p->d_tpos,
-                                   (const int64_t *)p->d_leaf_start, pend, (const uint32_t *)p->d_tkey, p->n_leaf,
-                                   ul, (const double *)p->d_near, p->d_le);
-            else
-                hipLaunchKernelGGL((k_t_l2p<kL2PTModels>), lgrid, dim3(256), lds, s, g, (const double *)p->d_tpos,
-                                   (const int64_t *)p->d_leaf_start, pend, (const uint32_t *)p->d_tkey, p->n_leaf,
-                                   ul, (const double *)p->d_near, p->d_le);
-            GRAV_HIP(hipGetLastError());
-        }
+        if (p->n_leaf > 0 && pts)
+            GRAV_CHECK(launch_t_l2p_points(p, g, s));
         if (p->lat_near)
             GRAV_CHECK(launch_t_l2p_lat(p, g, resid, pts ? 1 : 0, s));
         stage_end(p, s);

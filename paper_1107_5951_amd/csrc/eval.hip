@@ -655,65 +655,6 @@ k_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, const int64_t *cta
 }
 
 // --------------------------------------------------------------------------
-// L2P + combine: far field at each target from its leaf LE (phi and
-// g = -grad phi), plus the near field, times G and the lattice-to-physical
-// scale, scattered back to descriptor order.  One thread per (target, model),
-// targets fastest.
-// --------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-k_l2p_combine(DevGeom g, const double *tpos, const int32_t *tleaf, const uint32_t *tkey,
-              const uint32_t *perm, const double *le, const double *near, int64_t first_lattice,
-              double *out)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.M * g.B)
-        return;
-    const int bm = (int)(t / g.M);
-    const int64_t i = t - (int64_t)bm * g.M;
-    const int64_t dst_t = perm[i];
-    if (dst_t >= first_lattice)
-        return;  // a voxel centre written by the fused lattice kernel
-    const DevLev &lv = g.lev[g.L];
-    const int64_t leaf = tleaf[i];
-    double far[4] = {0, 0, 0, 0};
-    if (g.L >= 2) {
-        const uint32_t key = tkey[lv.tbox_off + leaf];
-        const int lc[3] = {(int)compact3(key), (int)compact3(key >> 1), (int)compact3(key >> 2)};
-        const double inv_w = 1.0 / (double)g.b;
-        double u[3];
-        for (int a = 0; a < 3; ++a) {
-            const double centre = ((double)(lc[a] - g.shift[a]) + 0.5) * g.b;
-            u[a] = (tpos[3 * i + a] - centre) * inv_w;
-        }
-        const double *L = le + ((lv.tgt_off + leaf) * g.B + bm) * g.PS;
-        l2p_eval(g.P, L, u[0], u[1], u[2], far);
-        far[0] *= inv_w;
-        const double s = inv_w * inv_w;
-        far[1] = -far[1] * s;  // g = -grad phi
-        far[2] = -far[2] * s;
-        far[3] = -far[3] * s;
-    }
-    const double *nr = near + (i * g.B + bm) * 4;
-    double v[4];
-    for (int c = 0; c < 4; ++c)
-        v[c] = nr[c] + far[c];
-    double *o = out + ((int64_t)bm * g.M + dst_t) * g.C;
-    const double sg = g.G * g.h, sp = g.G * g.h * g.h;
-    if (g.C == 1) {
-        o[0] = sg * v[3];
-    } else if (g.C == 3) {
-        o[0] = sg * v[1];
-        o[1] = sg * v[2];
-        o[2] = sg * v[3];
-    } else {
-        o[0] = sp * v[0];
-        o[1] = sg * v[1];
-        o[2] = sg * v[2];
-        o[3] = sg * v[3];
-    }
-}
-
-// --------------------------------------------------------------------------
 // host side
 // --------------------------------------------------------------------------
 DevGeom make_geom(const Plan *p)
@@ -916,12 +857,7 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
         GRAV_HIP(hipGetLastError());
         stage_end(p, s);
         stage_begin(p, "l2p", s);
-        hipLaunchKernelGGL(k_l2p_combine, dim3((unsigned)((p->M * p->B + 255) / 256)), dim3(256), 0, s, g,
-                           (const double *)p->d_tpos, (const int32_t *)p->d_tleaf,
-                           (const uint32_t *)p->d_tkey, (const uint32_t *)p->d_perm,
-                           (const double *)p->d_le, (const double *)p->d_near,
-                           p->lat_near ? p->d.n_points : p->M, out);
-        GRAV_HIP(hipGetLastError());
+        GRAV_CHECK(launch_l2p_points(p, g, out, s));
         stage_end(p, s);
     }
     return GRAV_OK;

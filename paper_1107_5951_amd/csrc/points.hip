@@ -1,0 +1,416 @@
+// L2P at user points (and at every target of plans without lattice matrices)
+// with the combine, and the transpose: one workgroup per target leaf that holds
+// such points and group of models.
+//
+// What bounds them: the chain of the harmonics' recurrences and the arithmetic
+// in FP64.  The order is a template parameter, so the recurrences' reciprocals
+// are constants (a division each before), and the orders m are split over the
+// four waves.  The leaf's expansions pass through LDS; a thread per point read
+// its own row from memory, one dependent load after the other.  p = 10: 32
+// models at 65536 stations forward 0.25 -> 0.12 ms, transpose 0.43 -> 0.09 ms
+// (sums on MFMA); one model at 262144 stations among 16.8 M cell centres 0.085 ->
+// 0.023 ms (the centres are no longer visited) and 0.106 -> 0.052 ms; FP64 p =
+// 14, 1024 stations 0.044 -> 0.006 ms.
+#include <algorithm>
+
+#include "harmonics.hpp"
+#include "octet.hpp"
+
+namespace grav {
+
+namespace {
+
+constexpr int kPointModels = 8;  // models per workgroup (1 on single-model plans)
+
+// Wave w of four takes the orders m = w, 7 - w, 8 + w, 15 - w: columns of
+// about equal length together.
+__host__ __device__ constexpr int wave_of_order(int m) { return (m & 4) ? 3 - (m & 3) : (m & 3); }
+
+// Visits R_n^m(u) of wave w's orders, f(n, m, Re, Im); n and m are constants
+// of the unrolled code.
+template <int P, int W, class F>
+__device__ __forceinline__ void harmonics_of_wave(double x, double y, double z, F &&f)
+{
+    const double r2 = x * x + y * y + z * z;
+    double mmr = 1.0, mmi = 0.0;
+#pragma unroll
+    for (int m = 0; m < P; ++m) {
+        if (m > 0) {
+            const double s = 1.0 / (2.0 * m);
+            const double nr = (x * mmr - y * mmi) * s;
+            const double ni = (x * mmi + y * mmr) * s;
+            mmr = nr;
+            mmi = ni;
+        }
+        if (wave_of_order(m) != W)
+            continue;
+        double p1r = 0.0, p1i = 0.0, p2r = 0.0, p2i = 0.0;
+#pragma unroll
+        for (int n = m; n < P; ++n) {
+            double Rr, Ri;
+            if (n == m) {
+                Rr = mmr;
+                Ri = mmi;
+            } else if (n == m + 1) {
+                Rr = z * p1r;
+                Ri = z * p1i;
+            } else {
+                const double c = 1.0 / (double)((n - m) * (n + m));
+                Rr = ((2.0 * n - 1.0) * z * p1r - r2 * p2r) * c;
+                Ri = ((2.0 * n - 1.0) * z * p1i - r2 * p2i) * c;
+            }
+            p2r = p1r;
+            p2i = p1i;
+            p1r = Rr;
+            p1i = Ri;
+            f(n, m, Rr, Ri);
+        }
+    }
+}
+template <int P, class F>
+__device__ __forceinline__ void harmonics_by_wave(int w, double x, double y, double z, F &&f)
+{
+    if (w == 0)
+        harmonics_of_wave<P, 0>(x, y, z, f);
+    else if (w == 1)
+        harmonics_of_wave<P, 1>(x, y, z, f);
+    else if (w == 2)
+        harmonics_of_wave<P, 2>(x, y, z, f);
+    else
+        harmonics_of_wave<P, 3>(x, y, z, f);
+}
+
+struct PointArgs {
+    const double *tpos;
+    const int64_t *start, *end;  // of a leaf's points in sorted order
+    const uint32_t *tkey;
+    const int32_t *leaves;  // the target leaves holding points
+    int64_t nleaf;          // their number
+    int64_t limit;          // points of the caller's order from here on are set elsewhere
+};
+
+__device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, double (&c)[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        c[a] = ((double)((int)compact3(key >> a) - g.shift[a]) + 0.5) * g.b;
+}
+
+// Forward: lanes are (point, model) pairs, points fastest; the four waves' sums
+// meet in LDS.  Where leaves hold few points (scattered ones), a workgroup of a
+// single-model plan takes LW leaves, so that its lanes are not mostly idle.
+// far: whether there is a far field (L >= 2).
+template <int P, int MG, int LW>
+__global__ void __launch_bounds__(256)
+k_l2p_points(DevGeom g, PointArgs ar, const uint32_t *perm, const double *le, const double *near, int far, double *out)
+{
+    static_assert(MG == 1 || LW == 1, "several leaves for several models");
+    constexpr int P2 = P * P, LS = P2 | 1, NS = MG * LW;
+    __shared__ double sL[NS * LS];
+    __shared__ double sum[4][4][64];
+    __shared__ double sc[LW][3];
+    __shared__ int64_t st[LW];
+    __shared__ int sn[LW + 1];  // first pair of each leaf
+    const DevLev &lv = g.lev[g.L];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bm0 = blockIdx.y * MG, nm = min(MG, g.B - bm0);
+    const int nl = (int)min((int64_t)LW, ar.nleaf - (int64_t)blockIdx.x * LW);
+    const int32_t *leaves = ar.leaves + (int64_t)blockIdx.x * LW;
+    const double inv_w = 1.0 / (double)g.b;
+    if (tid < nl) {
+        const int64_t leaf = leaves[tid];
+        double c[3];
+        leaf_centre(g, ar.tkey[lv.tbox_off + leaf], c);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            sc[tid][a] = c[a];
+        st[tid] = ar.start[leaf];
+        sn[tid + 1] = (int)(ar.end[leaf] - ar.start[leaf]);
+    }
+    if (far)
+        for (int i = tid; i < (LW == 1 ? nm : nl) * P2; i += 256) {
+            const int64_t leaf = leaves[LW == 1 ? 0 : i / P2];
+            sL[i / P2 * LS + i % P2] =
+                le[((lv.tgt_off + leaf) * g.B + bm0 + (LW == 1 ? i / P2 : 0)) * g.PS + i % P2];
+        }
+    __syncthreads();
+    if (tid == 0) {
+        sn[0] = 0;
+        for (int l = 0; l < nl; ++l)
+            sn[l + 1] += sn[l];
+    }
+    __syncthreads();
+    const int np = sn[nl];
+    for (int64_t u0 = 0; u0 < (int64_t)np * nm; u0 += 64) {
+        const int64_t u = min(u0 + lane, (int64_t)np * nm - 1);
+        const int mg = LW == 1 ? (int)(u / np) : 0;
+        int l = 0;
+        if constexpr (LW > 1)
+            for (int k = 1; k < nl; ++k)
+                l = u >= sn[k] ? k : l;
+        const int64_t i = st[l] + (u - (LW == 1 ? (int64_t)mg * np : sn[l]));
+        if (far) {
+            const double x = (ar.tpos[3 * i + 0] - sc[l][0]) * inv_w, y = (ar.tpos[3 * i + 1] - sc[l][1]) * inv_w,
+                         z = (ar.tpos[3 * i + 2] - sc[l][2]) * inv_w;
+            const CoefArray L{sL + (LW == 1 ? mg : l) * LS};
+            double phi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
+            // pairs R_n^m with the coefficients of l2p_eval_t
+            harmonics_by_wave<P>(w, x, y, z, [&](int n, int m, double Rr, double Ri) {
+                if (m == 0)
+                    phi += L.re(n, 0) * Rr;
+                else
+                    phi += 2.0 * (L.re(n, m) * Rr - L.im(n, m) * Ri);
+                if (n + 1 < P) {
+                    const int n1 = n + 1;
+                    if (m == 0) {
+                        gz += Rr * L.re(n1, 0);
+                        gx += Rr * L.re(n1, 1);
+                        gy -= Rr * L.im(n1, 1);
+                    } else {
+                        gz += 2.0 * (Rr * L.re(n1, m) - Ri * L.im(n1, m));
+                        gx += Rr * (L.re(n1, m + 1) - L.re(n1, m - 1)) - Ri * (L.im(n1, m + 1) - L.im(n1, m - 1));
+                        gy -= Rr * (L.im(n1, m + 1) + L.im(n1, m - 1)) + Ri * (L.re(n1, m + 1) + L.re(n1, m - 1));
+                    }
+                }
+            });
+            const double s = inv_w * inv_w;
+            sum[w][0][lane] = phi * inv_w;
+            sum[w][1][lane] = -gx * s;  // g = -grad phi
+            sum[w][2][lane] = -gy * s;
+            sum[w][3][lane] = -gz * s;
+        }
+        __syncthreads();
+        if (w == 0 && u0 + lane < (int64_t)np * nm) {
+            const int64_t dst = perm[i];
+            if (dst < ar.limit) {
+                const double *nr = near + (i * g.B + bm0 + mg) * 4;
+                double v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    v[k] = nr[k] + (far ? (sum[0][k][lane] + sum[1][k][lane]) + (sum[2][k][lane] + sum[3][k][lane]) : 0.0);
+                double *o = out + ((int64_t)(bm0 + mg) * g.M + dst) * g.C;
+                const double sg = g.G * g.h, sp = g.G * g.h * g.h;
+                if (g.C == 1) {
+                    o[0] = sg * v[3];
+                } else if (g.C == 3) {
+                    o[0] = sg * v[1];
+                    o[1] = sg * v[2];
+                    o[2] = sg * v[3];
+                } else {
+                    o[0] = sp * v[0];
+                    o[1] = sg * v[1];
+                    o[2] = sg * v[2];
+                    o[3] = sg * v[3];
+                }
+            }
+        }
+        __syncthreads();  // the sums have been read
+    }
+}
+
+// Transpose.  The adjoint LE of a leaf is the derivative, with respect to its
+// coefficients, of the sum over the leaf's points of a phi - (b1 gx + b2 gy +
+// b3 gz), with (a, b) the point's weights scaled as the combine scales the far
+// field (a = w0 / w, b = w_1..3 / w^2).  With the sums
+//   S_c[h] = sum over points of (a, b1, b2, b3)_c R_h(point)
+// coefficient (n, m) collects a R_n^m (x2 for m > 0) and the gradient terms of
+// degree n-1 and orders m-1, m, m+1, as the evaluation pairs them (d/dz R_n^m =
+// R_{n-1}^m, d/dx and d/dy from R_{n-1}^{m-1} and R_{n-1}^{m+1}).  S is a
+// product of the (component, model) weights and the points' harmonics, 16
+// points at a time on FP64 MFMA; points past the last weigh zero.
+template <int LS>
+__device__ __forceinline__ double l2pt_gather(const double *S, int CS, int n, int m, int part)
+{
+    auto h = [&](int c, int nn, int mm, int pp) -> double {
+        if (nn < 0 || mm > nn || (mm == 0 && pp == 1))
+            return 0.0;
+        return S[c * CS + harm_index(nn, mm, pp)];
+    };
+    const int q = n - 1;  // degree of the gradient terms
+    double v;
+    if (part == 0) {
+        v = (m == 0 ? 1.0 : 2.0) * h(0, n, m, 0);
+        if (q >= 0) {
+            if (m == 0) {
+                v += -h(3, q, 0, 0) + h(1, q, 1, 0) + h(2, q, 1, 1);
+            } else {
+                v += -2.0 * h(3, q, m, 0);
+                if (m == 1)
+                    v -= h(1, q, 0, 0);
+                else
+                    v += h(2, q, m - 1, 1) - h(1, q, m - 1, 0);
+                v += h(1, q, m + 1, 0) + h(2, q, m + 1, 1);
+            }
+        }
+    } else {
+        v = -2.0 * h(0, n, m, 1);
+        if (q >= 0) {
+            v += 2.0 * h(3, q, m, 1);
+            if (m == 1)
+                v += h(2, q, 0, 0);
+            else
+                v += h(1, q, m - 1, 1) + h(2, q, m - 1, 0);
+            v += h(2, q, m + 1, 0) - h(1, q, m + 1, 1);
+        }
+    }
+    return v;
+}
+
+template <int P, int MG>
+__global__ void __launch_bounds__(256)
+k_t_l2p_points(DevGeom g, PointArgs ar, const double *w, double *le)
+{
+    using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
+    constexpr int P2 = P * P, RB = (P2 + 15) / 16, PS = 16 * RB, HS = PS + 1;
+    constexpr int NR = (4 * MG + 15) / 16, NH = (RB + 3) / 4;  // row blocks; column blocks per wave
+    constexpr int kS = 16 * NR * HS, kH = 16 * HS;
+    __shared__ double sh[kS > kH ? kS : kH];  // harmonics [16][HS], then the sums [4][MG][HS]
+    __shared__ double sw[16 * NR][17];        // weights [component][model][point]
+    const DevLev &lv = g.lev[g.L];
+    const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t leaf = ar.leaves[blockIdx.x];
+    const int bm0 = blockIdx.y * MG;
+    const int64_t ts = ar.start[leaf], te = ar.end[leaf];
+    double c[3];
+    leaf_centre(g, ar.tkey[lv.tbox_off + leaf], c);
+    const double inv_w = 1.0 / (double)g.b, inv_w2 = inv_w * inv_w;
+    vec4 acc[NR][NH];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+            acc[r][j] = vec4{0, 0, 0, 0};
+    // (the columns past the coefficients are never read)
+    for (int64_t j0 = ts; j0 < te; j0 += 16) {
+        for (int i = tid; i < 16 * NR * 16; i += 256) {
+            const int t = i / (16 * NR), row = i % (16 * NR), mg = row / 4, k = row % 4;
+            const bool ok = j0 + t < te && mg < MG && bm0 + mg < g.B;
+            const double v = ok ? w[((j0 + t) * g.B + bm0 + mg) * 4 + k] : 0.0;
+            if (row < 4 * MG)
+                sw[k * MG + mg][t] = v * (k == 0 ? inv_w : inv_w2);
+            else
+                sw[row][t] = 0.0;
+        }
+        if (lane < 16) {
+            const int64_t j = min(j0 + lane, te - 1);
+            harmonics_by_wave<P>(wv, (ar.tpos[3 * j + 0] - c[0]) * inv_w, (ar.tpos[3 * j + 1] - c[1]) * inv_w,
+                                 (ar.tpos[3 * j + 2] - c[2]) * inv_w, [&](int n, int m, double Rr, double Ri) {
+                                     sh[lane * HS + (m == 0 ? n * n : n * n + 2 * m - 1)] = Rr;
+                                     if (m > 0)
+                                         sh[lane * HS + n * n + 2 * m] = Ri;
+                                 });
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            double a[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                a[r] = sw[16 * r + (lane & 15)][4 * ks + kr];
+#pragma unroll
+            for (int j = 0; j < NH; ++j) {
+                const int hb = min(wv + 4 * j, RB - 1);
+                const double b = sh[(4 * ks + kr) * HS + 16 * hb + (lane & 15)];
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    acc[r][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b, acc[r][j], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < NH; ++j)
+        if (wv + 4 * j < RB)
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    sh[(16 * r + kr + 4 * i) * HS + 16 * (wv + 4 * j) + (lane & 15)] = acc[r][j][i];
+    __syncthreads();
+    for (int i = tid; i < MG * PS; i += 256) {
+        const int mg = i / PS, k = i % PS, bm = bm0 + mg;
+        if (bm >= g.B)
+            break;
+        double v = 0.0;  // padding coefficients stay zero
+        if (k < P2) {
+            const int n = (int)sqrtf((float)k + 0.5f), r = k - n * n;
+            v = l2pt_gather<HS>(sh + mg * HS, MG * HS, n, (r + 1) / 2, (r > 0 && (r & 1) == 0) ? 1 : 0);
+        }
+        le[((lv.tgt_off + leaf) * g.B + bm) * PS + k] = v;
+    }
+}
+
+int64_t point_count(const Plan *p) { return p->lat_near ? p->d.n_points : p->M; }
+
+PointArgs point_args(const Plan *p)
+{
+    return PointArgs{p->d_tpos, p->d_leaf_start, p->d_leaf_pend, p->d_tkey, p->d_user_leaves,
+                     p->n_user_leaves, point_count(p)};
+}
+
+}  // namespace
+
+#define GRAV_ORDERS(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+
+grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s)
+{
+    // 65536 random points, two per leaf, p = 10: 122 us a leaf at a time,
+    // 68 us with 16
+    const bool few = p->B == 1 && point_count(p) < 8 * p->n_user_leaves;
+    const int MG = p->B == 1 ? 1 : kPointModels, LW = few ? 16 : 1;
+    const dim3 grid((unsigned)((p->n_user_leaves + LW - 1) / LW), (unsigned)((p->B + MG - 1) / MG));
+    if (grid.x == 0)
+        return GRAV_OK;
+#define L2P_LAUNCH(P, MG, LW)                                                                                    \
+    hipLaunchKernelGGL((k_l2p_points<P, MG, LW>), grid, dim3(256), 0, s, g, point_args(p),                       \
+                       (const uint32_t *)p->d_perm, (const double *)p->d_le, (const double *)p->d_near,          \
+                       p->L >= 2 ? 1 : 0, out)
+#define L2P_CASE(P)                                                                                              \
+    case P:                                                                                                      \
+        if (few)                                                                                                 \
+            L2P_LAUNCH(P, 1, 16);                                                                                \
+        else if (p->B == 1)                                                                                      \
+            L2P_LAUNCH(P, 1, 1);                                                                                 \
+        else                                                                                                     \
+            L2P_LAUNCH(P, kPointModels, 1);                                                                      \
+        break;
+    switch (p->P) {
+        GRAV_ORDERS(L2P_CASE)
+    default:
+        return GRAV_EUNSUPPORTED;
+    }
+#undef L2P_CASE
+#undef L2P_LAUNCH
+    GRAV_HIP(hipGetLastError());
+    return GRAV_OK;
+}
+
+grav_status launch_t_l2p_points(const Plan *p, const DevGeom &g, hipStream_t s)
+{
+    const int MG = p->B == 1 ? 1 : kPointModels;
+    const dim3 grid((unsigned)p->n_user_leaves, (unsigned)((p->B + MG - 1) / MG));
+    if (grid.x == 0)
+        return GRAV_OK;
+#define T_L2P_CASE(P)                                                                                            \
+    case P:                                                                                                      \
+        if (MG == 1)                                                                                             \
+            hipLaunchKernelGGL((k_t_l2p_points<P, 1>), grid, dim3(256), 0, s, g, point_args(p),                  \
+                               (const double *)p->d_near, p->d_le);                                              \
+        else                                                                                                     \
+            hipLaunchKernelGGL((k_t_l2p_points<P, kPointModels>), grid, dim3(256), 0, s, g, point_args(p),       \
+                               (const double *)p->d_near, p->d_le);                                              \
+        break;
+    switch (p->P) {
+        GRAV_ORDERS(T_L2P_CASE)
+    default:
+        return GRAV_EUNSUPPORTED;
+    }
+#undef T_L2P_CASE
+    GRAV_HIP(hipGetLastError());
+    return GRAV_OK;
+}
+
+}  // namespace grav
