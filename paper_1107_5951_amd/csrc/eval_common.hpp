@@ -37,6 +37,7 @@ grav_status launch_octet_up(const Plan *p, const OctPlan &o, int l, hipStream_t 
 grav_status launch_octet_down(const Plan *p, const OctPlan &o, int l, hipStream_t s, const double *A, double *x);
 grav_status launch_p2m(const Plan *p, const DevGeom &g, const double *rho, hipStream_t s);
 grav_status launch_t_p2m(const Plan *p, const DevGeom &g, double *drho, hipStream_t s);
+grav_status launch_p2m_src(const Plan *p, const DevGeom &g, hipStream_t s);
 grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s);
 grav_status launch_t_l2p_points(const Plan *p, const DevGeom &g, hipStream_t s);
 grav_status launch_near_par(const Plan *p, const DevGeom &g, const double *rho, double *out, hipStream_t s);

@@ -109,6 +109,7 @@ struct Plan {
     double *d_spos = nullptr;      // [n_spts][3]
     double *d_sw = nullptr;        // [n_spts]
     uint32_t *d_sperm = nullptr;   // [n_spts]
+    double *d_smass = nullptr;     // [B][n_spts] masses of the call's input, sorted
     int64_t *d_sstart = nullptr;   // [leaves of the leaf-level source block + 1]
     uint32_t *d_perm = nullptr;    // [M] sorted position -> user index
     double *d_tpos = nullptr;      // [M][3] sorted target positions

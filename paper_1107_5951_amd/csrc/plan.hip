@@ -273,7 +273,7 @@ void free_plan(Plan *p)
                     p->d_tn64, p->d_tn32, p->d_rho_blk, p->d_tl2p, p->d_dpart,
                     p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
                     p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
-                    p->d_spos, p->d_sw, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
+                    p->d_spos, p->d_sw, p->d_smass, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
                     p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_coef};
     for (OctPlan *o : {&p->m2l, &p->m2lt}) {
         void *ob[] = {o->d_key, o->d_child, o->d_parent, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
@@ -1454,6 +1454,7 @@ grav_status build_sources(Plan *p, const grav_plan_desc *desc, hipStream_t s)
     do {
         if ((st = dalloc(p, &p->d_spos, 3 * n, true)) != GRAV_OK || (st = dalloc(p, &p->d_sw, n, true)) != GRAV_OK ||
             (st = dalloc(p, &p->d_sperm, n, true)) != GRAV_OK ||
+            (st = dalloc(p, &p->d_smass, n * p->B, false)) != GRAV_OK ||
             (st = dalloc(p, &p->d_sstart, nleaf + 1, true)) != GRAV_OK)
             break;
         if (hipMemcpyAsync(src, desc->sources, sizeof(double) * 3 * n, hipMemcpyHostToDevice, s) != hipSuccess ||

@@ -342,6 +342,78 @@ k_t_l2p_points(DevGeom g, PointArgs ar, const double *w, double *le)
     }
 }
 
+// --------------------------------------------------------------------------
+// P2M of explicit sources: the expansion of a leaf is the sum over its sources
+// of the mass times the multipole basis at the source (the lattice P2M's basis:
+// R_n^0, Re R_n^m, -Im R_n^m at u = (x - centre) / b).  One workgroup per (leaf
+// of the source block, MG models); a lane per source of a chunk forms the
+// harmonics of its wave's orders, [coefficient][source] in LDS, and every
+// thread adds the products of the (model, coefficient) sums it owns in source
+// order (deterministic).  2.1 M sources, 64 a leaf, p = 10: 0.55 -> 0.20 ms.
+// --------------------------------------------------------------------------
+template <int P, int MG>
+__global__ void __launch_bounds__(256)
+k_p2m_src(DevGeom g, const double *spos, const double *mass, const int64_t *sstart, int64_t nsrc, double *me)
+{
+    constexpr int P2 = P * P, PS = (P2 + 15) / 16 * 16;
+    constexpr int TC = P <= 11 ? 64 : 32, TS = TC + 1;  // sources per chunk
+    constexpr int NJ = (MG * P2 + 255) / 256;           // sums per thread, o = model P2 + coefficient
+    __shared__ double H[P2 * TS], W[MG * TC];
+    const int64_t leaf = blockIdx.x;
+    const int bm0 = blockIdx.y * MG;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const DevLev &lv = g.lev[g.L];
+    const int lx = (int)(leaf % lv.ns[0]), ly = (int)((leaf / lv.ns[0]) % lv.ns[1]),
+              lz = (int)(leaf / ((int64_t)lv.ns[0] * lv.ns[1]));
+    const double inv_b = 1.0 / (double)g.b;
+    const double centre[3] = {(lx + 0.5) * g.b, (ly + 0.5) * g.b, (lz + 0.5) * g.b};
+    const int64_t ts = sstart[leaf], te = sstart[leaf + 1];
+    double acc[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+        acc[j] = 0.0;
+    for (int64_t j0 = ts; j0 < te; j0 += TC) {
+        const int nt = (int)min((int64_t)TC, te - j0);
+        for (int i = tid; i < nt * MG; i += 256) {
+            const int t = i % nt, bm = bm0 + i / nt;
+            W[i / nt * TC + t] = bm < g.B ? mass[(int64_t)bm * nsrc + j0 + t] : 0.0;
+        }
+        if (lane < nt) {
+            const int64_t i = j0 + lane;
+            harmonics_by_wave<P>(w, (spos[3 * i + 0] - centre[0]) * inv_b, (spos[3 * i + 1] - centre[1]) * inv_b,
+                                 (spos[3 * i + 2] - centre[2]) * inv_b, [&](int n, int m, double Rr, double Ri) {
+                                     H[(m == 0 ? n * n : n * n + 2 * m - 1) * TS + lane] = Rr;
+                                     if (m > 0)
+                                         H[(n * n + 2 * m) * TS + lane] = -Ri;  // the conjugate harmonic
+                                 });
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int o = min(tid + 256 * j, MG * P2 - 1);
+            const double *h = H + o % P2 * TS, *m = W + o / P2 * TC;
+            double v = acc[j];
+            for (int t = 0; t < nt; ++t)
+                v += h[t] * m[t];
+            acc[j] = v;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int o = tid + 256 * j, bm = bm0 + o / P2;
+        if (o < MG * P2 && bm < g.B)
+            me[((lv.me_off + leaf) * g.B + bm) * PS + o % P2] = acc[j];
+    }
+    if constexpr (PS > P2)
+        for (int i = tid; i < MG * (PS - P2); i += 256) {
+            const int bm = bm0 + i / (PS - P2);
+            if (bm < g.B)
+                me[((lv.me_off + leaf) * g.B + bm) * PS + P2 + i % (PS - P2)] = 0.0;
+        }
+}
+
 int64_t point_count(const Plan *p) { return p->lat_near ? p->d.n_points : p->M; }
 
 PointArgs point_args(const Plan *p)
@@ -384,6 +456,30 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
     }
 #undef L2P_CASE
 #undef L2P_LAUNCH
+    GRAV_HIP(hipGetLastError());
+    return GRAV_OK;
+}
+
+grav_status launch_p2m_src(const Plan *p, const DevGeom &g, hipStream_t s)
+{
+    constexpr int kModels = 4;
+    const int MG = p->B == 1 ? 1 : kModels;
+    const dim3 grid((unsigned)p->lev[p->L].n_src, (unsigned)((p->B + MG - 1) / MG));
+#define P2M_CASE(P)                                                                                              \
+    case P:                                                                                                      \
+        if (MG == 1)                                                                                             \
+            hipLaunchKernelGGL((k_p2m_src<P, 1>), grid, dim3(256), 0, s, g, (const double *)p->d_spos,           \
+                               (const double *)p->d_smass, (const int64_t *)p->d_sstart, p->n_spts, p->d_me);    \
+        else                                                                                                     \
+            hipLaunchKernelGGL((k_p2m_src<P, kModels>), grid, dim3(256), 0, s, g, (const double *)p->d_spos,     \
+                               (const double *)p->d_smass, (const int64_t *)p->d_sstart, p->n_spts, p->d_me);    \
+        break;
+    switch (p->P) {
+        GRAV_ORDERS(P2M_CASE)
+    default:
+        return GRAV_EUNSUPPORTED;
+    }
+#undef P2M_CASE
     GRAV_HIP(hipGetLastError());
     return GRAV_OK;
 }
