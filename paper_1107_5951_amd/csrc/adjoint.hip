@@ -658,7 +658,8 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
         if (p->n_leaf > 0 && pts)
             GRAV_CHECK(launch_t_l2p_points(p, g, s));
         if (p->lat_near)
-            GRAV_CHECK(launch_t_l2p_lat(p, g, resid, pts ? 1 : 0, s));
+            GRAV_CHECK(p->near_par ? launch_t_l2p_par(p, g, resid, pts ? 1 : 0, s)
+                                   : launch_t_l2p_lat(p, g, resid, pts ? 1 : 0, s));
         stage_end(p, s);
         stage_begin(p, "l2lT", s);
         for (int l = L; l >= 3; --l)

@@ -41,6 +41,7 @@ grav_status launch_p2m_src(const Plan *p, const DevGeom &g, hipStream_t s);
 grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s);
 grav_status launch_t_l2p_points(const Plan *p, const DevGeom &g, hipStream_t s);
 grav_status launch_near_par(const Plan *p, const DevGeom &g, const double *rho, double *out, hipStream_t s);
+grav_status launch_t_l2p_par(const Plan *p, const DevGeom &g, const double *resid, int add, hipStream_t s);
 grav_status launch_t_near_par(const Plan *p, const DevGeom &g, const double *resid, int add, double *drho, hipStream_t s);
 OctInfo octet_info(int P, bool f64);
 grav_status m2l_resident_workgroups(const Plan *p, int nc, int *workers);

@@ -137,7 +137,7 @@ struct Plan {
     // the base centres and its coefficients by class
     bool near_par = false;
     void *d_near_op = nullptr, *d_near_opt = nullptr;
-    double *d_near_far = nullptr;
+    double *d_near_far = nullptr, *d_near_fart = nullptr;  // and its transpose
     int32_t *d_near_coef = nullptr;
     int near_KC = 0;                               // k steps of a class
     double *d_tl2p = nullptr;                      // [PS/16][RB][64][4] far field (L2P) at the cell centres, FP64

@@ -274,7 +274,7 @@ void free_plan(Plan *p)
                     p->d_lat_tab, p->d_cell_slot, p->d_leaf_pend,
                     p->d_tnt64, p->d_tnt32, p->d_tl2pt, p->d_w_blk,
                     p->d_spos, p->d_sw, p->d_smass, p->d_sperm, p->d_sstart, p->d_pt_leaves, p->d_user_leaves,
-                    p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_coef};
+                    p->d_near_op, p->d_near_opt, p->d_near_far, p->d_near_fart, p->d_near_coef};
     for (OctPlan *o : {&p->m2l, &p->m2lt}) {
         void *ob[] = {o->d_key, o->d_child, o->d_parent, o->d_segs, o->d_wgseg, o->d_uslot, o->d_groups,
                       o->d_ops};
@@ -1117,7 +1117,20 @@ static grav_status build_near_far(Plan *p, const std::vector<double> &full)
             }
         }
     GRAV_CHECK(upload(p, &p->d_near_coef, coef));
-    return upload(p, &p->d_near_far, lm);
+    GRAV_CHECK(upload(p, &p->d_near_far, lm));
+    // its transpose: [parity][k step][row block of the class][lane], row =
+    // coefficient 16 rb + lane % 16 of the class, column R = 4 ks + lane / 16
+    const int RBC = (int)ceil_div((int64_t)KC * 4, 16);
+    std::vector<double> lt((size_t)8 * 2 * C * RBC * 64, 0.0);
+    for (int x = 0; x < 8; ++x)
+        for (size_t n = 0; n < cls[x].size(); ++n)
+            for (int R = 0; R < 8 * C; ++R) {
+                const int t = R % 8, comp = R / 8 + 4 - C;
+                const int tc = (2 + (t & 1)) + 4 * (2 + (t >> 1 & 1)) + 16 * (2 + (t >> 2));
+                lt[((size_t)(x * 2 * C + R / 4) * RBC + n / 16) * 64 + 16 * (R % 4) + n % 16] =
+                    full[(size_t)(4 * tc + comp) * PS + cls[x][n]];
+            }
+    return upload(p, &p->d_near_fart, lt);
 }
 
 // Near field of voxel-centre targets as 27 dense lattice matrices (leaf
@@ -1296,19 +1309,19 @@ grav_status build_near_lattice(Plan *p, hipStream_t s)
                                 t < b3 ? full[(size_t)(4 * t + comp) * PS + c] : 0.0;
                         }
             GRAV_CHECK(upload(p, &p->d_tl2p, lsw));
+            // its transpose for the adjoint: rows = coefficients (QL blocks),
+            // contraction over (t, component) as the transposed near field
+            std::vector<double> lst((size_t)TQ * QL * 256, 0.0);
+            for (int q = 0; q < TQ; ++q)
+                for (int rb = 0; rb < QL; ++rb)
+                    for (int lane = 0; lane < 64; ++lane)
+                        for (int u = 0; u < 4; ++u) {
+                            const int t = (lane >> 4) * TQ + q, c = 16 * rb + (lane & 15);
+                            lst[((size_t)q * QL + rb) * 256 + frag_pos(lane, u, 2)] =
+                                t < b3 ? full[(size_t)(4 * t + u) * PS + c] : 0.0;
+                        }
+            GRAV_CHECK(upload(p, &p->d_tl2pt, lst));
         }
-        // its transpose for the adjoint: rows = coefficients (QL blocks),
-        // contraction over (t, component) as the transposed near field
-        std::vector<double> lst((size_t)TQ * QL * 256, 0.0);
-        for (int q = 0; q < TQ; ++q)
-            for (int rb = 0; rb < QL; ++rb)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int u = 0; u < 4; ++u) {
-                        const int t = (lane >> 4) * TQ + q, c = 16 * rb + (lane & 15);
-                        lst[((size_t)q * QL + rb) * 256 + frag_pos(lane, u, 2)] =
-                            t < b3 ? full[(size_t)(4 * t + u) * PS + c] : 0.0;
-                    }
-        GRAV_CHECK(upload(p, &p->d_tl2pt, lst));
     }
     GRAV_HIP(hipStreamSynchronize(s));
     return GRAV_OK;
