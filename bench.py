@@ -208,7 +208,10 @@ def roofline(plan, stages, p, prec, profile):
     mm = "fp64_mfma" if f64 else "fp32_mfma"
     cand = {
         "m2l": (2.0 * p ** 4 * M2L_OPS_PER_PAIR * m2l_pairs * B, m2l_label(p, prec), "mfma", mm, "TFLOP/s"),
-        "near_lat": (27 * 2.0 * (plan.spec.components * b ** 3) * b ** 3 * n_leaf_src * B,
+        "near_lat": (8 * 2.0 * 8 * plan.spec.components * 216 * n_leaf_src * B,
+                     "k_near_par (near field by parity, %s MFMA 16x16x4)" % ("FP64" if f64 else "FP32"), "mfma", mm,
+                     "TFLOP/s") if b == 4 else
+                    (27 * 2.0 * (plan.spec.components * b ** 3) * b ** 3 * n_leaf_src * B,
                      "k_near_lat<%d,2,%s> (lattice near field, %s MFMA 16x16x4)"
                      % ((2, "double", "FP64") if f64 else (4, "float", "FP32")), "mfma", mm, "TFLOP/s"),
         # by parity: each coefficient row once per parent, not per child
@@ -216,7 +219,8 @@ def roofline(plan, stages, p, prec, profile):
                 "mfma", "fp64_mfma", "TFLOP/s"),
         # the leaf's cells times the lattice P2M matrix (p^2 x b^3, FP64), and an
         # octet's parity sums times its parent's
-        "p2m": (2.0 * p * p * b ** 3 * (n_leaf_src + n_leaf_src / 8) * B, "k_p2m_octet<%d> (P2M, FP64 MFMA 16x16x4)" % p,
+        # (leaves count where every one is read: volume targets)
+        "p2m": (2.0 * p * p * b ** 3 * (n_leaf_src * bool(plan.spec.voxel_centres) + n_leaf_src / 8) * B, "k_p2m_octet<%d> (P2M, FP64 MFMA 16x16x4)" % p,
                 "mfma", "fp64_mfma", "TFLOP/s"),
     }
     if "near_lat" not in stages:

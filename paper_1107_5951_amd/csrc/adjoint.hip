@@ -15,11 +15,10 @@
 // with the same operators (the FP32-rounded M2L matrices in mixed
 // precision), the same interaction lists and the same point pairs and
 // coincidence rule as the forward pass, so <A rho, r> = <rho, A^T r> holds to
-// rounding.  Every kernel computes one output element per thread by a plain
-// loop over its inputs, read from global memory: no atomics, no LDS, no
-// cross-lane operations, and a fixed summation order, so results are
+// rounding.  The far field's stages are the octet kernels with transposed
+// operators; every sum has a fixed order (no atomics), so results are
 // deterministic.  Every index that comes from a plan table is checked against
-// the size of the array it addresses before it is used.
+// the size of the array it addresses, here or when the plan is checked.
 #include <algorithm>
 
 #include "harmonics.hpp"
