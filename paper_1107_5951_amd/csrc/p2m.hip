@@ -10,12 +10,12 @@
 // transpose takes the leaf level's M2L slots as they are, by parity:
 //   drho_r[v] = sum_chi (-1)^(chi.r) (sum_k Pm[v][k] G_chi[k] + sum_{i of class chi} T[i][v] Y[i]).
 //
-// What bounds them: far from the stations the densities (read or written once)
-// and, with blocks this short, the latency of a workgroup's start; where the
-// leaves count, also the FP64 matrix instructions of Pm.  p = 10, leaf 4^3, from
+// What bounds them: far from the stations the densities (read or written once),
+// a workgroup's phases one after the other; where the leaves count, also the
+// FP64 matrix instructions of Pm.  p = 10, leaf 4^3, from
 // the densities to the level above the leaves and back, M2M and FP32 rows
-// included: 32 models of 128^3 cells under stations 0.85 -> 0.20 ms (2.7 TB/s
-// of densities) and 0.79 -> 0.25 ms; 256^3 cells with all leaves 0.27 -> 0.14 ms
+// included: 32 models of 128^3 cells under stations 0.85 -> 0.19 ms (2.8 TB/s
+// of densities) and 0.79 -> 0.22 ms; 256^3 cells with all leaves 0.27 -> 0.14 ms
 // and 0.29 -> 0.16 ms.
 #include <algorithm>
 
@@ -285,7 +285,7 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
 {
     using C = ClassShape<P>;
     using vec4 = __attribute__((__vector_size__(4 * sizeof(double)))) double;
-    constexpr int PS = OctShape<P, T>::PS, RB = PS / 16, XP = PS + 1, KC = C::KC, GP = 17, NV = 16 * NRB;
+    constexpr int PS = OctShape<P, T>::PS, RB = PS / 16, XP = PS + 1, KC = C::KC, GP = 17, NV = 32;
     constexpr int NX = 8 / OctShape<P, T>::RS, RS = OctShape<P, T>::RS;
     constexpr int kX = 16 * XP, kG = 8 * NV * GP, kA = 4 * NRB * 64, NA = kA / 512;
     static_assert(2 * kA <= kG, "operator chunks do not fit");
@@ -407,42 +407,48 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
                     acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[(u * NRB + r) * 64 + lane], b[u], acc[r], 0, 0, 0);
         }
     }
-    __syncthreads();  // LDS has been read
-#pragma unroll
-    for (int r = 0; r < NRB; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            sm[(chi * NV + 16 * r + kr + 4 * i) * GP + (lane & 15)] = acc[r][i];
-    __syncthreads();
+    // two row blocks at a time (35 KB: three workgroups per CU; all four at once
+    // left room for two, and the stores, half of the time, waited: 0.225 ms against
+    // 0.207 far from the stations); a thread takes the four images of a cell on
+    // one side of the x plane
     double *db = drho + (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
-    // a thread takes the four images of a cell on one side of the x plane
 #pragma unroll
-    for (int n = 0; n < 32 * NV / 512; ++n) {
-        const int e = tid + 512 * n, rx = e >> 2 & 1, f = (e & 3) | (e >> 1 & ~3), vi = f % NV, c = f / NV;
-        const int v = part * NV + vi;
-        double h[4];
+    for (int r0 = 0; r0 < NRB; r0 += 2) {
+        __syncthreads();  // LDS has been read
 #pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const double x0 = sm[(2 * y * NV + vi) * GP + c], x1 = sm[((2 * y + 1) * NV + vi) * GP + c];
-            h[y] = rx ? x0 - x1 : x0 + x1;
-        }
+        for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int bit = 1; bit < 4; bit <<= 1)
+            for (int i = 0; i < 4; ++i)
+                sm[(chi * NV + 16 * r + kr + 4 * i) * GP + (lane & 15)] = acc[r0 + r][i];
+        __syncthreads();
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if ((r & bit) == 0) {
-                    const double x = h[r], y = h[r | bit];
-                    h[r] = x + y;
-                    h[r | bit] = x - y;
-                }
-        const Centre ct = sctr[c];
-        const CellEntry ce = cell[min(v, b3 - 1)];
-        if (v < b3 && oct0 + c < ar.noct && image_in(g, ct, ce, 0, rx)) {
-            double *d = db + ct.at + image_off(g, ce, 0, rx);
+        for (int n = 0; n < 32 * NV / 512; ++n) {
+            const int e = tid + 512 * n, rx = e >> 2 & 1, f = (e & 3) | (e >> 1 & ~3), vi = f % NV, c = f / NV;
+            const int v = part * 16 * NRB + 16 * r0 + vi;
+            double h[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (image_in(g, ct, ce, 1, r & 1) & image_in(g, ct, ce, 2, r >> 1))
-                    d[image_off(g, ce, 1, r & 1) + image_off(g, ce, 2, r >> 1)] = h[r];
+            for (int y = 0; y < 4; ++y) {
+                const double x0 = sm[(2 * y * NV + vi) * GP + c], x1 = sm[((2 * y + 1) * NV + vi) * GP + c];
+                h[y] = rx ? x0 - x1 : x0 + x1;
+            }
+#pragma unroll
+            for (int bit = 1; bit < 4; bit <<= 1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((r & bit) == 0) {
+                        const double x = h[r], y = h[r | bit];
+                        h[r] = x + y;
+                        h[r | bit] = x - y;
+                    }
+            const Centre ct = sctr[c];
+            const CellEntry ce = cell[min(v, b3 - 1)];
+            if (v < b3 && oct0 + c < ar.noct && image_in(g, ct, ce, 0, rx)) {
+                double *d = db + ct.at + image_off(g, ce, 0, rx);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (image_in(g, ct, ce, 1, r & 1) & image_in(g, ct, ce, 2, r >> 1))
+                        d[image_off(g, ce, 1, r & 1) + image_off(g, ce, 2, r >> 1)] = h[r];
+            }
         }
     }
 }

@@ -866,6 +866,15 @@ static grav_status build_m2l(Plan *p)
         std::sort(oct.begin(), oct.end());
         const OctLev sl{{lv.s0[0], lv.s0[1], lv.s0[2]}, {lv.ns[0], lv.ns[1], lv.ns[2]}, 0};
         const size_t near = std::lower_bound(oct.begin(), oct.end(), (uint64_t)1 << 32) - oct.begin();
+        // no M2L shares the others' neighbours: x fastest, so that the P2M's blocks
+        // of 16 octets read and write long rows of the mesh
+        std::sort(oct.begin() + near, oct.end(), [](uint64_t a, uint64_t b) {
+            const uint32_t ka = (uint32_t)a, kb = (uint32_t)b;
+            for (int s = 2; s >= 0; --s)
+                if (compact3(ka >> s) != compact3(kb >> s))
+                    return compact3(ka >> s) < compact3(kb >> s);
+            return false;
+        });
         for (size_t i = 0; i <= oct.size(); ++i) {
             if (i == near)
                 to.reached(l);

@@ -114,9 +114,10 @@ k_l2p_points(DevGeom g, PointArgs ar, const uint32_t *perm, const double *le, co
     const DevLev &lv = g.lev[g.L];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int bm0 = blockIdx.y * MG, nm = min(MG, g.B - bm0);
-    const int nl = (int)min((int64_t)LW, ar.nleaf - (int64_t)blockIdx.x * LW);
-    const int32_t *leaves = ar.leaves + (int64_t)blockIdx.x * LW;
+    const uint32_t nblk = (uint32_t)((ar.nleaf + LW - 1) / LW), lb = blockIdx.x % nblk;
+    const int bm0 = (int)(blockIdx.x / nblk) * MG, nm = min(MG, g.B - bm0);
+    const int nl = (int)min((int64_t)LW, ar.nleaf - (int64_t)lb * LW);
+    const int32_t *leaves = ar.leaves + (int64_t)lb * LW;
     const double inv_w = 1.0 / (double)g.b;
     if (tid < nl) {
         const int64_t leaf = leaves[tid];
@@ -433,9 +434,12 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
     // 68 us with 16
     const bool few = p->B == 1 && point_count(p) < 8 * p->n_user_leaves;
     const int MG = p->B == 1 ? 1 : kPointModels, LW = few ? 16 : 1;
-    const dim3 grid((unsigned)((p->n_user_leaves + LW - 1) / LW), (unsigned)((p->B + MG - 1) / MG));
-    if (grid.x == 0)
+    const int64_t n = (p->n_user_leaves + LW - 1) / LW * ((p->B + MG - 1) / MG);
+    if (n > 0x7fffffffll)
+        return GRAV_EUNSUPPORTED;
+    if (n == 0)
         return GRAV_OK;
+    const dim3 grid((unsigned)n);
 #define L2P_LAUNCH(P, MG, LW)                                                                                    \
     hipLaunchKernelGGL((k_l2p_points<P, MG, LW>), grid, dim3(256), 0, s, g, point_args(p),                       \
                        (const uint32_t *)p->d_perm, (const double *)p->d_le, (const double *)p->d_near,          \
