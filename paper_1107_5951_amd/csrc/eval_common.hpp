@@ -27,6 +27,17 @@ struct DevGeom {
 };
 
 DevGeom make_geom(const Plan *p);
+
+// Grids of n workgroups, a second dimension from 2^22 on: a dimension of a
+// launch holds at most 2^32 - 1 work-items, and these have up to 512 a
+// workgroup.  block_id() runs past n in the last row.
+inline dim3 block_grid(int64_t n)
+{
+    const int64_t rows = (n + (1 << 22) - 1) >> 22;
+    return dim3((unsigned)((n + rows - 1) / rows), (unsigned)rows);
+}
+__device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 struct OctGeom;
 // The M2L of one direction on `in` ([row][model][PS], the element type of
 // the plan's M2L) into the segment slots.

@@ -76,6 +76,12 @@ struct OctInfo {
     bool tail4;
 };
 
+// Points start .. start + n - 1 (sorted order) of a target leaf.
+struct PointRun {
+    int64_t start;
+    int32_t leaf, n;
+};
+
 struct Stage {
     std::string name;
     hipEvent_t a = nullptr, b = nullptr;
@@ -159,6 +165,8 @@ struct Plan {
     int64_t n_pt_leaves = 0;                       // (any order), for the adjoint's point near field
     int32_t *d_user_leaves = nullptr;              // target leaves holding user points (any order), for
     int64_t n_user_leaves = 0;                     // the point near field
+    PointRun *d_runs = nullptr;                    // their points in runs (any order), for the L2P
+    int64_t n_runs = 0;
     int32_t *d_class_off = nullptr;  // [8][189][4] (dx, dy, dz, offset id)
     int32_t *d_tmap = nullptr;       // per level: target-box index over source block + halo 3
     struct DevGeom *d_geom = nullptr;

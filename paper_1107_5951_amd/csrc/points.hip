@@ -1,6 +1,6 @@
 // L2P at user points (and at every target of plans without lattice matrices)
-// with the combine, and the transpose: one workgroup per target leaf that holds
-// such points and group of models.
+// with the combine, and the transpose: one workgroup per run of points of a
+// target leaf (transposed: per leaf) and group of models.
 //
 // What bounds them: the chain of the harmonics' recurrences and the arithmetic
 // in FP64.  The order is a template parameter, so the recurrences' reciprocals
@@ -85,8 +85,13 @@ struct PointArgs {
     const int64_t *start, *end;  // of a leaf's points in sorted order
     const uint32_t *tkey;
     const int32_t *leaves;  // the target leaves holding points
-    int64_t nleaf;          // their number
     int64_t limit;          // points of the caller's order from here on are set elsewhere
+};
+
+// The forward's workgroups: nblk blocks of runs per group of models.
+struct RunArgs {
+    const PointRun *runs;
+    int64_t n, nblk, groups;
 };
 
 __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, double (&c)[3])
@@ -97,12 +102,16 @@ __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, doub
 }
 
 // Forward: lanes are (point, model) pairs, points fastest; the four waves' sums
-// meet in LDS.  Where leaves hold few points (scattered ones), a workgroup of a
-// single-model plan takes LW leaves, so that its lanes are not mostly idle.
+// meet in LDS.  A workgroup takes a run of a leaf's points (a workgroup per leaf
+// walked all of them: 1024^2 stations above 16^3 cells are 16 leaves of 65536
+// points, 2.20 ms a leaf at a time, 0.07 ms in runs; a thread per point took
+// 0.14).  Where leaves hold few points (scattered ones), a workgroup of a
+// single-model plan takes LW runs, so that its lanes are not mostly idle.
 // far: whether there is a far field (L >= 2).
 template <int P, int MG, int LW>
 __global__ void __launch_bounds__(256)
-k_l2p_points(DevGeom g, PointArgs ar, const uint32_t *perm, const double *le, const double *near, int far, double *out)
+k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const double *le, const double *near, int far,
+             double *out)
 {
     static_assert(MG == 1 || LW == 1, "several leaves for several models");
     constexpr int P2 = P * P, LS = P2 | 1, NS = MG * LW;
@@ -114,24 +123,27 @@ k_l2p_points(DevGeom g, PointArgs ar, const uint32_t *perm, const double *le, co
     const DevLev &lv = g.lev[g.L];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t nblk = (uint32_t)((ar.nleaf + LW - 1) / LW), lb = blockIdx.x % nblk;
-    const int bm0 = (int)(blockIdx.x / nblk) * MG, nm = min(MG, g.B - bm0);
-    const int nl = (int)min((int64_t)LW, ar.nleaf - (int64_t)lb * LW);
-    const int32_t *leaves = ar.leaves + (int64_t)lb * LW;
+    const int64_t blk = block_id();
+    if (blk >= rn.nblk * rn.groups)
+        return;
+    const int64_t lb = blk % rn.nblk;
+    const int bm0 = (int)(blk / rn.nblk) * MG, nm = min(MG, g.B - bm0);
+    const int nl = (int)min((int64_t)LW, rn.n - lb * LW);
+    const PointRun *runs = rn.runs + lb * LW;
     const double inv_w = 1.0 / (double)g.b;
     if (tid < nl) {
-        const int64_t leaf = leaves[tid];
+        const PointRun r = runs[tid];
         double c[3];
-        leaf_centre(g, ar.tkey[lv.tbox_off + leaf], c);
+        leaf_centre(g, ar.tkey[lv.tbox_off + r.leaf], c);
 #pragma unroll
         for (int a = 0; a < 3; ++a)
             sc[tid][a] = c[a];
-        st[tid] = ar.start[leaf];
-        sn[tid + 1] = (int)(ar.end[leaf] - ar.start[leaf]);
+        st[tid] = r.start;
+        sn[tid + 1] = r.n;
     }
     if (far)
         for (int i = tid; i < (LW == 1 ? nm : nl) * P2; i += 256) {
-            const int64_t leaf = leaves[LW == 1 ? 0 : i / P2];
+            const int64_t leaf = runs[LW == 1 ? 0 : i / P2].leaf;
             sL[i / P2 * LS + i % P2] =
                 le[((lv.tgt_off + leaf) * g.B + bm0 + (LW == 1 ? i / P2 : 0)) * g.PS + i % P2];
         }
@@ -419,8 +431,7 @@ int64_t point_count(const Plan *p) { return p->lat_near ? p->d.n_points : p->M; 
 
 PointArgs point_args(const Plan *p)
 {
-    return PointArgs{p->d_tpos, p->d_leaf_start, p->d_leaf_pend, p->d_tkey, p->d_user_leaves,
-                     p->n_user_leaves, point_count(p)};
+    return PointArgs{p->d_tpos, p->d_leaf_start, p->d_leaf_pend, p->d_tkey, p->d_user_leaves, point_count(p)};
 }
 
 }  // namespace
@@ -434,14 +445,12 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
     // 68 us with 16
     const bool few = p->B == 1 && point_count(p) < 8 * p->n_user_leaves;
     const int MG = p->B == 1 ? 1 : kPointModels, LW = few ? 16 : 1;
-    const int64_t n = (p->n_user_leaves + LW - 1) / LW * ((p->B + MG - 1) / MG);
-    if (n > 0x7fffffffll)
-        return GRAV_EUNSUPPORTED;
-    if (n == 0)
+    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + LW - 1) / LW, (p->B + MG - 1) / MG};
+    if (p->n_runs == 0)
         return GRAV_OK;
-    const dim3 grid((unsigned)n);
+    const dim3 grid = block_grid(rn.nblk * rn.groups);
 #define L2P_LAUNCH(P, MG, LW)                                                                                    \
-    hipLaunchKernelGGL((k_l2p_points<P, MG, LW>), grid, dim3(256), 0, s, g, point_args(p),                       \
+    hipLaunchKernelGGL((k_l2p_points<P, MG, LW>), grid, dim3(256), 0, s, g, point_args(p), rn,                   \
                        (const uint32_t *)p->d_perm, (const double *)p->d_le, (const double *)p->d_near,          \
                        p->L >= 2 ? 1 : 0, out)
 #define L2P_CASE(P)                                                                                              \
