@@ -434,8 +434,8 @@ k_t_wblocks(DevGeom g, const double *resid, int64_t npts, int KQ, int64_t nplB, 
     }
 }
 
-// near^T for leaves of 1 to 3 cells a side (4^3-cell leaves: near.hip): a
-// workgroup owns CW blocks of 16 (source leaf, model) columns and
+// near^T of the plans that k_near_lat serves (the others: near.hip): a workgroup
+// owns CW blocks of 16 (source leaf, model) columns and
 // four 16-cell row blocks (blockIdx.y); its four waves split the 27 KQ
 // chunks (neighbour d, chunk q of the target leaf's C b^3 weights) and add
 // their partial tiles through LDS in wave order (deterministic), as

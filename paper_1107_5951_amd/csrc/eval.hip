@@ -410,7 +410,8 @@ k_rho_blocks(DevGeom g, const double *rho, int Qn, int64_t nplB, T *blk)
 
 // --------------------------------------------------------------------------
 // The voxel-centre targets, fused: near field + far field + combine, for
-// leaves of 1 to 3 cells a side (4^3-cell leaves: near.hip).
+// leaves of 1 to 3 cells a side, and of 4 on plans whose blocks of leaves would
+// stay mostly empty in near.hip.
 // Targets and Gauss points both sit on the lattice, so the near field of a
 // leaf's b^3 cell centres is
 //   near[leaf] = sum over the 27 neighbour offsets d of  A_d rho[leaf + d],

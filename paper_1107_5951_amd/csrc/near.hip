@@ -14,7 +14,10 @@
 // A the direct sum's pair terms and L the far-field evaluation at the base
 // centres (class(c): the reflections that flip component c).  Eight products of
 // 8 C x 216 instead of one of 64 C x 1728: an eighth of the operations, and an
-// operator that stays in the L2.
+// operator that stays in the L2.  Rounding is relative to the largest pair term
+// among a cell's images: in norm as with dense matrices, but the coincident pair
+// leaves the rounding of its images' terms where those held a zero, and the FP32
+// field of a lone cell is good to 2.5e-7 (dense: 4e-8) five cells away.
 //
 // What bounds it: the passes around the products, which themselves would take
 // 0.18 ms at 256^3 cells and C = 3 in FP32: the neighbourhood's densities into
@@ -27,13 +30,15 @@
 #include "octet.hpp"
 #include "resolve.hpp"
 
-// The FP32 transposed near field takes blocks of 32 leaves from this many
-// (leaf, model) pairs on: three passes over the neighbourhood make the halo
-// (4.5 instead of 6 neighbours per leaf) count there (256^3, g: 0.90 ms against
-// 1.07 with 16), and smaller plans need the workgroups.  Everywhere else 16
-// leaves are as fast or faster: the smaller tiles leave room for more
-// workgroups per CU (256^3 forward, FP32 0.49 against 0.51 ms, FP64 0.96
-// against 1.18).
+// The FP32 transposed near field takes blocks of 4 x 4 x 2 leaves from this many
+// (leaf, model) pairs on: three passes over the neighbourhood make the halo (4.5
+// instead of 6 neighbours per leaf) count there (256^3, g: 0.90 ms against 1.07
+// with blocks of 4 x 2 x 2; 16384 pairs of 64^3 cells x 4 0.064 against 0.076),
+// smaller plans need the workgroups (8192 pairs 0.040 against 0.039, 4096 0.036
+// against 0.028), and so do meshes that fill them worse (8^3 cells x 2048, 2^3
+// leaves: 0.177 against 0.139).  Everywhere else 16 leaves are as fast or faster:
+// the smaller tiles leave room for more workgroups per CU (256^3 forward, FP32
+// 0.49 against 0.51 ms, FP64 0.96 against 1.18).
 #ifndef GRAV_NEAR_WIDE_LEAVES
 #define GRAV_NEAR_WIDE_LEAVES 16384
 #endif
@@ -615,8 +620,12 @@ grav_status launch_t_near_par(const Plan *p, const DevGeom &g, const double *res
 {
     if (p->d.precision == GRAV_FP64)
         return near_transposed<double, 1>(p, g, resid, add, drho, s);
-    return p->lev[p->L].n_src * p->B >= GRAV_NEAR_WIDE_LEAVES ? near_transposed<float, 2>(p, g, resid, add, drho, s)
-                                                              : near_transposed<float, 1>(p, g, resid, add, drho, s);
+    NearGrid n1{}, n2{};
+    dim3 grid;
+    GRAV_CHECK(near_grid<1>(p, n1, grid));
+    GRAV_CHECK(near_grid<2>(p, n2, grid));
+    const bool wide = p->lev[p->L].n_src * p->B >= GRAV_NEAR_WIDE_LEAVES && 20 * (int64_t)n2.n <= 11 * (int64_t)n1.n;
+    return wide ? near_transposed<float, 2>(p, g, resid, add, drho, s) : near_transposed<float, 1>(p, g, resid, add, drho, s);
 }
 
 }  // namespace grav

@@ -25,6 +25,18 @@
 #define GRAV_M2L_WIDE_ROUNDS 2
 #endif
 
+// Leaves of 4^3 cells take the dense near field where the parity kernels' blocks
+// (16 leaves of one model) hold at most a quarter of their leaves and there are
+// more of them (over all models) than this many per leaf held.  Dense against
+// parity, whole calls of cell centres in us, forward and adjoint, p = 10 (gz; g):
+// 4^3 cells (1 leaf) x 512 models 28 / 16, 37 / 21; 28 / 20, 79 / 37; x 2048 28 /
+// 37, 37 / 53; 32 / 54, 94 / 113; FP64 x 512 26 / 22, 57 / 24; 28 / 28, 143 / 49;
+// 8 x 8 x 4 cells (4 leaves) x 1024 29 / 24, 39 / 33; 47 / 33, 96 / 63; x 4096 53 /
+// 65, 62 / 94; 127 / 101, 137 / 214.
+#ifndef GRAV_NEAR_DENSE_BLOCKS
+#define GRAV_NEAR_DENSE_BLOCKS 512
+#endif
+
 // Workgroups that the runs of points are cut for (see build_adjoint_maps).  L2P
 // with 1024 / 2048 / 4096 / 8192: p = 10, one model at 1024^2 stations above
 // 16^3 cells 68 / 65 / 68 / 71 us, eight models at 256^2 37 / 38 / 43 / 51 us;
@@ -1228,7 +1240,14 @@ grav_status build_near_lattice(Plan *p, hipStream_t s)
     near_lattice(b, p->q, f64 ? 1e-20 : 1e-10, dense.data());
     const int TQ = (int)ceil_div(b3, 4), RBt = (int)ceil_div(b3, 16);
     p->lat_TQ = TQ;
-    p->near_par = b == 4;
+    {
+        // by parity unless its blocks of 4 x 2 x 2 leaves stay mostly empty
+        // (GRAV_NEAR_DENSE_BLOCKS)
+        const LevelInfo &lv = p->lev[p->L];
+        const int64_t blocks = ceil_div(lv.ns[0], 4) * ceil_div(lv.ns[1], 2) * ceil_div(lv.ns[2], 2);
+        p->near_par = b == 4 && (lv.n_src > 4 * blocks ||
+                                 blocks * blocks * p->B <= (int64_t)GRAV_NEAR_DENSE_BLOCKS * lv.n_src);
+    }
     if (p->near_par)
         GRAV_CHECK(f64 ? build_near_parity<double>(p, dense) : build_near_parity<float>(p, dense));
     auto row_target = [C, RBc](int row, int rb, bool swap, int &t, int &comp) {
