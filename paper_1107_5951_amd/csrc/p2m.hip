@@ -30,9 +30,15 @@ constexpr int kMaxCells = kMaxLeafCells * kMaxLeafCells * kMaxLeafCells;
 struct P2MArgs {
     const uint32_t *key;            // of the leaf level's octets
     const int32_t *child, *parent;  // (parent -1: leaves at level 2)
-    int64_t noct, nblk;             // octets, blocks of 16
+    uint32_t noct, ncol, nblk;      // octets; (octet, model) columns, octets fastest; blocks of 16
     int part;                       // parts of a block's rows
     int64_t at;                     // first octet's index in its level
+    __device__ void column(uint32_t col, int64_t &oct, int &bm) const
+    {
+        const uint32_t c = min(col, ncol - 1);
+        bm = ncol == noct ? 0 : (int)(c / noct);
+        oct = c - bm * noct;
+    }
 };
 
 // Cells of the (+,+,+) child: offsets from the octet's centre along the axes,
@@ -75,8 +81,10 @@ __device__ __forceinline__ int image_off(const DevGeom &g, const CellEntry &e, i
     return neg ? -e.o[a] - stride : e.o[a];
 }
 
-// A workgroup takes 16 octets of one model; wave w forms child w's leaf
-// expansions (LEAF) and the parents' rows of class w.  The cells pass through
+// A workgroup takes 16 columns (octet, model), octets fastest (16 octets of one
+// model left meshes of few octets mostly empty: 4096 models of 16 x 4 x 4 cells,
+// p = 10, 0.20 against 0.05 ms); wave w forms child w's leaf expansions (LEAF) and
+// the parents' rows of class w.  The cells pass through
 // LDS 16 at a time, as they are and as parity sums; a lane loads the four
 // children on one side of the x plane, its partner four lanes on the others
 // (with leaf edge 4, eight lanes then read 64 consecutive bytes).
@@ -99,25 +107,31 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     __shared__ double sa[LEAF ? NA * 512 : 1], sp[LEAF ? 8 * 4 * C::RBC * 64 : 1];
     __shared__ CellEntry cell[kMaxCells];
     __shared__ __align__(4) uint8_t scls[LEAF ? PS : 4];
-    __shared__ int32_t srow[16];
+    __shared__ int64_t srow[16];
     double *const par = sm, *const raw = sm + 8 * TILE;
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int part = (int)(blockIdx.x % (uint32_t)ar.part);
-    const int64_t bi = blockIdx.x / (uint32_t)ar.part;
-    const int bm = (int)(bi / ar.nblk);
-    const int64_t oct0 = (bi - bm * ar.nblk) * 16;
+    const uint32_t blk = (uint32_t)block_id(), bi = blk / (uint32_t)ar.part;
+    const int part = (int)(blk - bi * ar.part);
+    if (bi >= ar.nblk)
+        return;
+    const uint32_t col0 = bi * 16;
     const int b3 = g.b * g.b * g.b, NCH = (b3 + 15) / 16;
-    const double *rb_ = rho + (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
     cell_table(g, cell, tid);
-    if (tid < 16)
-        srow[tid] = ar.parent[min(oct0 + tid, ar.noct - 1)];
+    int64_t oct;
+    int bm;
+    if (tid < 16) {
+        ar.column(col0 + tid, oct, bm);
+        srow[tid] = (int64_t)ar.parent[oct] * g.B + bm;
+    }
     if (LEAF && tid < PS)
         scls[tid] = (uint8_t)sign_class(tid);
     // staging: column, cell of the chunk, side of the x plane
     const int scol = 2 * w + (lane >> 5), sv = (lane & 3) | (lane >> 1 & 12), half = lane >> 2 & 1;
     Centre ctr;
-    ctr.set(g, ar.key[min(oct0 + scol, ar.noct - 1)]);
+    ar.column(col0 + scol, oct, bm);
+    ctr.set(g, ar.key[oct]);
+    const double *rb_ = rho + (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
     const bool up = ar.parent[0] >= 0 && part == 0;
     vec4 acc[RBL], accp[C::RBC];
 #pragma unroll
@@ -218,15 +232,15 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     int32_t row = -1;
     if constexpr (LEAF) {
         const DevLev &lv = g.lev[g.L];
-        const int64_t o = min(oct0 + (lane & 15), ar.noct - 1);
-        const uint32_t k = ar.key[o];
-        bool need = oct0 + (lane & 15) < ar.noct;
+        ar.column(col0 + (lane & 15), oct, bm);
+        const uint32_t k = ar.key[oct];
+        bool need = col0 + (lane & 15) < ar.ncol;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const int c = 2 * (int)compact3(k >> a) + (w >> a & 1 ? 0 : 1);
             need = need && c >= lv.need_lo[a] && c <= lv.need_hi[a];
         }
-        row = ar.child[o * 8 + (7 ^ w)];
+        row = ar.child[oct * 8 + (7 ^ w)];
         row = need ? row : -1;
     }
     if (row >= 0) {
@@ -264,9 +278,9 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     __syncthreads();
     for (int i = tid; i < 16 * PS; i += 512) {
         const int c = i / PS, k = i % PS;
-        if (oct0 + c >= ar.noct)
+        if (col0 + c >= ar.ncol)
             continue;
-        const int64_t o = ((int64_t)srow[c] * g.B + bm) * PS + k;
+        const int64_t o = srow[c] * PS + k;
         const double v = sm[c * OP + k];
         me[o] = v;
         if (me32)
@@ -274,7 +288,7 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     }
 }
 
-// The transpose.  A workgroup takes 16 octets of one model and NRB blocks of
+// The transpose.  A workgroup takes 16 columns (octet, model) and NRB blocks of
 // 16 cells; wave chi the products of parity chi, its slots (U > 0: U at a time)
 // straight from memory, Pm's fragments and the parents' rows through LDS, where
 // the eight parities meet as well.
@@ -292,16 +306,27 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     __shared__ double sm[kX > kG ? kX : kG];
     __shared__ CellEntry cell[kMaxCells];
     __shared__ Centre sctr[16];
+    __shared__ int64_t srow[16];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int part = (int)(blockIdx.x % (uint32_t)ar.part);
-    const int64_t bi = blockIdx.x / (uint32_t)ar.part;
-    const int bm = (int)(bi / ar.nblk);
-    const int64_t oct0 = (bi - bm * ar.nblk) * 16;
+    const uint32_t blk = (uint32_t)block_id(), bi = blk / (uint32_t)ar.part;
+    const int part = (int)(blk - bi * ar.part);
+    if (bi >= ar.nblk)
+        return;
+    const uint32_t col0 = bi * 16;
     const int b3 = g.b * g.b * g.b, RBT = NRB * ar.part;
     cell_table(g, cell, tid);
-    if (tid < 16)
-        sctr[tid].set(g, ar.key[min(oct0 + tid, ar.noct - 1)]);
+    int64_t oct;
+    int bm;
+    if (tid < 16) {
+        ar.column(col0 + tid, oct, bm);
+        srow[tid] = (int64_t)ar.parent[oct] * g.B + bm;
+        Centre c;
+        c.set(g, ar.key[oct]);
+        c.at += (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
+        sctr[tid] = c;
+    }
+    __syncthreads();
     const bool down = ar.parent[0] >= 0;
     vec4 acc[NRB];
 #pragma unroll
@@ -315,7 +340,8 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     [[maybe_unused]] bool some = false;
     const int64_t xs = (int64_t)sl.ncol * PS;
     if constexpr (U > 0) {
-        const int64_t col = (ar.at + min(oct0 + (lane & 15), ar.noct - 1)) * g.B + bm;
+        ar.column(col0 + (lane & 15), oct, bm);
+        const int64_t col = (ar.at + oct) * g.B + bm;
         const int64_t un = (sl.g0 + col / sl.ncol) * RS + chi / NX;
         jb = sl.uslot[un];
         je = sl.uslot[un + 1];
@@ -345,7 +371,7 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
 #pragma unroll
         for (int n = 0; n < NI; ++n) {
             const int i = min(tid + 512 * n, 16 * PS - 1);
-            y[n] = me[((int64_t)ar.parent[min(oct0 + i / PS, ar.noct - 1)] * g.B + bm) * PS + i % PS];
+            y[n] = me[srow[i / PS] * PS + i % PS];
         }
 #pragma unroll
         for (int n = 0; n < NI; ++n) {
@@ -411,7 +437,6 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     // left room for two, and the stores, half of the time, waited: 0.225 ms against
     // 0.207 far from the stations); a thread takes the four images of a cell on
     // one side of the x plane
-    double *db = drho + (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
 #pragma unroll
     for (int r0 = 0; r0 < NRB; r0 += 2) {
         __syncthreads();  // LDS has been read
@@ -442,8 +467,8 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
                     }
             const Centre ct = sctr[c];
             const CellEntry ce = cell[min(v, b3 - 1)];
-            if (v < b3 && oct0 + c < ar.noct && image_in(g, ct, ce, 0, rx)) {
-                double *d = db + ct.at + image_off(g, ce, 0, rx);
+            if (v < b3 && col0 + c < ar.ncol && image_in(g, ct, ce, 0, rx)) {
+                double *d = drho + ct.at + image_off(g, ce, 0, rx);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (image_in(g, ct, ce, 1, r & 1) & image_in(g, ct, ce, 2, r >> 1))
@@ -458,7 +483,9 @@ P2MArgs p2m_args(const Plan *p, bool far, int part)
 {
     const OctPlan &o = p->m2lt;
     const int64_t mid = o.reach[p->L], o0 = far ? mid : o.first[p->L], noct = (far ? o.first[p->L + 1] : mid) - o0;
-    return P2MArgs{o.d_key + o0, o.d_child + 8 * o0, o.d_parent + o0, noct, (noct + 15) / 16, part, o0 - o.first[p->L]};
+    const int64_t ncol = noct * p->B;
+    return P2MArgs{o.d_key + o0,   o.d_child + 8 * o0, o.d_parent + o0,             (uint32_t)noct,
+                   (uint32_t)ncol, (uint32_t)((ncol + 15) / 16), part, o0 - o.first[p->L]};
 }
 
 }  // namespace
@@ -472,14 +499,14 @@ template <typename T>
 static grav_status p2m(const Plan *p, const DevGeom &g, const double *rho, T *leaf, float *rows, bool far, hipStream_t s)
 {
     const P2MArgs ar = p2m_args(p, far, !far && p->PS > 128 ? 2 : 1);
-    const int64_t grid = ar.nblk * p->B * ar.part;
-    if (grid > 0x7fffffffll)
-        return GRAV_EUNSUPPORTED;
+    const int64_t grid = (int64_t)ar.nblk * ar.part;
+    if ((int64_t)ar.noct * p->B + 16 * (1 << 22) > 0xffffffffll)
+        return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
     // with no level above (leaves at level 2) the others have nothing to set
     if (grid == 0 || (far && p->L < 3))
         return GRAV_OK;
 #define P2M_LAUNCH(P, LEAF)                                                                                      \
-    hipLaunchKernelGGL((k_p2m_octet<P, T, LEAF>), dim3((unsigned)grid), dim3(512), 0, s, g, ar, rho,             \
+    hipLaunchKernelGGL((k_p2m_octet<P, T, LEAF>), block_grid(grid), dim3(512), 0, s, g, ar, rho,             \
                        (const double *)p->d_pm, (const double *)p->d_pm_up, (const int32_t *)p->d_class_coef, leaf, \
                        p->d_me, rows)
 #define P2M_CASE(P)                                                                                              \
@@ -516,9 +543,9 @@ static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, bool far
     const int RBT = (p->b * p->b * p->b + 15) / 16, NRB = RBT <= 2 ? 2 : 4;
     const OctPlan &o = p->m2lt;
     const P2MArgs ar = p2m_args(p, far, (RBT <= 2 ? 2 : (RBT + 3) / 4 * 4) / NRB);
-    const int64_t grid = ar.nblk * p->B * ar.part;
-    if (grid > 0x7fffffffll)
-        return GRAV_EUNSUPPORTED;
+    const int64_t grid = (int64_t)ar.nblk * ar.part;
+    if ((int64_t)ar.noct * p->B + 16 * (1 << 22) > 0xffffffffll)
+        return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
     if (grid == 0)
         return GRAV_OK;
     const SlotArgs<T> sl{reinterpret_cast<const T *>(p->d_part), o.d_uslot, o.gfirst[p->L], 16 * o.nc};
@@ -526,7 +553,7 @@ static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, bool far
     // loads in flight there
     const bool many = o.nseg > 2 * (int64_t)o.nunit;
 #define T_P2M_LAUNCH(P, NRB, U)                                                                                  \
-    hipLaunchKernelGGL((k_t_p2m_octet<P, T, NRB, U>), dim3((unsigned)grid), dim3(512), 0, s, g, ar, sl,          \
+    hipLaunchKernelGGL((k_t_p2m_octet<P, T, NRB, U>), block_grid(grid), dim3(512), 0, s, g, ar, sl,          \
                        (const double *)p->d_pmt, (const double *)p->d_pmt_down, (const int32_t *)p->d_class_coef, \
                        (const double *)p->d_me, drho)
 #define T_P2M_CASE(P)                                                                                            \
