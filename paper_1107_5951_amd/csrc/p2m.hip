@@ -56,16 +56,17 @@ __device__ __forceinline__ void cell_table(const DevGeom &g, CellEntry *cell, in
     }
 }
 
-// An octet's centre: its coordinates and element index in the mesh.
+// An octet's centre: its coordinates in the mesh, and its element index in the
+// densities of model bm.
 struct Centre {
     int x[3];
     int64_t at;
-    __device__ void set(const DevGeom &g, uint32_t key)
+    __device__ void set(const DevGeom &g, uint32_t key, int bm)
     {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
             x[a] = (2 * (int)compact3(key >> a) + 1 - g.shift[a]) * g.b;
-        at = ((int64_t)x[2] * g.n[1] + x[1]) * g.n[0] + x[0];
+        at = (((int64_t)bm * g.n[2] + x[2]) * g.n[1] + x[1]) * g.n[0] + x[0];
     }
 };
 
@@ -111,7 +112,7 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     double *const par = sm, *const raw = sm + 8 * TILE;
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t blk = (uint32_t)block_id(), bi = blk / (uint32_t)ar.part;
+    const uint32_t blk = (uint32_t)block_id(), bi = __builtin_amdgcn_readfirstlane(blk / (uint32_t)ar.part);
     const int part = (int)(blk - bi * ar.part);
     if (bi >= ar.nblk)
         return;
@@ -130,8 +131,7 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     const int scol = 2 * w + (lane >> 5), sv = (lane & 3) | (lane >> 1 & 12), half = lane >> 2 & 1;
     Centre ctr;
     ar.column(col0 + scol, oct, bm);
-    ctr.set(g, ar.key[oct]);
-    const double *rb_ = rho + (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
+    ctr.set(g, ar.key[oct], bm);
     const bool up = ar.parent[0] >= 0 && part == 0;
     vec4 acc[RBL], accp[C::RBC];
 #pragma unroll
@@ -165,7 +165,7 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
         for (int r = 0; r < 4; ++r) {
             const int in = ix & image_in(g, ctr, e, 1, r & 1) & image_in(g, ctr, e, 2, r >> 1);
             ok |= in ? 1u << r : 0u;
-            m[r] = rb_[in ? x + (image_off(g, e, 1, r & 1) + image_off(g, e, 2, r >> 1)) : 0];
+            m[r] = rho[in ? x + (image_off(g, e, 1, r & 1) + image_off(g, e, 2, r >> 1)) : 0];
         }
     };
     __syncthreads();
@@ -309,7 +309,7 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     __shared__ int64_t srow[16];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t blk = (uint32_t)block_id(), bi = blk / (uint32_t)ar.part;
+    const uint32_t blk = (uint32_t)block_id(), bi = __builtin_amdgcn_readfirstlane(blk / (uint32_t)ar.part);
     const int part = (int)(blk - bi * ar.part);
     if (bi >= ar.nblk)
         return;
@@ -321,10 +321,7 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     if (tid < 16) {
         ar.column(col0 + tid, oct, bm);
         srow[tid] = (int64_t)ar.parent[oct] * g.B + bm;
-        Centre c;
-        c.set(g, ar.key[oct]);
-        c.at += (int64_t)bm * g.n[0] * g.n[1] * g.n[2];
-        sctr[tid] = c;
+        sctr[tid].set(g, ar.key[oct], bm);
     }
     __syncthreads();
     const bool down = ar.parent[0] >= 0;
