@@ -170,7 +170,7 @@ k_p2p(DevGeom g, const double *rho, const double *tpos, const int64_t *leaf_star
 __global__ void __launch_bounds__(256)
 k_src_mass(const double *rho, const double *sw, const uint32_t *sperm, int64_t nsrc, int64_t n, double *mass)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     if (t >= n)
         return;
     const int64_t i = t % nsrc;
@@ -775,7 +775,7 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
         return GRAV_OK;
     if (p->n_spts > 0) {
         const int64_t n = p->n_spts * p->B;
-        hipLaunchKernelGGL(k_src_mass, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rho, (const double *)p->d_sw,
+        hipLaunchKernelGGL(k_src_mass, block_grid((n + 255) / 256), dim3(256), 0, s, rho, (const double *)p->d_sw,
                            (const uint32_t *)p->d_sperm, p->n_spts, n, p->d_smass);
         GRAV_HIP(hipGetLastError());
     }

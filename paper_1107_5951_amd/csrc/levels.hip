@@ -64,7 +64,9 @@ k_octet_up(LevelArgs lv, const double *A, const int32_t *coef, const double *x, 
         for (int a = 0; a < 3; ++a)
             ssign[tid][a] = (c >> a & 1) ? -1.0 : 1.0;
     }
-    const int64_t col0 = (int64_t)blockIdx.x * NCOL;
+    const int64_t col0 = block_id() * NCOL;
+    if (col0 >= lv.ncols)
+        return;
     if (tid < NCOL) {
         const int64_t col = col0 + tid;
         srow[tid] = col < lv.ncols ? lv.parent[col / lv.B] : -1;
@@ -304,7 +306,10 @@ k_octet_down(LevelArgs lv, SlotArgs<T> sl, const double *A, const int32_t *coef,
     __shared__ double hs[H == 2 ? 2 * 8 * 256 : 1];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t col0 = (int64_t)blockIdx.x * NCOL;
+    // (blockIdx.y: NC = 2 the grid's rows, NC = 1 the row block)
+    const int64_t col0 = (NC == 2 ? block_id() : (int64_t)blockIdx.x) * NCOL;
+    if (NC == 2 && col0 >= lv.ncols)
+        return;
     // this thread's output: column, row of each block (and half of the slots)
     const int half = tid / (NCOL * 16), oc = tid / 16 % NCOL, orow = tid & 15;
     const int64_t col = col0 + oc;
@@ -478,7 +483,7 @@ grav_status launch_octet_up(const Plan *p, const OctPlan &o, int l, hipStream_t 
     if (lv.ncols == 0)
         return GRAV_OK;
     const bool wide = lv.ncols > kUpWideCols;
-    const dim3 grid((unsigned)(wide ? (lv.ncols + 31) / 32 : (lv.ncols + 15) / 16));
+    const dim3 grid = block_grid(wide ? (lv.ncols + 31) / 32 : (lv.ncols + 15) / 16);
 #define UP_CASE(P)                                                                                            \
     case P:                                                                                                   \
         if (wide)                                                                                             \
@@ -509,7 +514,8 @@ static grav_status octet_down(const Plan *p, const OctPlan &o, int l, hipStream_
     const SlotArgs<T> sl{reinterpret_cast<const T *>(p->d_part), o.d_uslot, o.gfirst[l], 16 * o.nc};
     const double *in = l > 2 ? x : nullptr;
     const bool wide = lv.ncols > kDownWideCols;
-    const dim3 grid((unsigned)(wide ? (lv.ncols + 31) / 32 : (lv.ncols + 15) / 16), (unsigned)(wide ? 1 : p->PS / 16));
+    const dim3 grid = wide ? block_grid((lv.ncols + 31) / 32)
+                           : dim3((unsigned)((lv.ncols + 15) / 16), (unsigned)(p->PS / 16));
 #define DOWN_CASE(P)                                                                                          \
     case P:                                                                                                   \
         if (wide)                                                                                             \
