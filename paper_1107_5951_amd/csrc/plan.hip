@@ -741,7 +741,21 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     }
     const int64_t nunit = (int64_t)umask.size(), nlive = (int64_t)live.size(), T = ustart.back();
     const int64_t W = T == 0 ? 0 : std::min<int64_t>(resident, T);
-    const int64_t rounds = W > 0 ? nlive / W : 0;
+    int64_t rounds = W > 0 ? nlive / W : 0;
+    {
+        // a round lasts as long as its longest unit: where units are so unequal
+        // (small leaf grids) that the rounds would take 1.15 times their mean, all
+        // items are shared out (p = 14 FP64, 12^3 cells x 1024: 2.07 -> 1.52 ms)
+        int64_t longest = 0;
+        for (int64_t r = 0; r < rounds; ++r) {
+            int64_t m = 0;
+            for (int64_t v = r * W; v < (r + 1) * W; ++v)
+                m = std::max(m, ustart[v + 1] - ustart[v]);
+            longest += m;
+        }
+        if (100 * longest * W > 115 * ustart[rounds * W])
+            rounds = 0;
+    }
     std::vector<int32_t> seg, wgseg(W + 1, 0);
     std::vector<std::vector<int32_t>> useg(nunit);
     const int64_t u0 = rounds * W, rest = T - ustart[u0];
