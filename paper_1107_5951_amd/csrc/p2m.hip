@@ -21,6 +21,16 @@
 
 #include "octet.hpp"
 
+// The transpose takes blocks across models from this many blocks of single
+// models on; fewer leave CUs idle, and a block reads as many slots a lane again.
+// Octets in one block, of a model against across models, us: 12^3 cells (8
+// octets), p = 10, x 64 models 40 against 59, x 256 28 / 32, x 512 37 / 29, x 2048
+// 91 / 54; FP64 p = 14 65 / 83, 39 / 47, 49 / 36, 162 / 94.  The P2M is as fast or
+// faster across models from 4 models on (12^3 x 512 40 against 21, 83 / 43).
+#ifndef GRAV_T_P2M_PACK_BLOCKS
+#define GRAV_T_P2M_PACK_BLOCKS 384
+#endif
+
 namespace grav {
 
 namespace {
@@ -30,14 +40,19 @@ constexpr int kMaxCells = kMaxLeafCells * kMaxLeafCells * kMaxLeafCells;
 struct P2MArgs {
     const uint32_t *key;            // of the leaf level's octets
     const int32_t *child, *parent;  // (parent -1: leaves at level 2)
-    uint32_t noct, ncol, nblk;      // octets; (octet, model) columns, octets fastest; blocks of 16
+    // octets; (octet, model) columns, octets fastest, `per` to a model (noct, or
+    // whole blocks); blocks of 16
+    uint32_t noct, per, ncol, nblk;
     int part;                       // parts of a block's rows
     int64_t at;                     // first octet's index in its level
-    __device__ void column(uint32_t col, int64_t &oct, int &bm) const
+    // octet and model of a column (past the last: the last one), whether there is one
+    __device__ bool column(uint32_t col, int64_t &oct, int &bm) const
     {
         const uint32_t c = min(col, ncol - 1);
-        bm = ncol == noct ? 0 : (int)(c / noct);
-        oct = c - bm * noct;
+        bm = ncol == per ? 0 : (int)(c / per);
+        const uint32_t j = c - bm * per;
+        oct = min(j, noct - 1);
+        return c == col && j < noct;
     }
 };
 
@@ -122,8 +137,8 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     int64_t oct;
     int bm;
     if (tid < 16) {
-        ar.column(col0 + tid, oct, bm);
-        srow[tid] = (int64_t)ar.parent[oct] * g.B + bm;
+        const bool valid = ar.column(col0 + tid, oct, bm);
+        srow[tid] = valid ? (int64_t)ar.parent[oct] * g.B + bm : -1;
     }
     if (LEAF && tid < PS)
         scls[tid] = (uint8_t)sign_class(tid);
@@ -232,9 +247,8 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     int32_t row = -1;
     if constexpr (LEAF) {
         const DevLev &lv = g.lev[g.L];
-        ar.column(col0 + (lane & 15), oct, bm);
+        bool need = ar.column(col0 + (lane & 15), oct, bm);
         const uint32_t k = ar.key[oct];
-        bool need = col0 + (lane & 15) < ar.ncol;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const int c = 2 * (int)compact3(k >> a) + (w >> a & 1 ? 0 : 1);
@@ -278,7 +292,7 @@ k_p2m_octet(DevGeom g, P2MArgs ar, const double *rho, const double *A, const dou
     __syncthreads();
     for (int i = tid; i < 16 * PS; i += 512) {
         const int c = i / PS, k = i % PS;
-        if (col0 + c >= ar.ncol)
+        if (srow[c] < 0)
             continue;
         const int64_t o = srow[c] * PS + k;
         const double v = sm[c * OP + k];
@@ -319,9 +333,11 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     int64_t oct;
     int bm;
     if (tid < 16) {
-        ar.column(col0 + tid, oct, bm);
+        const bool valid = ar.column(col0 + tid, oct, bm);
         srow[tid] = (int64_t)ar.parent[oct] * g.B + bm;
         sctr[tid].set(g, ar.key[oct], bm);
+        if (!valid)
+            sctr[tid].x[0] = g.n[0] + 2 * kMaxLeafCells;  // its cells lie outside the mesh
     }
     __syncthreads();
     const bool down = ar.parent[0] >= 0;
@@ -464,7 +480,7 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
                     }
             const Centre ct = sctr[c];
             const CellEntry ce = cell[min(v, b3 - 1)];
-            if (v < b3 && col0 + c < ar.ncol && image_in(g, ct, ce, 0, rx)) {
+            if (v < b3 && image_in(g, ct, ce, 0, rx)) {
                 double *d = drho + ct.at + image_off(g, ce, 0, rx);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
@@ -475,14 +491,16 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     }
 }
 
-// The leaf level's octets within reach of the M2L (far: the others).
-P2MArgs p2m_args(const Plan *p, bool far, int part)
+// The leaf level's octets within reach of the M2L (far: the others).  Blocks
+// across models where blocks of single ones would be more than `pack`.
+P2MArgs p2m_args(const Plan *p, bool far, int part, int64_t pack)
 {
     const OctPlan &o = p->m2lt;
     const int64_t mid = o.reach[p->L], o0 = far ? mid : o.first[p->L], noct = (far ? o.first[p->L + 1] : mid) - o0;
-    const int64_t ncol = noct * p->B;
-    return P2MArgs{o.d_key + o0,   o.d_child + 8 * o0, o.d_parent + o0,             (uint32_t)noct,
-                   (uint32_t)ncol, (uint32_t)((ncol + 15) / 16), part, o0 - o.first[p->L]};
+    const int64_t whole = (noct + 15) / 16;
+    const int64_t per = whole * p->B * part > pack ? noct : 16 * whole, ncol = per * p->B;
+    return P2MArgs{o.d_key + o0,  o.d_child + 8 * o0, o.d_parent + o0, (uint32_t)noct,
+                   (uint32_t)per, (uint32_t)ncol,     (uint32_t)((ncol + 15) / 16), part, o0 - o.first[p->L]};
 }
 
 }  // namespace
@@ -495,9 +513,9 @@ P2MArgs p2m_args(const Plan *p, bool far, int part)
 template <typename T>
 static grav_status p2m(const Plan *p, const DevGeom &g, const double *rho, T *leaf, float *rows, bool far, hipStream_t s)
 {
-    const P2MArgs ar = p2m_args(p, far, !far && p->PS > 128 ? 2 : 1);
+    const P2MArgs ar = p2m_args(p, far, !far && p->PS > 128 ? 2 : 1, 0);
     const int64_t grid = (int64_t)ar.nblk * ar.part;
-    if ((int64_t)ar.noct * p->B + 16 * (1 << 22) > 0xffffffffll)
+    if ((int64_t)ar.per * p->B + 16 * (1 << 22) > 0xffffffffll)
         return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
     // with no level above (leaves at level 2) the others have nothing to set
     if (grid == 0 || (far && p->L < 3))
@@ -539,9 +557,9 @@ static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, bool far
 {
     const int RBT = (p->b * p->b * p->b + 15) / 16, NRB = RBT <= 2 ? 2 : 4;
     const OctPlan &o = p->m2lt;
-    const P2MArgs ar = p2m_args(p, far, (RBT <= 2 ? 2 : (RBT + 3) / 4 * 4) / NRB);
+    const P2MArgs ar = p2m_args(p, far, (RBT <= 2 ? 2 : (RBT + 3) / 4 * 4) / NRB, GRAV_T_P2M_PACK_BLOCKS);
     const int64_t grid = (int64_t)ar.nblk * ar.part;
-    if ((int64_t)ar.noct * p->B + 16 * (1 << 22) > 0xffffffffll)
+    if ((int64_t)ar.per * p->B + 16 * (1 << 22) > 0xffffffffll)
         return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
     if (grid == 0)
         return GRAV_OK;
