@@ -21,6 +21,16 @@
 
 #include "octet.hpp"
 
+// Up to a block per CU the P2M runs all octets with the leaf part in one launch:
+// a block's chunks are a chain (1.2 us each), and two launches are two of them.
+// Calls with two launches against one, us, p = 4: 64^3 cells in leaves of 8^3
+// under stations 109 / 77 (the per-leaf form before 87); p = 10: 64^3 in leaves of
+// 4^3 103 / 97, 128^3 (256 blocks) 121 / 113, x 16 models of 128^3 in leaves of 8^3
+// (512 blocks) 311 / 331; FP64 p = 14 (two parts) 128^3 (512 blocks) 216 / 225.
+#ifndef GRAV_P2M_ONE_LAUNCH_BLOCKS
+#define GRAV_P2M_ONE_LAUNCH_BLOCKS 256
+#endif
+
 // The transpose takes blocks across models from this many blocks of single
 // models on; fewer leave CUs idle, and a block reads as many slots a lane again.
 // Octets in one block, of a model against across models, us: 12^3 cells (8
@@ -491,12 +501,14 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
     }
 }
 
-// The leaf level's octets within reach of the M2L (far: the others).  Blocks
-// across models where blocks of single ones would be more than `pack`.
-P2MArgs p2m_args(const Plan *p, bool far, int part, int64_t pack)
+// The leaf level's octets: within reach of the M2L, the others, or all of them.
+// Blocks across models where blocks of single ones would be more than `pack`.
+enum class Reach { near, far, all };
+P2MArgs p2m_args(const Plan *p, Reach r, int part, int64_t pack)
 {
     const OctPlan &o = p->m2lt;
-    const int64_t mid = o.reach[p->L], o0 = far ? mid : o.first[p->L], noct = (far ? o.first[p->L + 1] : mid) - o0;
+    const int64_t mid = o.reach[p->L], o0 = r == Reach::far ? mid : o.first[p->L];
+    const int64_t noct = (r == Reach::near ? mid : o.first[p->L + 1]) - o0;
     const int64_t whole = (noct + 15) / 16;
     const int64_t per = whole * p->B * part > pack ? noct : 16 * whole, ncol = per * p->B;
     return P2MArgs{o.d_key + o0,  o.d_child + 8 * o0, o.d_parent + o0, (uint32_t)noct,
@@ -511,9 +523,10 @@ P2MArgs p2m_args(const Plan *p, bool far, int part, int64_t pack)
 // Expansions of the parents of the leaves, and of the leaves that the M2L
 // reads into its input rows.
 template <typename T>
-static grav_status p2m(const Plan *p, const DevGeom &g, const double *rho, T *leaf, float *rows, bool far, hipStream_t s)
+static grav_status p2m(const Plan *p, const DevGeom &g, const double *rho, T *leaf, float *rows, Reach r, hipStream_t s)
 {
-    const P2MArgs ar = p2m_args(p, far, !far && p->PS > 128 ? 2 : 1, 0);
+    const bool far = r == Reach::far;
+    const P2MArgs ar = p2m_args(p, r, !far && p->PS > 128 ? 2 : 1, 0);
     const int64_t grid = (int64_t)ar.nblk * ar.part;
     if ((int64_t)ar.per * p->B + 16 * (1 << 22) > 0xffffffffll)
         return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
@@ -545,19 +558,25 @@ static grav_status p2m(const Plan *p, const DevGeom &g, const double *rho, T *le
 grav_status launch_p2m(const Plan *p, const DevGeom &g, const double *rho, hipStream_t s)
 {
     float *rows = reinterpret_cast<float *>(p->d_rows);
-    for (int far = 0; far < 2; ++far)
-        GRAV_CHECK(p->d.precision == GRAV_FP64 ? p2m<double>(p, g, rho, p->d_me, nullptr, far, s)
-                                               : p2m<float>(p, g, rho, rows, rows, far, s));
-    return GRAV_OK;
+    auto run = [&](Reach r) {
+        return p->d.precision == GRAV_FP64 ? p2m<double>(p, g, rho, p->d_me, nullptr, r, s)
+                                           : p2m<float>(p, g, rho, rows, rows, r, s);
+    };
+    const OctPlan &o = p->m2lt;
+    if ((o.first[p->L + 1] - o.first[p->L]) * p->B * (p->PS > 128 ? 2 : 1) <= 16 * GRAV_P2M_ONE_LAUNCH_BLOCKS)
+        return run(Reach::all);
+    GRAV_CHECK(run(Reach::near));
+    return run(Reach::far);
 }
 
 // drho from the parents' adjoint expansions and the leaf level's M2L slots.
 template <typename T>
-static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, bool far, hipStream_t s)
+static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, Reach r, hipStream_t s)
 {
+    const bool far = r == Reach::far;
     const int RBT = (p->b * p->b * p->b + 15) / 16, NRB = RBT <= 2 ? 2 : 4;
     const OctPlan &o = p->m2lt;
-    const P2MArgs ar = p2m_args(p, far, (RBT <= 2 ? 2 : (RBT + 3) / 4 * 4) / NRB, GRAV_T_P2M_PACK_BLOCKS);
+    const P2MArgs ar = p2m_args(p, r, (RBT <= 2 ? 2 : (RBT + 3) / 4 * 4) / NRB, GRAV_T_P2M_PACK_BLOCKS);
     const int64_t grid = (int64_t)ar.nblk * ar.part;
     if ((int64_t)ar.per * p->B + 16 * (1 << 22) > 0xffffffffll)
         return GRAV_EUNSUPPORTED;  // (half a terabyte of expansions)
@@ -597,8 +616,8 @@ static grav_status t_p2m(const Plan *p, const DevGeom &g, double *drho, bool far
 
 grav_status launch_t_p2m(const Plan *p, const DevGeom &g, double *drho, hipStream_t s)
 {
-    for (int far = 0; far < 2; ++far)
-        GRAV_CHECK(p->d.precision == GRAV_FP64 ? t_p2m<double>(p, g, drho, far, s) : t_p2m<float>(p, g, drho, far, s));
+    for (Reach r : {Reach::near, Reach::far})
+        GRAV_CHECK(p->d.precision == GRAV_FP64 ? t_p2m<double>(p, g, drho, r, s) : t_p2m<float>(p, g, drho, r, s));
     return GRAV_OK;
 }
 
