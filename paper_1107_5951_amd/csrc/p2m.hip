@@ -502,7 +502,10 @@ k_t_p2m_octet(DevGeom g, P2MArgs ar, SlotArgs<T> sl, const double *A, const doub
 }
 
 // The leaf level's octets: within reach of the M2L, the others, or all of them.
-// Blocks across models where blocks of single ones would be more than `pack`.
+// Blocks across models where blocks of single ones would be more than `pack` and
+// an eighth of their columns or more empty (blocks that start at an octet row of
+// the mesh read and write it in longer runs: 18 models of 76^3 cells, 4% empty,
+// 43.6 us against 44.5).
 enum class Reach { near, far, all };
 P2MArgs p2m_args(const Plan *p, Reach r, int part, int64_t pack)
 {
@@ -510,7 +513,7 @@ P2MArgs p2m_args(const Plan *p, Reach r, int part, int64_t pack)
     const int64_t mid = o.reach[p->L], o0 = r == Reach::far ? mid : o.first[p->L];
     const int64_t noct = (r == Reach::near ? mid : o.first[p->L + 1]) - o0;
     const int64_t whole = (noct + 15) / 16;
-    const int64_t per = whole * p->B * part > pack ? noct : 16 * whole, ncol = per * p->B;
+    const int64_t per = whole * p->B * part > pack && 8 * 16 * whole >= 9 * noct ? noct : 16 * whole, ncol = per * p->B;
     return P2MArgs{o.d_key + o0,  o.d_child + 8 * o0, o.d_parent + o0, (uint32_t)noct,
                    (uint32_t)per, (uint32_t)ncol,     (uint32_t)((ncol + 15) / 16), part, o0 - o.first[p->L]};
 }

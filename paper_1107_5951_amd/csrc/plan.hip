@@ -38,9 +38,10 @@
 #endif
 
 // Workgroups that the runs of points are cut for (see build_adjoint_maps).  L2P
-// with 1024 / 2048 / 4096 / 8192: p = 10, one model at 1024^2 stations above
-// 16^3 cells 68 / 65 / 68 / 71 us, eight models at 256^2 37 / 38 / 43 / 51 us;
-// FP64 p = 14 133 / 119 / 119 / 123 and 69 / 66 / 73 / 83 us.
+// with 1024 / 2048 / 4096 / 8192: one model at 1024^2 stations above 16^3 cells, p
+// = 10, 68 / 65 / 68 / 71 us, FP64 p = 14 133 / 119 / 119 / 123; several models load
+// their expansions again with every run: 64 at 64^2 stations 22 / 25 / 35 / 32 us, and
+// 18 over 76^3 cells, 16 points a leaf, 14.7 whole and 19.0 in two runs of one step.
 #ifndef GRAV_RUN_BLOCKS
 #define GRAV_RUN_BLOCKS 2048
 #endif
@@ -1071,9 +1072,10 @@ grav_status build_adjoint_maps(Plan *p)
         p->n_pt_leaves = (int64_t)n[0];
         p->n_user_leaves = (int64_t)n[1];
         // runs for the L2P: steps of 64 (point, model) pairs, as many a run as
-        // leave kRunBlocks workgroups
+        // leave kRunBlocks workgroups, half as many with several models
         const int64_t np = p->lat_near ? p->d.n_points : p->M, mg = std::min(p->B, 8);
-        const int64_t len = std::max<int64_t>(ceil_div(np * p->B, (int64_t)64 * kRunBlocks) * 64 / mg, 1);
+        const int64_t blocks = p->B == 1 ? kRunBlocks : kRunBlocks / 2, least = p->B == 1 ? 1 : 2;
+        const int64_t len = std::max(ceil_div(np * p->B, 64 * blocks), least) * 64 / mg;
         if (st == GRAV_OK && p->n_user_leaves > 0) {
             p->n_runs = 0;
             st = dalloc(p, &p->d_runs, (size_t)(p->n_user_leaves + np / len), true);
