@@ -60,7 +60,7 @@ __device__ __forceinline__ void combine_weights(const DevGeom &g, const double *
 __global__ void __launch_bounds__(256)
 k_t_weights(DevGeom g, const double *resid, const uint32_t *perm, int64_t limit, double *w)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     if (t >= g.M * g.B)
         return;
     const int64_t i = t / g.B;
@@ -104,7 +104,7 @@ k_t_cells(DevGeom g, const double *tpos, const int64_t *leaf_start, const int64_
 {
     const int NG = (g.B + MT - 1) / MT;
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     const int b = g.b;
     const DevLev &lv = g.lev[g.L];
     int grp, ix, iy, iz;
@@ -241,7 +241,7 @@ k_t_src(DevGeom g, const double *spos, const double *sw, const uint32_t *sperm, 
         const double *me, double *drho)
 {
     const int NG = (g.B + MT - 1) / MT;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     if (t >= nsrc * NG)
         return;
     const int grp = (int)(t / nsrc);
@@ -317,7 +317,7 @@ k_t_src(DevGeom g, const double *spos, const double *sw, const uint32_t *sperm, 
 
 __global__ void __launch_bounds__(256) k_t_zero(double *x, int64_t n)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_id() * blockDim.x + threadIdx.x;
     if (i < n)
         x[i] = 0.0;
 }
@@ -332,7 +332,7 @@ template <typename T>
 __global__ void __launch_bounds__(256)
 k_le_rows(DevGeom g, OctGeom og, const int32_t *tmap, const double *le, int64_t n4, T *out)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_id() * blockDim.x + threadIdx.x;
     if (i >= n4)
         return;
     const int P4 = g.PS / 4;
@@ -371,7 +371,7 @@ static grav_status enqueue_m2l_transposed(Plan *p, const DevGeom &g, hipStream_t
     T *rows = reinterpret_cast<T *>(p->d_rows);
     const int64_t n4 = p->n_grow * p->B * (p->PS / 4);
     if (n4 > 0) {
-        hipLaunchKernelGGL((k_le_rows<T>), dim3((unsigned)ceil_div(n4, 256)), dim3(256), 0, s, g, og,
+        hipLaunchKernelGGL((k_le_rows<T>), block_grid(ceil_div(n4, 256)), dim3(256), 0, s, g, og,
                            (const int32_t *)p->d_tmap, (const double *)p->d_le, n4, rows);
         GRAV_HIP(hipGetLastError());
     }
@@ -417,7 +417,7 @@ k_t_wblocks(DevGeom g, const double *resid, int64_t npts, int KQ, int64_t nplB, 
     const DevLev &lv = g.lev[g.L];
     const int b = g.b, b3 = b * b * b;
     const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_id() * blockDim.x + threadIdx.x;
     if (i >= nleaf * g.B * b3)
         return;
     const int t = (int)(i % b3);
@@ -435,8 +435,8 @@ k_t_wblocks(DevGeom g, const double *resid, int64_t npts, int KQ, int64_t nplB, 
 }
 
 // near^T of the plans that k_near_lat serves (the others: near.hip): a workgroup
-// owns CW blocks of 16 (source leaf, model) columns and
-// four 16-cell row blocks (blockIdx.y); its four waves split the 27 KQ
+// owns CW blocks of 16 (source leaf, model) columns and the (up to four) 16-cell
+// row blocks; its four waves split the 27 KQ
 // chunks (neighbour d, chunk q of the target leaf's C b^3 weights) and add
 // their partial tiles through LDS in wave order (deterministic), as
 // k_near_lat does.  Target leaf T = S - d reads the padded weight blocks (no
@@ -453,13 +453,12 @@ k_t_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, int RBt, int KQ,
     const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
     const int b = g.b, b3 = b * b * b;
     const int px = lv.ns[0] + 2, py = lv.ns[1] + 2;
-    const int rb0 = 4 * blockIdx.y;
     bool cvalid[CW];
     int bm[CW], sx[CW], sy[CW], sz[CW];
     const T *bbase[CW];
 #pragma unroll
     for (int c = 0; c < CW; ++c) {
-        const int64_t col = ((int64_t)blockIdx.x * CW + c) * 16 + (lane & 15);
+        const int64_t col = (block_id() * CW + c) * 16 + (lane & 15);
         cvalid[c] = col < nleaf * g.B;
         const int64_t leaf = cvalid[c] ? col / g.B : 0;
         bm[c] = cvalid[c] ? (int)(col % g.B) : 0;
@@ -489,7 +488,7 @@ k_t_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, int RBt, int KQ,
         T av[4][4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            load_frags<T, 4>(A + (((int64_t)nb * KQ + q) * RBt + min(rb0 + r, RBt - 1)) * 256, lane, av[r]);
+            load_frags<T, 4>(A + (((int64_t)nb * KQ + q) * RBt + min(r, RBt - 1)) * 256, lane, av[r]);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -514,11 +513,11 @@ k_t_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, int RBt, int KQ,
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
     for (int j = wave; j < CW * 4; j += 4) {
         const int c = j / 4, r = j % 4;
-        if (!cvalid[c] || rb0 + r >= RBt)
+        if (!cvalid[c] || r >= RBt)
             continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int v = 16 * (rb0 + r) + (sizeof(T) == 8 ? kr + 4 * i : 4 * kr + i);
+            const int v = 16 * r + (sizeof(T) == 8 ? kr + 4 * i : 4 * kr + i);
             if (v >= b3)
                 continue;
             const int ix = sx[c] * b + v % b, iy = sy[c] * b + (v / b) % b, iz = sz[c] * b + v / (b * b);
@@ -546,7 +545,7 @@ k_t_l2p_lat(DevGeom g, const double *A, int TQ, const int32_t *tmap, const doubl
     const int lane = threadIdx.x, kr = lane >> 4;
     const DevLev &lv = g.lev[g.L];
     const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t col = (int64_t)blockIdx.x * 16 + (lane & 15);
+    const int64_t col = block_id() * 16 + (lane & 15);
     const bool cvalid = col < nleaf * g.B;
     const int64_t leaf = cvalid ? col / g.B : 0;
     const int bm = cvalid ? (int)(col % g.B) : 0;
@@ -588,7 +587,7 @@ k_t_l2p_lat(DevGeom g, const double *A, int TQ, const int32_t *tmap, const doubl
 
 static grav_status launch_t_l2p_lat(Plan *p, const DevGeom &g, const double *resid, int add, hipStream_t s)
 {
-    const dim3 grid((unsigned)ceil_div(p->lev[p->L].n_src * p->B, 16));
+    const dim3 grid = block_grid(ceil_div(p->lev[p->L].n_src * p->B, 16));
 #define CASE(R)                                                                                             \
     case R:                                                                                                 \
         hipLaunchKernelGGL((k_t_l2p_lat<R>), grid, dim3(64), 0, s, g, (const double *)p->d_tl2pt, p->lat_TQ, \
@@ -615,8 +614,8 @@ static grav_status launch_t_near_lat(Plan *p, const DevGeom &g, const double *re
     const int KQ = (int)ceil_div((int64_t)p->d.components * b3, 16);
     const int64_t nplB = (int64_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B;
     const bool f64 = p->d.precision == GRAV_FP64;
-    const dim3 fgrid((unsigned)ceil_div(lv.n_src * p->B * b3, 256));
-    const dim3 grid((unsigned)ceil_div(lv.n_src * p->B, 16 * CW), (unsigned)ceil_div(RBt, 4));
+    const dim3 fgrid = block_grid(ceil_div(lv.n_src * p->B * b3, 256));
+    const dim3 grid = block_grid(ceil_div(lv.n_src * p->B, 16 * CW));
     if (f64) {
         hipLaunchKernelGGL((k_t_wblocks<double>), fgrid, dim3(256), 0, s, g, resid, p->d.n_points, KQ, nplB,
                            p->d_w_blk);
@@ -641,7 +640,7 @@ static grav_status enqueue_adjoint_mt(Plan *p, const double *resid, double *drho
     const int64_t ncell = (int64_t)p->d.nx * p->d.ny * p->d.nz;
     const int64_t NG = (p->B + MT - 1) / MT;
     const dim3 blk(256);
-    auto grid = [](int64_t n) { return dim3((unsigned)ceil_div(n, 256)); };
+    auto grid = [](int64_t n) { return block_grid(ceil_div(n, 256)); };
     if (ncell * NG > 0x7fffffffll * 256 || p->n_me > 0x7fffffffll || p->P2 > 256)
         return GRAV_EUNSUPPORTED;
     stage_begin(p, "weights", s);
@@ -763,7 +762,7 @@ extern "C" grav_status grav_adjoint(grav_plan_t plan, const double *resid, doubl
             // no evaluation points: the transpose is zero (a fill kernel, not a
             // memset, so that the call can be recorded in a graph)
             const int64_t n = (p->n_spts > 0 ? p->n_spts : (int64_t)p->d.nx * p->d.ny * p->d.nz) * p->B;
-            hipLaunchKernelGGL(k_t_zero, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, drho_out, n);
+            hipLaunchKernelGGL(k_t_zero, block_grid(ceil_div(n, 256)), dim3(256), 0, s, drho_out, n);
             st = hipGetLastError() == hipSuccess ? GRAV_OK : GRAV_EDEVICE;
         } else {
             st = enqueue_adjoint(p, resid, drho_out, s);

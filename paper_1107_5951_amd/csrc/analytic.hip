@@ -106,7 +106,7 @@ k_analytic(DevGeom g, const double *rho, const double *tpos, int64_t chunk, doub
 __global__ void __launch_bounds__(256)
 k_analytic_finish(DevGeom g, const double *part, int nchunk, const uint32_t *perm, double *out)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     if (t >= g.M * g.B)
         return;
     const int64_t i = t / g.B;
@@ -150,7 +150,7 @@ extern "C" grav_status grav_analytic(grav_plan_t plan, const double *rho, double
                            (const uint32_t *)p->d_perm, gz_out);
         st = hipGetLastError() == hipSuccess ? GRAV_OK : GRAV_EDEVICE;
         if (st == GRAV_OK && nchunk > 1) {
-            hipLaunchKernelGGL(k_analytic_finish, dim3((unsigned)((p->M * p->B + 255) / 256)), dim3(256), 0, s, g,
+            hipLaunchKernelGGL(k_analytic_finish, block_grid((p->M * p->B + 255) / 256), dim3(256), 0, s, g,
                                (const double *)p->d_dpart, nchunk, (const uint32_t *)p->d_perm, gz_out);
             st = hipGetLastError() == hipSuccess ? GRAV_OK : GRAV_EDEVICE;
         }

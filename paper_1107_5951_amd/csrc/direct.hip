@@ -138,7 +138,7 @@ k_direct(DevGeom g, const double *rho, const double *tpos, int64_t chunk, double
 __global__ void __launch_bounds__(256)
 k_direct_finish(DevGeom g, const double *part, int nchunk, const uint32_t *perm, double *out)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = block_id() * blockDim.x + threadIdx.x;
     if (t >= g.M * g.B)
         return;
     const int64_t i = t / g.B;
@@ -184,7 +184,7 @@ static grav_status enqueue_direct(Plan *p, const double *rho, double *g_out, dou
                            (const uint32_t *)p->d_perm, g_out);
     GRAV_HIP(hipGetLastError());
     if (nchunk > 1) {
-        hipLaunchKernelGGL(k_direct_finish, dim3((unsigned)((p->M * p->B + 255) / 256)), dim3(256), 0, s, g,
+        hipLaunchKernelGGL(k_direct_finish, block_grid((p->M * p->B + 255) / 256), dim3(256), 0, s, g,
                            (const double *)part, nchunk, (const uint32_t *)p->d_perm, g_out);
         GRAV_HIP(hipGetLastError());
     }

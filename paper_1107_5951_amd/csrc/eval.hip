@@ -16,7 +16,7 @@ namespace grav {
 // One thread per four coefficients; src and dst at the level's first row.
 __global__ void __launch_bounds__(256) k_leaf_f32(DevGeom g, const double *src, int64_t n4, float *dst)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_id() * blockDim.x + threadIdx.x;
     if (i >= n4)
         return;
     const int64_t j = i / ((int64_t)(g.PS / 4) * g.B);
@@ -63,12 +63,14 @@ __device__ __forceinline__ void add_pair(T cx, T cy, T cz, T mass, T (&acc)[4])
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_p2p(DevGeom g, const double *rho, const double *tpos, const int64_t *leaf_start,
-      const int64_t *leaf_end, const uint32_t *tkey, const int32_t *leaves, double *near)
+      const int64_t *leaf_end, const uint32_t *tkey, const int32_t *leaves, int64_t n_leaves, double *near)
 {
     __shared__ __align__(16) T sp[kP2PChunk][4];
     __shared__ double red[256][4];
     const DevLev &lv = g.lev[g.L];
-    const int64_t leaf = leaves[blockIdx.x];  // the target leaves holding user points
+    if (block_id() >= n_leaves)
+        return;
+    const int64_t leaf = leaves[block_id()];  // the target leaves holding user points
     const int64_t ts = leaf_start[leaf], te = leaf_end[leaf];
     const int64_t nt = te - ts;
     if (nt <= 0)
@@ -262,12 +264,15 @@ __device__ __forceinline__ void p2p_few(const SourceRuns &run, const double *spo
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_p2p_src(DevGeom g, const double *mass, const double *spos, const int64_t *sstart, int64_t nsrc, const double *tpos,
-          const int64_t *leaf_start, const int64_t *leaf_end, const uint32_t *tkey, const int32_t *leaves, double *near)
+          const int64_t *leaf_start, const int64_t *leaf_end, const uint32_t *tkey, const int32_t *leaves, int64_t n_leaves,
+          double *near)
 {
     __shared__ T sp[256][4];
     __shared__ double red[256][4];
     const DevLev &lv = g.lev[g.L];
-    const int64_t leaf = leaves[blockIdx.x];  // the target leaves holding user points
+    if (block_id() >= n_leaves)
+        return;
+    const int64_t leaf = leaves[block_id()];  // the target leaves holding user points
     const int64_t ts = leaf_start[leaf], te = leaf_end[leaf];
     const int64_t nt = te - ts;
     if (nt <= 0)
@@ -368,7 +373,7 @@ k_rho_blocks(DevGeom g, const double *rho, int Qn, int64_t nplB, T *blk)
     const DevLev &lv = g.lev[g.L];
     const int b = g.b, b2 = b * b, b3 = b2 * b;
     const int64_t nleaf = (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = block_id() * blockDim.x + threadIdx.x;
     if (i >= nleaf * g.B * b3)
         return;
     const int v = (int)(i % b3);
@@ -446,9 +451,9 @@ k_near_lat(DevGeom g, const T *blk, int64_t nplB, const T *A, const int64_t *cta
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // NW = 4: the workgroup's four waves share one tile; NW = 1: each wave
     // owns a tile of its own
-    const int64_t tile = NW == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+    const int64_t tile = NW == 4 ? block_id() : block_id() * 4 + wave;
     if (tile >= ntile)
-        return;  // NW = 1 only (no barrier there): the grid's last waves
+        return;  // past the grid's last: whole workgroups, or waves where there is no barrier (NW = 1)
     const int64_t cg = tile / nrg;
     const int rb0 = (int)(tile % nrg) * RW;
     const DevLev &lv = g.lev[g.L];
@@ -724,7 +729,7 @@ static grav_status launch_near_lat(Plan *p, const DevGeom &g, const double *rho,
     const int64_t nfill = lv.n_src * p->B * b3;
     const int64_t nplB = (int64_t)(lv.ns[0] + 2) * (lv.ns[1] + 2) * (lv.ns[2] + 2) * p->B;
     const bool f64 = p->d.precision == GRAV_FP64;
-    const dim3 fgrid((unsigned)((nfill + 255) / 256));
+    const dim3 fgrid = block_grid((nfill + 255) / 256);
     if (f64)
         hipLaunchKernelGGL((k_rho_blocks<double>), fgrid, dim3(256), 0, s, g, rho, p->lat_Q, nplB,
                            p->d_rho_blk);
@@ -744,7 +749,7 @@ static grav_status launch_near_lat(Plan *p, const DevGeom &g, const double *rho,
     // a tile per wave once there are tiles for every wave slot of the chip,
     // else four waves per tile
     const bool per_wave = ntile >= GRAV_NEAR_WAVE_TILES;
-    dim3 grid((unsigned)(per_wave ? (ntile + 3) / 4 : ntile)), blk(256);
+    const dim3 grid = block_grid(per_wave ? (ntile + 3) / 4 : ntile), blk(256);
     const int64_t npts = p->d.n_points;
 #define NEAR_LAUNCH(NW)                                                                                            \
     if (f64)                                                                                                       \
@@ -802,7 +807,7 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
             } else {
                 if (p->n_spts > 0) {
                     const int64_t at = p->lev[L].me_off * p->B * p->PS, n4 = p->lev[L].n_src * p->B * (p->PS / 4);
-                    hipLaunchKernelGGL(k_leaf_f32, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, g,
+                    hipLaunchKernelGGL(k_leaf_f32, block_grid((n4 + 255) / 256), dim3(256), 0, s, g,
                                        (const double *)(p->d_me + at), n4, rows + at);
                     GRAV_HIP(hipGetLastError());
                 }
@@ -823,27 +828,27 @@ grav_status enqueue_forward(Plan *p, const double *rho, double *out, hipStream_t
     if (!p->lat_near || p->d.n_points > 0) {
         stage_begin(p, "p2p", s);
         // one workgroup per target leaf holding user points
-        const dim3 pgrid((unsigned)p->n_user_leaves);
+        const dim3 pgrid = block_grid(std::max<int64_t>(p->n_user_leaves, 1));
         const int32_t *ul = (const int32_t *)p->d_user_leaves;
         if (p->n_user_leaves == 0) {
         } else if (p->n_spts > 0 && p->d.precision == GRAV_FP64)
             hipLaunchKernelGGL(k_p2p_src<double>, pgrid, dim3(256), 0, s, g, (const double *)p->d_smass,
                                (const double *)p->d_spos, (const int64_t *)p->d_sstart, p->n_spts, (const double *)p->d_tpos,
                                (const int64_t *)p->d_leaf_start, (const int64_t *)p->d_leaf_pend,
-                               (const uint32_t *)p->d_tkey, ul, p->d_near);
+                               (const uint32_t *)p->d_tkey, ul, p->n_user_leaves, p->d_near);
         else if (p->n_spts > 0)
             hipLaunchKernelGGL(k_p2p_src<float>, pgrid, dim3(256), 0, s, g, (const double *)p->d_smass,
                                (const double *)p->d_spos, (const int64_t *)p->d_sstart, p->n_spts, (const double *)p->d_tpos,
                                (const int64_t *)p->d_leaf_start, (const int64_t *)p->d_leaf_pend,
-                               (const uint32_t *)p->d_tkey, ul, p->d_near);
+                               (const uint32_t *)p->d_tkey, ul, p->n_user_leaves, p->d_near);
         else if (p->d.precision == GRAV_FP64)
             hipLaunchKernelGGL(k_p2p<double>, pgrid, dim3(256), 0, s, g, rho,
                                (const double *)p->d_tpos, (const int64_t *)p->d_leaf_start,
-                               (const int64_t *)p->d_leaf_pend, (const uint32_t *)p->d_tkey, ul, p->d_near);
+                               (const int64_t *)p->d_leaf_pend, (const uint32_t *)p->d_tkey, ul, p->n_user_leaves, p->d_near);
         else
             hipLaunchKernelGGL(k_p2p<float>, pgrid, dim3(256), 0, s, g, rho,
                                (const double *)p->d_tpos, (const int64_t *)p->d_leaf_start,
-                               (const int64_t *)p->d_leaf_pend, (const uint32_t *)p->d_tkey, ul, p->d_near);
+                               (const int64_t *)p->d_leaf_pend, (const uint32_t *)p->d_tkey, ul, p->n_user_leaves, p->d_near);
         GRAV_HIP(hipGetLastError());
         stage_end(p, s);
         stage_begin(p, "l2p", s);

@@ -242,7 +242,10 @@ k_near_par(DevGeom g, NearGrid ng, const double *rho, const T *A, const double *
     double *ex = reinterpret_cast<double *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int blk = blockIdx.x % ng.n, bm = blockIdx.x / ng.n;
+    const int64_t id = block_id();
+    if (id >= (int64_t)ng.n * g.B)
+        return;
+    const int bm = (int)((uint32_t)id / (uint32_t)ng.n), blk = (int)((uint32_t)id - (uint32_t)bm * (uint32_t)ng.n);
     const int bx = blk % ng.nx, by = blk / ng.nx % ng.ny, bz = blk / (ng.nx * ng.ny);
     const int lx0 = bx * NB::LX, ly0 = by * NB::LY, lz0 = bz * NB::LZ;  // the block's first leaf
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
@@ -359,7 +362,10 @@ k_t_near_par(DevGeom g, NearGrid ng, const double *resid, int64_t npts, const T 
     double *ex = reinterpret_cast<double *>(smem);
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int blk = blockIdx.x % ng.n, bm = blockIdx.x / ng.n;
+    const int64_t id = block_id();
+    if (id >= (int64_t)ng.n * g.B)
+        return;
+    const int bm = (int)((uint32_t)id / (uint32_t)ng.n), blk = (int)((uint32_t)id - (uint32_t)bm * (uint32_t)ng.n);
     const int bx = blk % ng.nx, by = blk / ng.nx % ng.ny, bz = blk / (ng.nx * ng.ny);
     const int lx0 = bx * NB::LX, ly0 = by * NB::LY, lz0 = bz * NB::LZ;
     const double *r0 = resid + ((int64_t)bm * g.M + npts) * g.C;
@@ -441,7 +447,10 @@ k_t_l2p_par(DevGeom g, NearGrid ng, const double *resid, int64_t npts, const dou
     __shared__ int32_t srow[16], sadd[16];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int chi = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int blk = blockIdx.x % ng.n, bm = blockIdx.x / ng.n;
+    const int64_t id = block_id();
+    if (id >= (int64_t)ng.n * g.B)
+        return;
+    const int bm = (int)((uint32_t)id / (uint32_t)ng.n), blk = (int)((uint32_t)id - (uint32_t)bm * (uint32_t)ng.n);
     const int bx = blk % ng.nx, by = blk / ng.nx % ng.ny, bz = blk / (ng.nx * ng.ny);
     const int lx0 = bx * NB::LX, ly0 = by * NB::LY, lz0 = bz * NB::LZ;
     const DevLev &lv = g.lev[g.L];
@@ -536,7 +545,7 @@ grav_status near_grid(const Plan *p, NearGrid &ng, dim3 &grid)
     ng.n = ng.nx * ng.ny * ((lv.ns[2] + NB::LZ - 1) / NB::LZ);
     if ((int64_t)ng.n * p->B > 0x7fffffffll)
         return GRAV_EUNSUPPORTED;
-    grid = dim3((unsigned)(ng.n * p->B));
+    grid = block_grid((int64_t)ng.n * p->B);
     return GRAV_OK;
 }
 

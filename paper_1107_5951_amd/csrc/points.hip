@@ -85,6 +85,7 @@ struct PointArgs {
     const int64_t *start, *end;  // of a leaf's points in sorted order
     const uint32_t *tkey;
     const int32_t *leaves;  // the target leaves holding points
+    int64_t nleaf;          // their number
     int64_t limit;          // points of the caller's order from here on are set elsewhere
 };
 
@@ -283,8 +284,10 @@ k_t_l2p_points(DevGeom g, PointArgs ar, const double *w, double *le)
     const DevLev &lv = g.lev[g.L];
     const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t leaf = ar.leaves[blockIdx.x];
-    const int bm0 = blockIdx.y * MG;
+    if (block_id() >= ar.nleaf)
+        return;
+    const int64_t leaf = ar.leaves[block_id()];
+    const int bm0 = blockIdx.z * MG;
     const int64_t ts = ar.start[leaf], te = ar.end[leaf];
     double c[3];
     leaf_centre(g, ar.tkey[lv.tbox_off + leaf], c);
@@ -372,11 +375,13 @@ k_p2m_src(DevGeom g, const double *spos, const double *mass, const int64_t *ssta
     constexpr int TC = P <= 11 ? 64 : 32, TS = TC + 1;  // sources per chunk
     constexpr int NJ = (MG * P2 + 255) / 256;           // sums per thread, o = model P2 + coefficient
     __shared__ double H[P2 * TS], W[MG * TC];
-    const int64_t leaf = blockIdx.x;
-    const int bm0 = blockIdx.y * MG;
+    const DevLev &lv = g.lev[g.L];
+    const int64_t leaf = block_id();
+    if (leaf >= (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2])
+        return;
+    const int bm0 = blockIdx.z * MG;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const DevLev &lv = g.lev[g.L];
     const int lx = (int)(leaf % lv.ns[0]), ly = (int)((leaf / lv.ns[0]) % lv.ns[1]),
               lz = (int)(leaf / ((int64_t)lv.ns[0] * lv.ns[1]));
     const double inv_b = 1.0 / (double)g.b;
@@ -431,7 +436,8 @@ int64_t point_count(const Plan *p) { return p->lat_near ? p->d.n_points : p->M; 
 
 PointArgs point_args(const Plan *p)
 {
-    return PointArgs{p->d_tpos, p->d_leaf_start, p->d_leaf_pend, p->d_tkey, p->d_user_leaves, point_count(p)};
+    return PointArgs{p->d_tpos, p->d_leaf_start, p->d_leaf_pend, p->d_tkey, p->d_user_leaves, p->n_user_leaves,
+                     point_count(p)};
 }
 
 }  // namespace
@@ -477,7 +483,8 @@ grav_status launch_p2m_src(const Plan *p, const DevGeom &g, hipStream_t s)
 {
     constexpr int kModels = 4;
     const int MG = p->B == 1 ? 1 : kModels;
-    const dim3 grid((unsigned)p->lev[p->L].n_src, (unsigned)((p->B + MG - 1) / MG));
+    dim3 grid = block_grid(p->lev[p->L].n_src);
+    grid.z = (unsigned)((p->B + MG - 1) / MG);
 #define P2M_CASE(P)                                                                                              \
     case P:                                                                                                      \
         if (MG == 1)                                                                                             \
@@ -500,9 +507,10 @@ grav_status launch_p2m_src(const Plan *p, const DevGeom &g, hipStream_t s)
 grav_status launch_t_l2p_points(const Plan *p, const DevGeom &g, hipStream_t s)
 {
     const int MG = p->B == 1 ? 1 : kPointModels;
-    const dim3 grid((unsigned)p->n_user_leaves, (unsigned)((p->B + MG - 1) / MG));
-    if (grid.x == 0)
+    if (p->n_user_leaves == 0)
         return GRAV_OK;
+    dim3 grid = block_grid(p->n_user_leaves);
+    grid.z = (unsigned)((p->B + MG - 1) / MG);
 #define T_L2P_CASE(P)                                                                                            \
     case P:                                                                                                      \
         if (MG == 1)                                                                                             \
