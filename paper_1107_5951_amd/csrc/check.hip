@@ -169,7 +169,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
     const auto tkey = fetch(p->d_tkey, (size_t)ntb);
     const auto tmap = fetch(p->d_tmap, (size_t)p->n_tmap);
     const auto leaf_start = fetch(p->d_leaf_start, (size_t)p->n_leaf + 1);
-    const auto tleaf = fetch(p->d_tleaf, (size_t)p->M);
     const auto perm = fetch(p->d_perm, (size_t)p->M);
     const auto leaf_pend = fetch(p->d_leaf_pend, (size_t)p->n_leaf);
     const int64_t ncell = (int64_t)p->d.nx * p->d.ny * p->d.nz;
@@ -184,10 +183,6 @@ extern "C" grav_status grav_plan_check(grav_plan_t plan, char *msg, int32_t msgl
         ck.fail("tree", "leaf ranges do not cover the targets", leaf_start[p->n_leaf], p->M);
     std::vector<char> seen(p->M, 0);
     for (int64_t i = 0; i < p->M && ck.ok; ++i) {
-        if (tleaf[i] < 0 || tleaf[i] >= p->n_leaf)
-            ck.fail("tree", "target leaf out of range", tleaf[i], p->n_leaf);
-        else if (i < leaf_start[tleaf[i]] || i >= leaf_start[tleaf[i] + 1])
-            ck.fail("tree", "target outside its leaf range", i, tleaf[i]);
         if (perm[i] >= (uint64_t)p->M || seen[perm[i]])
             ck.fail("tree", "permutation not a bijection", perm[i], p->M);
         else

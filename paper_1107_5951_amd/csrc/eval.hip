@@ -685,7 +685,6 @@ DevGeom make_geom(const Plan *p)
     g.P = p->P;
     g.P2 = p->P2;
     g.PS = p->PS;
-    g.KS = p->KS;
     g.B = p->B;
     g.C = p->C;
     g.n[0] = p->d.nx;

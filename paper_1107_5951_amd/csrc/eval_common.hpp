@@ -19,7 +19,7 @@ struct DevLev {
 
 struct DevGeom {
     DevLev lev[kMaxLevels + 1];
-    int L, b, q, P, P2, PS, KS, B, C;
+    int L, b, q, P, P2, PS, B, C;
     int n[3];
     int shift[3];
     int64_t M;

@@ -47,7 +47,6 @@ struct OctGroup {      // 16 nc columns of one level
 };
 struct OctTables {
     const uint32_t *key;       // [noct] Morton key of the parent
-    const int32_t *child;      // [noct][8] row of each child octant, -1: none
     const OctGroup *groups;
     const int32_t *segs;       // [nseg][4] unit, its orbits (bit o - 1), slot, 0
     const int32_t *wgseg;      // [wgs + 1] segments of a workgroup
@@ -61,13 +60,14 @@ struct OctPlan {
     int64_t reach[kMaxLevels + 1] = {0};  // those from reach[l] on have no M2L input
     int32_t gfirst[kMaxLevels + 1] = {0}; // first group of level l
     int32_t *d_parent = nullptr;          // [noct] row of the parent, -1 at level 2
-    int32_t *d_child = nullptr, *d_segs = nullptr, *d_wgseg = nullptr;
+    int32_t *d_child = nullptr;           // [noct][8] row of each child octant, -1: none
+    int32_t *d_segs = nullptr, *d_wgseg = nullptr;
     int32_t *d_uslot = nullptr;
     OctGroup *d_groups = nullptr;
     void *d_ops = nullptr;  // operators as MFMA A fragments, in the M2L's element type
     OctTables tables() const
     {
-        return OctTables{d_key, d_child, d_groups, d_segs, d_wgseg, d_uslot};
+        return OctTables{d_key, d_groups, d_segs, d_wgseg, d_uslot};
     }
 };
 // Compile-time shape of the M2L kernel (OctShape in octet.hpp).
@@ -91,7 +91,6 @@ struct Plan {
     grav_plan_desc d{};
     int device = 0;
     int P = 0, P2 = 0, PS = 0;     // order, p^2, padded stride (multiple of 16)
-    int KS = 0;                    // k-steps of 4 covering P2
     int q = 1, nq3 = 1, b = 1;     // quadrature points per axis, per cell, leaf edge in cells
     int L = 0;                     // leaf level
     int B = 1, C = 3;
@@ -119,7 +118,6 @@ struct Plan {
     int64_t *d_sstart = nullptr;   // [leaves of the leaf-level source block + 1]
     uint32_t *d_perm = nullptr;    // [M] sorted position -> user index
     double *d_tpos = nullptr;      // [M][3] sorted target positions
-    int32_t *d_tleaf = nullptr;    // [M] sorted target -> leaf (index in level-L list)
     int64_t *d_leaf_start = nullptr; // [n_leaf + 1]
     uint32_t *d_tkey = nullptr;    // [n_tbox_all] Morton key of every target box, per level
     int64_t tbox_off[kMaxLevels + 1] = {0}; // start of each level in the array above
@@ -174,7 +172,7 @@ struct Plan {
     // lattice P2M by octets (p2m.hip) as MFMA A fragments: leaf, parent by
     // class, and their transposes (rows: cells, to whole sets of row blocks)
     double *d_pm = nullptr, *d_pm_up = nullptr, *d_pmt = nullptr, *d_pmt_down = nullptr;
-    double *d_me = nullptr;        // [n_me][B][PS]
+    double *d_me = nullptr;        // [n_me][B][PS], without the leaves' in mixed plans with lattice sources
     double *d_le = nullptr;        // [n_tbox][B][PS]
     double *d_near = nullptr;      // [M][B][4] near field (phi, gx, gy, gz), sorted order
 

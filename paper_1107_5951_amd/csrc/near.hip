@@ -52,7 +52,7 @@ constexpr int kOctant = 216;  // base cells of a leaf's neighbourhood
 // A workgroup's leaves: 4 x LY x LZ = 16 NC columns, the cells around them.
 template <int NC>
 struct NearBlock {
-    static constexpr int LX = 4, LY = NC == 1 ? 2 : 4, LZ = NC == 4 ? 4 : 2;
+    static constexpr int LX = 4, LY = NC == 1 ? 2 : 4, LZ = 2;
     static constexpr int DX = 4 * (LX + 2), DY = 4 * (LY + 2), DZ = 4 * (LZ + 2);
     static constexpr int NCOL = 16 * NC;
 };

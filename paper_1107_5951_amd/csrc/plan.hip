@@ -123,15 +123,14 @@ __global__ void k_head_flags(const uint32_t *keys, int64_t n, int sh, uint32_t *
     flags[i] = (i == 0 || (keys[i] >> sh) != (keys[i - 1] >> sh)) ? 1u : 0u;
 }
 
-// Leaf level: sorted target -> leaf id, leaf start offsets, leaf keys.
+// Leaf level: leaf start offsets, leaf keys.
 __global__ void k_leaf_build(const uint32_t *keys, const uint32_t *flags, const uint32_t *scan,
-                             int64_t n, int32_t *tleaf, int64_t *leaf_start, uint32_t *leaf_key)
+                             int64_t n, int64_t *leaf_start, uint32_t *leaf_key)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
     const uint32_t id = scan[i] + flags[i] - 1u;
-    tleaf[i] = (int32_t)id;
     if (flags[i]) {
         leaf_start[id] = i;
         leaf_key[id] = keys[i];
@@ -292,7 +291,7 @@ void free_plan(Plan *p)
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p->device);
-    void *bufs[] = {p->d_points, p->d_perm, p->d_tpos, p->d_tleaf, p->d_leaf_start, p->d_tkey,
+    void *bufs[] = {p->d_points, p->d_perm, p->d_tpos, p->d_leaf_start, p->d_tkey,
                     p->d_class_off, p->d_tmap, p->d_geom, p->d_pm, p->d_pm_up, p->d_pmt, p->d_pmt_down, p->d_m2m, p->d_l2l, p->d_m2mt,
                     p->d_l2lt, p->d_class_coef, p->d_me, p->d_le, p->d_near, p->d_part, p->d_rows,
                     p->d_tn64, p->d_tn32, p->d_rho_blk, p->d_tl2p, p->d_dpart,
@@ -1634,8 +1633,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
     ka.L = p->L;
 
     do {
-        if (dalloc(p, &p->d_perm, M, true) || dalloc(p, &p->d_tpos, 3 * M, true) ||
-            dalloc(p, &p->d_tleaf, M, true)) {
+        if (dalloc(p, &p->d_perm, M, true) || dalloc(p, &p->d_tpos, 3 * M, true)) {
             fail(GRAV_ENOMEM);
             break;
         }
@@ -1702,7 +1700,7 @@ grav_status build_tree(Plan *p, hipStream_t s)
             break;
         }
         hipLaunchKernelGGL(k_leaf_build, dim3(gM), dim3(T), 0, s, (const uint32_t *)keys,
-                           (const uint32_t *)flags, (const uint32_t *)scan, M, p->d_tleaf,
+                           (const uint32_t *)flags, (const uint32_t *)scan, M,
                            p->d_leaf_start, bk + off_bound[L]);
         hipLaunchKernelGGL(k_fill_last, dim3(1), dim3(1), 0, s, p->d_leaf_start, p->n_leaf, M);
         bool ok = true;
@@ -1819,7 +1817,6 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
         p->P = desc->p;
         p->P2 = p->P * p->P;
         p->PS = (int)ceil_div(p->P2, 16) * 16;
-        p->KS = (int)ceil_div(p->P2, 4);
         p->q = desc->quad_order;
         p->nq3 = p->q * p->q * p->q;
         p->B = desc->batch;
@@ -1919,7 +1916,10 @@ extern "C" grav_status grav_plan(const grav_plan_desc *desc, grav_plan_t *out)
         if (p->M > 0 && (st = count_work(p)) != GRAV_OK)
             break;
         // workspace
-        if ((st = dalloc(p, &p->d_me, (size_t)p->n_me * p->B * p->PS, false)) != GRAV_OK)
+        // (mixed plans keep the expansions of lattice leaves in FP32 alone: d_rows)
+        const bool leaves = p->d.precision == GRAV_FP64 || p->n_spts > 0 || p->L < 2;
+        if ((st = dalloc(p, &p->d_me, (size_t)(leaves ? p->n_me : p->lev[p->L].me_off) * p->B * p->PS, false)) !=
+            GRAV_OK)
             break;
         if ((st = dalloc(p, &p->d_le, (size_t)p->n_tbox * p->B * p->PS, false)) != GRAV_OK)
             break;
