@@ -1001,18 +1001,22 @@ __global__ void k_user_leaves(const int64_t *leaf_start, const int64_t *pend, in
         list[atomicAdd(count, 1ull)] = (int32_t)tl;
 }
 
-// The points of those leaves in runs of at most `len`, in any order.
+// The points of those leaves in runs of about len, whole multiples of `step`, in
+// any order; a leaf of less than 2 len stays whole (cut at len, 2048 leaves of
+// about 160 points leave a few short runs over that no longer fit the CUs at
+// once: 17.0 against 14.6 us).
 __global__ void k_point_runs(const int64_t *leaf_start, const int64_t *pend, const int32_t *leaves, int64_t n,
-                             int64_t len, PointRun *runs, unsigned long long *count)
+                             int64_t len, int64_t step, PointRun *runs, unsigned long long *count)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
     const int32_t leaf = leaves[i];
     const int64_t s = max(leaf_start[leaf], (int64_t)0), m = pend[leaf] - s;
-    unsigned long long at = atomicAdd(count, (unsigned long long)((m + len - 1) / len));
-    for (int64_t k = 0; k < m; k += len)
-        runs[at++] = PointRun{s + k, leaf, (int32_t)min(len, m - k)};
+    const int64_t parts = max(m / len, (int64_t)1), per = (m + parts * step - 1) / (parts * step) * step;
+    unsigned long long at = atomicAdd(count, (unsigned long long)((m + per - 1) / per));
+    for (int64_t k = 0; k < m; k += per)
+        runs[at++] = PointRun{s + k, leaf, (int32_t)min(per, m - k)};
 }
 
 grav_status build_adjoint_maps(Plan *p)
@@ -1074,7 +1078,7 @@ grav_status build_adjoint_maps(Plan *p)
         // leave kRunBlocks workgroups, half as many with several models
         const int64_t np = p->lat_near ? p->d.n_points : p->M, mg = std::min(p->B, 8);
         const int64_t blocks = p->B == 1 ? kRunBlocks : kRunBlocks / 2, least = p->B == 1 ? 1 : 2;
-        const int64_t len = std::max(ceil_div(np * p->B, 64 * blocks), least) * 64 / mg;
+        const int64_t step = 64 / mg, len = std::max(ceil_div(np * p->B, 64 * blocks), least) * step;
         if (st == GRAV_OK && p->n_user_leaves > 0) {
             p->n_runs = 0;
             st = dalloc(p, &p->d_runs, (size_t)(p->n_user_leaves + np / len), true);
@@ -1083,7 +1087,7 @@ grav_status build_adjoint_maps(Plan *p)
             if (st == GRAV_OK) {
                 hipLaunchKernelGGL(k_point_runs, dim3((unsigned)ceil_div(p->n_user_leaves, 256)), dim3(256), 0, p->bs,
                                    (const int64_t *)p->d_leaf_start, (const int64_t *)p->d_leaf_pend,
-                                   (const int32_t *)p->d_user_leaves, p->n_user_leaves, len, p->d_runs, cnt);
+                                   (const int32_t *)p->d_user_leaves, p->n_user_leaves, len, step, p->d_runs, cnt);
                 if (hipGetLastError() != hipSuccess ||
                     hipMemcpyAsync(n, cnt, sizeof(n[0]), hipMemcpyDeviceToHost, p->bs) != hipSuccess ||
                     hipStreamSynchronize(p->bs) != hipSuccess)

@@ -93,6 +93,7 @@ struct PointArgs {
 struct RunArgs {
     const PointRun *runs;
     int64_t n, nblk, groups;
+    int lw;  // runs per workgroup
 };
 
 __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, double (&c)[3])
@@ -106,9 +107,9 @@ __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, doub
 // meet in LDS.  A workgroup takes a run of a leaf's points (a workgroup per leaf
 // walked all of them: 1024^2 stations above 16^3 cells are 16 leaves of 65536
 // points, 2.20 ms a leaf at a time, 0.07 ms in runs; a thread per point took
-// 0.14).  Where leaves hold few points (scattered ones), a workgroup of a
-// single-model plan takes LW runs, so that its lanes are not mostly idle.
-// far: whether there is a far field (L >= 2).
+// 0.14).  A workgroup of a single-model plan with many runs takes up to LW of
+// them, so that its lanes are not mostly idle (runs_per_workgroup).  far: whether
+// there is a far field (L >= 2).
 template <int P, int MG, int LW>
 __global__ void __launch_bounds__(256)
 k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const double *le, const double *near, int far,
@@ -129,8 +130,9 @@ k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const do
         return;
     const int64_t lb = blk % rn.nblk;
     const int bm0 = (int)(blk / rn.nblk) * MG, nm = min(MG, g.B - bm0);
-    const int nl = (int)min((int64_t)LW, rn.n - lb * LW);
-    const PointRun *runs = rn.runs + lb * LW;
+    const int lw = LW == 1 ? 1 : rn.lw;
+    const int nl = (int)min((int64_t)lw, rn.n - lb * lw);
+    const PointRun *runs = rn.runs + lb * lw;
     const double inv_w = 1.0 / (double)g.b;
     if (tid < nl) {
         const PointRun r = runs[tid];
@@ -445,13 +447,34 @@ PointArgs point_args(const Plan *p)
 #define GRAV_ORDERS(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
+// Runs per workgroup of a single-model plan: so many that about 1024 workgroups,
+// all resident at once, take all, up to 8, or 16 where there are very many; 512
+// up to 16 where leaves hold few points; fewer at low orders, whose steps cost
+// less than idle lanes; a run of more than a step fills the lanes by itself and
+// gains from 4 at most.
+// Points per leaf, 9 unless given, p = 10, us, with 1 / 2 / 4 / 8 / 16 runs:
+//   512 leaves   8.0 / 7.8 / 8.5 / 11.8 / 16.5;  4096   24.5 / 15.7 / 10.9 / 13.0 / 16.7
+//   8192         43.8 / 26.2 / 16.9 / 15.6 / 18.5;  of 1   29.4 / 18.8 / 14.2 / 10.8 / 12.0
+//   16384 of 3   76.7 / 43.7 / 27.6 / 19.2 / 16.2;  of 20  81.0 / 46.3 / 41.8 / 35.6 / 34.8
+//   32768        152 / 83 / 51 / 46 / 40;  p = 4, of 160 in 4096   23.0 / 21.3 / 27.0 / 46 / 85
+//   p = 6, of 40 in 16384   47.8 / 37.5 / 31.6 / 35.9 / 37.8;  p = 8   73.0 / 60.0 / 47.6 / 45.9 / 46.0
+static int runs_per_workgroup(const Plan *p)
+{
+    if (p->B > 1)
+        return 1;
+    const int64_t n = p->n_runs, np = point_count(p);
+    if (np < 8 * n)
+        return (int)std::clamp<int64_t>((n + 511) / 512, 1, 16);
+    if (np > 64 * n)
+        return (int)std::clamp<int64_t>((n + 2047) / 2048, 1, 4);
+    const int wgs = p->P < 6 ? 2048 : 1024;
+    return (int)std::clamp<int64_t>((n + wgs - 1) / wgs, 1, n > 24576 ? 16 : 8);
+}
+
 grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s)
 {
-    // 65536 random points, two per leaf, p = 10: 122 us a leaf at a time,
-    // 68 us with 16
-    const bool few = p->B == 1 && point_count(p) < 8 * p->n_user_leaves;
-    const int MG = p->B == 1 ? 1 : kPointModels, LW = few ? 16 : 1;
-    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + LW - 1) / LW, (p->B + MG - 1) / MG};
+    const int MG = p->B == 1 ? 1 : kPointModels, lw = runs_per_workgroup(p);
+    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + MG - 1) / MG, lw};
     if (p->n_runs == 0)
         return GRAV_OK;
     const dim3 grid = block_grid(rn.nblk * rn.groups);
@@ -461,8 +484,10 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
                        p->L >= 2 ? 1 : 0, out)
 #define L2P_CASE(P)                                                                                              \
     case P:                                                                                                      \
-        if (few)                                                                                                 \
+        if (lw > 4)                                                                                              \
             L2P_LAUNCH(P, 1, 16);                                                                                \
+        else if (lw > 1)                                                                                         \
+            L2P_LAUNCH(P, 1, 4);                                                                                 \
         else if (p->B == 1)                                                                                      \
             L2P_LAUNCH(P, 1, 1);                                                                                 \
         else                                                                                                     \

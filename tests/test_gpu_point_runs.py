@@ -1,6 +1,7 @@
 """L2P of leaves that hold many points, whose points are cut into runs: run
 ends on and off whole steps of 64 (point, model) pairs, one and several groups
-of models, single points in other leaves.
+of models, single points in other leaves.  Many leaves of a single model, up to
+16 of whose runs share a workgroup.
 
 Bar: a point's field does not depend on the other points of its plan, so every
 field equals that of the same point in plans of few points (the same tree, no
@@ -15,7 +16,7 @@ G = pytest.importorskip("paper_1107_5951_amd")
 
 
 @pytest.mark.parametrize("batch", [1, 3, 8, 9])
-@pytest.mark.parametrize("npts", [63, 64, 65, 1000])
+@pytest.mark.parametrize("npts", [63, 64, 65, 127, 128, 1000])
 def test_point_runs(npts, batch):
     rng = np.random.default_rng(npts)
     frame = np.array([[-3.0, -3.0, -3.0], [30.0, 30.0, 30.0]])  # in every plan: one root box
@@ -34,3 +35,26 @@ def test_point_runs(npts, batch):
     for at in range(0, npts, few):
         ref = plan(pts[at:at + few]).eval(rho)[:, :-2]
         assert float((g[:, at:at + few][:, :ref.shape[1]] - ref).norm() / ref.norm()) <= 1e-12
+
+
+@pytest.mark.parametrize("p, leaves, per", [(10, 512, 1), (10, 513, 1), (10, 1024, 9), (10, 1025, 9), (10, 2049, 70),
+                                            (3, 4097, 20), (10, 8191, 3), (10, 8192, 11)])
+def test_runs_per_workgroup(p, leaves, per):
+    """Two models take a workgroup per run."""
+    n = np.array([128, 64, 64])
+    rng = np.random.default_rng(leaves)
+    ids = rng.permutation(n.prod() // 64)[:leaves]
+    corner = 4.0 * np.stack([ids % 32, ids // 32 % 16, ids // 512], axis=1)
+    pts = np.repeat(corner, per, axis=0)
+    pts = pts + rng.uniform(0.1, 3.9, size=pts.shape)
+
+    def plan(batch):
+        return G.Plan(G.PlanSpec(n=tuple(int(v) for v in n), h=1.0, voxel_centres=False, components=3, p=p, leaf_size=64,
+                                 points=pts, precision=G.GRAV_FP64, batch=batch))
+
+    one, two = plan(1), plan(2)
+    assert one.n_target_leaves == leaves
+    rho = torch.randn(one.rho_shape, dtype=torch.float64, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(leaves))
+    ref = two.eval(torch.stack([rho.reshape(two.rho_shape[1:])] * 2))[1]
+    assert float((one.eval(rho).reshape(ref.shape) - ref).norm() / ref.norm()) <= 1e-12
