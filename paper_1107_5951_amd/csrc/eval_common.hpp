@@ -56,6 +56,7 @@ grav_status launch_t_l2p_par(const Plan *p, const DevGeom &g, const double *resi
 grav_status launch_t_near_par(const Plan *p, const DevGeom &g, const double *resid, int add, double *drho, hipStream_t s);
 OctInfo octet_info(int P, bool f64);
 grav_status m2l_resident_workgroups(const Plan *p, int nc, int *workers);
+grav_status l2p_resident_workgroups(const Plan *p, int *workers);
 grav_status begin_call(Plan *p, hipStream_t s);
 grav_status end_call(Plan *p, hipStream_t s);
 

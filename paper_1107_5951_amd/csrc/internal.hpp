@@ -165,6 +165,7 @@ struct Plan {
     int64_t n_user_leaves = 0;                     // the point near field
     PointRun *d_runs = nullptr;                    // their points in runs (any order), for the L2P
     int64_t n_runs = 0;
+    int l2p_wgs = 0;                               // workgroups of the L2P that are resident at once
     int32_t *d_class_off = nullptr;  // [8][189][4] (dx, dy, dz, offset id)
     int32_t *d_tmap = nullptr;       // per level: target-box index over source block + halo 3
     struct DevGeom *d_geom = nullptr;

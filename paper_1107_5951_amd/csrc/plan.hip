@@ -37,8 +37,7 @@
 #define GRAV_NEAR_DENSE_BLOCKS 512
 #endif
 
-// Workgroups that the runs of points are cut for (see build_adjoint_maps).  L2P
-// with 1024 / 2048 / 4096 / 8192: one model at 1024^2 stations above 16^3 cells, p
+// Workgroups that the runs of points are cut for on single-model plans.  L2P with 1024 / 2048 / 4096 / 8192: one model at 1024^2 stations above 16^3 cells, p
 // = 10, 68 / 65 / 68 / 71 us, FP64 p = 14 133 / 119 / 119 / 123; several models load
 // their expansions again with every run: 64 at 64^2 stations 22 / 25 / 35 / 32 us, and
 // 18 over 76^3 cells, 16 points a leaf, 14.7 whole and 19.0 in two runs of one step.
@@ -1001,19 +1000,18 @@ __global__ void k_user_leaves(const int64_t *leaf_start, const int64_t *pend, in
         list[atomicAdd(count, 1ull)] = (int32_t)tl;
 }
 
-// The points of those leaves in runs of about len, whole multiples of `step`, in
-// any order; a leaf of less than 2 len stays whole (cut at len, 2048 leaves of
-// about 160 points leave a few short runs over that no longer fit the CUs at
-// once: 17.0 against 14.6 us).
+// The points of those leaves in runs of about len, multiples of `step`, in any
+// order; a leaf of less than `whole` stays whole.
 __global__ void k_point_runs(const int64_t *leaf_start, const int64_t *pend, const int32_t *leaves, int64_t n,
-                             int64_t len, int64_t step, PointRun *runs, unsigned long long *count)
+                             int64_t len, int64_t step, int64_t whole,
+                             PointRun *runs, unsigned long long *count)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
     const int32_t leaf = leaves[i];
     const int64_t s = max(leaf_start[leaf], (int64_t)0), m = pend[leaf] - s;
-    const int64_t parts = max(m / len, (int64_t)1), per = (m + parts * step - 1) / (parts * step) * step;
+    const int64_t parts = m < whole ? 1 : max(m / len, (int64_t)1), per = (m + parts * step - 1) / (parts * step) * step;
     unsigned long long at = atomicAdd(count, (unsigned long long)((m + per - 1) / per));
     for (int64_t k = 0; k < m; k += per)
         runs[at++] = PointRun{s + k, leaf, (int32_t)min(per, m - k)};
@@ -1075,10 +1073,16 @@ grav_status build_adjoint_maps(Plan *p)
         p->n_pt_leaves = (int64_t)n[0];
         p->n_user_leaves = (int64_t)n[1];
         // runs for the L2P: steps of 64 (point, model) pairs, as many a run as
-        // leave kRunBlocks workgroups, half as many with several models
-        const int64_t np = p->lat_near ? p->d.n_points : p->M, mg = std::min(p->B, 8);
-        const int64_t blocks = p->B == 1 ? kRunBlocks : kRunBlocks / 2, least = p->B == 1 ? 1 : 2;
-        const int64_t step = 64 / mg, len = std::max(ceil_div(np * p->B, 64 * blocks), least) * step;
+        // leave kRunBlocks workgroups, those resident with several models.
+        // Leaves that a resident workgroup takes in two rounds stay whole: a few
+        // cut ones more than fit the CUs at once cost a round (p = 16, 512 leaves
+        // of about 100 points: 16.3 us, 24.2 with some cut)
+        if (st == GRAV_OK)
+            st = l2p_resident_workgroups(p, &p->l2p_wgs);
+        const int64_t np = p->lat_near ? p->d.n_points : p->M, mg = std::min(p->B, 8), wgs = std::max(p->l2p_wgs, 1);
+        const int64_t blocks = p->B == 1 ? kRunBlocks : wgs, least = p->B == 1 ? 1 : 2, step = 64 / mg;
+        const int64_t len = std::max(ceil_div(np * p->B, 64 * blocks), least) * step;
+        const int64_t whole = 2 * std::max(len, ceil_div(np * p->B, 64 * wgs) * step);
         if (st == GRAV_OK && p->n_user_leaves > 0) {
             p->n_runs = 0;
             st = dalloc(p, &p->d_runs, (size_t)(p->n_user_leaves + np / len), true);
@@ -1087,7 +1091,8 @@ grav_status build_adjoint_maps(Plan *p)
             if (st == GRAV_OK) {
                 hipLaunchKernelGGL(k_point_runs, dim3((unsigned)ceil_div(p->n_user_leaves, 256)), dim3(256), 0, p->bs,
                                    (const int64_t *)p->d_leaf_start, (const int64_t *)p->d_leaf_pend,
-                                   (const int32_t *)p->d_user_leaves, p->n_user_leaves, len, step, p->d_runs, cnt);
+                                   (const int32_t *)p->d_user_leaves, p->n_user_leaves, len, step, whole, p->d_runs,
+                                   cnt);
                 if (hipGetLastError() != hipSuccess ||
                     hipMemcpyAsync(n, cnt, sizeof(n[0]), hipMemcpyDeviceToHost, p->bs) != hipSuccess ||
                     hipStreamSynchronize(p->bs) != hipSuccess)

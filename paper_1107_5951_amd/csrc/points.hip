@@ -21,6 +21,7 @@ namespace grav {
 namespace {
 
 constexpr int kPointModels = 8;  // models per workgroup (1 on single-model plans)
+constexpr int kRunsPerWorkgroup = 16;
 
 // Wave w of four takes the orders m = w, 7 - w, 8 + w, 15 - w: columns of
 // about equal length together.
@@ -93,8 +94,12 @@ struct PointArgs {
 struct RunArgs {
     const PointRun *runs;
     int64_t n, nblk, groups;
-    int lw;  // runs per workgroup
+    int lw, mg;  // runs and models per workgroup
 };
+
+// Expansions of a workgroup of several runs: within 16 KB up to p = 11, 16 above
+// (all that the registers let a CU hold fit its LDS).
+__host__ __device__ constexpr int l2p_slots(int P) { return P > 11 ? 16 : 2048 / (P * P) < 64 ? 2048 / (P * P) : 64; }
 
 __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, double (&c)[3])
 {
@@ -107,16 +112,16 @@ __device__ __forceinline__ void leaf_centre(const DevGeom &g, uint32_t key, doub
 // meet in LDS.  A workgroup takes a run of a leaf's points (a workgroup per leaf
 // walked all of them: 1024^2 stations above 16^3 cells are 16 leaves of 65536
 // points, 2.20 ms a leaf at a time, 0.07 ms in runs; a thread per point took
-// 0.14).  A workgroup of a single-model plan with many runs takes up to LW of
-// them, so that its lanes are not mostly idle (runs_per_workgroup).  far: whether
-// there is a far field (L >= 2).
+// 0.14).  With LW > 1 it takes rn.lw runs, at most LW, so that its lanes are not
+// mostly idle (runs_per_workgroup); their (run, model) pairs share the MG LW
+// expansions in LDS.  far: whether there is a far field (L >= 2).
 template <int P, int MG, int LW>
 __global__ void __launch_bounds__(256)
 k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const double *le, const double *near, int far,
              double *out)
 {
-    static_assert(MG == 1 || LW == 1, "several leaves for several models");
-    constexpr int P2 = P * P, LS = P2 | 1, NS = MG * LW;
+    static_assert(MG == 1 || LW == 1, "the expansions in LDS are counted for one of the two");
+    constexpr int P2 = P * P, LS = P2 | 1, NS = LW == 1 ? MG : l2p_slots(P);
     __shared__ double sL[NS * LS];
     __shared__ double sum[4][4][64];
     __shared__ double sc[LW][3];
@@ -129,7 +134,8 @@ k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const do
     if (blk >= rn.nblk * rn.groups)
         return;
     const int64_t lb = blk % rn.nblk;
-    const int bm0 = (int)(blk / rn.nblk) * MG, nm = min(MG, g.B - bm0);
+    const int mgrp = LW == 1 ? MG : rn.mg;
+    const int bm0 = (int)(blk / rn.nblk) * mgrp, nm = min(mgrp, g.B - bm0);
     const int lw = LW == 1 ? 1 : rn.lw;
     const int nl = (int)min((int64_t)lw, rn.n - lb * lw);
     const PointRun *runs = rn.runs + lb * lw;
@@ -144,12 +150,21 @@ k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const do
         st[tid] = r.start;
         sn[tid + 1] = r.n;
     }
-    if (far)
-        for (int i = tid; i < (LW == 1 ? nm : nl) * P2; i += 256) {
-            const int64_t leaf = runs[LW == 1 ? 0 : i / P2].leaf;
-            sL[i / P2 * LS + i % P2] =
-                le[((lv.tgt_off + leaf) * g.B + bm0 + (LW == 1 ? i / P2 : 0)) * g.PS + i % P2];
+    auto fetch = [&](int sl, int l, int m, int k) {
+        sL[sl * LS + k] = le[((lv.tgt_off + runs[l].leaf) * g.B + bm0 + m) * g.PS + k];
+    };
+    // a run's models lie side by side
+    if (far && (LW == 1 || nm == 1 || P2 < 64)) {
+        for (int i = tid; i < nl * nm * P2; i += 256) {
+            const int sl = i / P2, l = LW == 1 ? 0 : nm == 1 ? sl : sl / nm;
+            fetch(sl, l, LW == 1 ? sl : sl - l * nm, i - sl * P2);
         }
+    } else if (far) {
+        // (a division for each of many coefficients takes longer)
+        for (int l = 0; l < nl; ++l)
+            for (int i = tid; i < nm * P2; i += 256)
+                fetch(l * nm + i / P2, l, i / P2, i % P2);
+    }
     __syncthreads();
     if (tid == 0) {
         sn[0] = 0;
@@ -160,16 +175,20 @@ k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const do
     const int np = sn[nl];
     for (int64_t u0 = 0; u0 < (int64_t)np * nm; u0 += 64) {
         const int64_t u = min(u0 + lane, (int64_t)np * nm - 1);
-        const int mg = LW == 1 ? (int)(u / np) : 0;
-        int l = 0;
-        if constexpr (LW > 1)
+        int mg = 0, l = 0;
+        if (LW == 1 || nm > 1)
+            mg = (int)(u / np);
+        int64_t at = u - (int64_t)mg * np;  // among the model's points
+        if constexpr (LW > 1) {
             for (int k = 1; k < nl; ++k)
-                l = u >= sn[k] ? k : l;
-        const int64_t i = st[l] + (u - (LW == 1 ? (int64_t)mg * np : sn[l]));
+                l = at >= sn[k] ? k : l;
+            at -= sn[l];
+        }
+        const int64_t i = st[l] + at;
         if (far) {
             const double x = (ar.tpos[3 * i + 0] - sc[l][0]) * inv_w, y = (ar.tpos[3 * i + 1] - sc[l][1]) * inv_w,
                          z = (ar.tpos[3 * i + 2] - sc[l][2]) * inv_w;
-            const CoefArray L{sL + (LW == 1 ? mg : l) * LS};
+            const CoefArray L{sL + (l * nm + mg) * LS};
             double phi = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
             // pairs R_n^m with the coefficients of l2p_eval_t
             harmonics_by_wave<P>(w, x, y, z, [&](int n, int m, double Rr, double Ri) {
@@ -378,8 +397,8 @@ k_p2m_src(DevGeom g, const double *spos, const double *mass, const int64_t *ssta
     constexpr int NJ = (MG * P2 + 255) / 256;           // sums per thread, o = model P2 + coefficient
     __shared__ double H[P2 * TS], W[MG * TC];
     const DevLev &lv = g.lev[g.L];
-    const int64_t leaf = block_id();
-    if (leaf >= (int64_t)lv.ns[0] * lv.ns[1] * lv.ns[2])
+    const uint32_t leaf = (uint32_t)block_id();
+    if (leaf >= (uint32_t)lv.ns[0] * lv.ns[1] * lv.ns[2])
         return;
     const int bm0 = blockIdx.z * MG;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -447,34 +466,54 @@ PointArgs point_args(const Plan *p)
 #define GRAV_ORDERS(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
-// Runs per workgroup of a single-model plan: so many that about 1024 workgroups,
-// all resident at once, take all, up to 8, or 16 where there are very many; 512
-// up to 16 where leaves hold few points; fewer at low orders, whose steps cost
-// less than idle lanes; a run of more than a step fills the lanes by itself and
-// gains from 4 at most.
-// Points per leaf, 9 unless given, p = 10, us, with 1 / 2 / 4 / 8 / 16 runs:
-//   512 leaves   8.0 / 7.8 / 8.5 / 11.8 / 16.5;  4096   24.5 / 15.7 / 10.9 / 13.0 / 16.7
-//   8192         43.8 / 26.2 / 16.9 / 15.6 / 18.5;  of 1   29.4 / 18.8 / 14.2 / 10.8 / 12.0
-//   16384 of 3   76.7 / 43.7 / 27.6 / 19.2 / 16.2;  of 20  81.0 / 46.3 / 41.8 / 35.6 / 34.8
-//   32768        152 / 83 / 51 / 46 / 40;  p = 4, of 160 in 4096   23.0 / 21.3 / 27.0 / 46 / 85
-//   p = 6, of 40 in 16384   47.8 / 37.5 / 31.6 / 35.9 / 37.8;  p = 8   73.0 / 60.0 / 47.6 / 45.9 / 46.0
-static int runs_per_workgroup(const Plan *p)
+// Workgroups of the L2P that the GPU holds at once.
+grav_status l2p_resident_workgroups(const Plan *p, int *workers)
 {
-    if (p->B > 1)
+    const void *fn = nullptr;
+#define FN_CASE(X)                                                                                               \
+    case X:                                                                                                      \
+        fn = p->B == 1 ? reinterpret_cast<const void *>(&k_l2p_points<X, 1, 1>)                                  \
+                       : reinterpret_cast<const void *>(&k_l2p_points<X, kPointModels, 1>);                      \
+        break;
+    switch (p->P) {
+        GRAV_ORDERS(FN_CASE)
+    default:
+        return GRAV_EUNSUPPORTED;
+    }
+#undef FN_CASE
+    int per_cu = 0, cus = 0;
+    GRAV_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0));
+    GRAV_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    *workers = std::max(per_cu * cus, 1);
+    return GRAV_OK;
+}
+
+// Runs per workgroup: so many that those resident at once take all, up to 16;
+// where runs are longer than a step, and so fill the lanes by themselves, so many
+// that twice as many workgroups take all, up to 4; one of two steps or more with
+// several models (p = 16, 4096 leaves of 20, 8 models: 161 us, with two 172).  One
+// model, points per leaf, 9 unless given, us, with 1 / 2 / 4 / 8 / 16 runs:
+//   p = 10 (1024 resident)  512 leaves  8.0 / 7.8 / 8.5 / 11.8 / 16.5
+//     4096   24.5 / 15.7 / 10.9 / 13.0 / 16.7;  8192   43.8 / 26.2 / 16.9 / 15.6 / 18.5
+//     16384 of 20   81.0 / 46.3 / 41.8 / 35.6 / 34.8;  32768   152 / 83 / 51 / 46 / 40
+//     8192 of 80   69.6 / 53.8 / 51.6 / 52.2 / 75.1
+//   p = 4 (2048)   4096   12.0 / 8.7 / 7.6 / 8.9 / 11.2;  of 160   23.0 / 21.3 / 27.0 / 46 / 85
+//     8192 of 40   21.2 / 18.0 / 15.0 / 18.8 / 29.6
+//   p = 16 (512)   2048   30.9 / 19.3 / 12.6 / 16.5 / 24.0;  8192   104 / 59 / 37 / 35 / 29
+static int runs_per_workgroup(const Plan *p, int mg)
+{
+    const int64_t n = p->n_runs * ((p->B + mg - 1) / mg), pairs = point_count(p) * p->B;
+    if (mg > 1 && pairs >= 128 * n)
         return 1;
-    const int64_t n = p->n_runs, np = point_count(p);
-    if (np < 8 * n)
-        return (int)std::clamp<int64_t>((n + 511) / 512, 1, 16);
-    if (np > 64 * n)
-        return (int)std::clamp<int64_t>((n + 2047) / 2048, 1, 4);
-    const int wgs = p->P < 6 ? 2048 : 1024;
-    return (int)std::clamp<int64_t>((n + wgs - 1) / wgs, 1, n > 24576 ? 16 : 8);
+    const bool full = pairs > 64 * n;
+    const int64_t wgs = (int64_t)p->l2p_wgs * (full ? 2 : 1);
+    return (int)std::clamp<int64_t>((n + wgs - 1) / wgs, 1, std::min(full ? 4 : kRunsPerWorkgroup, l2p_slots(p->P) / mg));
 }
 
 grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s)
 {
-    const int MG = p->B == 1 ? 1 : kPointModels, lw = runs_per_workgroup(p);
-    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + MG - 1) / MG, lw};
+    const int mg = std::min(p->B, kPointModels), lw = runs_per_workgroup(p, mg);
+    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + mg - 1) / mg, lw, mg};
     if (p->n_runs == 0)
         return GRAV_OK;
     const dim3 grid = block_grid(rn.nblk * rn.groups);
@@ -484,10 +523,8 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
                        p->L >= 2 ? 1 : 0, out)
 #define L2P_CASE(P)                                                                                              \
     case P:                                                                                                      \
-        if (lw > 4)                                                                                              \
-            L2P_LAUNCH(P, 1, 16);                                                                                \
-        else if (lw > 1)                                                                                         \
-            L2P_LAUNCH(P, 1, 4);                                                                                 \
+        if (lw > 1)                                                                                              \
+            L2P_LAUNCH(P, 1, kRunsPerWorkgroup);                                                                 \
         else if (p->B == 1)                                                                                      \
             L2P_LAUNCH(P, 1, 1);                                                                                 \
         else                                                                                                     \

@@ -37,10 +37,11 @@ def test_point_runs(npts, batch):
         assert float((g[:, at:at + few][:, :ref.shape[1]] - ref).norm() / ref.norm()) <= 1e-12
 
 
-@pytest.mark.parametrize("p, leaves, per", [(10, 512, 1), (10, 513, 1), (10, 1024, 9), (10, 1025, 9), (10, 2049, 70),
-                                            (3, 4097, 20), (10, 8191, 3), (10, 8192, 11)])
-def test_runs_per_workgroup(p, leaves, per):
-    """Two models take a workgroup per run."""
+@pytest.mark.parametrize("p, leaves, per, batch", [(10, 512, 1, 1), (10, 1025, 9, 1), (10, 2049, 70, 1), (3, 4097, 20, 1),
+                                                   (10, 8191, 3, 1), (16, 8192, 11, 1), (10, 4096, 5, 2), (16, 4096, 2, 3),
+                                                   (4, 8192, 3, 8), (16, 2049, 2, 9), (10, 4096, 1, 17)])
+def test_runs_per_workgroup(p, leaves, per, batch):
+    """Plans of no more than 256 leaves take a workgroup per run."""
     n = np.array([128, 64, 64])
     rng = np.random.default_rng(leaves)
     ids = rng.permutation(n.prod() // 64)[:leaves]
@@ -48,13 +49,17 @@ def test_runs_per_workgroup(p, leaves, per):
     pts = np.repeat(corner, per, axis=0)
     pts = pts + rng.uniform(0.1, 3.9, size=pts.shape)
 
-    def plan(batch):
+    def plan(pts, batch):
         return G.Plan(G.PlanSpec(n=tuple(int(v) for v in n), h=1.0, voxel_centres=False, components=3, p=p, leaf_size=64,
                                  points=pts, precision=G.GRAV_FP64, batch=batch))
 
-    one, two = plan(1), plan(2)
-    assert one.n_target_leaves == leaves
-    rho = torch.randn(one.rho_shape, dtype=torch.float64, device="cuda",
+    whole = plan(pts, batch)
+    assert whole.n_target_leaves == leaves
+    rho = torch.randn(whole.rho_shape, dtype=torch.float64, device="cuda",
                       generator=torch.Generator(device="cuda").manual_seed(leaves))
-    ref = two.eval(torch.stack([rho.reshape(two.rho_shape[1:])] * 2))[1]
-    assert float((one.eval(rho).reshape(ref.shape) - ref).norm() / ref.norm()) <= 1e-12
+    g = whole.eval(rho).reshape(batch, -1, 3)
+    for at in (0, leaves // 2, leaves - 256):
+        few = plan(pts[at * per:(at + 256) * per], 1)
+        for b in (0, batch - 1):
+            ref = few.eval(rho.reshape(batch, -1)[b].reshape(few.rho_shape)).reshape(-1, 3)
+            assert float((g[b, at * per:(at + 256) * per] - ref).norm() / ref.norm()) <= 1e-12
