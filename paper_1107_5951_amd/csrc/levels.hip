@@ -20,8 +20,10 @@
 
 #include "octet.hpp"
 
-// Up: one workgroup of 32 columns per CU.  p = 10, 4096 columns: 17.2 us wide,
-// 12.3 us short; 512 columns: 14.8 and 8.9 us.
+// Up: one workgroup of 32 columns per CU.  All levels, wide against short, us:
+// p = 10, 2048 columns 18.3 / 11.6, 4096 19.7 / 13.7, 8192 24.4 / 24.2, 16384 43.1 /
+// 46.3, 32768 81.8 / 91.1; p = 16, 4096 51.6 / 37.5, 8192 62.9 / 78.6, 16384 108 / 150;
+// p = 4, where both are short, 4096 6.7 / 7.7, 16384 9.4 / 15.9.
 #ifndef GRAV_UP_WIDE_COLS
 #define GRAV_UP_WIDE_COLS 8192
 #endif

@@ -31,7 +31,13 @@ namespace grav {
 // targets, the form before this one).  Measured: 256^3 cells at leaf 4^3,
 // p = 10 in FP32 6.82 -> 1.52 ms (its matrix cycles 1.0 ms), p = 16 in FP64
 // 128.5 -> 17.0 ms (13.0 ms); 64^3 with two Gauss points 0.17 -> 0.05 ms and
-// p = 12 in FP64 0.61 -> 0.14 ms.  The rest is building the tiles: without it
+// p = 12 in FP64 0.61 -> 0.14 ms.  A unit costs the same however few of its octets'
+// children are targets or sources.  Sparse targets gain all the same, as the form
+// before was bound by its loads there: 128^3 cells, p = 10, 4000 random points, about
+// one target leaf per octet, 0.27 -> 0.16 ms, 200 points 0.17 -> 0.04.  Leaf grids of three boxes an axis or a
+// row of boxes lose at 128 models or more: 12^3 cells have 936 products of a parity
+// per model in octets and 386 of pairs, and 1024 of them, FP64 p = 14, take 1.85 ms in
+// all where that form took 0.81.  The rest is building the tiles: without it
 // the FP32 kernel takes 1.2 ms, without the loads behind it 1.1 ms.
 // --------------------------------------------------------------------------
 template <int P, typename T, int NC>

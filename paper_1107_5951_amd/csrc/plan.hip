@@ -37,10 +37,12 @@
 #define GRAV_NEAR_DENSE_BLOCKS 512
 #endif
 
-// Workgroups that the runs of points are cut for on single-model plans.  L2P with 1024 / 2048 / 4096 / 8192: one model at 1024^2 stations above 16^3 cells, p
-// = 10, 68 / 65 / 68 / 71 us, FP64 p = 14 133 / 119 / 119 / 123; several models load
-// their expansions again with every run: 64 at 64^2 stations 22 / 25 / 35 / 32 us, and
-// 18 over 76^3 cells, 16 points a leaf, 14.7 whole and 19.0 in two runs of one step.
+// Workgroups that the runs of points of single-model plans are cut for.  L2P with
+// 1024 / 2048 / 4096 / 8192: one model at 1024^2 stations above 16^3 cells, p = 10,
+// 68 / 65 / 68 / 71 us, FP64 p = 14 133 / 119 / 119 / 123.  Several models load their
+// expansions again with every run (64 at 64^2 stations 22 / 25 / 35 / 32 us; 18 over
+// 76^3 cells, 16 points a leaf, 14.7 whole and 19.0 in two runs of one step): runs of
+// two steps or more, cut for the workgroups that are resident.
 #ifndef GRAV_RUN_BLOCKS
 #define GRAV_RUN_BLOCKS 2048
 #endif
@@ -691,8 +693,9 @@ static grav_status build_octet_schedule(Plan *p, const Octets &oc, OctPlan &o, H
     o.noct = (int64_t)oc.key.size();
     std::copy(std::begin(oc.first), std::end(oc.first), std::begin(o.first));
     std::copy(std::begin(oc.reach), std::end(oc.reach), std::begin(o.reach));
-    // four (or two) column blocks per wave once there are units for every CU
-    // twice over; else single blocks, for more units than CUs on small plans
+    // two to four column blocks per wave once the work items (units times
+    // orbits) are two for every resident workgroup; else single blocks, for more
+    // items on small plans
     int resident = 0;
     GRAV_CHECK(m2l_resident_workgroups(p, in.NCW, &resident));
     int64_t near = 0;
