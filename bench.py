@@ -152,7 +152,7 @@ def measured_traffic(profile, kernel_name):
             k, v = line.strip().split(":", 1)
             fields[k.strip()] = v.strip()
     src = b"".join(open(os.path.join(ROOT, "paper_1107_5951_amd", "csrc", f), "rb").read()
-                   for f in ("m2l.hip", "eval_common.hpp", "internal.hpp", "resolve.hpp"))
+                   for f in ("m2l.hip", "octet.hpp", "eval_common.hpp", "internal.hpp", "resolve.hpp"))
     if fields.get("source_sha256_16") != hashlib.sha256(src).hexdigest()[:16]:
         return None
     if not kernel_name.startswith(fields.get("kernel", "?")):
