@@ -68,10 +68,10 @@ k_p2p(DevGeom g, const double *rho, const double *tpos, const int64_t *leaf_star
     __shared__ __align__(16) T sp[kP2PChunk][4];
     __shared__ double red[256][4];
     const DevLev &lv = g.lev[g.L];
-    if (block_id() >= n_leaves)
-        return;
-    const int64_t leaf = leaves[block_id()];  // the target leaves holding user points
-    const int64_t ts = leaf_start[leaf], te = leaf_end[leaf];
+    // a target leaf holding user points (past the last: the first without any)
+    const bool in = block_id() < n_leaves;
+    const int64_t leaf = leaves[in ? block_id() : 0];
+    const int64_t ts = leaf_start[leaf], te = in ? leaf_end[leaf] : ts;
     const int64_t nt = te - ts;
     if (nt <= 0)
         return;  // no explicit points in this leaf (uniform over the workgroup)
@@ -270,10 +270,10 @@ k_p2p_src(DevGeom g, const double *mass, const double *spos, const int64_t *ssta
     __shared__ T sp[256][4];
     __shared__ double red[256][4];
     const DevLev &lv = g.lev[g.L];
-    if (block_id() >= n_leaves)
-        return;
-    const int64_t leaf = leaves[block_id()];  // the target leaves holding user points
-    const int64_t ts = leaf_start[leaf], te = leaf_end[leaf];
+    // a target leaf holding user points (past the last: the first without any)
+    const bool in = block_id() < n_leaves;
+    const int64_t leaf = leaves[in ? block_id() : 0];
+    const int64_t ts = leaf_start[leaf], te = in ? leaf_end[leaf] : ts;
     const int64_t nt = te - ts;
     if (nt <= 0)
         return;

@@ -130,15 +130,15 @@ k_l2p_points(DevGeom g, PointArgs ar, RunArgs rn, const uint32_t *perm, const do
     const DevLev &lv = g.lev[g.L];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t blk = block_id();
-    if (blk >= rn.nblk * rn.groups)
+    const uint32_t blk = (uint32_t)block_id(), nblk = (uint32_t)rn.nblk;
+    if (blk >= nblk * (uint32_t)rn.groups)
         return;
-    const int64_t lb = blk % rn.nblk;
+    const uint32_t lb = blk % nblk;
     const int mgrp = LW == 1 ? MG : rn.mg;
-    const int bm0 = (int)(blk / rn.nblk) * mgrp, nm = min(mgrp, g.B - bm0);
+    const int bm0 = (int)(blk / nblk) * mgrp, nm = min(mgrp, g.B - bm0);
     const int lw = LW == 1 ? 1 : rn.lw;
-    const int nl = (int)min((int64_t)lw, rn.n - lb * lw);
-    const PointRun *runs = rn.runs + lb * lw;
+    const int nl = (int)min((int64_t)lw, rn.n - (int64_t)lb * lw);
+    const PointRun *runs = rn.runs + (int64_t)lb * lw;
     const double inv_w = 1.0 / (double)g.b;
     if (tid < nl) {
         const PointRun r = runs[tid];
@@ -516,6 +516,8 @@ grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipS
     const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + mg - 1) / mg, lw, mg};
     if (p->n_runs == 0)
         return GRAV_OK;
+    if (rn.nblk * rn.groups > 0xffff0000ll)
+        return GRAV_EUNSUPPORTED;  // (outputs of a quarter of a terabyte)
     const dim3 grid = block_grid(rn.nblk * rn.groups);
 #define L2P_LAUNCH(P, MG, LW)                                                                                    \
     hipLaunchKernelGGL((k_l2p_points<P, MG, LW>), grid, dim3(256), 0, s, g, point_args(p), rn,                   \
