@@ -512,10 +512,10 @@ static int runs_per_workgroup(const Plan *p, int mg)
 
 grav_status launch_l2p_points(const Plan *p, const DevGeom &g, double *out, hipStream_t s)
 {
-    const int mg = std::min(p->B, kPointModels), lw = runs_per_workgroup(p, mg);
-    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + mg - 1) / mg, lw, mg};
     if (p->n_runs == 0)
         return GRAV_OK;
+    const int mg = std::min(p->B, kPointModels), lw = runs_per_workgroup(p, mg);
+    const RunArgs rn{p->d_runs, p->n_runs, (p->n_runs + lw - 1) / lw, (p->B + mg - 1) / mg, lw, mg};
     if (rn.nblk * rn.groups > 0xffff0000ll)
         return GRAV_EUNSUPPORTED;  // (outputs of a quarter of a terabyte)
     const dim3 grid = block_grid(rn.nblk * rn.groups);
