@@ -27,11 +27,12 @@
 
 // Leaves of 4^3 cells take the dense near field where the parity kernels' blocks
 // (16 leaves of one model) hold at most a quarter of their leaves and there are
-// more of them (over all models) than this many per leaf held.  Dense against
-// parity, whole calls of cell centres in us, forward and adjoint, p = 10 (gz; g):
-// 4^3 cells (1 leaf) x 512 models 28 / 16, 37 / 21; 28 / 20, 79 / 37; x 2048 28 /
-// 37, 37 / 53; 32 / 54, 94 / 113; FP64 x 512 26 / 22, 57 / 24; 28 / 28, 143 / 49;
-// 8 x 8 x 4 cells (4 leaves) x 1024 29 / 24, 39 / 33; 47 / 33, 96 / 63; x 4096 53 /
+// more of them (over all models) than this many per leaf held and twice as many in
+// all.  Dense against parity, whole calls of cell centres in us, forward and
+// adjoint, p = 10 (gz; g): 4^3 cells (1 leaf) x 512 models 28 / 16, 37 / 21; 28 / 20,
+// 79 / 37; x 1024 28 / 22, 37 / 31; 29 / 31, 92 / 62; x 2048 28 / 37, 37 / 53; 32 / 54,
+// 94 / 113; FP64 x 512 26 / 22, 57 / 24; 28 / 28, 143 / 49; x 1024 26 / 37, 57 / 38;
+// 29 / 49, 145 / 86; x 2048 28 / 67, 59 / 66; 45 / 92, 146 / 161; 8 x 8 x 4 cells (4 leaves) x 1024 29 / 24, 39 / 33; 47 / 33, 96 / 63; x 4096 53 /
 // 65, 62 / 94; 127 / 101, 137 / 214.
 #ifndef GRAV_NEAR_DENSE_BLOCKS
 #define GRAV_NEAR_DENSE_BLOCKS 512
@@ -1273,7 +1274,7 @@ grav_status build_near_lattice(Plan *p, hipStream_t s)
         const LevelInfo &lv = p->lev[p->L];
         const int64_t blocks = ceil_div(lv.ns[0], 4) * ceil_div(lv.ns[1], 2) * ceil_div(lv.ns[2], 2);
         p->near_par = b == 4 && (lv.n_src > 4 * blocks ||
-                                 blocks * blocks * p->B <= (int64_t)GRAV_NEAR_DENSE_BLOCKS * lv.n_src);
+                                 blocks * blocks * p->B <= (int64_t)GRAV_NEAR_DENSE_BLOCKS * std::max(lv.n_src, 2 * blocks));
     }
     if (p->near_par)
         GRAV_CHECK(f64 ? build_near_parity<double>(p, dense) : build_near_parity<float>(p, dense));

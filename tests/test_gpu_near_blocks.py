@@ -32,7 +32,7 @@ def _gap(g, r, rho, d):
 
 @PREC
 @pytest.mark.parametrize("comps", [1, 3, 4])
-@pytest.mark.parametrize("n, batch", [((4, 4, 4), 513), ((3, 4, 2), 600), ((16, 4, 4), 2049), ((4, 4, 17), 700),
+@pytest.mark.parametrize("n, batch", [((4, 4, 4), 1025), ((3, 4, 2), 1100), ((16, 4, 4), 2049), ((4, 4, 17), 700),
                                       ((7, 8, 3), 2100)])
 def test_mostly_empty_blocks(n, batch, comps, prec, bar):
     pts = np.array([[1.2, 2.3, 0.7], [n[0] + 5.0, 1.0, 2.0]]) if n[0] > 4 else None
